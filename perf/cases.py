@@ -1,0 +1,349 @@
+"""What a user of this package runs, as cases that can be timed: whole encoder passes, single
+convolutions of both data types, strided convolutions, decoder layers and batches that are new.
+
+Shapes are unions of surface shells of random spheres, boxes and tori on a u^3 grid (the kind of
+input the rest of the repository uses), cut by a plane so that a batch has exactly `voxels`
+occupied voxels, unevenly shared by its shapes.  Everything is drawn from the seed."""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+import paper_1803_11385_amd as hch
+from paper_1803_11385_amd import pipeline
+
+ALGO = {"fused": hch.HCH_ALGO_FUSED, "columns": hch.HCH_ALGO_COLUMNS}
+DTYPE = {"f32": (hch.HCH_F32, torch.float32), "bf16": (hch.HCH_BF16, torch.bfloat16)}
+
+
+def _channels(case):
+    """Channels of an encoder: the input's, then `width` doubled from level to level."""
+    return [case["c_in"]] + [case["width"] << l for l in range(case["convs"])]
+
+
+def listed():
+    return [
+        # one scanned shape is classified while somebody waits: nothing but latency and launches
+        # (32^3 sphere-sized shape, normals as the three input channels)
+        dict(name="infer_32x1", kind="encoder", train=False, u=32, batch=1, voxels=3177, c_in=3, width=16, convs=3,
+             algo="fused", two_streams=False),
+        # training step of the small net on a mini-batch of 32 low-resolution shapes
+        dict(name="train_32x32", kind="encoder", train=True, u=32, batch=32, voxels=31007, c_in=4, width=16, convs=3,
+             algo="fused", two_streams=False),
+        # the usual mini-batch of 32 shapes at 64^3, gradients overlapped on a second stream
+        dict(name="train_64x32", kind="encoder", train=True, u=64, batch=32, voxels=126665, c_in=4, width=32, convs=4,
+             algo="fused", two_streams=True),
+        # the five-level 256^3 encoder that bench.py reports
+        dict(name="train_256x8", kind="encoder", train=True, u=256, batch=8, voxels=609323, c_in=4, width=16, convs=5,
+             algo="fused", two_streams=False),
+        # the paper's own three steps (hash2col, dense product, col2hash), 128^3
+        dict(name="train_columns_128x16", kind="encoder", train=True, u=128, batch=16, voxels=279722, c_in=4, width=16,
+             convs=4, algo="columns", two_streams=False),
+        # one fp32 layer with its two gradients, 128^3, 32 -> 64 (bench.py --conv-bench 3)
+        dict(name="conv_f32_128x16", kind="conv", u=128, batch=16, voxels=279722, thick=False, dtype="f32", c_in=32, c_out=64),
+        # a segmentation head: 50 part labels, a channel count that is a multiple of nothing
+        dict(name="conv_f32_head_64x16", kind="conv", u=64, batch=16, voxels=63331, thick=False, dtype="f32", c_in=32, c_out=50),
+        # bf16 training at the usual resolution
+        dict(name="conv_bf16_64x32", kind="conv", u=64, batch=32, voxels=126665, thick=False, dtype="bf16", c_in=32, c_out=64),
+        # the largest: 512^3, two voxels thick shells, bf16 (bench.py --conv-bench 5)
+        dict(name="conv_bf16_512x4", kind="conv", u=512, batch=4, voxels=2976869, thick=True, dtype="bf16", c_in=64, c_out=64),
+        # a strided convolution in place of pooling, with the index rows of its fields
+        dict(name="sconv_256x8", kind="sconv", u=256, batch=8, voxels=609323, dtype="f32", F=3, stride=2, pad=1, c_in=16, c_out=32),
+        # one layer of a decoder: max-unpooling and transposed convolution, forward and backward
+        dict(name="decode_128x16", kind="decode", u=128, batch=16, voxels=279722, dtype="f32", c_in=64, c_out=32),
+        # a batch that was never seen: tables, index lists and the first layer, from host coordinates
+        dict(name="newbatch_256x8", kind="newbatch", u=256, batch=8, voxels=609323, levels=6, c_in=4, c_out=16),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["encoder", "encoder", "encoder", "conv", "conv", "conv", "sconv", "decode", "newbatch"])
+    u = rng.choice([32, 64, 128, 256])
+    most = {32: 40, 64: 40, 128: 20, 256: 8}[u]
+    batch = _log_int(rng, 1, most)
+    voxels = int(batch * u * u * rng.uniform(0.6, 1.4))          # shells of u^2 voxels, more or less
+    case = dict(kind=kind, u=u, batch=batch, voxels=voxels)
+    if kind == "encoder":
+        algo = rng.choice(["fused", "fused", "columns"])
+        case.update(train=rng.random() < 0.7, c_in=rng.choice([3, 4, 6]), width=rng.choice([8, 16, 32]),
+                    convs=min(5, int(math.log2(u)) - rng.choice([2, 3])), algo=algo,
+                    two_streams=algo == "fused" and rng.random() < 0.3)
+    elif kind == "conv":
+        dtype = rng.choice(["f32", "bf16"])
+        step = rng.choice([1, 4, 8, 16, 16, 32])
+        c = [max(3 if step == 1 else step, round(_log_int(rng, 4, 128) / step) * step) for _ in range(2)]
+        thick = rng.random() < 0.25
+        case.update(thick=thick, dtype=dtype, c_in=c[0], c_out=c[1])
+        if thick:
+            case["voxels"] *= 2
+    elif kind == "sconv":
+        F, stride, pad = rng.choice([(3, 2, 1), (3, 2, 1), (2, 2, 0), (5, 1, 2), (3, 4, 1)])
+        case.update(dtype="f32", F=F, stride=stride, pad=pad, c_in=rng.choice([4, 16, 24, 32]), c_out=rng.choice([16, 32, 40, 64]))
+    elif kind == "decode":
+        case.update(dtype="f32", c_in=rng.choice([16, 32, 64, 128]), c_out=rng.choice([8, 16, 32, 64]))
+    else:
+        case.update(levels=rng.randint(3, int(math.log2(u)) - 1), c_in=4, c_out=rng.choice([16, 32]))
+    return case
+
+
+# ---- inputs -----------------------------------------------------------------------------
+
+def _primitive_shell(occupied, rng, u, thick):
+    """Adds the shell of one random primitive (lengths scale with u / 64) to `occupied`: its inside
+    voxels with a face neighbour outside and, when thick, the outside voxels that touch it."""
+    s = u / 64.0
+    kind = int(rng.integers(0, 3))
+    c = rng.uniform(16.0, 48.0, 3) * s
+    if kind == 0:
+        size = [rng.uniform(6.0, 20.0) * s]
+        reach = np.full(3, size[0])
+    elif kind == 1:
+        size = rng.uniform(4.0, 16.0, 3) * s
+        reach = size
+    else:
+        size = [rng.uniform(8.0, 18.0) * s, rng.uniform(2.0, 5.0) * s]
+        reach = np.array([size[0] + size[1], size[0] + size[1], size[1]])
+    lo = np.floor(c - reach).astype(int) - 3
+    hi = np.ceil(c + reach).astype(int) + 3
+    ax = [torch.arange(int(lo[a]), int(hi[a]), device="cuda", dtype=torch.float32) + (0.5 - float(c[a])) for a in range(3)]
+    x, y, z = ax[0][:, None, None], ax[1][None, :, None], ax[2][None, None, :]
+    if kind == 0:
+        inside = x * x + y * y + z * z < size[0] ** 2
+    elif kind == 1:
+        inside = (x.abs() < size[0]) & (y.abs() < size[1]) & (z.abs() < size[2])
+    else:
+        inside = ((x * x + y * y).sqrt() - size[0]) ** 2 + z * z < size[1] ** 2
+    mid = inside[1:-1, 1:-1, 1:-1]
+    sides = [inside[2:, 1:-1, 1:-1], inside[:-2, 1:-1, 1:-1], inside[1:-1, 2:, 1:-1], inside[1:-1, :-2, 1:-1],
+             inside[1:-1, 1:-1, 2:], inside[1:-1, 1:-1, :-2]]
+    every, some = sides[0].clone(), sides[0].clone()
+    for t in sides[1:]:
+        every &= t
+        some |= t
+    shell = mid & ~every
+    if thick:
+        shell |= ~mid & some
+    a = np.maximum(lo + 1, 0)
+    b = np.minimum(hi - 1, u)
+    o = a - (lo + 1)
+    occupied[a[0]:b[0], a[1]:b[1], a[2]:b[2]] |= shell[o[0]:o[0] + b[0] - a[0], o[1]:o[1] + b[1] - a[1], o[2]:o[2] + b[2] - a[2]]
+
+
+def _batch(case, seed):
+    """Host coordinates (sorted by position within a shape, as a voxeliser leaves them) and model
+    offsets of a batch with exactly case["voxels"] voxels.  The case fixes the shapes; the seed turns
+    and mirrors each of them within its grid and deals them out anew, so that every seed has a batch
+    of its own with the same number of voxels at every level."""
+    u, b, n = case["u"], case["batch"], case["voxels"]
+    rng = np.random.default_rng([u, b, n])
+    share = rng.uniform(0.7, 1.3, b)
+    cut = np.floor(np.cumsum(share) / share.sum() * n).astype(np.int64)
+    cut[-1] = n
+    size = np.diff(np.concatenate([[0], cut]))
+    shapes = []
+    for want in size.tolist():
+        occupied = torch.zeros((u, u, u), dtype=torch.bool, device="cuda")
+        for _ in range(60):
+            _primitive_shell(occupied, rng, u, case.get("thick", False))
+            if int(torch.count_nonzero(occupied)) >= want:
+                break
+        p = torch.nonzero(occupied)[:want]
+        assert p.shape[0] == want, "the grid is too small for this many voxels"
+        shapes.append(p)
+    turn = np.random.default_rng(seed)
+    parts, offs = [], [0]
+    for v in turn.permutation(b).tolist():
+        p = shapes[v][:, turn.permutation(3).tolist()]
+        mirror = torch.tensor(turn.integers(0, 2, 3).tolist(), device="cuda", dtype=torch.bool)
+        p = torch.where(mirror, u - 1 - p, p)
+        lin = torch.sort((p[:, 0] * u + p[:, 1]) * u + p[:, 2])[0]
+        parts.append(torch.stack([lin // (u * u), lin // u % u, lin % u], 1).to(torch.int32).cpu().numpy())
+        offs.append(offs[-1] + p.shape[0])
+    return np.ascontiguousarray(np.concatenate(parts)), np.asarray(offs, dtype=np.int64)
+
+
+def _normals_and_one(n, c, gen):
+    """Input features of a first layer: unit vectors, ones, and positions in [0, 1) behind them."""
+    v = torch.randn((n, 3), device="cuda", generator=gen)
+    parts = [v / v.norm(dim=1, keepdim=True)]
+    if c == 4:
+        parts.append(torch.ones((n, 1), device="cuda"))
+    elif c > 4:
+        parts.append(torch.rand((n, c - 3), device="cuda", generator=gen))
+    return torch.cat(parts, 1).contiguous()
+
+
+def _workspace(nbytes):
+    t = torch.empty(int(nbytes) + 256, dtype=torch.uint8, device="cuda")
+    off = (-t.data_ptr()) % 256
+    return t[off: off + int(nbytes)]
+
+
+def prepare(case, seed):
+    coords, offs = _batch(case, seed)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(int(seed) + 1)
+    kind = case["kind"]
+
+    def gauss(shape, std, dtype=torch.float32):
+        return (torch.randn(shape, device="cuda", generator=gen) * std).to(dtype)
+
+    if kind == "encoder":
+        ch = _channels(case)
+        lv = hch.hch_build_levels_device(coords, offs, case["u"], case["convs"] + 1)
+        enc = pipeline.Encoder(lv, ch, algo=ALGO[case["algo"]], two_streams=case["two_streams"])
+        enc.X[0].copy_(_normals_and_one(enc.n[0], ch[0], gen))
+        for l in range(enc.L):
+            enc.W[l].copy_(gauss(tuple(enc.W[l].shape), math.sqrt(2.0 / (27 * ch[l]))))
+        enc.dX[enc.L].copy_(gauss(tuple(enc.dX[enc.L].shape), 1.0))
+        return dict(case=case, enc=enc)
+
+    ci, co = case["c_in"], case["c_out"]
+    if kind == "newbatch":
+        lv = hch.hch_build_levels_device(coords, offs, case["u"], case["levels"])
+        n, nc = lv.n(0), lv.n(1)
+        ws = _workspace(hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_F32, hch.HCH_WS_FWD, hch.HCH_ALGO_FUSED))
+        lv.free()
+        return dict(case=case, coords=coords, offs=offs, ws=ws, X=_normals_and_one(n, ci, gen),
+                    W=gauss((27, ci, co), math.sqrt(2.0 / (27 * ci))), Y=torch.empty((n, co), device="cuda"),
+                    P=torch.empty((nc, co), device="cuda"), sw=torch.empty((nc, co), dtype=torch.int32, device="cuda"))
+
+    dt, tdt = DTYPE[case["dtype"]]
+    s = dict(case=case)
+    if kind == "conv":
+        lv = hch.hch_build_levels_device(coords, offs, case["u"], 1)
+        if case["dtype"] == "bf16":
+            hch.hch_build_tap_major(lv, 0)
+        n = lv.n(0)
+        ws = max(hch.hch_conv_workspace_bytes(lv, 0, ci, co, dt, k, hch.HCH_ALGO_FUSED)
+                 for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT))
+        s.update(X=gauss((n, ci), 1.0, tdt), W=gauss((27, ci, co), math.sqrt(2.0 / (27 * ci)), tdt), dY=gauss((n, co), 1.0, tdt),
+                 Y=torch.empty((n, co), device="cuda"), dX=torch.empty((n, ci), device="cuda"),
+                 dW=torch.empty((27, ci, co), device="cuda"))
+    elif kind == "sconv":
+        F, S = case["F"], case["stride"]
+        lv = hch.hch_build_levels_device(coords, offs, case["u"], 1 + int(math.log2(S)))
+        n, no, F3 = lv.n(0), lv.n(lv.n_levels - 1), F ** 3
+        ws = max(hch.hch_sconv_workspace_bytes(lv, 0, F, S, ci, co, dt, k)
+                 for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT))
+        s.update(X=gauss((n, ci), 1.0, tdt), W=gauss((F3, ci, co), math.sqrt(2.0 / (F3 * ci)), tdt), dY=gauss((no, co), 1.0, tdt),
+                 Y=torch.empty((no, co), device="cuda"), dX=torch.empty((n, ci), device="cuda"),
+                 dW=torch.empty((F3, ci, co), device="cuda"),
+                 field=torch.empty((no, F3), dtype=torch.int32, device="cuda"),
+                 field_t=torch.empty((n, F3), dtype=torch.int32, device="cuda"))
+    else:
+        lv = hch.hch_build_levels_device(coords, offs, case["u"], 2)
+        n, nc = lv.n(0), lv.n(1)
+        # transposed convolutions take the workspace of the convolution they transpose
+        ws = max(hch.hch_conv_workspace_bytes(lv, 0, co, ci, dt, k, hch.HCH_ALGO_FUSED)
+                 for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT))
+        sw = torch.empty((nc, ci), dtype=torch.int32, device="cuda")
+        P = torch.empty((nc, ci), device="cuda")
+        hch.hch_pool_fwd(lv, 0, gauss((n, ci), 1.0), P, sw, ci)      # the encoder's switches at this level
+        s.update(Xc=gauss((nc, ci), 1.0), sw=sw, W=gauss((27, co, ci), math.sqrt(2.0 / (27 * ci))), dY=gauss((n, co), 1.0),
+                 U=torch.empty((n, ci), device="cuda"), Y=torch.empty((n, co), device="cuda"),
+                 dW=torch.empty((27, co, ci), device="cuda"), dU=torch.empty((n, ci), device="cuda"),
+                 dXc=torch.empty((nc, ci), device="cuda"))
+    s.update(lv=lv, ws=_workspace(ws))
+    return s
+
+
+# ---- one pass ---------------------------------------------------------------------------
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "encoder":
+        enc = s["enc"]
+        if case["train"]:
+            enc.step()
+            return {"pooled": enc.X[1:], "dW": enc.dW, "dX": enc.dX[0]}
+        enc.build_indices()
+        enc.forward()
+        return {"pooled": enc.X[1:], "switches": enc.sw}
+    ci, co = case["c_in"], case["c_out"]
+    if kind == "newbatch":
+        lv = hch.hch_build_levels_device(s["coords"], s["offs"], case["u"], case["levels"])
+        hch.hch_conv_fwd(lv, 0, hch.HCH_F32, s["X"], s["W"], s["Y"], ci, co, s["ws"], hch.HCH_ALGO_FUSED)
+        hch.hch_relu_pool_fwd(lv, 0, s["Y"], None, s["P"], s["sw"], co)
+        lv.free()
+        return {"Y": s["Y"], "P": s["P"], "switches": s["sw"]}
+    lv, ws, dt = s["lv"], s["ws"], DTYPE[case["dtype"]][0]
+    if kind == "conv":
+        hch.hch_conv_fwd(lv, 0, dt, s["X"], s["W"], s["Y"], ci, co, ws, hch.HCH_ALGO_FUSED)
+        hch.hch_conv_bwd_weight(lv, 0, dt, s["X"], s["dY"], s["dW"], ci, co, ws, hch.HCH_ALGO_FUSED)
+        hch.hch_conv_bwd_data(lv, 0, dt, s["dY"], s["W"], s["dX"], ci, co, ws, hch.HCH_ALGO_FUSED)
+        return {"Y": s["Y"], "dW": s["dW"], "dX": s["dX"]}
+    if kind == "sconv":
+        F, S = case["F"], case["stride"]
+        hch.hch_field_build(lv, 0, F, S, case["pad"], s["field"], s["field_t"])
+        hch.hch_sconv_fwd(lv, 0, F, S, dt, s["X"], s["W"], s["Y"], s["field"], ci, co, ws)
+        hch.hch_sconv_bwd_weight(lv, 0, F, S, dt, s["X"], s["dY"], s["dW"], s["field"], ci, co, ws)
+        hch.hch_sconv_bwd_data(lv, 0, F, S, dt, s["dY"], s["W"], s["dX"], s["field_t"], ci, co, ws)
+        return {"field": s["field"], "Y": s["Y"], "dW": s["dW"], "dX": s["dX"]}
+    hch.hch_unpool_fwd(lv, 0, s["Xc"], s["sw"], s["U"], ci)
+    hch.hch_deconv_fwd(lv, 0, dt, s["U"], s["W"], s["Y"], ci, co, ws, hch.HCH_ALGO_FUSED)
+    hch.hch_deconv_bwd_weight(lv, 0, dt, s["U"], s["dY"], s["dW"], ci, co, ws, hch.HCH_ALGO_FUSED)
+    hch.hch_deconv_bwd_data(lv, 0, dt, s["dY"], s["W"], s["dU"], ci, co, ws, hch.HCH_ALGO_FUSED)
+    hch.hch_unpool_bwd(lv, 0, s["dU"], s["sw"], s["dXc"], ci)
+    return {"Y": s["Y"], "dW": s["dW"], "dXc": s["dXc"]}
+
+
+# ---- what a pass cannot do without --------------------------------------------------------
+
+TAPS = [9.0, 10.6, 11.6, 12.4, 13.7, 14.5]      # occupied neighbours per voxel, thin shells, by level
+TAPS_THICK = 17.2
+COARSER = 3.7                                    # voxels of a level over those of the next
+
+
+def work(case):
+    n, kind = case["voxels"], case["kind"]
+    lookup = lambda rows, taps: rows * (12.0 + 4.0 * taps)       # position in, index row out
+    if kind == "encoder":
+        ch, by, fl = _channels(case), 0.0, 0.0
+        for l in range(case["convs"]):
+            nl, nn = n / COARSER ** l, n / COARSER ** (l + 1)
+            passes = 3 if case["train"] else 1
+            w = 27 * ch[l] * ch[l + 1]
+            fl += passes * 2.0 * TAPS[l] * nl * ch[l] * ch[l + 1]
+            by += lookup(nl, 27) + lookup(nn, 8) + 4.0 * w
+            by += 4.0 * (nl * ch[l] + 2 * nn * ch[l + 1])                    # input row; pooled row and switch
+            if case["train"]:
+                by += 4.0 * (2 * nl * ch[l] + nn * ch[l + 1] + w)            # input row again, its gradient; switch; dW
+        return {"bytes": by, "flops": fl}
+    ci, co = case["c_in"], case["c_out"]
+    if kind == "conv":
+        es = 4 if case["dtype"] == "f32" else 2
+        taps = TAPS_THICK if case["thick"] else TAPS[0]
+        w = 27 * ci * co
+        return {"bytes": n * (es * (ci + co) + 4.0 * (ci + co) + 108.0) + w * (es + 4.0), "flops": 6.0 * taps * n * ci * co}
+    if kind == "sconv":
+        F3 = case["F"] ** 3
+        no = n / COARSER ** math.log2(case["stride"])
+        taps = TAPS[0] * F3 / 27.0 if case["stride"] > 1 else F3 ** (2.0 / 3.0)
+        return {"bytes": lookup(no, F3) + lookup(n, F3) + 4.0 * (2 * n * ci + 2 * no * co + 2 * F3 * ci * co),
+                "flops": 6.0 * taps * no * ci * co}
+    if kind == "decode":
+        nc = n / COARSER
+        return {"bytes": 4.0 * (3 * nc * ci + 2 * n * co + 2 * 27 * ci * co) + 108.0 * n, "flops": 6.0 * TAPS[0] * n * ci * co}
+    by, nl = 4.0 * (n * ci + n * co + 2 * n / COARSER * co), float(n)
+    for l in range(case["levels"]):
+        by += lookup(nl, 27) + lookup(nl / COARSER, 8) + 16.0 * nl           # index lists; tables of one slot per voxel
+        nl /= COARSER
+    return {"bytes": by, "flops": 2.0 * TAPS[0] * n * ci * co}
+
+
+def tolerance(case):
+    """Four times the largest difference measured against the same path summed in 64 bits (single
+    layers) or by the other algorithm (encoders).  Where a maximum nearly ties, another order of the
+    sums moves a switch, and with it one gradient from one voxel to another: 2e-6 of the switches,
+    which shows as 2e-3 in the norm of a gradient."""
+    if case["kind"] == "encoder" and case["train"]:
+        return {"rel": 8e-3, "max": 0.99}
+    return {"rel": 3e-6, "max": 3e-5, "differ": 0.0 if case["kind"] in ("conv", "sconv", "decode") else 1e-5}
