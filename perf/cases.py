@@ -185,8 +185,9 @@ def _workspace(nbytes):
     return t[off: off + int(nbytes)]
 
 
-def prepare(case, seed):
-    coords, offs = _batch(case, seed)
+def _inputs(case, seed, n):
+    """The numbers of a case, from its seed and the voxels per level `n` (an encoder reads all of
+    `n`, the others the finest level, the level below and the last one)."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(int(seed) + 1)
     kind = case["kind"]
@@ -196,61 +197,82 @@ def prepare(case, seed):
 
     if kind == "encoder":
         ch = _channels(case)
-        lv = hch.hch_build_levels_device(coords, offs, case["u"], case["convs"] + 1)
-        enc = pipeline.Encoder(lv, ch, algo=ALGO[case["algo"]], two_streams=case["two_streams"])
-        enc.X[0].copy_(_normals_and_one(enc.n[0], ch[0], gen))
+        return dict(X=_normals_and_one(n[0], ch[0], gen),
+                    W=[gauss((27, ch[l], ch[l + 1]), math.sqrt(2.0 / (27 * ch[l]))) for l in range(case["convs"])],
+                    G=gauss((n[case["convs"]], ch[-1]), 1.0))
+    ci, co = case["c_in"], case["c_out"]
+    if kind == "newbatch":
+        return dict(X=_normals_and_one(n[0], ci, gen), W=gauss((27, ci, co), math.sqrt(2.0 / (27 * ci))))
+    tdt = DTYPE[case["dtype"]][1]
+    if kind == "conv":
+        return dict(X=gauss((n[0], ci), 1.0, tdt), W=gauss((27, ci, co), math.sqrt(2.0 / (27 * ci)), tdt), dY=gauss((n[0], co), 1.0, tdt))
+    if kind == "sconv":
+        F3 = case["F"] ** 3
+        return dict(X=gauss((n[0], ci), 1.0, tdt), W=gauss((F3, ci, co), math.sqrt(2.0 / (F3 * ci)), tdt), dY=gauss((n[-1], co), 1.0, tdt))
+    return dict(A=gauss((n[0], ci), 1.0), Xc=gauss((n[1], ci), 1.0), W=gauss((27, co, ci), math.sqrt(2.0 / (27 * ci))), dY=gauss((n[0], co), 1.0))
+
+
+def _n_levels(case):
+    kind = case["kind"]
+    if kind == "encoder":
+        return case["convs"] + 1
+    if kind == "newbatch":
+        return case["levels"]
+    if kind == "sconv":
+        return 1 + int(math.log2(case["stride"]))
+    return 1 if kind == "conv" else 2
+
+
+def prepare(case, seed):
+    coords, offs = _batch(case, seed)
+    kind = case["kind"]
+    lv = hch.hch_build_levels_device(coords, offs, case["u"], _n_levels(case))
+    n = [lv.n(l) for l in range(lv.n_levels)]
+    x = _inputs(case, seed, n)
+
+    if kind == "encoder":
+        enc = pipeline.Encoder(lv, _channels(case), algo=ALGO[case["algo"]], two_streams=case["two_streams"])
+        enc.X[0].copy_(x["X"])
         for l in range(enc.L):
-            enc.W[l].copy_(gauss(tuple(enc.W[l].shape), math.sqrt(2.0 / (27 * ch[l]))))
-        enc.dX[enc.L].copy_(gauss(tuple(enc.dX[enc.L].shape), 1.0))
+            enc.W[l].copy_(x["W"][l])
+        enc.dX[enc.L].copy_(x["G"])
         return dict(case=case, enc=enc)
 
     ci, co = case["c_in"], case["c_out"]
     if kind == "newbatch":
-        lv = hch.hch_build_levels_device(coords, offs, case["u"], case["levels"])
-        n, nc = lv.n(0), lv.n(1)
         ws = _workspace(hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_F32, hch.HCH_WS_FWD, hch.HCH_ALGO_FUSED))
         lv.free()
-        return dict(case=case, coords=coords, offs=offs, ws=ws, X=_normals_and_one(n, ci, gen),
-                    W=gauss((27, ci, co), math.sqrt(2.0 / (27 * ci))), Y=torch.empty((n, co), device="cuda"),
-                    P=torch.empty((nc, co), device="cuda"), sw=torch.empty((nc, co), dtype=torch.int32, device="cuda"))
+        return dict(case=case, coords=coords, offs=offs, ws=ws, Y=torch.empty((n[0], co), device="cuda"),
+                    P=torch.empty((n[1], co), device="cuda"), sw=torch.empty((n[1], co), dtype=torch.int32, device="cuda"), **x)
 
-    dt, tdt = DTYPE[case["dtype"]]
-    s = dict(case=case)
+    dt = DTYPE[case["dtype"]][0]
+    s = dict(case=case, lv=lv, **x)
     if kind == "conv":
-        lv = hch.hch_build_levels_device(coords, offs, case["u"], 1)
         if case["dtype"] == "bf16":
             hch.hch_build_tap_major(lv, 0)
-        n = lv.n(0)
         ws = max(hch.hch_conv_workspace_bytes(lv, 0, ci, co, dt, k, hch.HCH_ALGO_FUSED)
                  for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT))
-        s.update(X=gauss((n, ci), 1.0, tdt), W=gauss((27, ci, co), math.sqrt(2.0 / (27 * ci)), tdt), dY=gauss((n, co), 1.0, tdt),
-                 Y=torch.empty((n, co), device="cuda"), dX=torch.empty((n, ci), device="cuda"),
+        s.update(Y=torch.empty((n[0], co), device="cuda"), dX=torch.empty((n[0], ci), device="cuda"),
                  dW=torch.empty((27, ci, co), device="cuda"))
     elif kind == "sconv":
-        F, S = case["F"], case["stride"]
-        lv = hch.hch_build_levels_device(coords, offs, case["u"], 1 + int(math.log2(S)))
-        n, no, F3 = lv.n(0), lv.n(lv.n_levels - 1), F ** 3
+        F, S, F3 = case["F"], case["stride"], case["F"] ** 3
         ws = max(hch.hch_sconv_workspace_bytes(lv, 0, F, S, ci, co, dt, k)
                  for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT))
-        s.update(X=gauss((n, ci), 1.0, tdt), W=gauss((F3, ci, co), math.sqrt(2.0 / (F3 * ci)), tdt), dY=gauss((no, co), 1.0, tdt),
-                 Y=torch.empty((no, co), device="cuda"), dX=torch.empty((n, ci), device="cuda"),
+        s.update(Y=torch.empty((n[-1], co), device="cuda"), dX=torch.empty((n[0], ci), device="cuda"),
                  dW=torch.empty((F3, ci, co), device="cuda"),
-                 field=torch.empty((no, F3), dtype=torch.int32, device="cuda"),
-                 field_t=torch.empty((n, F3), dtype=torch.int32, device="cuda"))
+                 field=torch.empty((n[-1], F3), dtype=torch.int32, device="cuda"),
+                 field_t=torch.empty((n[0], F3), dtype=torch.int32, device="cuda"))
     else:
-        lv = hch.hch_build_levels_device(coords, offs, case["u"], 2)
-        n, nc = lv.n(0), lv.n(1)
         # transposed convolutions take the workspace of the convolution they transpose
         ws = max(hch.hch_conv_workspace_bytes(lv, 0, co, ci, dt, k, hch.HCH_ALGO_FUSED)
                  for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT))
-        sw = torch.empty((nc, ci), dtype=torch.int32, device="cuda")
-        P = torch.empty((nc, ci), device="cuda")
-        hch.hch_pool_fwd(lv, 0, gauss((n, ci), 1.0), P, sw, ci)      # the encoder's switches at this level
-        s.update(Xc=gauss((nc, ci), 1.0), sw=sw, W=gauss((27, co, ci), math.sqrt(2.0 / (27 * ci))), dY=gauss((n, co), 1.0),
-                 U=torch.empty((n, ci), device="cuda"), Y=torch.empty((n, co), device="cuda"),
-                 dW=torch.empty((27, co, ci), device="cuda"), dU=torch.empty((n, ci), device="cuda"),
-                 dXc=torch.empty((nc, ci), device="cuda"))
-    s.update(lv=lv, ws=_workspace(ws))
+        sw = torch.empty((n[1], ci), dtype=torch.int32, device="cuda")
+        P = torch.empty((n[1], ci), device="cuda")
+        hch.hch_pool_fwd(lv, 0, s.pop("A"), P, sw, ci)               # the encoder's switches at this level
+        s.update(sw=sw, U=torch.empty((n[0], ci), device="cuda"), Y=torch.empty((n[0], co), device="cuda"),
+                 dW=torch.empty((27, co, ci), device="cuda"), dU=torch.empty((n[0], ci), device="cuda"),
+                 dXc=torch.empty((n[1], ci), device="cuda"))
+    s.update(ws=_workspace(ws))
     return s
 
 
@@ -347,3 +369,110 @@ def tolerance(case):
     if case["kind"] == "encoder" and case["train"]:
         return {"rel": 8e-3, "max": 0.99}
     return {"rel": 3e-6, "max": 3e-5, "differ": 0.0 if case["kind"] in ("conv", "sconv", "decode") else 1e-5}
+
+
+# ---- the same results in 64 bits ----------------------------------------------------------
+
+class _Grid:
+    """The occupied positions of one level: model, position and a sorted key per voxel, in data order
+    (the finest level as given, which is sorted; a coarser one sorted by position)."""
+
+    def __init__(self, model, pos, u):
+        self.model, self.pos, self.u = model, pos, u
+        self.key = self._key(model, pos)
+
+    def _key(self, model, pos):
+        return ((model * self.u + pos[:, 0]) * self.u + pos[:, 1]) * self.u + pos[:, 2]
+
+    def coarser(self):
+        u = (self.u + 1) // 2
+        key = torch.unique(((self.model * u + self.pos[:, 0] // 2) * u + self.pos[:, 1] // 2) * u + self.pos[:, 2] // 2)
+        pos = torch.stack([key // (u * u) % u, key // u % u, key % u], 1)
+        return _Grid(key // (u * u * u), pos, u)
+
+    def find(self, model, pos):
+        """Index of the voxel at `pos` of `model`, or -1."""
+        at = torch.searchsorted(self.key, self._key(model, pos)).clamp(max=self.key.numel() - 1)
+        hit = (self.key[at] == self._key(model, pos)) & (pos >= 0).all(1) & (pos < self.u).all(1)
+        return torch.where(hit, at, torch.full_like(at, -1))
+
+    def shift(self, d):
+        return self.find(self.model, self.pos + torch.tensor(d, device="cuda"))
+
+
+def _taps(F):
+    return [(x, y, z) for x in range(F) for y in range(F) for z in range(F)]
+
+
+def _rows(X, index):
+    return torch.where(index[:, None] >= 0, X[index.clamp(min=0)], torch.zeros((), dtype=X.dtype, device="cuda"))
+
+
+def _max_children(fine, coarse, X):
+    """Maximum over the occupied children and the child it comes from (the first of equal ones)."""
+    best = torch.full((coarse.key.numel(), X.shape[1]), -math.inf, dtype=X.dtype, device="cuda")
+    who = torch.full(best.shape, -1, dtype=torch.int64, device="cuda")
+    for d in _taps(2):
+        i = fine.find(coarse.model, 2 * coarse.pos + torch.tensor(d, device="cuda"))
+        v = torch.where(i[:, None] >= 0, X[i.clamp(min=0)], torch.full((), -math.inf, dtype=X.dtype, device="cuda"))
+        better = v > best
+        best = torch.where(better, v, best)
+        who = torch.where(better, i[:, None], who)
+    return best, who
+
+
+def _conv(rows_of, taps, X, W):
+    Y = 0.0
+    for k in range(taps):
+        Y = Y + _rows(X, rows_of(k)) @ W[k]
+    return Y
+
+
+def exact(case, seed):
+    """The gradients of an encoder have no such value: where two children nearly tie, the rounding of
+    the forward sums decides which of them a gradient goes to (see tolerance)."""
+    coords, offs = _batch(case, seed)
+    sizes = torch.from_numpy(np.diff(offs)).cuda()
+    grids = [_Grid(torch.repeat_interleave(torch.arange(len(offs) - 1, device="cuda"), sizes), torch.from_numpy(coords).cuda().long(), case["u"])]
+    for _ in range(_n_levels(case) - 1):
+        grids.append(grids[-1].coarser())
+    x = _inputs(case, seed, [g.key.numel() for g in grids])
+    kind, centred = case["kind"], [(a - 1, b - 1, c - 1) for a, b, c in _taps(3)]
+    D = lambda t: t.double()
+    g = grids[0]
+    if kind == "encoder":
+        X, pooled = D(x["X"]), []
+        for l in range(case["convs"]):
+            Y = _conv(lambda k: grids[l].shift(centred[k]), 27, X, D(x["W"][l]))
+            X = _max_children(grids[l], grids[l + 1], Y.clamp(min=0))[0]
+            pooled.append(X)
+        if case["train"]:
+            return {"pooled": pooled, "dW": [None] * case["convs"], "dX": None}
+        return {"pooled": pooled, "switches": [None] * case["convs"]}
+    W = D(x["W"])
+    if kind == "newbatch":
+        Y = _conv(lambda k: g.shift(centred[k]), 27, D(x["X"]), W)
+        return {"Y": Y, "P": _max_children(g, grids[1], Y.clamp(min=0))[0], "switches": None}
+    if kind == "conv":
+        X, dY = D(x["X"]), D(x["dY"])
+        return {"Y": _conv(lambda k: g.shift(centred[k]), 27, X, W),
+                "dW": torch.stack([_rows(X, g.shift(centred[k])).T @ dY for k in range(27)]),
+                "dX": _conv(lambda k: g.shift(centred[k]), 27, dY, W.flip(0).transpose(1, 2))}
+    if kind == "sconv":
+        F, S, P, out = case["F"], case["stride"], case["pad"], grids[-1]
+        X, dY, field = D(x["X"]), D(x["dY"]), [torch.tensor(f, device="cuda") for f in _taps(F)]
+        read = lambda k: g.find(out.model, out.pos * S - P + field[k])
+
+        def owner(k):
+            q = g.pos + P - field[k]
+            i = out.find(g.model, q // S)
+            return torch.where((q % S == 0).all(1), i, torch.full_like(i, -1))
+        return {"field": None, "Y": _conv(read, F ** 3, X, W), "dW": torch.stack([_rows(X, read(k)).T @ dY for k in range(F ** 3)]),
+                "dX": _conv(owner, F ** 3, dY, W.transpose(1, 2))}
+    who, dY = _max_children(g, grids[1], x["A"])[1], D(x["dY"])
+    U = torch.zeros((g.key.numel(), case["c_in"]), dtype=torch.float64, device="cuda")
+    U.scatter_(0, who, D(x["Xc"]))
+    dU = _conv(lambda k: g.shift(centred[k]), 27, dY, W)
+    return {"Y": _conv(lambda k: g.shift(centred[k]), 27, U, W.flip(0).transpose(1, 2)),
+            "dW": torch.stack([_rows(dY, g.shift(centred[k])).T @ U for k in range(27)]),
+            "dXc": torch.gather(dU, 0, who)}
