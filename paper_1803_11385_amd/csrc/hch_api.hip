@@ -72,6 +72,10 @@ struct Level {
     uint32_t *dmask27 = nullptr;               // [n_total] bit k: neighbour k exists
     uint32_t *dtilemask = nullptr;             // [ceil(n_total/64)] taps present in each tile of the pattern order
     const int32_t *dorder = nullptr;           // [n_total] the level's voxels in pattern order (into hch_levels' sort output)
+    const int32_t *dforder = nullptr;          // the same in the fine order, and its tiles' taps; null on small levels
+    uint32_t *dftilemask = nullptr;
+    const int32_t *rows() const { return dforder ? dforder : dorder; }            // the order the products walk
+    const uint32_t *row_taps() const { return dforder ? dftilemask : dtilemask; }
     uint16_t *dT = nullptr;
     uint8_t *dPhi = nullptr;
     uint32_t *dslot3 = nullptr, *dphi4 = nullptr;   // packed copies of H*,T* and Phi* for the lookups
@@ -93,7 +97,7 @@ void free_level(Level &L)
     void *ptrs[] = {L.dH, L.dV, L.dcoords, L.dnbr, L.dchild, L.dT, L.dPhi, L.dmeta, L.dslot3, L.dphi4, L.dnbr_t, L.dmask27, L.dtilemask};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     L.dH = L.dV = L.dcoords = L.dnbr = L.dchild = L.dmeta = L.dnbr_t = nullptr;
-    L.dmask27 = L.dtilemask = nullptr; L.dorder = nullptr;
+    L.dmask27 = L.dtilemask = L.dftilemask = nullptr; L.dorder = L.dforder = nullptr;
     L.dT = nullptr; L.dPhi = nullptr; L.dslot3 = L.dphi4 = nullptr;
 }
 
@@ -101,6 +105,8 @@ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline unsigned blocks_for(int64_t items) { return (unsigned)((items + 255) / 256); }
 
+// levels with a fine order (see corner_key): below, what it saves no longer pays for its launches
+constexpr int64_t FINE_MIN_VOXELS = 32768;
 constexpr int64_t MAX_GRID_ITEMS = (int64_t)2147483647 * 256;   // grid.x limit * block size
 
 }  // namespace
@@ -117,6 +123,7 @@ struct hch_levels {
     std::vector<int32_t> sort_off;
     uint8_t *d_sort_key = nullptr;
     int32_t *d_tile_hist = nullptr, *d_key_total = nullptr, *d_order = nullptr;
+    uint32_t *d_fine = nullptr;                // everything of the fine order, in one allocation
 };
 
 extern "C" const char *hch_last_error(void) { return g_err.c_str(); }
@@ -127,7 +134,7 @@ extern "C" void hch_free_levels(hch_levels *levels)
     for (Level &L : levels->lv) free_level(L);
     if (levels->d_nbr_prefix) (void)hipFree(levels->d_nbr_prefix);
     if (levels->d_child_prefix) (void)hipFree(levels->d_child_prefix);
-    void *sort_ptrs[] = {levels->d_sort_key, levels->d_tile_hist, levels->d_key_total, levels->d_order};
+    void *sort_ptrs[] = {levels->d_sort_key, levels->d_tile_hist, levels->d_key_total, levels->d_order, levels->d_fine};
     for (void *p : sort_ptrs) if (p) (void)hipFree(p);
     delete levels;
 }
@@ -198,18 +205,42 @@ static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipSt
                            hl->d_nbr_prefix, n_entries, first, (unsigned)(last - first), hl->d_key_total, hl->d_order);
             }
             HCH_LAUNCH_CHECK("pattern_scatter_kernel");
-            hch::TileMaskArgs A{};
-            A.n_levels = l1 - l0;
-            A.tile_prefix[0] = 0;
+            hch::TileMaskArgs A{}, F{};           // tile masks of the pattern order, of the fine order
+            A.n_levels = F.n_levels = l1 - l0;
+            int fine_most = 0;
             for (int l = l0; l < l1; ++l) {
                 const Level &L = hl->lv[l];
-                A.mask27[l - l0] = L.dmask27; A.tile_mask[l - l0] = L.dtilemask; A.order[l - l0] = L.dorder;
-                A.n[l - l0] = (int32_t)L.n_total;
-                A.tile_prefix[l - l0 + 1] = A.tile_prefix[l - l0] + (int32_t)((L.n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
+                const int q = l - l0, stretches = (int)((L.n_total + hch::FINE_TILE - 1) / hch::FINE_TILE);
+                A.tile_mask[q] = L.dtilemask; F.tile_mask[q] = L.dftilemask;
+                A.off[q] = F.off[q] = hl->sort_off[l];
+                A.n[q] = F.n[q] = (int32_t)L.n_total;
+                A.hist_off[q] = hl->set.fine_off[l]; A.hist_tiles[q] = hl->set.fine_tiles[l];
+                A.tile_prefix[q + 1] = A.tile_prefix[q] + stretches;
+                F.tile_prefix[q + 1] = F.tile_prefix[q] + (L.dforder ? stretches : 0);
+                fine_most = std::max(fine_most, hl->set.fine_tiles[l]);
             }
-            const int tiles = A.tile_prefix[A.n_levels];
-            hch::LaunchTimer lt(HCH_KERNEL_ID("tile_mask_kernel"), s, 8.0 * (double)cnt, 0.0);
-            HCH_LAUNCH(hch::tile_mask_kernel, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, s, A);
+            {
+                hch::LaunchTimer lt(HCH_KERNEL_ID("tile_mask_kernel<true>"), s, 4.0 * (double)cnt, 0.0);
+                HCH_LAUNCH(hch::tile_mask_kernel<true>, dim3((unsigned)A.tile_prefix[A.n_levels]), dim3(256), 0, s, A,
+                           (const uint32_t *)hl->set.sorted_mask, hl->set.fine_hist);
+            }
+            HCH_LAUNCH_CHECK("tile_mask_kernel");
+            if (fine_most > 0) {
+                {
+                    hch::LaunchTimer lt(HCH_KERNEL_ID("fine_scan_kernel"), s, 8.0 * hch::FINE_BINS * F.tile_prefix[F.n_levels], 0.0);
+                    HCH_LAUNCH(hch::fine_scan_kernel, dim3(hch::FINE_BINS, (unsigned)(l1 - l0)), dim3(256), 0, s, hl->set, l0);
+                }
+                HCH_LAUNCH_CHECK("fine_scan_kernel");
+                {
+                    hch::LaunchTimer lt(HCH_KERNEL_ID("fine_scatter_kernel"), s, 16.0 * (double)cnt, 0.0);
+                    HCH_LAUNCH(hch::fine_scatter_kernel, dim3((unsigned)fine_most, (unsigned)(l1 - l0)), dim3(256), 0, s, hl->set,
+                               (const int32_t *)hl->d_order, l0);
+                }
+                HCH_LAUNCH_CHECK("fine_scatter_kernel");
+                hch::LaunchTimer lt(HCH_KERNEL_ID("tile_mask_kernel<false>"), s, 4.0 * (double)cnt, 0.0);
+                HCH_LAUNCH(hch::tile_mask_kernel<false>, dim3((unsigned)F.tile_prefix[F.n_levels]), dim3(256), 0, s, F,
+                           (const uint32_t *)hl->set.fine_mask, (int32_t *)nullptr);
+            }
             HCH_LAUNCH_CHECK("tile_mask_kernel");
         }
     }
@@ -713,6 +744,38 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
                 if (hipMalloc((void **)&L.dmask27, std::max<size_t>((size_t)L.n_total, 64) * 4) != hipSuccess) { L.dmask27 = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(mask27) failed"); break; }
                 if (hipMalloc((void **)&L.dtilemask, std::max<size_t>(tiles, 64) * 4) != hipSuccess) { L.dtilemask = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(tile masks) failed"); break; }
                 L.dorder = hl->d_order + hl->sort_off[l];
+            }
+            // the fine order: neighbour sets by position in both orders, the order, its tiles' taps,
+            // the histograms and their totals
+            if (st == HCH_OK) {
+                const size_t na = round_up(std::max<size_t>(n_all, 64), 64);
+                size_t tiles = 0, hist = 0;
+                for (int l = 0; l < n_levels; ++l) {
+                    const int64_t n = hl->lv[l].n_total;
+                    hl->set.n_total[l] = (int32_t)n;
+                    hl->set.fine_off[l] = (int32_t)hist;
+                    hl->set.fine_tiles[l] = n >= FINE_MIN_VOXELS ? (int32_t)((n + hch::FINE_TILE - 1) / hch::FINE_TILE) : 0;
+                    hist += (size_t)hl->set.fine_tiles[l] * hch::FINE_BINS;
+                    if (hl->set.fine_tiles[l]) tiles += (size_t)((n + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
+                }
+                const size_t totals = hist ? (size_t)hch::MAX_LEVELS * hch::FINE_BINS : 0;
+                if (hipMalloc((void **)&hl->d_fine, (na + (hist ? 2 * na : 0) + tiles + hist + totals) * 4) != hipSuccess) { hl->d_fine = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(fine order) failed"); }
+                else {
+                    uint32_t *p = hl->d_fine;
+                    hl->set.sorted_mask = p; p += na;
+                    if (hist) {
+                        hl->set.fine_mask = p; p += na;
+                        hl->set.fine_order = (int32_t *)p; p += na;
+                        hl->set.fine_hist = (int32_t *)p; p += hist;
+                        hl->set.fine_total = (int32_t *)p; p += totals;
+                        for (int l = 0; l < n_levels; ++l)
+                            if (hl->set.fine_tiles[l]) {
+                                hl->lv[l].dforder = hl->set.fine_order + hl->sort_off[l];
+                                hl->lv[l].dftilemask = p;
+                                p += (hl->lv[l].n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE;
+                            }
+                    }
+                }
             }
         }
         if (st == HCH_OK && with_device) {
@@ -1534,13 +1597,13 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
         if (narrow4_ok(n, c_in, c_out) && dtype == HCH_F32 && aligned16(X) && aligned16(W) && aligned16(Y)) {
             const double bytes = (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out) + 4.0 * Kc * c_out;
             return launch_narrow4((const float *)X, L->dnbr, (const float *)W, Y, n, c_in, bytes, s, 0,
-                                  skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr);
+                                  skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr);
         }
         const DirectPlan d = plan_direct(n, c_in, c_out);
         if (d.ok && dtype == HCH_F32 && aligned16(X) && aligned16(W) && aligned16(Y)) {
             const double bytes = (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out * d.splits) + 4.0 * Kc * c_out;
             st = launch_direct(d, (const float *)X, L->dnbr, (const float *)W, d.splits > 1 ? part : Y, n, c_in, c_out, bytes, s, 0,
-                               skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr);
+                               skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr);
             if (st != HCH_OK) return st;
             if (d.splits > 1) st = launch_reduce(part, Y, n * c_out, d.splits, s);
             return st;
@@ -1564,7 +1627,7 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
         st = launch_gemm<hch::A_GATHER, false>(dtype, p, X, W,
                                                p.splits > 1 ? part : Y, L->dnbr, (int)n, c_out, Kc, c_in,
                                                c_out, c_out, n * c_out, bytes, s, 0, 27, 0, 0, L->dnbr_t,
-                                               skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr, n);
+                                               skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr, n);
         if (st != HCH_OK) return st;
         if (p.splits > 1) st = launch_reduce(part, Y, n * c_out, p.splits, s);
         return st;
@@ -1617,7 +1680,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
         if (narrow4_ok(n, c_out, c_in) && dtype == HCH_F32 && aligned16(dY) && aligned16(dX) && aligned16(W)) {
             const double bytes = (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in) + 4.0 * wn;
             return launch_narrow4((const float *)dY, L->dnbr, (const float *)W, dX, n, c_out, bytes, s, 1,
-                                  skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr);
+                                  skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr);
         }
         const DirectPlan d = plan_direct(n, c_out, c_in);
         // (gradients whose rows hold a multiple of 32 channels go to the LDS-tiled kernel's lean loop,
@@ -1625,7 +1688,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
         if (d.ok && c_out % 32 != 0 && dtype == HCH_F32 && aligned16(dY) && aligned16(dX) && aligned16(W)) {
             const double bytes = (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in * d.splits) + 4.0 * wn;
             st = launch_direct(d, (const float *)dY, L->dnbr, (const float *)W, d.splits > 1 ? part : dX, n, c_out, c_in, bytes, s, 1,
-                               skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr);
+                               skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr);
             if (st != HCH_OK) return st;
             if (d.splits > 1) st = launch_reduce(part, dX, n * c_in, d.splits, s);
             return st;
@@ -1639,7 +1702,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
             const double bytes = (double)n * (108.0 + es * c_out + 4.0 * c_in * p.splits) + es * wn;
             st = launch_gemm<hch::A_GATHER, true>(dtype, p, dY, Wlast, p.splits > 1 ? part : dX, L->dnbr, (int)n, c_in, Kd,
                                                   c_out, c_out, c_in, n * c_in, bytes, s, 0, 27, c_out, -per_tap, L->dnbr_t,
-                                                  skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr, n);
+                                                  skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr, n);
             if (st != HCH_OK) return st;
             if (p.splits > 1) st = launch_reduce(part, dX, n * c_in, p.splits, s);
             return st;
@@ -1658,7 +1721,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
         st = launch_gemm<hch::A_GATHER, false>(dtype, p, dY, Wt,
                                                p.splits > 1 ? part : dX, L->dnbr, (int)n, c_in, Kd, c_out,
                                                c_in, c_in, n * c_in, bytes, s, 0, 27, 0, 0, L->dnbr_t,
-                                               skip ? L->dorder : nullptr, skip ? L->dtilemask : nullptr, n);
+                                               skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr, n);
         if (st != HCH_OK) return st;
         if (p.splits > 1) st = launch_reduce(part, dX, n * c_in, p.splits, s);
         return st;

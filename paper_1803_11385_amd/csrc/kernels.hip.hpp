@@ -137,6 +137,13 @@ struct LevelSet {
     int32_t hist_off[MAX_LEVELS];
     int32_t level_tiles[MAX_LEVELS]; // 256-voxel tiles of the index-list kernels at level l
     int32_t level_tile0[MAX_LEVELS]; // flat number of the level's first tile
+    // the second, finer sort (fine_*_kernel): neighbour sets by position of the pattern order and of the
+    // fine order, the fine order itself (level l at sort_off[l]), digit histograms per FINE_TILE
+    // positions (level l at fine_off[l], digit-major; fine_tiles[l] = 0: the level has no fine order)
+    uint32_t *sorted_mask, *fine_mask;
+    int32_t *fine_order, *fine_hist, *fine_total;
+    int32_t fine_off[MAX_LEVELS], fine_tiles[MAX_LEVELS];
+    int32_t n_total[MAX_LEVELS];
     int32_t batch;
 };
 
@@ -152,6 +159,23 @@ __device__ __forceinline__ uint32_t pattern_key(uint32_t mask27)
     // edge-adjacent taps below the centre: 1, 3, 5, 7, 9, 11
 #pragma unroll
     for (int k = 1; k < 13; k += 2) key = (key << 1) | (((mask27 >> k) | (mask27 >> (26 - k))) & 1u);
+    return key;
+}
+
+// Tiles of that order still touch 0.58 / 0.71 / 0.80 of the (64 voxels, tap) pairs at the three
+// finest levels of a 256^3 batch, 0.91 with two voxels thick shells, where 0.33 / 0.43 / 0.49 / 0.62
+// of the (voxel, tap) pairs exist.  A second stable sort of it by the 8 corner neighbours (a corner
+// tells on which side of the surface a voxel lies) leaves 0.39 / 0.57 / 0.68 and 0.68; other choices
+// of 8 bits measured: the 6 faces and 2 corners 0.42 / 0.58 / - / 0.70, the lower edges and 2 corners
+// 0.42 / 0.60 / - / 0.72; all 26 neighbours, in four passes: 0.36 / 0.54 / 0.68 / 0.62.  It costs three
+// launches, so small levels go without (the products use whichever order the level has).
+constexpr int FINE_BINS = 256, FINE_TILE = 1024;
+__device__ __forceinline__ uint32_t corner_key(uint32_t mask27)
+{
+    constexpr int corners[8] = {0, 2, 6, 8, 18, 20, 24, 26};
+    uint32_t key = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) key = (key << 1) | ((mask27 >> corners[q]) & 1u);
     return key;
 }
 
@@ -428,6 +452,93 @@ __global__ __launch_bounds__(256) void pattern_scatter_kernel(
                       S.tile_hist[S.hist_off[lev] + (int64_t)key * S.level_tiles[lev] + (flat - S.level_tile0[lev])];
         for (int w = 0; w < wave; ++w) pos += wcnt[w][key];
         order[pos] = base + i;
+        S.sorted_mask[pos] = S.mask27[lev][base + i];
+    }
+}
+
+// The fine order: a stable counting sort of the pattern order by corner_key, in the manner of the
+// pattern sort above.  tile_mask_kernel counts the keys of
+// every FINE_TILE positions; one workgroup per (key, level) turns a key's counts into offsets; then
+// every voxel finds its rank within its tile and moves, and its neighbour set with it.
+__global__ __launch_bounds__(256) void fine_scan_kernel(LevelSet S, int level_first)
+{
+    __shared__ int32_t sums[256];
+    const int lev = level_first + blockIdx.y, key = blockIdx.x;
+    const int T = S.fine_tiles[lev];
+    if (T == 0) return;
+    int32_t *row = S.fine_hist + S.fine_off[lev] + (int64_t)key * T;
+    const int per = (T + 255) / 256;
+    const int a = min(T, (int)threadIdx.x * per), b = min(T, a + per);
+    int32_t sum = 0;
+    for (int t = a; t < b; ++t) sum += row[t];
+    sums[threadIdx.x] = sum;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+        const int32_t add = (int)threadIdx.x >= o ? sums[threadIdx.x - o] : 0;
+        __syncthreads();
+        sums[threadIdx.x] += add;
+        __syncthreads();
+    }
+    int32_t run = sums[threadIdx.x] - sum;
+    for (int t = a; t < b; ++t) {
+        const int32_t c = row[t];
+        row[t] = run;
+        run += c;
+    }
+    if (threadIdx.x == 255) S.fine_total[lev * FINE_BINS + key] = sums[255];
+}
+
+// grid.y = level; a wavefront takes 256 consecutive positions of the tile, 64 at a time
+__global__ __launch_bounds__(256) void fine_scatter_kernel(LevelSet S, const int32_t *__restrict__ order, int level_first)
+{
+    __shared__ int32_t wcnt[4][FINE_BINS];
+    __shared__ int32_t below[FINE_BINS];
+    const int lev = level_first + blockIdx.y, tile = blockIdx.x, T = S.fine_tiles[lev];
+    if (tile >= T) return;
+    const int n = S.n_total[lev], off = S.sort_off[lev];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t total = S.fine_total[lev * FINE_BINS + threadIdx.x];
+    below[threadIdx.x] = total;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) wcnt[w][threadIdx.x] = 0;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {                   // voxels with a smaller key: prefix of the totals
+        const int32_t add = (int)threadIdx.x >= o ? below[threadIdx.x - o] : 0;
+        __syncthreads();
+        below[threadIdx.x] += add;
+        __syncthreads();
+    }
+    const int32_t first = below[threadIdx.x] - total + S.fine_hist[S.fine_off[lev] + (int64_t)threadIdx.x * T + tile];
+    __syncthreads();
+    below[threadIdx.x] = first;                           // where the tile's first voxel with this key goes
+    uint32_t mask[4], key[4];
+    int rank[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int p = tile * FINE_TILE + wave * 256 + q * 64 + lane;
+        mask[q] = p < n ? S.sorted_mask[off + p] : 0u;
+        key[q] = corner_key(mask[q]);
+        unsigned long long same = __ballot(p < n);        // lanes with the same key (those past the end match nobody)
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const unsigned long long bal = __ballot((key[q] >> b) & 1u);
+            same &= ((key[q] >> b) & 1u) ? bal : ~bal;
+        }
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+        rank[q] = wcnt[wave][key[q]] + before;
+        __builtin_amdgcn_wave_barrier();
+        if (p < n && before == 0) wcnt[wave][key[q]] = rank[q] + __popcll(same);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int p = tile * FINE_TILE + wave * 256 + q * 64 + lane;
+        if (p >= n) continue;
+        int pos = off + below[key[q]] + rank[q];
+        for (int w = 0; w < wave; ++w) pos += wcnt[w][key[q]];
+        S.fine_order[pos] = order[off + p];
+        S.fine_mask[pos] = mask[q];
     }
 }
 
@@ -446,31 +557,48 @@ __global__ __launch_bounds__(256) void index_transpose_kernel(
         for (int t = 0; t < taps; ++t) dst[(int64_t)t * n + r0 + threadIdx.x] = tile[threadIdx.x * taps + t];
 }
 
-// Tap masks of the tiles of the pattern order: tile b of level l covers rows 64b .. 64b+63 of the
-// level's sorted voxel list `order`, and bit k of its mask says whether any of them has
-// neighbour k.  One wavefront per tile; tiles of all levels of the range in one launch
-// (tile_prefix[l - l0] = tiles before level l).
+// Tap masks of the tiles of an order: tile b of level l covers positions 64b .. 64b+63 of it, and bit
+// k of its mask says whether any voxel there has neighbour k.  `mask` holds the neighbour sets by
+// position (level l at off[l - l0]).  One wavefront per tile; tiles of all levels of the range in one
+// launch (tile_prefix[l - l0] = tiles before level l; a level without tiles is left out).
+// HIST: a workgroup's tiles belong to one FINE_TILE stretch, whose corner keys it counts as well
+// (FINE_TILE / 64 = 16 tiles, 4 per wavefront; every level starts a new stretch).
 struct TileMaskArgs {
-    const uint32_t *mask27[MAX_LEVELS];
     uint32_t *tile_mask[MAX_LEVELS];
-    const int32_t *order[MAX_LEVELS];
-    int32_t n[MAX_LEVELS];
-    int32_t tile_prefix[MAX_LEVELS + 1];
+    int32_t off[MAX_LEVELS], n[MAX_LEVELS];
+    int32_t tile_prefix[MAX_LEVELS + 1];              // in workgroups
+    int32_t hist_off[MAX_LEVELS], hist_tiles[MAX_LEVELS];
     int32_t n_levels;
 };
 constexpr int PATTERN_TILE = 64;
-__global__ __launch_bounds__(256) void tile_mask_kernel(TileMaskArgs A)
+template <bool HIST>
+__global__ __launch_bounds__(256) void tile_mask_kernel(TileMaskArgs A, const uint32_t *__restrict__ mask, int32_t *__restrict__ hist)
 {
-    const int flat = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (flat >= A.tile_prefix[A.n_levels]) return;
+    constexpr int PER_WAVE = FINE_TILE / PATTERN_TILE / 4;
+    __shared__ int32_t cnt[HIST ? FINE_BINS : 1];
+    const int block = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int l = 0;
-    while (l + 1 < A.n_levels && A.tile_prefix[l + 1] <= flat) ++l;
-    const int b = flat - A.tile_prefix[l];
-    const int r = b * PATTERN_TILE + lane;
-    uint32_t m = r < A.n[l] ? A.mask27[l][A.order[l][r]] : 0u;
+    while (l + 1 < A.n_levels && A.tile_prefix[l + 1] <= block) ++l;
+    const int stretch = block - A.tile_prefix[l];
+    const bool count = HIST && A.hist_tiles[l] > 0;
+    if constexpr (HIST) {
+        cnt[threadIdx.x] = 0;
+        __syncthreads();
+    }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) m |= (uint32_t)__shfl_xor((int)m, d);
-    if (lane == 0) A.tile_mask[l][b] = m;
+    for (int q = 0; q < PER_WAVE; ++q) {
+        const int b = stretch * (FINE_TILE / PATTERN_TILE) + wave * PER_WAVE + q;
+        const int r = b * PATTERN_TILE + lane;
+        uint32_t m = r < A.n[l] ? mask[A.off[l] + r] : 0u;
+        if constexpr (HIST) { if (count && r < A.n[l]) atomicAdd(&cnt[corner_key(m)], 1); }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) m |= (uint32_t)__shfl_xor((int)m, d);
+        if (lane == 0 && b * PATTERN_TILE < A.n[l]) A.tile_mask[l][b] = m;
+    }
+    if constexpr (HIST) {
+        __syncthreads();
+        if (count) hist[A.hist_off[l] + (int64_t)threadIdx.x * A.hist_tiles[l] + stretch] = cnt[threadIdx.x];
+    }
 }
 
 // For every coarse voxel the global data indices, at the next finer level, of its 8 children
