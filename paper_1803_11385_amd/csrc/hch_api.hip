@@ -16,6 +16,7 @@
 #include "kernels.hip.hpp"
 #include "direct.hip.hpp"
 #include "gemm_bf16.hip.hpp"
+#include "split_wgrad.hip.hpp"
 #include "psh_device.hip.hpp"
 #include "profile.hpp"
 #include "psh_build.hpp"
@@ -1480,6 +1481,54 @@ static hch_status launch_reduce(const float *part, float *out, int64_t n, int sp
     return HCH_OK;
 }
 
+// The weight gradient on split operands (wgrad_split_kernel): rows of `nbr` hold `taps` indices into
+// the x_rows rows of X; `max_slices` partial sums fit the caller's workspace.
+struct WgradSplitPlan { bool ok; int slices, m_tiles, n_tiles; };
+
+static WgradSplitPlan plan_wgrad_split(int64_t n, int64_t x_rows, int c, int N, int taps, int64_t max_slices)
+{
+    WgradSplitPlan p{false, 1, 1, 1};
+    const int64_t lim = (int64_t)1 << 31;
+    // 32-bit byte offsets reach everything, a negative one nothing; a workgroup's rows touch 28 taps
+    if (x_rows * c * 4 >= lim || n * N * 4 >= lim || n * taps * 4 >= lim || x_rows >= (1 << 23) || c * 4 >= (1 << 23) || (c < 16 && taps > hch::WG_UNITS)) return p;
+    if (N <= 16 || (int64_t)taps * c < 16) return p;
+    // a workgroup needs some blocks of voxels to get going, gemm_f32_kernel is ahead on little work: 16 -> 32
+    // at 32k voxels 21.7 us against 30.3, 32 -> 64 at 8k 21 against 34; 32 -> 64 at 32k 45 against 39, 64 -> 128
+    // at 8k 50 against 39, 16 -> 32 at 110k 42 against 38 (its path for channel counts that are not a
+    // multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 36 against 22)
+    if (c % 4 == 0 && N % 4 == 0 && (double)n * c * N < 40e6) return p;
+    const int64_t m_tiles = ((int64_t)taps * c + hch::WG_UNITS * 16 - 1) / (hch::WG_UNITS * 16), n_tiles = N <= 32 ? 1 : (N + 63) / 64;
+    // one workgroup per CU; as a multiple of 8 (whole slices per XCD) where there are that many
+    int64_t s = std::max<int64_t>(1, 256 / (m_tiles * n_tiles));
+    s = std::min({s, (n + hch::WG_VOX - 1) / hch::WG_VOX, max_slices});
+    if (s >= 8) s = s / 8 * 8;
+    p.ok = true; p.slices = (int)s; p.m_tiles = (int)m_tiles; p.n_tiles = (int)n_tiles;
+    return p;
+}
+
+static hch_status launch_wgrad_split(const WgradSplitPlan &p, const float *X, const float *dY, float *out, float *part,
+                                     const int32_t *nbr, const int32_t *order, int64_t n, int64_t x_rows, int c, int N, int taps,
+                                     double bytes, hipStream_t s)
+{
+    const int64_t wsize = (int64_t)taps * c * N;
+    {
+        const bool c16 = c % 16 == 0;
+        const int kid = N <= 32 ? (c16 ? HCH_KERNEL_ID("wgrad_split_kernel<2, true>") : HCH_KERNEL_ID("wgrad_split_kernel<2, false>"))
+                                : (c16 ? HCH_KERNEL_ID("wgrad_split_kernel<4, true>") : HCH_KERNEL_ID("wgrad_split_kernel<4, false>"));
+        hch::LaunchTimer lt(kid, s, bytes + 4.0 * wsize * p.slices, 2.0 * wsize * n);
+        float *dst = p.slices == 1 ? out : part;
+        const dim3 grid((unsigned)(p.slices * p.m_tiles * p.n_tiles));
+#define HCH_WGRAD_CASE(NT_, C16_)                                                                                  \
+        HCH_LAUNCH((hch::wgrad_split_kernel<NT_, C16_>), grid, dim3(512), 0, s, X, dY, dst, nbr, order, taps * c, N, \
+                   (int)n, x_rows, c, taps, p.slices, p.m_tiles, p.n_tiles, wsize)
+        if (N <= 32) { if (c16) HCH_WGRAD_CASE(2, true); else HCH_WGRAD_CASE(2, false); }
+        else { if (c16) HCH_WGRAD_CASE(4, true); else HCH_WGRAD_CASE(4, false); }
+#undef HCH_WGRAD_CASE
+    }
+    HCH_LAUNCH_CHECK("wgrad_split_kernel");
+    return p.slices > 1 ? launch_reduce(part, out, wsize, p.slices, s) : HCH_OK;
+}
+
 // workspace layout, all offsets 256-byte aligned:
 //   columns algorithm : [ column matrix | split-K partial sums ]
 //   fused algorithm   : [ flipped+transposed weights (bwd_data only) | split-K partial sums ]
@@ -1494,7 +1543,8 @@ static bool fwd_transposed_weights(hch_dtype dtype, int c_in, int c_out)
     return dtype == HCH_BF16 && c_in % hch::BF16_BK == 0 && c_out % 8 == 0;
 }
 
-static WsLayout ws_layout(const Level &L, int c_in, int c_out, hch_dtype dtype, hch_ws_kind kind, hch_algo algo)
+// least: what a call needs; else what it can make use of (the query's answer)
+static WsLayout ws_layout(const Level &L, int c_in, int c_out, hch_dtype dtype, hch_ws_kind kind, hch_algo algo, bool least = false)
 {
     const size_t Kc = (size_t)27 * c_in, n = (size_t)L.n_total;
     WsLayout w{0, 0};
@@ -1517,7 +1567,12 @@ static WsLayout ws_layout(const Level &L, int c_in, int c_out, hch_dtype dtype, 
     } else if (kind == HCH_WS_BWD_WEIGHT) {
         const GemmPlan p = plan_wgrad(L.n_total, c_in, c_out, 27, k_gran(dtype));
         if (algo == HCH_ALGO_COLUMNS) w.first_bytes = round_up(n * Kc * elem_size(dtype), 256);
-        if (p.splits > 1) w.part_bytes = round_up((size_t)p.splits * Kc * c_out * 4, 256);
+        int splits = p.splits;
+        if (algo == HCH_ALGO_FUSED && dtype == HCH_F32 && !least) {
+            const WgradSplitPlan q = plan_wgrad_split(L.n_total, L.n_total, c_in, c_out, 27, INT32_MAX);
+            if (q.ok) splits = std::max(splits, q.slices);
+        }
+        if (splits > 1) w.part_bytes = round_up((size_t)splits * Kc * c_out * 4, 256);
     }
     return w;
 }
@@ -1761,16 +1816,17 @@ static hch_status conv_bwd_weight_impl(const hch_levels *levels, int32_t level, 
     const Level *L;
     const bool resident = algo == HCH_ALGO_COLUMNS_RESIDENT;     // the column matrix is in the workspace already
     if (resident) algo = HCH_ALGO_COLUMNS;
+    const bool skip = algo == HCH_ALGO_FUSED;                    // absent taps may be left out
     if (algo == HCH_ALGO_FUSED_DENSE) algo = HCH_ALGO_FUSED;
     hch_status st = conv_args(levels, level, dtype, X, dY, dW, c_in, c_out, workspace, algo, &L, who);
     if (st != HCH_OK) return st;
-    if (ws_bytes < hch_conv_workspace_bytes(levels, level, c_in, c_out, dtype, HCH_WS_BWD_WEIGHT, algo))
+    const WsLayout w = ws_layout(*L, c_in, c_out, dtype, HCH_WS_BWD_WEIGHT, algo, true);
+    if (ws_bytes < std::max<size_t>(256, w.first_bytes + w.part_bytes))
         return fail(HCH_EWORKSPACE, std::string(who) + ": workspace too small");
     hipStream_t s = (hipStream_t)stream;
     const int Kc = 27 * c_in;
     const int64_t n = L->n_total;
     const double es = elem_size(dtype);
-    const WsLayout w = ws_layout(*L, c_in, c_out, dtype, HCH_WS_BWD_WEIGHT, algo);
     const GemmPlan p = plan_wgrad(n, c_in, c_out, 27, k_gran(dtype));
     const int64_t wsize = (int64_t)Kc * c_out;
     float *part = (float *)((char *)workspace + w.first_bytes);
@@ -1778,6 +1834,12 @@ static hch_status conv_bwd_weight_impl(const hch_levels *levels, int32_t level, 
 
     // dW[Kc x c_out] = col^T[Kc x N] . dY[N x c_out], reduction over the voxels split in slices
     if (algo == HCH_ALGO_FUSED) {
+        if (skip && dtype == HCH_F32 && L->rows()) {
+            const WgradSplitPlan q = plan_wgrad_split(n, n, c_in, c_out, 27, std::max<int64_t>(1, (int64_t)(ws_bytes / (4 * (size_t)wsize))));
+            if (q.ok)
+                return launch_wgrad_split(q, (const float *)X, (const float *)dY, dW, part, L->dnbr, L->rows(), n, n, c_in, c_out, 27,
+                                          (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out), s);
+        }
         const double bytes = (double)n * (108.0 + es * c_in + es * c_out) + 4.0 * wsize * p.splits;
         st = launch_gemm<hch::A_GATHER_T, false>(dtype, p, X, dY, dst,
                                                  L->dnbr, Kc, c_out, (int)n, c_in, c_out, c_out, wsize, bytes, s, 0, 27, 0, 0, L->dnbr_t,
