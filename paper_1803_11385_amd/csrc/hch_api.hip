@@ -17,6 +17,7 @@
 #include "direct.hip.hpp"
 #include "gemm_bf16.hip.hpp"
 #include "split_wgrad.hip.hpp"
+#include "split_conv.hip.hpp"
 #include "psh_device.hip.hpp"
 #include "profile.hpp"
 #include "psh_build.hpp"
@@ -1529,6 +1530,63 @@ static hch_status launch_wgrad_split(const WgradSplitPlan &p, const float *X, co
     return p.slices > 1 ? launch_reduce(part, out, wsize, p.slices, s) : HCH_OK;
 }
 
+// Forward product and data gradient on split operands (conv_split_kernel); `max_splits` partial results fit
+// the caller's workspace.
+struct ConvSplitPlan { bool ok; int nt, splits; unsigned m_tiles; };
+
+static ConvSplitPlan plan_conv_split(int64_t n, int c, int N, int max_splits)
+{
+    ConvSplitPlan p{false, 4, 1, 0};
+    const int64_t lim = (int64_t)1 << 31;
+    // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors
+    if (n >= (1 << 23) || c * 4 >= (1 << 23) || n * c * 4 >= lim || n * 108 >= lim || (int64_t)108 * c * N >= lim) return p;
+    p.nt = N <= 16 ? 1 : (N <= 32 ? 2 : 4);
+    const int64_t n_tiles = (N + 16 * p.nt - 1) / (16 * p.nt);
+    p.m_tiles = (unsigned)((n + 63) / 64);
+    // 4 workgroups of 64 rows per CU (wider ones of 128 rows, two per CU, were slower from 2 500 to
+    // 280 000 voxels: 32 -> 64 at 280k 130 against 116 us); small levels split the reduction to fill them
+    const int64_t blocks = p.m_tiles * n_tiles, steps = (int64_t)27 * ((c + 7) / 8) / 4;
+    if (blocks < 512) p.splits = (int)std::max<int64_t>(1, std::min<int64_t>({1024 / blocks, steps / 6, max_splits}));
+    p.ok = true;
+    return p;
+}
+
+// transposed: W(t, k, n) = W[26 - t][n][k]
+static hch_status launch_conv_split(const ConvSplitPlan &p, const Level &L, const float *X, const float *W, float *out, float *part,
+                                    int64_t n, int c, int N, bool transposed, double bytes, hipStream_t s)
+{
+    float *dst = p.splits > 1 ? part : out;
+    const unsigned n_tiles = (unsigned)((N + 16 * p.nt - 1) / (16 * p.nt));
+    const bool fast = c % 32 == 0;
+    static int ids[3][2][2];                           // [columns][fast][transposed]
+    static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
+    (void)ids_ready;
+    int &id = ids[p.nt / 2][fast][transposed];
+    if (id < 0) {
+        char nm[96];
+        snprintf(nm, sizeof nm, "conv_split_kernel<%d, %s, %s>", p.nt, fast ? "true" : "false", transposed ? "true" : "false");
+        id = hch::Profiler::get().id_for(nm);
+    }
+    {
+        hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
+        const dim3 grid(hch::skip_grid(p.m_tiles, hch::skip_chunk(p.m_tiles, 1)), n_tiles, (unsigned)p.splits);
+        const int vec_out = N % 4 == 0 && aligned16(dst);
+#define HCH_CONV_SPLIT(NT_, F_, T_)                                                                            \
+        HCH_LAUNCH((hch::conv_split_kernel<NT_, F_, T_>), grid, dim3(256), 0, s, X, W, dst, L.dnbr, L.rows(),  \
+                   (const uint32_t *)L.row_taps(), (const uint32_t *)L.dmask27, (int)n, N, c, p.m_tiles, n * N, vec_out)
+#define HCH_CONV_SPLIT_FT(NT_)                                                                                 \
+        do {                                                                                                   \
+            if (fast) { if (transposed) HCH_CONV_SPLIT(NT_, true, true); else HCH_CONV_SPLIT(NT_, true, false); } \
+            else { if (transposed) HCH_CONV_SPLIT(NT_, false, true); else HCH_CONV_SPLIT(NT_, false, false); } \
+        } while (0)
+        if (p.nt == 1) HCH_CONV_SPLIT_FT(1); else if (p.nt == 2) HCH_CONV_SPLIT_FT(2); else HCH_CONV_SPLIT_FT(4);
+#undef HCH_CONV_SPLIT_FT
+#undef HCH_CONV_SPLIT
+    }
+    HCH_LAUNCH_CHECK("conv_split_kernel");
+    return p.splits > 1 ? launch_reduce(part, out, n * N, p.splits, s) : HCH_OK;
+}
+
 // workspace layout, all offsets 256-byte aligned:
 //   columns algorithm : [ column matrix | split-K partial sums ]
 //   fused algorithm   : [ flipped+transposed weights (bwd_data only) | split-K partial sums ]
@@ -1663,6 +1721,12 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
             if (d.splits > 1) st = launch_reduce(part, Y, n * c_out, d.splits, s);
             return st;
         }
+        if (skip && dtype == HCH_F32 && L->rows()) {
+            const ConvSplitPlan q = plan_conv_split(n, c_in, c_out, p.splits);
+            if (q.ok)
+                return launch_conv_split(q, *L, (const float *)X, (const float *)W, Y, part, n, c_in, c_out, false,
+                                         (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out * q.splits) + 4.0 * Kc * c_out, s);
+        }
         const double bytes = (double)n * (108.0 + es * c_in + 4.0 * c_out * p.splits) + es * Kc * c_out;
         if (fwd_transposed_weights(dtype, c_in, c_out) && aligned16(X) && aligned16(W) && aligned16(workspace)) {
             const int64_t wn = (int64_t)Kc * c_out, per_tap = (int64_t)c_in * c_out;
@@ -1749,6 +1813,12 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
             return st;
         }
         const GemmPlan p = plan_rows(n, c_in, Kd, true, k_gran(dtype));
+        if (skip && dtype == HCH_F32 && L->rows()) {
+            const ConvSplitPlan q = plan_conv_split(n, c_out, c_in, p.splits);
+            if (q.ok)
+                return launch_conv_split(q, *L, (const float *)dY, (const float *)W, dX, part, n, c_out, c_in, true,
+                                         (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in * q.splits) + 4.0 * wn, s);
+        }
         if (c_out % k_gran(dtype) == 0 && c_in % 4 == 0 && aligned16(dY) && aligned16(W)) {
             // the LDS-tiled kernel reads W[27][c_in][c_out] in place as the flipped, transposed
             // matrix: tap 26 - t of the weights for rows t*c_out .. (t+1)*c_out - 1

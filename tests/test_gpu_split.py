@@ -1,0 +1,157 @@
+"""The products on split operands (fp32 inputs cut into bf16 pieces, conv_split_kernel and
+wgrad_split_kernel) and the finer of the two row orders, at the sizes where they can go wrong:
+channel counts around the tiles of 16, 32 and 64 and with remainders of 8 and of 4, a single voxel,
+one voxel around the 64- and 128-row tiles, levels with and without a fine order.
+
+The reference is the definition in fp64 over the oracle's neighbour lists.  Bound: every product is
+exact to 2^-23.4 (what the six piece products leave out), a sum of K terms is rounded about
+K / 32 times to 2^-24 of its size, K <= 27 * 64 forward and <= 400 voxels per partial sum of the
+weight gradient, and partial sums add up to 256 more roundings: below 2^-24 * (1.5 + sqrt(256)) ~ 1e-6
+of the result's norm in any order."""
+import numpy as np
+import pytest
+
+import synth_shapes as S
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+hch = pytest.importorskip("paper_1803_11385_amd")
+
+BOUND = 1e-6
+
+
+def _workspace(nbytes):
+    t = torch.full((max(nbytes, 256) + 256,), 255, dtype=torch.uint8, device="cuda")
+    off = (-t.data_ptr()) % 256
+    return t[off: off + max(nbytes, 256)]
+
+
+def _ws(lv, l, ci, co):
+    return _workspace(max(hch.hch_conv_workspace_bytes(lv, l, ci, co, hch.HCH_F32, k, hch.HCH_ALGO_FUSED)
+                          for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT)))
+
+
+def _run(lv, l, X, W, G):
+    n, ci = X.shape
+    co = G.shape[1]
+    Y = torch.full((n, co), float("nan"), device="cuda")
+    dX = torch.full((n, ci), float("nan"), device="cuda")
+    dW = torch.full((27, ci, co), float("nan"), device="cuda")
+    a = hch.HCH_ALGO_FUSED
+    hch.hch_conv_fwd(lv, l, hch.HCH_F32, X, W, Y, ci, co, _ws(lv, l, ci, co), a)
+    hch.hch_conv_bwd_data(lv, l, hch.HCH_F32, G, W, dX, ci, co, _ws(lv, l, ci, co), a)
+    hch.hch_conv_bwd_weight(lv, l, hch.HCH_F32, X, G, dW, ci, co, _ws(lv, l, ci, co), a)
+    return Y, dX, dW
+
+
+def _reference(nbr, X, W, G):
+    nb = torch.from_numpy(nbr.astype(np.int64)).cuda()
+    X, W, G = X.double(), W.double(), G.double()
+
+    def rows(T, k):
+        return torch.where(nb[:, k:k + 1] >= 0, T[nb[:, k].clamp(min=0)], torch.zeros((), dtype=T.dtype, device="cuda"))
+    Y = sum(rows(X, k) @ W[k] for k in range(27))
+    dX = sum(rows(G, k) @ W[26 - k].T for k in range(27))
+    dW = torch.stack([rows(X, k).T @ G for k in range(27)])
+    return Y, dX, dW
+
+
+def _check(got, want):
+    for g, w, what in zip(got, want, ("Y", "dX", "dW")):
+        err = float((g.double() - w).norm() / w.norm())
+        assert err < BOUND, f"{what}: {err:.2e}"          # NaN fails too
+
+
+@pytest.fixture(scope="module")
+def batch(oracle):
+    coords, offs, _ = S.config_batch(2)
+    return hch.hch_build_levels(coords, offs, 64, 3), oracle.build_hierarchy(coords, offs, 64, 3)
+
+
+@pytest.mark.parametrize("level", [0, 1, 2])            # 126k and 39k voxels with a fine order, 10k without
+@pytest.mark.parametrize("ci,co", [(3, 16), (5, 7), (16, 32), (18, 22), (24, 40), (33, 17), (50, 50), (64, 64), (96, 20), (32, 130)])
+def test_products_on_split_operands(oracle, batch, level, ci, co):
+    lv, olv = batch
+    n = olv[level].Ntot
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * level + 10 * ci + co)
+    X, W, G = (torch.randn(s, device="cuda", generator=g) for s in ((n, ci), (27, ci, co), (n, co)))
+    _check(_run(lv, level, X, W, G), _reference(oracle.neighbours(olv[level]), X, W, G))
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 1000])
+@pytest.mark.parametrize("ci,co", [(33, 50), (64, 18)])
+def test_small_batches_in_any_order(oracle, n, ci, co):
+    """Voxels in an order of their own (not by position), in two models."""
+    rng = np.random.default_rng(n)
+    pos = rng.permutation(12 ** 3)[:n]
+    coords = np.stack([pos // 144, pos // 12 % 12, pos % 12], 1).astype(np.int32)
+    offs = [0, n // 3, n] if n >= 3 else [0, n]
+    lv = hch.hch_build_levels(coords, offs, 16, 1)
+    nbr = oracle.neighbours(oracle.build_hierarchy(coords, offs, 16, 1)[0])
+    X, W, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda() for s in ((n, ci), (27, ci, co), (n, co)))
+    _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e12])
+def test_any_scale(oracle, batch, scale):
+    """The pieces have the exponent range of fp32: nothing is lost for small or large numbers."""
+    lv, olv = batch
+    n = olv[2].Ntot
+    X, W, G = (torch.randn(s, device="cuda") for s in ((n, 50), (27, 50, 50), (n, 50)))
+    X, G = X * scale, G * scale
+    W = W / max(scale, 1.0)
+    got, want = _run(lv, 2, X, W, G), _reference(oracle.neighbours(olv[2]), X, W, G)
+    _check(got[:2], want[:2])
+    if scale >= 1e-12:
+        _check([got[2]], [want[2]])
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.2e38])
+def test_numbers_that_are_not_finite(oracle, batch, value):
+    """One infinity, NaN or number whose products leave the range: exactly the results it takes part
+    in are not finite (or as large as they come), the others keep their values."""
+    lv, olv = batch
+    n = olv[2].Ntot
+    nbr = oracle.neighbours(olv[2])
+    X, W, G = (torch.randn(s, device="cuda") for s in ((n, 50), (27, 50, 50), (n, 50)))
+    clean = _run(lv, 2, X, W, G)
+    v = n // 2
+    X[v, 7] = value
+    G[v, 9] = value
+    Y, dX, dW = _run(lv, 2, X, W, G)
+    near = torch.zeros(n, dtype=torch.bool, device="cuda")
+    near[torch.from_numpy(np.unique(nbr[v][nbr[v] >= 0]).astype(np.int64)).cuda()] = True
+    for got, ref in ((Y, clean[0]), (dX, clean[1])):
+        assert torch.isfinite(got[~near]).all()
+        err = (got[~near].double() - ref[~near].double()).norm() / ref.double().norm()
+        assert float(err) < BOUND
+        big = ~torch.isfinite(got[near]) | (got[near].abs() > 1e35)
+        assert bool(big.all())
+    hit = torch.zeros((27, 50, 50), dtype=torch.bool, device="cuda")
+    for k in range(27):
+        if (nbr[:, k] == v).any():
+            hit[k, 7, :] = True                          # X[v][7] times some row of G
+        if nbr[v, k] >= 0:
+            hit[k, :, 9] = True                          # some row of X times G[v][9]
+    assert torch.isfinite(dW[~hit]).all()
+    assert float((dW[~hit].double() - clean[2][~hit].double()).norm() / clean[2].double().norm()) < BOUND
+    assert bool((~torch.isfinite(dW[hit]) | (dW[hit].abs() > 1e35)).all())
+
+
+def test_weight_gradient_with_the_smallest_workspace(oracle, batch):
+    """A workspace that holds fewer partial sums than the query suggests gives the same result."""
+    lv, olv = batch
+    n, ci, co = olv[0].Ntot, 32, 64
+    X, G = torch.randn((n, ci), device="cuda"), torch.randn((n, co), device="cuda")
+    full = hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_WEIGHT, hch.HCH_ALGO_FUSED)
+    want = _reference(oracle.neighbours(olv[0]), X, torch.zeros((27, ci, co), device="cuda"), G)[2]
+    for part in (104, 128):
+        ws = _workspace(part * 27 * ci * co * 4)
+        assert ws.numel() <= full
+        dW = torch.full((27, ci, co), float("nan"), device="cuda")
+        hch.hch_conv_bwd_weight(lv, 0, hch.HCH_F32, X, G, dW, ci, co, ws, hch.HCH_ALGO_FUSED)
+        _check([dW], [want])
+    with pytest.raises(hch.HchError):
+        hch.hch_conv_bwd_weight(lv, 0, hch.HCH_F32, X, G, dW, ci, co, _workspace(8 * 27 * ci * co * 4), hch.HCH_ALGO_FUSED)
