@@ -382,7 +382,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         if (cells >= ((int64_t)1 << 31) / hch::PSH_CLASSES || vox >= ((int64_t)1 << 31) || slots >= ((int64_t)1 << 31))
             return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: offset tables exceed 32-bit indexing");
         hch::PairDesc *d_desc = nullptr;
-        int32_t *d_cnt = nullptr, *d_first = nullptr, *d_fill = nullptr, *d_bucket = nullptr, *d_members = nullptr;
+        int32_t *d_cnt = nullptr, *d_first = nullptr, *d_sums = nullptr, *d_fill = nullptr, *d_bucket = nullptr, *d_members = nullptr;
         int32_t *d_counters = nullptr, *d_free = nullptr;
         uint32_t *d_phi = nullptr, *d_res = nullptr;
         int2 *d_cells = nullptr;
@@ -390,6 +390,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         HCH_HIP(hipMemcpyAsync(d_desc, desc.data(), desc.size() * sizeof(hch::PairDesc), hipMemcpyHostToDevice, s));
         if ((st = tmp.get((void **)&d_cnt, (size_t)cells * 4, 0, s)) != HCH_OK) return st;
         if ((st = tmp.get((void **)&d_first, (size_t)cells * 4, -1, s)) != HCH_OK) return st;
+        if ((st = tmp.get((void **)&d_sums, ((size_t)cells / hch::PSH_SCAN + 1) * 4, -1, s)) != HCH_OK) return st;
         if ((st = tmp.get((void **)&d_fill, (size_t)cells * 4, 0, s)) != HCH_OK) return st;
         if ((st = tmp.get((void **)&d_phi, (size_t)cells * 4, 0, s)) != HCH_OK) return st;
         if ((st = tmp.get((void **)&d_bucket, (size_t)vox * 4, -1, s)) != HCH_OK) return st;
@@ -404,9 +405,11 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         HCH_HIP(hipMemsetAsync(d_fail, 0, (size_t)n_pairs * 4, s));
 
         const dim3 gv((unsigned)((max_n + 255) / 256), (unsigned)na), gc((unsigned)((max_r3 + 255) / 256), (unsigned)na);
-        const dim3 gs((unsigned)((max_m3 + 255) / 256), (unsigned)na);
+        const dim3 gs((unsigned)((max_m3 + hch::PSH_FREE - 1) / hch::PSH_FREE), (unsigned)na);
         HCH_LAUNCH(hch::psh_count_kernel, gv, dim3(256), 0, s, d_desc, d_cnt, d_bucket);
-        HCH_LAUNCH(hch::psh_scan_kernel, dim3(1), dim3(1024), 0, s, d_cnt, d_first, (int)cells);
+        const unsigned stretches = (unsigned)((cells + hch::PSH_SCAN - 1) / hch::PSH_SCAN);
+        HCH_LAUNCH(hch::psh_sum_kernel, dim3(stretches), dim3(256), 0, s, d_cnt, d_sums, (int)cells);
+        HCH_LAUNCH(hch::psh_scan_kernel, dim3(stretches), dim3(256), 0, s, d_cnt, d_sums, d_first, (int)cells);
         HCH_LAUNCH(hch::psh_fill_kernel, gv, dim3(256), 0, s, d_desc, d_bucket, d_first, d_fill, d_members, d_res);
         HCH_LAUNCH(hch::psh_classify_kernel, gc, dim3(256), 0, s, d_desc, d_cnt, d_class_count, d_cells, cells);
         HCH_LAUNCH_CHECK("psh construction");
@@ -823,9 +826,9 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
             if (st == HCH_OK) {
                 hipError_t e = hipMemsetAsync(d_cnt, 0, (size_t)n_levels * 8, s);
                 for (int l = 0; l < n_levels && e == hipSuccess; ++l) {
-                    const int64_t items = hl->lv[l].n_total * 27;
-                    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (items + 255) / 256));
-                    HCH_LAUNCH(hch::count_valid_kernel, dim3(grid), dim3(256), 0, s, hl->lv[l].dnbr, items, d_cnt + l);
+                    const int64_t n = hl->lv[l].n_total;
+                    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(512, (n + 1023) / 1024));
+                    HCH_LAUNCH(hch::count_taps_kernel, dim3(grid), dim3(256), 0, s, (const uint32_t *)hl->lv[l].dmask27, n, d_cnt + l);
                     e = hipGetLastError();
                 }
                 if (e == hipSuccess) e = hipMemcpyAsync(h_cnt.data(), d_cnt, (size_t)n_levels * 8, hipMemcpyDeviceToHost, s);

@@ -1602,16 +1602,18 @@ __global__ __launch_bounds__(256) void mfma_probe_kernel(float *__restrict__ sin
     sink[(int64_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-// number of entries >= 0 in an index list (the occupied neighbours of a level: the nnz of the
-// traffic model); count must be zero before the launch
-__global__ __launch_bounds__(256) void count_valid_kernel(const int32_t *__restrict__ idx, int64_t n,
-                                                          unsigned long long *__restrict__ count)
+// number of existing neighbours: bits set in the per-voxel tap masks
+__global__ __launch_bounds__(256) void count_taps_kernel(const uint32_t *__restrict__ mask27, int64_t n,
+                                                         unsigned long long *__restrict__ count)
 {
+    __shared__ int32_t part[4];
     int local = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) local += idx[i] >= 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) local += __popc(mask27[i]);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) local += __shfl_xor(local, d);
-    if ((threadIdx.x & 63) == 0 && local) atomicAdd(count, (unsigned long long)local);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = local;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(count, (unsigned long long)(part[0] + part[1] + part[2] + part[3]));
 }
 
 // ---------------------------------------------------------------------------------------

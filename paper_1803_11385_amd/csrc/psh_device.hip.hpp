@@ -55,26 +55,56 @@ __global__ __launch_bounds__(256) void psh_count_kernel(const PairDesc *__restri
     atomicAdd(&cnt[P.cell_base + g], 1);
 }
 
-// exclusive prefix sum of `n` counts, one workgroup of 1024 threads (the arrays here have at most
-// a few million entries)
-__global__ __launch_bounds__(1024) void psh_scan_kernel(const int32_t *__restrict__ in, int32_t *__restrict__ out, int n)
+// Exclusive prefix sum of `n` counts in two launches: the sum of every PSH_SCAN counts, then each
+// stretch on top of the stretches before it (a few hundred at most, added up by its workgroup).  One
+// workgroup that walked through all of them took 290 us for the 140 000 cells of a 256^3 batch of 8.
+constexpr int PSH_SCAN = 2048;       // 8 per thread, consecutive
+__global__ __launch_bounds__(256) void psh_sum_kernel(const int32_t *__restrict__ in, int32_t *__restrict__ sums, int n)
 {
-    __shared__ int32_t part[1024];
-    const int t = threadIdx.x;
-    const int per = (n + 1023) / 1024;
-    const int a = min(n, t * per), b = min(n, a + per);
+    __shared__ int32_t part[4];
     int32_t s = 0;
-    for (int i = a; i < b; ++i) s += in[i];
-    part[t] = s;
+#pragma unroll
+    for (int q = 0; q < PSH_SCAN / 256; ++q) {
+        const int i = (int)blockIdx.x * PSH_SCAN + q * 256 + (int)threadIdx.x;
+        s += i < n ? in[i] : 0;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {            // inclusive scan of the 1024 partial sums
-        const int32_t v = t >= d ? part[t - d] : 0;
-        __syncthreads();
-        part[t] += v;
+    if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+__global__ __launch_bounds__(256) void psh_scan_kernel(const int32_t *__restrict__ in, const int32_t *__restrict__ sums,
+                                                       int32_t *__restrict__ out, int n)
+{
+    __shared__ int32_t part[256];
+    constexpr int PER = PSH_SCAN / 256;
+    const int t = threadIdx.x, i0 = (int)blockIdx.x * PSH_SCAN + t * PER;
+    int32_t before = 0;
+    for (int q = t; q < (int)blockIdx.x; q += 256) before += sums[q];
+    int32_t v[PER], s = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { v[q] = i0 + q < n ? in[i0 + q] : 0; s += v[q]; }
+    part[t] = before;
+    __syncthreads();
+    for (int d = 128; d >= 1; d >>= 1) {
+        if (t < d) part[t] += part[t + d];
         __syncthreads();
     }
-    int32_t run = part[t] - s;
-    for (int i = a; i < b; ++i) { const int32_t v = in[i]; out[i] = run; run += v; }
+    before = part[0];
+    __syncthreads();
+    part[t] = s;
+    __syncthreads();
+    for (int d = 1; d < 256; d <<= 1) {
+        const int32_t add = t >= d ? part[t - d] : 0;
+        __syncthreads();
+        part[t] += add;
+        __syncthreads();
+    }
+    int32_t run = before + part[t] - s;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (i0 + q < n) { out[i0 + q] = run; run += v[q]; }
 }
 
 // member lists: the voxels of every bucket (order inside a bucket is arbitrary) with their
@@ -96,46 +126,56 @@ __global__ __launch_bounds__(256) void psh_fill_kernel(const PairDesc *__restric
     residues[pos] = (uint32_t)(p[0] % m) | ((uint32_t)(p[1] % m) << 8) | ((uint32_t)(p[2] % m) << 16);
 }
 
-// position of this lane among the lanes of its wavefront for which `flag` is set, after a
-// counter has been advanced once for all of them (one atomic per wavefront instead of per lane)
-__device__ __forceinline__ int psh_wave_append(bool flag, int32_t *counter)
-{
-    const unsigned long long mask = __ballot(flag);
-    if (mask == 0) return 0;
-    const int lane = threadIdx.x & 63;
-    const int leader = __builtin_ctzll(mask);
-    int base = 0;
-    if (lane == leader) base = atomicAdd(counter, __builtin_popcountll(mask));
-    base = __shfl(base, leader);
-    return base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
-}
-
-// the buckets of 2 and more voxels, listed by class: entry = (active pair, bucket number)
+// The buckets of 2 and more voxels, listed by class: entry = (active pair, bucket number).  Positions
+// are counted in LDS and a class's counter is advanced once per workgroup: with one advance per
+// wavefront the atomics on these few addresses took 213 us (256^3, batch of 8).
 __global__ __launch_bounds__(256) void psh_classify_kernel(const PairDesc *__restrict__ pairs,
                                                            const int32_t *__restrict__ cnt,
                                                            int32_t *__restrict__ class_count,
                                                            int2 *__restrict__ class_cells, int64_t class_stride)
 {
+    __shared__ int32_t count[PSH_CLASSES], base[PSH_CLASSES];
     const PairDesc P = pairs[blockIdx.y];
+    const int cells = P.r * P.r * P.r;
+    if ((int)blockIdx.x * 256 >= cells) return;       // whole workgroups
     const int g = blockIdx.x * 256 + threadIdx.x;
-    const int c = g < P.r * P.r * P.r ? cnt[P.cell_base + g] : 0;
+    const int c = g < cells ? cnt[P.cell_base + g] : 0;
     const int mine = c < 2 ? 0 : (c < PSH_CLASSES - 1 ? c : PSH_CLASSES - 1);
-#pragma unroll
-    for (int k = 2; k < PSH_CLASSES; ++k) {           // no lane leaves before the last ballot
-        const int pos = psh_wave_append(mine == k, &class_count[k]);
-        if (mine == k) class_cells[k * class_stride + pos] = make_int2((int)blockIdx.y, g);
-    }
+    if (threadIdx.x < PSH_CLASSES) count[threadIdx.x] = 0;
+    __syncthreads();
+    const int pos = mine ? atomicAdd(&count[mine], 1) : 0;
+    __syncthreads();
+    if (threadIdx.x < PSH_CLASSES && count[threadIdx.x]) base[threadIdx.x] = atomicAdd(&class_count[threadIdx.x], count[threadIdx.x]);
+    __syncthreads();
+    if (mine) class_cells[mine * class_stride + base[mine] + pos] = make_int2((int)blockIdx.y, g);
 }
 
-// the free slots of every table (any order)
+// The free slots of every table (any order), PSH_FREE slots per workgroup, which advances its table's
+// counter once (one advance per wavefront: 155 us a launch, and a build has a dozen of them).
+constexpr int PSH_FREE = 4096;
 __global__ __launch_bounds__(256) void psh_free_list_kernel(const PairDesc *__restrict__ pairs,
                                                             int32_t *__restrict__ n_free, int32_t *__restrict__ free_list)
 {
+    __shared__ int32_t count, base;
     const PairDesc P = pairs[blockIdx.y];
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const bool is_free = e < P.m * P.m * P.m && P.H[e] == -1;
-    const int pos = psh_wave_append(is_free, &n_free[blockIdx.y]);
-    if (is_free) free_list[P.slot_base + pos] = e;
+    const int slots = P.m * P.m * P.m, e0 = (int)blockIdx.x * PSH_FREE;
+    if (e0 >= slots) return;                          // whole workgroups
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    uint32_t is_free = 0;
+#pragma unroll
+    for (int q = 0; q < PSH_FREE / 256; ++q) {
+        const int e = e0 + q * 256 + (int)threadIdx.x;
+        is_free |= e < slots && P.H[min(e, slots - 1)] == -1 ? 1u << q : 0u;
+    }
+    int pos = atomicAdd(&count, __popc(is_free));
+    __syncthreads();
+    if (threadIdx.x == 0) base = atomicAdd(&n_free[blockIdx.y], count);
+    __syncthreads();
+    pos += base;
+#pragma unroll
+    for (int q = 0; q < PSH_FREE / 256; ++q)
+        if (is_free >> q & 1u) free_list[P.slot_base + pos++] = e0 + q * 256 + (int)threadIdx.x;
 }
 
 __device__ __forceinline__ int32_t psh_peek(const int32_t *p)
@@ -154,6 +194,7 @@ __device__ __forceinline__ int psh_slot_of(uint32_t h, int ox, int oy, int oz, i
 
 // Place the buckets of one class (2 voxels and more): one wavefront per bucket, 4 per workgroup.
 // phi4[cell] receives the offset, packed x | y << 8 | z << 16.
+constexpr int PSH_WIDE = 4;
 __global__ __launch_bounds__(256) void psh_place_kernel(
     const PairDesc *__restrict__ pairs, const int2 *__restrict__ cells, int n_buckets,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ first, const int32_t *__restrict__ members,
@@ -175,52 +216,77 @@ __global__ __launch_bounds__(256) void psh_place_kernel(
     const int ax = h_first & 255u, ay = (h_first >> 8) & 255u, az = h_first >> 16;
     const int start = nf > 0 ? (int)(((uint32_t)g * 2654435761u) % (uint32_t)nf) : 0;
 
-    for (int i0 = 0; i0 < nf; i0 += 64) {
+    // 64 candidates at first, the usual case; then four times as many at a time, their loads side by
+    // side: a bucket that finds no room at all has to look at every free slot, and those buckets
+    // (their pair then tries the next r) are what a launch waits for at the end
+    for (int i0 = 0, wide = 1; i0 < nf; i0 += 64 * wide, wide = PSH_WIDE) {
         if (psh_peek(&fail[P.pair_id])) return;       // the pair is lost anyway
-        const int i = i0 + lane;
-        bool room = i < nf;
-        int ox = 0, oy = 0, oz = 0;
-        if (room) {
-            int w = start + i; if (w >= nf) w -= nf;
-            const int e = list[w];
-            room = psh_peek(H + e) == -1;
-            if (room) {
-                const int sx = e / (m * m), sy = (e / m) % m, sz = e % m;
-                ox = sx - ax; if (ox < 0) ox += m;
-                oy = sy - ay; if (oy < 0) oy += m;
-                oz = sz - az; if (oz < 0) oz += m;
-                for (int k = 1; k < c && room; ++k)
-                    room = psh_peek(H + psh_slot_of(residues[base + k], ox, oy, oz, m)) == -1;
-            }
+        int slot[PSH_WIDE];
+        bool rooms[PSH_WIDE];
+#pragma unroll
+        for (int q = 0; q < PSH_WIDE; ++q) {
+            const int i = i0 + q * 64 + lane;
+            rooms[q] = q < wide && i < nf;
+            int w = start + (rooms[q] ? i : 0); if (w >= nf) w -= nf;
+            slot[q] = list[w];
         }
-        unsigned long long cand = __ballot(room);
-        while (cand) {                                // wave-uniform loop
-            const int j = __builtin_ctzll(cand);
-            cand &= cand - 1;
-            int won = 0;
-            if (lane == j) {
-                int got = 0;
-                bool twice = false;     // two voxels of the bucket on one slot: no offset can separate them
-                for (int k = 0; k < c && got == k; ++k) {
-                    const int32_t old = atomicCAS(H + psh_slot_of(residues[base + k], ox, oy, oz, m), -1, members[base + k]);
-                    if (old == -1) got = k + 1;
-                    else for (int kk = 0; kk < k; ++kk) twice |= old == members[base + kk];
-                }
-                if (twice) { fail[P.pair_id] = 1; won = 1; }
-                if (got == c) {
-                    for (int k = 0; k < c; ++k) {
-                        const int32_t *p = P.coords + 3 * (int64_t)members[base + k];
-                        uint16_t *tag = P.T + 3 * (int64_t)psh_slot_of(residues[base + k], ox, oy, oz, m);
-                        tag[0] = (uint16_t)p[0]; tag[1] = (uint16_t)p[1]; tag[2] = (uint16_t)p[2];
+#pragma unroll
+        for (int q = 0; q < PSH_WIDE; ++q) rooms[q] &= psh_peek(H + slot[q]) == -1;
+        int off[PSH_WIDE];
+#pragma unroll
+        for (int q = 0; q < PSH_WIDE; ++q) {
+            const int sx = slot[q] / (m * m), sy = (slot[q] / m) % m, sz = slot[q] % m;
+            int x = sx - ax; if (x < 0) x += m;
+            int y = sy - ay; if (y < 0) y += m;
+            int z = sz - az; if (z < 0) z += m;
+            off[q] = x | y << 8 | z << 16;
+        }
+        for (int k = 1; k < c; ++k) {
+            bool any = false;
+#pragma unroll
+            for (int q = 0; q < PSH_WIDE; ++q) any |= rooms[q];
+            if (!__ballot(any)) break;
+            const uint32_t h = residues[base + k];
+            int32_t seen[PSH_WIDE];
+#pragma unroll
+            for (int q = 0; q < PSH_WIDE; ++q)
+                seen[q] = rooms[q] ? psh_peek(H + psh_slot_of(h, off[q] & 255, off[q] >> 8 & 255, off[q] >> 16, m)) : 0;
+#pragma unroll
+            for (int q = 0; q < PSH_WIDE; ++q) rooms[q] &= seen[q] == -1;
+        }
+        for (int q = 0; q < wide; ++q) {
+            const bool room = q == 0 ? rooms[0] : q == 1 ? rooms[1] : q == 2 ? rooms[2] : rooms[3];
+            const int o = q == 0 ? off[0] : q == 1 ? off[1] : q == 2 ? off[2] : off[3];
+            const int ox = o & 255, oy = o >> 8 & 255, oz = o >> 16;
+            unsigned long long cand = __ballot(room);
+            while (cand) {                                // wave-uniform loop
+                const int j = __builtin_ctzll(cand);
+                cand &= cand - 1;
+                int won = 0;
+                if (lane == j) {
+                    int got = 0;
+                    bool twice = false;     // two voxels of the bucket on one slot: no offset can separate them
+                    for (int k = 0; k < c && got == k; ++k) {
+                        const int32_t old = atomicCAS(H + psh_slot_of(residues[base + k], ox, oy, oz, m), -1, members[base + k]);
+                        if (old == -1) got = k + 1;
+                        else for (int kk = 0; kk < k; ++kk) twice |= old == members[base + kk];
                     }
-                    phi4[cell] = (uint32_t)ox | ((uint32_t)oy << 8) | ((uint32_t)oz << 16);
-                    won = 1;
-                } else {
-                    for (int k = 0; k < got; ++k)     // give the claimed slots back
-                        atomicExch(H + psh_slot_of(residues[base + k], ox, oy, oz, m), -1);
+                    if (twice) { fail[P.pair_id] = 1; won = 1; }
+                    if (got == c) {
+                        for (int k = 0; k < c; ++k) {
+                            const int32_t *p = P.coords + 3 * (int64_t)members[base + k];
+                            uint16_t *tag = P.T + 3 * (int64_t)psh_slot_of(residues[base + k], ox, oy, oz, m);
+                            tag[0] = (uint16_t)p[0]; tag[1] = (uint16_t)p[1]; tag[2] = (uint16_t)p[2];
+                        }
+                        phi4[cell] = (uint32_t)ox | ((uint32_t)oy << 8) | ((uint32_t)oz << 16);
+                        won = 1;
+                    } else {
+                        for (int k = 0; k < got; ++k)     // give the claimed slots back
+                            atomicExch(H + psh_slot_of(residues[base + k], ox, oy, oz, m), -1);
+                    }
                 }
+                if (__ballot(won)) return;
             }
-            if (__ballot(won)) return;
         }
     }
     if (lane == 0) fail[P.pair_id] = 1;
