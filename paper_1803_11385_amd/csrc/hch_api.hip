@@ -2235,17 +2235,17 @@ extern "C" hch_status hch_field_build(const hch_levels *levels, int32_t level_in
     if (!field && !field_t) return fail(HCH_EINVAL, "hch_field_build: nothing to build");
     const int F3 = F * F * F;
     hipStream_t s = (hipStream_t)stream;
+    const int tv = F <= 6 ? 64 : 32;                   // voxels per workgroup: their rows fit 64 KB of LDS
+    const size_t lds = (size_t)tv * F3 * 4;
     if (field) {
-        const int64_t items = (int64_t)Lo->max_n * F3;
         hch::LaunchTimer lt(HCH_KERNEL_ID("field_kernel<false>"), s, (double)Lo->n_total * (12.0 + 4.0 * F3), 0.0);
-        HCH_LAUNCH(hch::field_kernel<false>, dim3(blocks_for(items), (unsigned)Lo->b), dim3(256), 0, s,
-                           Li->view(), Lo->dcoords, Lo->dN(), field, F, stride, pad);
+        HCH_LAUNCH(hch::field_kernel<false>, dim3((unsigned)((Lo->max_n + tv - 1) / tv), (unsigned)Lo->b), dim3(256), lds, s,
+                           Li->view(), Lo->dcoords, Lo->dN(), field, F, stride, pad, tv);
     }
     if (field_t) {
-        const int64_t items = (int64_t)Li->max_n * F3;
         hch::LaunchTimer lt(HCH_KERNEL_ID("field_kernel<true>"), s, (double)Li->n_total * (12.0 + 4.0 * F3), 0.0);
-        HCH_LAUNCH(hch::field_kernel<true>, dim3(blocks_for(items), (unsigned)Li->b), dim3(256), 0, s,
-                           Lo->view(), Li->dcoords, Li->dN(), field_t, F, stride, pad);
+        HCH_LAUNCH(hch::field_kernel<true>, dim3((unsigned)((Li->max_n + tv - 1) / tv), (unsigned)Li->b), dim3(256), lds, s,
+                           Lo->view(), Li->dcoords, Li->dN(), field_t, F, stride, pad, tv);
     }
     HCH_LAUNCH_CHECK("field_kernel");
     return HCH_OK;
@@ -2340,6 +2340,12 @@ extern "C" hch_status hch_sconv_bwd_weight(const hch_levels *levels, int32_t lev
     const int64_t n = Lo->n_total, wsize = (int64_t)K * c_out;
     const double es = elem_size(dtype);
     const GemmPlan p = plan_wgrad(n, c_in, c_out, taps, k_gran(dtype));
+    if (dtype == HCH_F32) {
+        const WgradSplitPlan q = plan_wgrad_split(n, Li->n_total, c_in, c_out, taps, std::max<int64_t>(1, (int64_t)(ws_bytes / (4 * (size_t)wsize))));
+        if (q.ok)
+            return launch_wgrad_split(q, (const float *)X, (const float *)dY, dW, (float *)workspace, field, nullptr, n, Li->n_total,
+                                      c_in, c_out, taps, (double)n * (4.0 * taps + 4.0 * c_out) + 4.0 * (double)Li->n_total * c_in, s);
+    }
     float *part = (float *)workspace;
     const double bytes = (double)n * (4.0 * taps + es * c_out) + es * (double)Li->n_total * c_in + 4.0 * wsize * p.splits;
     st = launch_gemm<hch::A_GATHER_T, false>(dtype, p, X, dY, p.splits == 1 ? dW : part, field, K, c_out, (int)n, c_in,

@@ -651,17 +651,6 @@ __global__ __launch_bounds__(256) void child_kernel(
     dst[1] = make_int4(out[4], out[5], out[6], out[7]);
 }
 
-// One probe at an arbitrary position (Eq.1, Eq.4-6 and the tag test): global data index or -1.
-// The position must be inside the grid.
-__device__ __forceinline__ int32_t psh_lookup(const PshView &L, int v, unsigned x, unsigned y, unsigned z)
-{
-    const unsigned m = (unsigned)L.mbar[v], r = (unsigned)L.rbar[v];
-    const uint32_t ph = psh_offset(L, (unsigned)L.R[v], r, x % r, y % r, z % r);
-    const u32x3 rec = psh_record(psh_slot(L, (unsigned)L.M[v], m, ph, x % m, y % m, z % m));
-    const int32_t h = psh_match(rec[0], rec[1], rec[2], x, y, z);
-    return h >= 0 ? L.N[v] + h : -1;
-}
-
 // Receptive fields of the general traversal of Algorithm 1 (kernel side F, stride S, padding P)
 // between an input level and an output level S times coarser (the same level when S = 1):
 // output voxel p covers the input positions lo(p) + (fx,fy,fz), 0 <= f < F, with lo(p) =
@@ -672,35 +661,73 @@ __device__ __forceinline__ int32_t psh_lookup(const PshView &L, int v, unsigned 
 //                        voxel i at this row, or -1 (rows owned by the input voxels; probes go to
 //                        the output level's tables): the index rows of Algorithm 2 turned into
 //                        a gather.
-// One thread per (voxel, row); grid.y = model.  `owner` = coordinates and N* prefix of the level
-// that owns the rows, `probe` = tables of the other level.
+// grid.y = model; a workgroup has `tv` voxels (64, or 32 with the longest rows), one per lane, and its wavefronts take the rows in
+// turn, so that a row's numbers are the same for all lanes.  `owner` = coordinates and N* prefix of the
+// level that owns the rows, `probe` = tables of the other level.  Per axis, output position minus input
+// position changes by one from row to row, so the residues of the hash are stepped, not divided; and of
+// the transposed rows of a stride S only every S-th per axis can have an owner: the ceil(F/S)^3 of them
+// are probed, the others are -1.  (With a thread per row and its divisions the kernel was bound by them:
+// 3^3, stride 2, 609k voxels 123 us.)  Rows leave through LDS, coalesced.
 template <bool TRANSPOSED>
 __global__ __launch_bounds__(256) void field_kernel(
     PshView probe, const int32_t *__restrict__ owner_coords, const int32_t *__restrict__ owner_N,
-    int32_t *__restrict__ out, int F, int S, int P)
+    int32_t *__restrict__ out, int F, int S, int P, int tv)
 {
-    const int v = blockIdx.y;
-    const int F3 = F * F * F;
+    extern __shared__ int32_t rows[];                 // tv * F^3
+    const int v = blockIdx.y, F3 = F * F * F;
     const int32_t base = owner_N[v], n = owner_N[v + 1] - base;
-    const int64_t item = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (item >= (int64_t)n * F3) return;
-    const int i = (int)(item / F3), row = (int)(item - (int64_t)i * F3);
-    const int f[3] = {row / (F * F), (row / F) % F, row % F};
-    const int32_t *p = owner_coords + 3 * (int64_t)(base + i);
-    int q[3];
-    bool ok = true;
+    const int i0 = (int)blockIdx.x * tv;
+    if (i0 >= n) return;                              // whole workgroups
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = min(tv, n - i0);
+    const int m = probe.mbar[v], r = probe.rbar[v];
+    const unsigned Mv = (unsigned)probe.M[v], Rv = (unsigned)probe.R[v];
+    const int32_t first = probe.N[v];
+    const int32_t *p = owner_coords + 3 * (int64_t)(base + i0 + min(lane, nv - 1));
+    // per axis: the position q0 of row f0 (the first that can have an owner), row f0 + step*j has q0 +- j
+    int q0[3], f0[3], qm[3], qr[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (!TRANSPOSED) q[a] = (S == 1 ? p[a] - (F - 1) / 2 : p[a] * S - P) + f[a];
-        else if (S == 1) q[a] = p[a] - f[a] + (F - 1) / 2;
-        else {
-            const int t = p[a] + P - f[a];
-            ok &= t >= 0 && t % S == 0;
-            q[a] = t / S;
+        if (TRANSPOSED) {
+            const int t = p[a] + (S == 1 ? (F - 1) / 2 : P);
+            q0[a] = t / S; f0[a] = t - q0[a] * S;
+        } else {
+            q0[a] = S == 1 ? p[a] - (F - 1) / 2 : p[a] * S - P;
+            f0[a] = 0;
         }
-        ok &= q[a] >= 0 && q[a] < probe.ubar;
+        qm[a] = q0[a] % m; if (qm[a] < 0) qm[a] += m;
+        qr[a] = q0[a] % r; if (qr[a] < 0) qr[a] += r;
     }
-    out[(int64_t)(base + i) * F3 + row] = ok ? psh_lookup(probe, v, (unsigned)q[0], (unsigned)q[1], (unsigned)q[2]) : -1;
+    const int step = TRANSPOSED ? S : 1, K = (F + step - 1) / step;
+    if (step > 1) {
+        for (int t = threadIdx.x; t < nv * F3; t += 256) rows[t] = -1;
+        __syncthreads();
+    }
+    auto moved = [](int x, int j, int d) {            // x +- j modulo d, given 0 <= x < d
+        if (TRANSPOSED) { x -= j; while (x < 0) x += d; }
+        else { x += j; while (x >= d) x -= d; }
+        return (unsigned)x;
+    };
+#pragma unroll 2
+    for (int j = wave; j < K * K * K; j += 4) {
+        const int js[3] = {j / (K * K), j / K % K, j % K};
+        int q[3], row = 0;
+        bool ok = lane < nv;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            q[a] = TRANSPOSED ? q0[a] - js[a] : q0[a] + js[a];
+            const int f = f0[a] + step * js[a];
+            ok &= f < F && q[a] >= 0 && q[a] < probe.ubar;
+            row = row * F + f;
+        }
+        const uint32_t ph = psh_offset(probe, Rv, (unsigned)r, moved(qr[0], js[0], r), moved(qr[1], js[1], r), moved(qr[2], js[2], r));
+        const u32x3 rec = psh_record(psh_slot(probe, Mv, (unsigned)m, ph, moved(qm[0], js[0], m), moved(qm[1], js[1], m), moved(qm[2], js[2], m)));
+        const int32_t h = psh_match(rec[0], rec[1], rec[2], (unsigned)q[0], (unsigned)q[1], (unsigned)q[2]);
+        if (ok) rows[lane * F3 + row] = h >= 0 ? first + h : -1;
+        else if (step == 1 && lane < nv) rows[lane * F3 + row] = -1;
+    }
+    __syncthreads();
+    int32_t *dst = out + (int64_t)(base + i0) * F3;
+    for (int t = threadIdx.x; t < nv * F3; t += 256) dst[t] = rows[t];
 }
 
 // ---------------------------------------------------------------------------------------
