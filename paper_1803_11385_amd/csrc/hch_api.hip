@@ -69,6 +69,7 @@ struct Level {
     std::vector<uint16_t> T;
     std::vector<uint8_t> Phi;
     // device
+    bool in_block = false;                     // tables and lists lie in blocks of the whole level set
     int32_t *dH = nullptr, *dV = nullptr, *dcoords = nullptr, *dnbr = nullptr, *dchild = nullptr;
     int32_t *dnbr_t = nullptr;                 // tap-major copy of dnbr ([27][n_total]), built on request
     uint32_t *dmask27 = nullptr;               // [n_total] bit k: neighbour k exists
@@ -96,6 +97,12 @@ struct Level {
 
 void free_level(Level &L)
 {
+    if (L.in_block) {                          // everything but the tap-major copy belongs to hch_levels::blocks
+        void *own = L.dnbr_t;
+        L = Level();
+        if (own) (void)hipFree(own);
+        return;
+    }
     void *ptrs[] = {L.dH, L.dV, L.dcoords, L.dnbr, L.dchild, L.dT, L.dPhi, L.dmeta, L.dslot3, L.dphi4, L.dnbr_t, L.dmask27, L.dtilemask};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     L.dH = L.dV = L.dcoords = L.dnbr = L.dchild = L.dmeta = L.dnbr_t = nullptr;
@@ -126,6 +133,7 @@ struct hch_levels {
     uint8_t *d_sort_key = nullptr;
     int32_t *d_tile_hist = nullptr, *d_key_total = nullptr, *d_order = nullptr;
     uint32_t *d_fine = nullptr;                // everything of the fine order, in one allocation
+    std::vector<void *> blocks;                // device construction: one allocation for what is known before it, one after
 };
 
 extern "C" const char *hch_last_error(void) { return g_err.c_str(); }
@@ -138,6 +146,7 @@ extern "C" void hch_free_levels(hch_levels *levels)
     if (levels->d_child_prefix) (void)hipFree(levels->d_child_prefix);
     void *sort_ptrs[] = {levels->d_sort_key, levels->d_tile_hist, levels->d_key_total, levels->d_order, levels->d_fine};
     for (void *p : sort_ptrs) if (p) (void)hipFree(p);
+    for (void *p : levels->blocks) (void)hipFree(p);
     delete levels;
 }
 
@@ -302,16 +311,26 @@ extern "C" hch_status hch_build_neighbours_range(hch_levels *levels, int32_t fir
 // ---- PSH construction on the device (psh_device.hip.hpp) ----
 
 namespace {
+// Device memory by the piece, 256-byte aligned, out of one allocation: sized first (null base), then
+// handed out in the same order.
+struct Pieces {
+    char *base = nullptr;
+    size_t used = 0;
+    template <typename T> void take(T *&p, size_t bytes)
+    {
+        if (base) p = reinterpret_cast<T *>(base + used);
+        used += round_up(std::max<size_t>(bytes, 16), 256);
+    }
+};
 struct DeviceBlocks {            // device allocations that live until the end of the build call
     std::vector<void *> ptrs;
     ~DeviceBlocks() { for (void *p : ptrs) if (p) (void)hipFree(p); }
-    hch_status get(void **out, size_t bytes, int fill, hipStream_t s)
+    hch_status get(void **out, size_t bytes)
     {
         *out = nullptr;
         hipError_t e = hipMalloc(out, bytes ? bytes : 16);
         if (e != hipSuccess) { *out = nullptr; return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)); }
         ptrs.push_back(*out);
-        if (fill >= 0 && bytes) HCH_HIP(hipMemsetAsync(*out, fill, bytes, s));
         return HCH_OK;
     }
 };
@@ -347,16 +366,40 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         }
         L.m_total = L.M[batch];
         if (L.m_total >= ((int64_t)1 << 31)) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: super table exceeds 32-bit indexing");
-        HCH_HIP(hipMalloc((void **)&L.dH, (size_t)L.m_total * 4));
-        HCH_HIP(hipMalloc((void **)&L.dT, (size_t)L.m_total * 6));
-        HCH_HIP(hipMalloc((void **)&L.dV, (size_t)L.m_total * 4));
-        HCH_HIP(hipMemsetAsync(L.dH, 0xFF, (size_t)L.m_total * 4, s));     // -1 = free slot
-        HCH_HIP(hipMemsetAsync(L.dT, 0xFF, (size_t)L.m_total * 6, s));     // 0xFFFF = no position
-        if ((st = upload((void **)&L.dcoords, L.coords.data(), L.coords.size() * 4, s)) != HCH_OK) return st;
+    }
+    // what the level set keeps and whose size is known now, in one allocation (one by one the
+    // allocations and frees of a build took 6 ms); H* and T* first, so that one fill empties them
+    auto lay = [&](Pieces &P, size_t *tables) {
+        for (Level &L : hl->lv) { P.take(L.dH, (size_t)L.m_total * 4); P.take(L.dT, (size_t)L.m_total * 6); }
+        *tables = P.used;
+        for (Level &L : hl->lv) {
+            const size_t n = (size_t)L.n_total;
+            P.take(L.dV, (size_t)L.m_total * 4);
+            P.take(L.dslot3, (size_t)L.m_total * 4 * hch::SLOT_WORDS);
+            P.take(L.dcoords, n * 12);
+            P.take(L.dnbr, n * 27 * 4);
+            if (&L != &hl->lv[0] && L.ratio == 2) P.take(L.dchild, n * 8 * 4);
+            P.take(L.dmask27, std::max<size_t>(n, 64) * 4);
+            P.take(L.dtilemask, std::max<size_t>((n + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE, 64) * 4);
+        }
+    };
+    {
+        Pieces size, place;
+        size_t tables = 0;
+        lay(size, &tables);
+        void *block = nullptr;
+        hipError_t e = hipMalloc(&block, size.used);
+        if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        hl->blocks.push_back(block);
+        place.base = (char *)block;
+        for (Level &L : hl->lv) L.in_block = true;
+        lay(place, &tables);
+        HCH_HIP(hipMemsetAsync(block, 0xFF, tables, s));      // H* = -1: free slot; T* = 0xFFFF: no position
+        for (Level &L : hl->lv) HCH_HIP(hipMemcpyAsync(L.dcoords, L.coords.data(), L.coords.size() * 4, hipMemcpyHostToDevice, s));
     }
     const int n_pairs = (int)work.size();
     int32_t *d_fail = nullptr;
-    if ((st = tmp.get((void **)&d_fail, (size_t)n_pairs * 4, -1, s)) != HCH_OK) return st;
+    if ((st = tmp.get((void **)&d_fail, (size_t)n_pairs * 4)) != HCH_OK) return st;
     std::vector<int32_t> h_fail((size_t)n_pairs);
 
     std::vector<int> active((size_t)n_pairs);
@@ -386,21 +429,30 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         int32_t *d_counters = nullptr, *d_free = nullptr;
         uint32_t *d_phi = nullptr, *d_res = nullptr;
         int2 *d_cells = nullptr;
-        if ((st = tmp.get((void **)&d_desc, desc.size() * sizeof(hch::PairDesc), -1, s)) != HCH_OK) return st;
-        HCH_HIP(hipMemcpyAsync(d_desc, desc.data(), desc.size() * sizeof(hch::PairDesc), hipMemcpyHostToDevice, s));
-        if ((st = tmp.get((void **)&d_cnt, (size_t)cells * 4, 0, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_first, (size_t)cells * 4, -1, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_sums, ((size_t)cells / hch::PSH_SCAN + 1) * 4, -1, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_fill, (size_t)cells * 4, 0, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_phi, (size_t)cells * 4, 0, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_bucket, (size_t)vox * 4, -1, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_members, (size_t)vox * 4, -1, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_res, (size_t)vox * 4, -1, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_free, (size_t)slots * 4, -1, s)) != HCH_OK) return st;
-        if ((st = tmp.get((void **)&d_cells, (size_t)cells * hch::PSH_CLASSES * sizeof(int2), -1, s)) != HCH_OK) return st;
         // counters: [0, CLASSES) buckets per class, then per active pair: free slots, singles placed
         const size_t n_counters = (size_t)hch::PSH_CLASSES + 2 * (size_t)na;
-        if ((st = tmp.get((void **)&d_counters, n_counters * 4, 0, s)) != HCH_OK) return st;
+        auto lay_round = [&](Pieces &P, size_t *zeroed) {      // the arrays that start from zero first
+            P.take(d_cnt, (size_t)cells * 4);
+            P.take(d_fill, (size_t)cells * 4);
+            P.take(d_phi, (size_t)cells * 4);
+            P.take(d_counters, n_counters * 4);
+            *zeroed = P.used;
+            P.take(d_desc, desc.size() * sizeof(hch::PairDesc));
+            P.take(d_first, (size_t)cells * 4);
+            P.take(d_sums, ((size_t)cells / hch::PSH_SCAN + 1) * 4);
+            P.take(d_bucket, (size_t)vox * 4);
+            P.take(d_members, (size_t)vox * 4);
+            P.take(d_res, (size_t)vox * 4);
+            P.take(d_free, (size_t)slots * 4);
+            P.take(d_cells, (size_t)cells * hch::PSH_CLASSES * sizeof(int2));
+        };
+        Pieces size, place;
+        size_t zeroed = 0;
+        lay_round(size, &zeroed);
+        if ((st = tmp.get((void **)&place.base, size.used)) != HCH_OK) return st;
+        lay_round(place, &zeroed);
+        HCH_HIP(hipMemsetAsync(place.base, 0, zeroed, s));
+        HCH_HIP(hipMemcpyAsync(d_desc, desc.data(), desc.size() * sizeof(hch::PairDesc), hipMemcpyHostToDevice, s));
         int32_t *d_class_count = d_counters, *d_nfree = d_counters + hch::PSH_CLASSES, *d_rank = d_nfree + na;
         HCH_HIP(hipMemsetAsync(d_fail, 0, (size_t)n_pairs * 4, s));
 
@@ -429,6 +481,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         HCH_LAUNCH(hch::psh_free_list_kernel, gs, dim3(256), 0, s, d_desc, d_nfree, d_free);
         HCH_LAUNCH(hch::psh_place_single_kernel, gc, dim3(256), 0, s, d_desc, d_cnt, d_first, d_members, d_res,
                            d_nfree, d_free, d_rank, d_phi, d_fail);
+        HCH_LAUNCH(hch::psh_clear_kernel, gs, dim3(256), 0, s, d_desc, d_fail);
         HCH_LAUNCH_CHECK("psh construction");
         HCH_HIP(hipMemcpyAsync(h_fail.data(), d_fail, (size_t)n_pairs * 4, hipMemcpyDeviceToHost, s));
         HCH_HIP(hipStreamSynchronize(s));
@@ -436,15 +489,11 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         std::vector<int> again;
         for (int a = 0; a < na; ++a) {
             PairWork &w = work[active[a]];
-            Level &L = hl->lv[w.l];
             if (!h_fail[active[a]]) {
                 w.done = true;
                 w.phi = d_phi + desc[a].cell_base;
                 continue;
             }
-            const size_t m3 = (size_t)w.m * w.m * w.m;
-            HCH_HIP(hipMemsetAsync(L.dH + L.M[w.v], 0xFF, m3 * 4, s));
-            HCH_HIP(hipMemsetAsync(L.dT + 3 * L.M[w.v], 0xFF, m3 * 6, s));
             w.r = hch::offset_side_next(w.r, w.m);
             again.push_back(active[a]);
         }
@@ -452,10 +501,11 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
     }
 
     // super tables of every level from the pairs' results
+    std::vector<hch::PackDesc> pd((size_t)n_pairs);
+    std::vector<int32_t> meta;
+    const size_t meta_len = 5 * (size_t)batch + 3;            // mbar, rbar, M, R, N
     for (int l = 0; l < n_levels; ++l) {
         Level &L = hl->lv[l];
-        std::vector<hch::PackDesc> pd((size_t)batch);
-        int32_t widest = 0;
         for (int v = 0; v < batch; ++v) {
             const PairWork &w = work[(size_t)l * batch + v];
             L.rbar[v] = w.r; L.attempts[v] = w.attempts;
@@ -465,34 +515,55 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         if (L.r_total >= ((int64_t)1 << 31) / 3) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: super table exceeds 32-bit indexing");
         for (int v = 0; v < batch; ++v) {
             const PairWork &w = work[(size_t)l * batch + v];
-            pd[v] = hch::PackDesc{w.phi, w.m * w.m * w.m, w.r * w.r * w.r, (int32_t)L.M[v], (int32_t)L.R[v]};
-            widest = std::max(widest, std::max(pd[v].m3, pd[v].r3));
+            pd[(size_t)l * batch + v] = hch::PackDesc{w.phi, w.m * w.m * w.m, w.r * w.r * w.r, (int32_t)L.M[v], (int32_t)L.R[v]};
         }
-        hch::PackDesc *d_pd = nullptr;
-        if ((st = tmp.get((void **)&d_pd, pd.size() * sizeof(hch::PackDesc), -1, s)) != HCH_OK) return st;
-        HCH_HIP(hipMemcpyAsync(d_pd, pd.data(), pd.size() * sizeof(hch::PackDesc), hipMemcpyHostToDevice, s));
-        HCH_HIP(hipMalloc((void **)&L.dPhi, std::max<size_t>(16, (size_t)L.r_total * 3)));
-        HCH_HIP(hipMalloc((void **)&L.dphi4, std::max<size_t>(16, (size_t)L.r_total * 4)));
-        HCH_HIP(hipMalloc((void **)&L.dslot3, (size_t)L.m_total * 4 * hch::SLOT_WORDS));
-        HCH_LAUNCH(hch::psh_pack_kernel, dim3((unsigned)((widest + 255) / 256), (unsigned)batch), dim3(256), 0, s,
-                           d_pd, L.dH, L.dT, L.dslot3, L.dV, L.dphi4, L.dPhi);
-        HCH_LAUNCH_CHECK("psh_pack_kernel");
-        std::vector<int32_t> meta;
         meta.insert(meta.end(), L.mbar.begin(), L.mbar.end());
         meta.insert(meta.end(), L.rbar.begin(), L.rbar.end());
         for (int64_t x : L.M) meta.push_back((int32_t)x);
         for (int64_t x : L.R) meta.push_back((int32_t)x);
         for (int64_t x : L.N) meta.push_back((int32_t)x);
-        if ((st = upload((void **)&L.dmeta, meta.data(), meta.size() * 4, s)) != HCH_OK) return st;
-        // host copies for hch_level_info
+    }
+    int32_t *d_meta = nullptr;
+    hch::PackDesc *d_pd = nullptr;
+    if ((st = tmp.get((void **)&d_pd, pd.size() * sizeof(hch::PackDesc))) != HCH_OK) return st;
+    {
+        auto lay_offsets = [&](Pieces &P) {
+            for (Level &L : hl->lv) { P.take(L.dPhi, (size_t)L.r_total * 3); P.take(L.dphi4, (size_t)L.r_total * 4); }
+            P.take(d_meta, meta.size() * 4);
+        };
+        Pieces size, place;
+        lay_offsets(size);
+        void *block = nullptr;
+        hipError_t e = hipMalloc(&block, size.used);
+        if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        hl->blocks.push_back(block);
+        place.base = (char *)block;
+        lay_offsets(place);
+    }
+    HCH_HIP(hipMemcpyAsync(d_pd, pd.data(), pd.size() * sizeof(hch::PackDesc), hipMemcpyHostToDevice, s));
+    HCH_HIP(hipMemcpyAsync(d_meta, meta.data(), meta.size() * 4, hipMemcpyHostToDevice, s));
+    for (int l = 0; l < n_levels; ++l) {
+        Level &L = hl->lv[l];
+        L.dmeta = d_meta + (size_t)l * meta_len;
+        int32_t widest = 0;
+        for (int v = 0; v < batch; ++v) {
+            const hch::PackDesc &q = pd[(size_t)l * batch + v];
+            widest = std::max(widest, std::max(q.m3, q.r3));
+        }
+        HCH_LAUNCH(hch::psh_pack_kernel, dim3((unsigned)((widest + 255) / 256), (unsigned)batch), dim3(256), 0, s,
+                           d_pd + (size_t)l * batch, L.dH, L.dT, L.dslot3, L.dV, L.dphi4, L.dPhi);
+        HCH_LAUNCH_CHECK("psh_pack_kernel");
+    }
+    for (Level &L : hl->lv) {
+        // host copies for hch_level_info; the model index of every slot follows from M*
         L.H.resize((size_t)L.m_total); L.V.resize((size_t)L.m_total);
         L.T.resize((size_t)L.m_total * 3); L.Phi.resize((size_t)L.r_total * 3);
+        for (int v = 0; v < batch; ++v) std::fill(L.V.begin() + L.M[v], L.V.begin() + L.M[v + 1], v);
         HCH_HIP(hipMemcpyAsync(L.H.data(), L.dH, L.H.size() * 4, hipMemcpyDeviceToHost, s));
-        HCH_HIP(hipMemcpyAsync(L.V.data(), L.dV, L.V.size() * 4, hipMemcpyDeviceToHost, s));
         HCH_HIP(hipMemcpyAsync(L.T.data(), L.dT, L.T.size() * 2, hipMemcpyDeviceToHost, s));
         if (L.r_total) HCH_HIP(hipMemcpyAsync(L.Phi.data(), L.dPhi, L.Phi.size(), hipMemcpyDeviceToHost, s));
-        HCH_HIP(hipStreamSynchronize(s));     // `meta` and `pd` die here
     }
+    HCH_HIP(hipStreamSynchronize(s));         // `meta`, `pd` and the coordinates' copies are done
     return HCH_OK;
 }
 
@@ -574,7 +645,7 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
                     const int32_t *p = coords_xyz + 3 * (a + i);
                     lin[i] = ((int64_t)p[0] * resolution + p[1]) * resolution + p[2];
                 }
-                std::sort(lin.begin(), lin.end());
+                if (!std::is_sorted(lin.begin(), lin.end())) std::sort(lin.begin(), lin.end());
                 if (std::adjacent_find(lin.begin(), lin.end()) != lin.end()) dup = 1;
             }
         };
@@ -661,15 +732,7 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
         // ---- super tables (Section 3.2) and upload ----
         for (int l = 0; l < n_levels && st == HCH_OK; ++l) {
             Level &L = hl->lv[l];
-            if (device_tables) {      // tables are already resident; only the index lists are missing
-                if (hipMalloc((void **)&L.dnbr, (size_t)L.n_total * 27 * 4) != hipSuccess) {
-                    L.dnbr = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(nbr27) failed"); break;
-                }
-                if (l > 0 && L.ratio == 2 && hipMalloc((void **)&L.dchild, (size_t)L.n_total * 8 * 4) != hipSuccess) {
-                    L.dchild = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(child8) failed"); break;
-                }
-                continue;
-            }
+            if (device_tables) continue;              // all of it is in the blocks of device_construct
             L.mbar.resize((size_t)batch); L.rbar.resize((size_t)batch); L.attempts.resize((size_t)batch);
             L.M.assign((size_t)batch + 1, 0); L.R.assign((size_t)batch + 1, 0);
             for (int v = 0; v < batch; ++v) {
@@ -746,9 +809,10 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
             for (int l = 0; l < n_levels && st == HCH_OK; ++l) {
                 Level &L = hl->lv[l];
                 const size_t tiles = (size_t)((L.n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
+                L.dorder = hl->d_order + hl->sort_off[l];
+                if (L.in_block) continue;
                 if (hipMalloc((void **)&L.dmask27, std::max<size_t>((size_t)L.n_total, 64) * 4) != hipSuccess) { L.dmask27 = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(mask27) failed"); break; }
                 if (hipMalloc((void **)&L.dtilemask, std::max<size_t>(tiles, 64) * 4) != hipSuccess) { L.dtilemask = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(tile masks) failed"); break; }
-                L.dorder = hl->d_order + hl->sort_off[l];
             }
             // the fine order: neighbour sets by position in both orders, the order, its tiles' taps,
             // the histograms and their totals

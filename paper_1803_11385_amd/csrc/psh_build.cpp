@@ -178,6 +178,26 @@ BuildResult build_model_tables(const int32_t *xyz, int64_t n, int ubar, ModelTab
 void coarsen_model(const int32_t *xyz, int64_t n, int ubar_fine, int ratio, std::vector<int32_t> &out_xyz)
 {
     const int64_t uc = (ubar_fine + ratio - 1) / ratio;
+    // one bit per position of the coarse grid, read back in order, where the grid is no larger than
+    // the list (shapes of a mini-batch: about a tenth of the time of sorting); else a sorted list
+    const int64_t words = (uc * uc * uc + 63) / 64;
+    if (words <= 4 * n + 1024) {
+        std::vector<uint64_t> bits((size_t)words, 0);
+        for (int64_t i = 0; i < n; ++i) {
+            const int64_t q = ((int64_t)(xyz[3 * i] / ratio) * uc + (xyz[3 * i + 1] / ratio)) * uc + (xyz[3 * i + 2] / ratio);
+            bits[(size_t)(q >> 6)] |= (uint64_t)1 << (q & 63);
+        }
+        out_xyz.clear();
+        out_xyz.reserve((size_t)n * 3);
+        for (int64_t w = 0; w < words; ++w)
+            for (uint64_t b = bits[(size_t)w]; b; b &= b - 1) {
+                const int64_t q = w * 64 + __builtin_ctzll(b);
+                out_xyz.push_back((int32_t)(q / (uc * uc)));
+                out_xyz.push_back((int32_t)((q / uc) % uc));
+                out_xyz.push_back((int32_t)(q % uc));
+            }
+        return;
+    }
     std::vector<int64_t> lin((size_t)n);
     for (int64_t i = 0; i < n; ++i)
         lin[i] = ((int64_t)(xyz[3 * i] / ratio) * uc + (xyz[3 * i + 1] / ratio)) * uc + (xyz[3 * i + 2] / ratio);

@@ -321,6 +321,16 @@ __global__ __launch_bounds__(256) void psh_place_single_kernel(
     phi4[cell] = (uint32_t)ox | ((uint32_t)oy << 8) | ((uint32_t)oz << 16);
 }
 
+// Empties the tables of the pairs that failed, for their next attempt (grid as for the free-slot list).
+__global__ __launch_bounds__(256) void psh_clear_kernel(const PairDesc *__restrict__ pairs, const int32_t *__restrict__ fail)
+{
+    const PairDesc P = pairs[blockIdx.y];
+    if (!fail[P.pair_id]) return;
+    const int slots = P.m * P.m * P.m, e1 = min(slots, (int)(blockIdx.x + 1) * PSH_FREE);
+    for (int e = (int)blockIdx.x * PSH_FREE + (int)threadIdx.x; e < e1; e += 256) P.H[e] = -1;
+    for (int e = 3 * (int)blockIdx.x * PSH_FREE + (int)threadIdx.x; e < 3 * e1; e += 256) P.T[e] = 0xFFFFu;
+}
+
 // One level's packed lookup records, model indices and byte offset table from H*, T* and the
 // per-pair offset words.  grid.y = model.
 struct PackDesc {
