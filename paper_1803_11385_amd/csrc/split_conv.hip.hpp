@@ -17,6 +17,9 @@ namespace hch {
 //   * Weights: one unit per thread and step, cut before it goes to LDS, two stages, one barrier a step.
 //   * Loads run two steps ahead in two sets of registers, as in gemm_f32_kernel.
 //   * The index rows of a wavefront are read once, whole rows at a time, into LDS.
+// Bound by vector and matrix instructions together (44 + 44 to cut a step's 16 rows and its share of the
+// weights, 24 matrix instructions) at four wavefronts per SIMD: 32 -> 64 at 280 000 voxels 116 us (159
+// with gemm_f32_kernel in the same row order), 64 -> 64 202 (293), 50 -> 50 206 (1109: element by element).
 // FAST: rows of a multiple of 32 channels; a step lies within one tap, offsets that change from step
 // to step are scalar, and a wavefront whose own rows lack the tap sits the step out.  Otherwise any
 // number of channels: a tap is padded to a multiple of 8, with weights of zero.

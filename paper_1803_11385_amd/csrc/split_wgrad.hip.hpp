@@ -71,6 +71,11 @@ __device__ __forceinline__ bool non_finite(float v) { return (__float_as_uint(v)
 // The rows of the next unit are requested before a unit is multiplied, across blocks as well; the
 // index rows run two blocks ahead, dY one.  The two halves of a block are added through LDS at the
 // end, which halves the partial sums that go to memory.
+// Bound by the issue of matrix and vector instructions (96 cycles and about 90 vector instructions
+// per unit and 16 columns x 32 voxels) and by the wait for the slowest wavefront of a block: 32 -> 64 at
+// 280 000 voxels 148 us (265 with every tap at the fp32 rate), 64 -> 64 225 (535), 50 -> 50 228 (885).
+// A form with the units in a loop and a switch over their sums copied the sums through other registers
+// (254 us); requests further ahead than two units changed nothing.
 constexpr int WG_VOX = 128, WG_UNITS = 28, WG_SLOTS = WG_UNITS + 1, WG_RS = WG_VOX + 4;
 template <int NT>
 struct WgradLds {
@@ -360,6 +365,247 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
                 if (m < M && col < N) C[(int64_t)m * N + col] = v[e];
             }
         }
+}
+
+// The same product with bf16 operands, which need no cutting.  Rows are taken in pairs of channels (a
+// lane loads 32 bits and gives one half to each of two operands), so a unit is 32 rows of dW; a
+// wavefront has 4 of the 16 units of a workgroup.  The second half of every block enters with the
+// opposite sign and is subtracted at the end: the instruction rounds its sums down, and so the two
+// halves err in opposite directions.
+constexpr int WGB_UNITS = 16;
+template <int NT>
+struct WgradBfLds {
+    static constexpr int BN = 16 * NT;
+    static constexpr int DY = WG_VOX / 32 * 4 * BN * 16;
+    static constexpr int IDX = WG_SLOTS * WG_RS * 4;
+    static constexpr int O_IDX = 2 * DY, O_ORD = O_IDX + 3 * IDX, O_MASK = O_ORD + 3 * WG_VOX * 4;
+    static constexpr int O_TAB = O_MASK + 3 * 8 * 4, TOTAL = O_TAB + WGB_UNITS * 16 * 4;
+    static constexpr int HALF = 4 * 8 * NT * 4 * 64 * 4;
+    static constexpr int BYTES = TOTAL > HALF ? TOTAL : HALF;
+};
+
+template <int NT>
+__global__ __launch_bounds__(512) void wgrad_bf16_kernel(
+    const uint16_t *__restrict__ X, const uint16_t *__restrict__ dY, float *__restrict__ C,
+    const int32_t *__restrict__ nbr, const int32_t *__restrict__ order, int M, int N, int n, int64_t x_rows, int c, int taps,
+    int slices, int m_tiles, int n_tiles, int64_t c_split_stride)
+{
+    typedef WgradBfLds<NT> L;
+    constexpr int BN = L::BN;
+    constexpr uint32_t OUT = 0x80000000u;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[L::BYTES];
+
+    const unsigned tiles = (unsigned)(m_tiles * n_tiles);
+    unsigned slice, t;
+    if (slices % (int)NUM_XCD == 0) {
+        const unsigned q = blockIdx.x / NUM_XCD;
+        t = q % tiles;
+        slice = (q / tiles) * NUM_XCD + blockIdx.x % NUM_XCD;
+    } else {
+        t = blockIdx.x % tiles;
+        slice = blockIdx.x / tiles;
+    }
+    const int m0 = (int)(t % (unsigned)m_tiles) * (WGB_UNITS * 32), n0 = (int)(t / (unsigned)m_tiles) * BN;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = wave & 3, half = wave >> 2;
+    const int tap0 = m0 / c;
+    const int n_blocks = (n + WG_VOX - 1) / WG_VOX;
+    const int my_blocks = (int)slice < n_blocks ? (n_blocks - 1 - (int)slice) / slices + 1 : 0;
+
+    constexpr int SRD3 = 0x00020000;
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)X, 0, (int)(x_rows * c * 2), SRD3);
+    const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc((void *)dY, 0, (int)((int64_t)n * N * 2), SRD3);
+    const __amdgpu_buffer_rsrc_t rs_n = __builtin_amdgcn_make_buffer_rsrc((void *)nbr, 0, (int)((int64_t)n * taps * 4), SRD3);
+
+    uint32_t *tab = reinterpret_cast<uint32_t *>(lds + L::O_TAB);
+    if (tid < WGB_UNITS * 16) {
+        const int m = m0 + 2 * tid, tap = m / c;
+        tab[tid] = m < M ? (uint32_t)(tap - tap0) << 24 | (uint32_t)(m - tap * c) * 2u : (uint32_t)WG_UNITS << 24;
+    }
+    for (int q = tid; q < 3 * WG_RS; q += 512)
+        reinterpret_cast<uint32_t *>(lds + L::O_IDX + (q / WG_RS) * L::IDX)[WG_UNITS * WG_RS + q % WG_RS] = OUT;
+    uint32_t unit_slots[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int a = m0 + (g + 4 * i) * 32, b = min(a + 31, M - 1);
+        const int lo = a / c - tap0, hi = b / c - tap0;
+        unit_slots[i] = a < M ? ((2u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
+    }
+
+    // ---- staging: index rows two blocks ahead, dY one
+    const int sr = tid >> 2, sq = (tid & 3) * 7;                           // this thread's voxel and first slot
+    auto voxel = [&](int k) -> int {                                       // voxel sr of the slice's k-th block, or -1
+        const int64_t p = ((int64_t)slice + (int64_t)k * slices) * WG_VOX + sr;
+        const bool ok = k < my_blocks && p < n;
+        const int v = order ? order[ok ? p : 0] : (int)p;
+        return ok ? v : -1;
+    };
+    int32_t ix[7];
+    auto fetch_idx = [&](int vox) {
+        const uint32_t row = vox >= 0 ? (uint32_t)(vox * taps + tap0 + sq) * 4u : OUT;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) ix[j] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_n, (int)(row + 4u * j), 0, 0);
+    };
+    // an absent neighbour (-1) becomes a negative, i.e. huge unsigned, byte offset; slots past the
+    // last tap hold whatever follows in memory and are read by nobody
+    auto store_idx = [&](int ring, int vox) {
+        uint32_t *dst = reinterpret_cast<uint32_t *>(lds + L::O_IDX + ring * L::IDX) + sq * WG_RS + sr;
+        uint32_t have = 0;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            const int32_t q = vox >= 0 ? ix[j] : -1;
+            dst[j * WG_RS] = (uint32_t)__mul24(q, c * 2);
+            have |= (uint32_t)(~q >> 31) & (1u << j);
+        }
+        have <<= sq;
+        if ((tid & 3) == 0)
+            reinterpret_cast<uint32_t *>(lds + L::O_ORD)[ring * WG_VOX + sr] = vox >= 0 ? (uint32_t)vox * (uint32_t)(N * 2) : OUT;
+        // or of the wavefront's 16 voxels, which ends up in its last lane
+        int h = (int)have;
+        h |= __builtin_amdgcn_update_dpp(0, h, 0x111, 0xF, 0xF, true);     // row_shr 1, 2, 4, 8
+        h |= __builtin_amdgcn_update_dpp(0, h, 0x112, 0xF, 0xF, true);
+        h |= __builtin_amdgcn_update_dpp(0, h, 0x114, 0xF, 0xF, true);
+        h |= __builtin_amdgcn_update_dpp(0, h, 0x118, 0xF, 0xF, true);
+        h |= __builtin_amdgcn_update_dpp(0, h, 0x142, 0xA, 0xF, true);     // lane 15 of a row to the next, ...
+        h |= __builtin_amdgcn_update_dpp(0, h, 0x143, 0xC, 0xF, true);     // ... lane 31 to the upper half
+        if (lane == 63) reinterpret_cast<int *>(lds + L::O_MASK)[ring * 8 + wave] = h;
+    };
+    // columns come in pairs as well
+    const int yn = tid % (BN / 2), yg = tid / (BN / 2);
+    const bool y_mine = yg < WG_VOX / 8;
+    const uint32_t y_off = n0 + 2 * yn < N ? (uint32_t)(n0 + 2 * yn) * 2u : OUT - 1u;
+    uint32_t yv[8];
+    auto fetch_dy = [&](int ring) {
+        const uint32_t *ord = reinterpret_cast<const uint32_t *>(lds + L::O_ORD) + ring * WG_VOX + (yg % (WG_VOX / 8)) * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) yv[j] = __builtin_amdgcn_raw_buffer_load_b32(rs_y, (int)(ord[j] + y_off), 0, 0);
+    };
+    auto store_dy = [&](int stage) {
+        if (!y_mine) return;
+        const uint32_t sign = yg & 8 ? 0x80008000u : 0u;                   // the second half of the block
+        u32x4 e, o;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            e[p] = pack_lo(yv[2 * p], yv[2 * p + 1]) ^ sign;
+            o[p] = pack_hi(yv[2 * p], yv[2 * p + 1]) ^ sign;
+        }
+        u32x4 *dst = reinterpret_cast<u32x4 *>(lds + stage * L::DY + (yg * BN + 2 * yn) * 16);
+        dst[0] = e;
+        dst[1] = o;
+    };
+
+    f32x4 acc[4][2][NT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[i][q][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto part_taps = [&](int ring, int part) -> uint32_t {
+        const uint32_t *mk = reinterpret_cast<const uint32_t *>(lds + L::O_MASK) + ring * 8 + half * 4 + part * 2;
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(mk[0] | mk[1]));
+    };
+    auto fetch_off = [&](int ring, int part, int i, u32x4 *o) {
+        const uint32_t e = tab[(g + 4 * i) * 16 + li], ch = e & 0xFFFFFFu;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(lds + L::O_IDX + ring * L::IDX) + (e >> 24) * WG_RS + (half * 2 + part) * 32 + lk * 8;
+        o[0] = *reinterpret_cast<const u32x4 *>(src);
+        o[1] = *reinterpret_cast<const u32x4 *>(src + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { o[0][j] += ch; o[1][j] += ch; }
+    };
+    auto fetch_x = [&](const u32x4 *o, uint32_t *raw) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) raw[j] = __builtin_amdgcn_raw_buffer_load_b32(rs_x, (int)o[j >> 2][j & 3], 0, 0);
+    };
+
+    if (my_blocks > 0) {
+        int v0 = voxel(0), v1 = voxel(1), v2 = voxel(2);
+        fetch_idx(v0);
+        store_idx(0, v0);
+        fetch_idx(v1);
+        store_idx(1, v1);
+        __syncthreads();
+        fetch_dy(0);
+        store_dy(0);
+        __syncthreads();
+        constexpr int D = 4;                                               // units whose rows are on their way (divides 8)
+        uint32_t raw[D][8];
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            u32x4 o[2];
+            fetch_off(0, 0, i, o);
+            fetch_x(o, raw[i]);
+        }
+        int r0 = 0, r1 = 1, r2 = 2;
+        for (int k = 0; k < my_blocks; ++k) {
+            fetch_idx(v2);
+            const int v3 = voxel(k + 3);
+            fetch_dy(r1);
+            const unsigned char *dy = lds + (k & 1) * L::DY;
+#pragma unroll
+            for (int part = 0; part < 2; ++part) {
+                if (part == 1) {
+                    store_idx(r2, v2);
+                    store_dy((k + 1) & 1);
+                }
+                const uint32_t have = part_taps(r0, part);
+                u32x4 b[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    b[nt] = *reinterpret_cast<const u32x4 *>(dy + (((half * 2 + part) * 4 + lk) * BN + nt * 16 + li) * 16);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int it = part * 4 + i, next = (it + D) % 8;
+                    u32x4 o[2];
+                    fetch_off(it + D < 8 ? r0 : r1, next / 4, next % 4, o);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (have & unit_slots[i]) {
+                        u32x4 a[2];
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) {
+                            a[0][p] = pack_lo(raw[it % D][2 * p], raw[it % D][2 * p + 1]);
+                            a[1][p] = pack_hi(raw[it % D][2 * p], raw[it % D][2 * p + 1]);
+                        }
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) acc[i][q][nt] = mfma_bf16(a[q], b[nt], acc[i][q][nt]);
+                    }
+                    fetch_x(o, raw[it % D]);
+                }
+            }
+            v2 = v3;
+            const int r = r0; r0 = r1; r1 = r2; r2 = r;
+            __syncthreads();
+        }
+    }
+
+    f32x4 *sums = reinterpret_cast<f32x4 *>(lds) + g * 8 * NT * 64 + lane;
+    if (half == 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) sums[((i * 2 + q) * NT + nt) * 64] = acc[i][q][nt];
+    }
+    __syncthreads();
+    if (half == 1) return;
+    C += (int64_t)slice * c_split_stride;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const f32x4 v = acc[i][q][nt] - sums[((i * 2 + q) * NT + nt) * 64];
+                const int col = n0 + nt * 16 + li;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int m = m0 + (g + 4 * i) * 32 + 2 * (lk * 4 + e) + q;
+                    if (m < M && col < N) C[(int64_t)m * N + col] = v[e];
+                }
+            }
 }
 
 }  // namespace hch

@@ -155,3 +155,18 @@ def test_weight_gradient_with_the_smallest_workspace(oracle, batch):
         _check([dW], [want])
     with pytest.raises(hch.HchError):
         hch.hch_conv_bwd_weight(lv, 0, hch.HCH_F32, X, G, dW, ci, co, _workspace(8 * 27 * ci * co * 4), hch.HCH_ALGO_FUSED)
+
+
+@pytest.mark.parametrize("level", [0, 2])
+@pytest.mark.parametrize("ci,co", [(6, 18), (50, 50), (64, 64), (32, 130), (34, 20)])
+def test_bf16_weight_gradient(oracle, batch, level, ci, co):
+    """Even channel counts of any kind (wgrad_bf16_kernel; 64 -> 64 takes it on the finest level only).
+    bf16 inputs, exact products, fp32 sums: the same bound."""
+    lv, olv = batch
+    n = olv[level].Ntot
+    X, G = torch.randn((n, ci), device="cuda").bfloat16(), torch.randn((n, co), device="cuda").bfloat16()
+    ws = _workspace(hch.hch_conv_workspace_bytes(lv, level, ci, co, hch.HCH_BF16, hch.HCH_WS_BWD_WEIGHT, hch.HCH_ALGO_FUSED))
+    dW = torch.full((27, ci, co), float("nan"), device="cuda")
+    hch.hch_conv_bwd_weight(lv, level, hch.HCH_BF16, X, G, dW, ci, co, ws, hch.HCH_ALGO_FUSED)
+    want = _reference(oracle.neighbours(olv[level]), X, torch.zeros((27, ci, co), device="cuda"), G)[2]
+    _check([dW], [want])
