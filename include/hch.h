@@ -187,6 +187,11 @@ hch_status hch_build_neighbours(hch_levels *levels, int32_t level, void *stream)
  * caller can build the finest level on one stream and the coarser ones beside it on another. */
 hch_status hch_build_neighbours_range(hch_levels *levels, int32_t first, int32_t count, void *stream);
 
+/* The index lists alone: what the columns algorithm, pooling and hch_hash2col / hch_col2hash read.  The
+ * row orders that the fused products walk (row_order, tile_taps) keep their contents; a level set has
+ * them from its construction on.  Same errors as hch_build_neighbours_range. */
+hch_status hch_build_index_lists(hch_levels *levels, int32_t first, int32_t count, void *stream);
+
 /*
  * Optional tap-major copy of nbr27, [27][N_l] instead of [N_l][27], of `level` (-1: every level).
  * The products with bf16 inputs are bound by the number of cache accesses of their gathers, and

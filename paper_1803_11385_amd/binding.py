@@ -13,7 +13,7 @@ __all__ = [
     "HCH_ALGO_COLUMNS", "HCH_ALGO_FUSED", "HCH_ALGO_COLUMNS_RESIDENT", "HCH_ALGO_FUSED_DENSE",
     "library_path", "load_library", "exported_symbols",
     "hch_build_levels", "hch_build_levels_device", "hch_build_tables_host", "hch_build_neighbours",
-    "hch_build_neighbours_range", "hch_hash2col", "hch_col2hash", "hch_conv_workspace_bytes", "hch_conv_fwd", "hch_conv_bwd_data",
+    "hch_build_neighbours_range", "hch_build_index_lists", "hch_hash2col", "hch_col2hash", "hch_conv_workspace_bytes", "hch_conv_fwd", "hch_conv_bwd_data",
     "hch_conv_bwd_weight", "hch_pool_fwd", "hch_pool_bwd", "hch_relu_fwd", "hch_relu_bwd", "hch_relu_pool_fwd",
     "hch_pool_relu_bwd", "hch_pool_relu_bwd_pooled", "hch_deconv_fwd", "hch_deconv_bwd_data", "hch_deconv_bwd_weight",
     "hch_unpool_fwd", "hch_unpool_bwd", "hch_kernel_count", "hch_kernel_name", "hch_profile_enable", "hch_profile_read",
@@ -33,7 +33,7 @@ _LIBPATH = os.path.join(_HERE, "libhch.so")
 # every symbol include/hch.h declares
 exported_symbols = [
     "hch_last_error", "hch_build_levels", "hch_build_levels_device", "hch_build_tables_host", "hch_free_levels",
-    "hch_num_levels", "hch_level_info", "hch_build_neighbours", "hch_build_neighbours_range", "hch_hash2col",
+    "hch_num_levels", "hch_level_info", "hch_build_neighbours", "hch_build_neighbours_range", "hch_build_index_lists", "hch_hash2col",
     "hch_col2hash",
     "hch_conv_workspace_bytes", "hch_conv_fwd", "hch_conv_bwd_data", "hch_conv_bwd_weight",
     "hch_pool_fwd", "hch_pool_bwd", "hch_relu_fwd", "hch_relu_bwd", "hch_relu_pool_fwd",
@@ -103,6 +103,7 @@ def load_library():
     L.hch_level_info.argtypes = [vp, i32, C.POINTER(_Desc)]
     L.hch_build_neighbours.argtypes = [vp, i32, vp]
     L.hch_build_neighbours_range.argtypes = [vp, i32, i32, vp]
+    L.hch_build_index_lists.argtypes = [vp, i32, i32, vp]
     L.hch_build_tap_major.argtypes = [vp, i32, vp]
     L.hch_hash2col.argtypes = [vp, i32, C.c_int, vp, i32, i64, i64, vp, vp]
     L.hch_col2hash.argtypes = [vp, i32, vp, i32, vp, vp]
@@ -417,6 +418,10 @@ def hch_build_tap_major(levels, level=-1, stream=None):
 
 def hch_build_neighbours_range(levels, first, count, stream=None):
     _check(load_library().hch_build_neighbours_range(levels.handle, first, count, _stream(stream)))
+
+
+def hch_build_index_lists(levels, first, count, stream=None):
+    _check(load_library().hch_build_index_lists(levels.handle, first, count, _stream(stream)))
 
 
 def hch_hash2col(levels, level, dtype, X, c_in, row_begin, row_count, col, stream=None):

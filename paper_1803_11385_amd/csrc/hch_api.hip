@@ -179,7 +179,8 @@ static hch_status transpose_neighbours(const Level &L, hipStream_t s)
 }
 
 // index lists of levels [l0, l1) in one launch each
-static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipStream_t s)
+// (orders: and the row orders of the fused products)
+static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipStream_t s, bool orders = true)
 {
     const int b = hl->lv[0].b;
     const int n_entries = (int)hl->lv.size() * b;
@@ -203,7 +204,7 @@ static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipSt
         // pattern order of the levels' voxels (stable counting sort by pattern key), then the tap
         // masks of its 64-row tiles
         const int64_t cnt = (int64_t)hl->sort_off[l1] - hl->sort_off[l0];
-        if (cnt > 0) {
+        if (orders && cnt > 0) {
             {
                 hch::LaunchTimer lt(HCH_KERNEL_ID("pattern_scan_kernel"), s, 8.0 * 64.0 * (double)(last - first), 0.0);
                 HCH_LAUNCH(hch::pattern_scan_kernel, dim3(hch::PATTERN_BINS, (unsigned)(l1 - l0)), dim3(256), 0, s, hl->set,
@@ -306,6 +307,15 @@ extern "C" hch_status hch_build_neighbours_range(hch_levels *levels, int32_t fir
     if (!levels->d_nbr_prefix) return fail(HCH_EINVAL, "hch_build_neighbours_range: levels were built without device tables");
     if (count == 0) return HCH_OK;
     return launch_index_lists(levels, first, first + count, (hipStream_t)stream);
+}
+
+extern "C" hch_status hch_build_index_lists(hch_levels *levels, int32_t first, int32_t count, void *stream)
+{
+    if (!levels || first < 0 || count < 0 || (int64_t)first + count > (int64_t)levels->lv.size())
+        return fail(HCH_EINVAL, "hch_build_index_lists: bad level range");
+    if (!levels->d_nbr_prefix) return fail(HCH_EINVAL, "hch_build_index_lists: levels were built without device tables");
+    if (count == 0) return HCH_OK;
+    return launch_index_lists(levels, first, first + count, (hipStream_t)stream, false);
 }
 
 // ---- PSH construction on the device (psh_device.hip.hpp) ----

@@ -72,7 +72,10 @@ class Encoder:
 
     def build_indices(self):
         if not self.two_streams:
-            B.hch_build_neighbours(self.levels, -1)
+            if self.algo == B.HCH_ALGO_COLUMNS:       # its products take the voxels as they come: no row orders
+                B.hch_build_index_lists(self.levels, 0, self.levels.n_levels)
+            else:
+                B.hch_build_neighbours(self.levels, -1)
             return
         # the finest level's lists on the main stream, the coarser levels' beside it; the main
         # stream picks them up before the first pooling (forward)

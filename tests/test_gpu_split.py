@@ -170,3 +170,21 @@ def test_bf16_weight_gradient(oracle, batch, level, ci, co):
     hch.hch_conv_bwd_weight(lv, level, hch.HCH_BF16, X, G, dW, ci, co, ws, hch.HCH_ALGO_FUSED)
     want = _reference(oracle.neighbours(olv[level]), X, torch.zeros((27, ci, co), device="cuda"), G)[2]
     _check([dW], [want])
+
+
+def test_index_lists_alone(oracle):
+    """hch_build_index_lists rewrites the lists and leaves the row orders as they are."""
+    coords, offs, _ = S.config_batch(3, batch=4, u=64)
+    lv, olv = hch.hch_build_levels(coords, offs, 64, 3), oracle.build_hierarchy(coords, offs, 64, 3)
+    before = [(lv.info(l).device_row_order(), lv.info(l).device_tile_taps()) for l in range(3)]
+    hch.hch_build_index_lists(lv, 0, 3)
+    hch.hch_build_index_lists(lv, 1, 0)
+    torch.cuda.synchronize()
+    for l in range(3):
+        assert np.array_equal(lv.info(l).device_nbr27(), oracle.neighbours(olv[l]))
+        if l:
+            assert np.array_equal(lv.info(l).device_child8(), oracle.children(olv[l - 1], olv[l]))
+        assert np.array_equal(lv.info(l).device_row_order(), before[l][0])
+        assert np.array_equal(lv.info(l).device_tile_taps(), before[l][1])
+    with pytest.raises(hch.HchError):
+        hch.hch_build_index_lists(lv, 2, 2)
