@@ -1227,6 +1227,7 @@ static hch_status launch_gemm_t(const GemmPlan &plan, const void *A, const void 
         }
     }
     if (!g_lean_loops.load(std::memory_order_relaxed)) lean = false;
+    if (tilemask) lean = false;        // rows in an order, taps left out: conv_split_kernel, or operands beyond the lean loop's reach
     const int ln = lean ? 1 : 0;
     if (ids[ln][pl][v][cfg] < 0) {
         char nm[128];
@@ -1239,8 +1240,7 @@ static hch_status launch_gemm_t(const GemmPlan &plan, const void *A, const void 
     }
     int kid = ids[ln][pl][v][cfg];
     if (lean && lean16)
-        kid = tilemask ? HCH_KERNEL_ID("gemm_f32_kernel<float, 128, 32, 16, 4, 2, false, true, false, true, true>")
-                       : HCH_KERNEL_ID("gemm_f32_kernel<float, 128, 32, 16, 4, 2, false, true, false, false, true>");
+        kid = HCH_KERNEL_ID("gemm_f32_kernel<float, 128, 32, 16, 4, 2, false, true, false, false, true>");
     const bool short_k = AMODE == hch::A_ROWS && B_KC && pl == 1 && vec && p.bm == 128 && K <= 16 && p.splits == 1;
     if (short_k) kid = HCH_KERNEL_ID("gemm_f32_kernel<float, 128, 64, 16, 4, 0, true, true, true, false, false>");
     hch::LaunchTimer lt(kid, s, alg_bytes, 2.0 * M * (double)N * K);
@@ -1262,32 +1262,21 @@ static hch_status launch_gemm_t(const GemmPlan &plan, const void *A, const void 
             return HCH_OK;
         }
     }
-#define HCH_GEMM_LEAN_CASE(BM_, BN_, WM_, SKIP_)                                                                     \
-    HCH_LAUNCH((hch::gemm_f32_kernel<TIN, BM_, BN_, 32, WM_, AMODE, B_KC, true, false, SKIP_, true>), grid, dim3(256), 0, s, HCH_GEMM_ARGS)
+#define HCH_GEMM_LEAN_CASE(BM_, BN_, WM_)                                                                            \
+    HCH_LAUNCH((hch::gemm_f32_kernel<TIN, BM_, BN_, 32, WM_, AMODE, B_KC, true, false, false, true>), grid, dim3(256), 0, s, HCH_GEMM_ARGS)
     if constexpr (lean_mode) {
         if (lean) {
             if constexpr (AMODE == hch::A_GATHER && !B_KC) {
                 if (lean16) {
-                    if (tilemask) HCH_LAUNCH((hch::gemm_f32_kernel<TIN, 128, 32, 16, 4, AMODE, B_KC, true, false, true, true>), grid, dim3(256), 0, s, HCH_GEMM_ARGS);
-                    else HCH_LAUNCH((hch::gemm_f32_kernel<TIN, 128, 32, 16, 4, AMODE, B_KC, true, false, false, true>), grid, dim3(256), 0, s, HCH_GEMM_ARGS);
+                    HCH_LAUNCH((hch::gemm_f32_kernel<TIN, 128, 32, 16, 4, AMODE, B_KC, true, false, false, true>), grid, dim3(256), 0, s, HCH_GEMM_ARGS);
                     HCH_LAUNCH_CHECK("gemm_f32_kernel");
                     return HCH_OK;
                 }
             }
-            if constexpr (AMODE == hch::A_GATHER) {
-                if (tilemask) {
-                    if (p.bm == 64) HCH_GEMM_LEAN_CASE(64, 64, 2, true);
-                    else if (p.bn == 16) HCH_GEMM_LEAN_CASE(128, 16, 4, true);
-                    else if (p.bn == 32) HCH_GEMM_LEAN_CASE(128, 32, 4, true);
-                    else HCH_GEMM_LEAN_CASE(128, 64, 4, true);
-                    HCH_LAUNCH_CHECK("gemm_f32_kernel");
-                    return HCH_OK;
-                }
-            }
-            if (p.bm == 64) HCH_GEMM_LEAN_CASE(64, 64, 2, false);
-            else if (p.bn == 16) HCH_GEMM_LEAN_CASE(128, 16, 4, false);
-            else if (p.bn == 32) HCH_GEMM_LEAN_CASE(128, 32, 4, false);
-            else HCH_GEMM_LEAN_CASE(128, 64, 4, false);
+            if (p.bm == 64) HCH_GEMM_LEAN_CASE(64, 64, 2);
+            else if (p.bn == 16) HCH_GEMM_LEAN_CASE(128, 16, 4);
+            else if (p.bn == 32) HCH_GEMM_LEAN_CASE(128, 32, 4);
+            else HCH_GEMM_LEAN_CASE(128, 64, 4);
             HCH_LAUNCH_CHECK("gemm_f32_kernel");
             return HCH_OK;
         }
