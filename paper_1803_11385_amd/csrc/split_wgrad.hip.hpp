@@ -371,7 +371,8 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
 // lane loads 32 bits and gives one half to each of two operands), so a unit is 32 rows of dW; a
 // wavefront has 4 of the 16 units of a workgroup.  The second half of every block enters with the
 // opposite sign and is subtracted at the end: the instruction rounds its sums down, and so the two
-// halves err in opposite directions.
+// halves err in opposite directions.  64 -> 64 at 2.98 M voxels (512^3, thick shells): 1170 -> 873 us with
+// the taps that 32 voxels lack left out; bound by the gathered loads, 8 per 8 matrix instructions.
 constexpr int WGB_UNITS = 16;
 template <int NT>
 struct WgradBfLds {
