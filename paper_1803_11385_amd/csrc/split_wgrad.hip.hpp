@@ -1,32 +1,38 @@
 // Weight gradient of a gathered convolution (Eq.7), dW[tap*c + ch][n] = sum over the voxels i of
 // X[nbr[i][tap]][ch] * dY[i][n], with fp32 operands on the bf16 matrix instruction.
 //
-// An fp32 number is the exact sum of three bf16 numbers (its 24 significant bits cut into three
-// times eight), a product of two therefore the sum of nine bf16 products; the six largest are
-// computed (what is left out is below 2^-23 of the product), each exact, summed in fp32 by
-// v_mfma_f32_16x16x32_bf16.  Six of those take 96 cycles for what takes v_mfma_f32_16x16x4_f32 256,
-// and they round once per 32 terms instead of once per 4.
+// An fp32 number is the exact sum of three bf16 numbers, each the rest of it rounded to 8 bits, a
+// product of two therefore the sum of nine bf16 products; the six largest are computed, each exact,
+// summed in fp32 by v_mfma_f32_16x16x32_bf16.  The second piece is at most 2^-8 of the number and the
+// third 2^-17, of either sign, so what is left out is at most 2^-24 of the product (on random
+// numbers 2^-27.4 in the mean square, without a preferred sign; pieces that are cut off instead lose up to 2^-21,
+// always towards zero).  Six of those take 96 cycles for what takes v_mfma_f32_16x16x4_f32 256, and
+// they round once per 8 terms instead of once per 4.
 #pragma once
 #include "gemm_bf16.hip.hpp"
 
 namespace hch {
 
-// x[0..7] = h + m + l, as three MFMA operands of 8 bf16 each.  Cutting (not rounding) keeps every
-// piece finite for finite x and both differences exact; an infinity or NaN makes m a NaN, so that
-// whatever it is multiplied into comes out non-finite (the caller then takes the plain fp32 sum).
+// two fp32 numbers rounded to the nearest bf16, the first in the lower half
+__device__ __forceinline__ uint32_t round_bf16(float a, float b)
+{
+    typedef float f32x2v __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2v));
+}
+
+// x[0..7] = h + m + l, as three MFMA operands of 8 bf16 each.  Both differences are exact.  An infinity,
+// a NaN or a number that rounds beyond the largest bf16 makes m a NaN, so that whatever it is
+// multiplied into comes out non-finite (the caller then takes the plain fp32 sum).
 // (v_dot2_f32_bf16 with (-1, 0) would subtract straight from the packed pair, but its sum is not exact.)
 __device__ __forceinline__ void split3(const float *x, u32x4 &h, u32x4 &m, u32x4 &l)
 {
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        const uint32_t a = __float_as_uint(x[2 * p]), b = __float_as_uint(x[2 * p + 1]);
-        h[p] = pack_hi(a, b);
-        const uint32_t ra = __float_as_uint(x[2 * p] - __uint_as_float(a & 0xFFFF0000u));
-        const uint32_t rb = __float_as_uint(x[2 * p + 1] - __uint_as_float(b & 0xFFFF0000u));
-        m[p] = pack_hi(ra, rb);
-        const uint32_t sa = __float_as_uint(__uint_as_float(ra) - __uint_as_float(ra & 0xFFFF0000u));
-        const uint32_t sb = __float_as_uint(__uint_as_float(rb) - __uint_as_float(rb & 0xFFFF0000u));
-        l[p] = pack_hi(sa, sb);
+        h[p] = round_bf16(x[2 * p], x[2 * p + 1]);
+        const float ra = x[2 * p] - __uint_as_float(h[p] << 16), rb = x[2 * p + 1] - __uint_as_float(h[p] & 0xFFFF0000u);
+        m[p] = round_bf16(ra, rb);
+        l[p] = round_bf16(ra - __uint_as_float(m[p] << 16), rb - __uint_as_float(m[p] & 0xFFFF0000u));
     }
 }
 
@@ -35,25 +41,31 @@ __device__ __forceinline__ f32x4 mfma_bf16(const u32x4 &a, const u32x4 &b, const
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// c[nt] += a * b[nt] for split operands, or c[nt] -= a * b[nt] (MINUS).  The 32 terms are summed by
-// themselves, smallest first, so that the long sum in c is rounded once per 32 terms; consecutive
-// instructions belong to different sums, so that none waits for the one before it.  The instruction
+// c[nt] += a * b[nt] for split operands, or c[nt] -= a * b[nt] (MINUS).  The leading products of the 32
+// terms are summed by themselves and so are the five smaller ones, so that both sums are rounded once
+// when they meet and the long sum in c once per 32 terms (a single product ends up as close as
+// the fp32 instruction's: 2.5e-8 in the mean square, 3.4e-8 with the leading products added to the smaller
+// ones by the instruction, which rounds less well there; 250 against 260 us, 64 -> 64 at 280 000
+// voxels).  Consecutive instructions belong to different sums, so that none waits for the one before
+// it.  The instruction
 // rounds its sum down: the caller negates b and takes MINUS for every other stretch of 32 terms,
 // which turns what would add up over a long reduction (-3.6e-7 of the result's size at 280 000
 // voxels) into something that cancels.
 template <int NT, bool MINUS>
 __device__ __forceinline__ void mfma_split(const u32x4 *a, const u32x4 (*b)[3], f32x4 *c)
 {
-    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-    f32x4 t[NT];
+    constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
+    f32x4 t[NT], low[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) t[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < NT; ++nt) low[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
+    for (int q = 0; q < 5; ++q)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) t[nt] = mfma_bf16(a[PA[q]], b[nt][PB[q]], t[nt]);
+        for (int nt = 0; nt < NT; ++nt) low[nt] = mfma_bf16(a[PA[q]], b[nt][PB[q]], low[nt]);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) c[nt] = MINUS ? c[nt] - t[nt] : c[nt] + t[nt];
+    for (int nt = 0; nt < NT; ++nt) t[nt] = mfma_bf16(a[0], b[nt][0], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) c[nt] = MINUS ? c[nt] - (t[nt] + low[nt]) : c[nt] + (t[nt] + low[nt]);
 }
 
 __device__ __forceinline__ bool non_finite(float v) { return (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u; }

@@ -3,11 +3,12 @@ wgrad_split_kernel) and the finer of the two row orders, at the sizes where they
 channel counts around the tiles of 16, 32 and 64 and with remainders of 8 and of 4, a single voxel,
 one voxel around the 64- and 128-row tiles, levels with and without a fine order.
 
-The reference is the definition in fp64 over the oracle's neighbour lists.  Bound: every product is
-exact to 2^-23.4 (what the six piece products leave out), a sum of K terms is rounded about
-K / 32 times to 2^-24 of its size, K <= 27 * 64 forward and <= 400 voxels per partial sum of the
-weight gradient, and partial sums add up to 256 more roundings: below 2^-24 * (1.5 + sqrt(256)) ~ 1e-6
-of the result's norm in any order."""
+The reference is the definition in fp64 over the oracle's neighbour lists.  Bound: what the six
+piece products leave out is at most 2^-24 of a product and 2^-27 in the mean square; a sum of K terms is
+rounded about K / 8 times to 2^-24 of its size at the time (the instruction rounds once per 8 terms),
+0.29 * 2^-23 * sqrt(K / 16) of the result in any order: 5e-7 for K <= 27 * 130 forward and in the data
+gradient.  The weight gradient rounds once per 32 voxels and adds at most 256 partial sums: 4e-7.
+Together below 1e-6 of the result's norm."""
 import numpy as np
 import pytest
 
@@ -92,6 +93,42 @@ def test_small_batches_in_any_order(oracle, n, ci, co):
     nbr = oracle.neighbours(oracle.build_hierarchy(coords, offs, 16, 1)[0])
     X, W, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda() for s in ((n, ci), (27, ci, co), (n, co)))
     _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
+
+
+WORST = np.array([0x3F80FFFF, 0x3F807FC0, 0x3F800001, 0x3FFFFFFF], np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("values", ["worst", "random"])
+@pytest.mark.parametrize("ci,co", [(33, 50), (64, 64)])
+def test_single_products(values, ci, co):
+    """Voxels without neighbours and rows with one number that is not zero: every result is one
+    product.  The pieces leave out at most
+    2^-24 of it and it is rounded once more, to 2^-24; neither has a preferred direction: the mean
+    over all products is far below one rounding.  The mantissas 0x00FFFF and 0x007FC0 are the worst
+    for pieces that are cut off and for pieces that are rounded."""
+    rng = np.random.default_rng(7 * ci + co)
+    n = min(ci, co)
+    q = np.arange(n)
+    coords = np.stack([q // 256 * 4 + 1, q // 16 % 16 * 4 + 1, q % 16 * 4 + 1], 1).astype(np.int32)
+    lv = hch.hch_build_levels(coords, [0, n], 64, 1)
+
+    def draw(*shape):
+        a = rng.standard_normal(shape, dtype=np.float32) if values == "random" else rng.choice(WORST, shape) * rng.choice([-1.0, 1.0], shape)
+        return torch.from_numpy(a.astype(np.float32)).cuda()
+
+    W = draw(27, ci, co)
+    X, G = torch.zeros((n, ci), device="cuda"), torch.zeros((n, co), device="cuda")
+    X[q, q], G[q, q] = draw(n), draw(n)
+    full = draw(n, co)
+    Y, dX, _ = _run(lv, 0, X, W, G)
+    dW = _run(lv, 0, X, W, full)[2]
+    C = W[13].double()
+    x, g = X[q, q].double(), G[q, q].double()
+    for got, want in ((Y, x[:, None] * C[:n]), (dX, g[:, None] * C.T[:n]), (dW[13, :n], x[:, None] * full.double())):
+        err = (got.double() - want) / want.abs()
+        assert float(err.abs().max()) <= 2.0 ** -23
+        if values == "random":               # (a dozen mantissas have a mean of their own)
+            assert abs(float((err * want.sign()).mean())) < 2.0 ** -27      # 2^-25 / sqrt(1650 products), five times
 
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e12])
