@@ -152,7 +152,11 @@ def test_numbers_that_are_not_finite(oracle, batch, value):
     lv, olv = batch
     n = olv[2].Ntot
     nbr = oracle.neighbours(olv[2])
-    X, W, G = (torch.randn(s, device="cuda") for s in ((n, 50), (27, 50, 50), (n, 50)))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    # no number below 0.01, whose product with 3.2e38 would not pass for a large one
+    X, W, G = (t + torch.copysign(torch.full_like(t, 0.01), t) for t in
+               (torch.randn(s, device="cuda", generator=g) for s in ((n, 50), (27, 50, 50), (n, 50))))
     clean = _run(lv, 2, X, W, G)
     v = n // 2
     X[v, 7] = value
@@ -164,7 +168,7 @@ def test_numbers_that_are_not_finite(oracle, batch, value):
         assert torch.isfinite(got[~near]).all()
         err = (got[~near].double() - ref[~near].double()).norm() / ref.double().norm()
         assert float(err) < BOUND
-        big = ~torch.isfinite(got[near]) | (got[near].abs() > 1e35)
+        big = ~torch.isfinite(got[near]) | (got[near].abs() > 1e35)      # 3.2e38 * 0.01 = 3.2e36
         assert bool(big.all())
     hit = torch.zeros((27, 50, 50), dtype=torch.bool, device="cuda")
     for k in range(27):
