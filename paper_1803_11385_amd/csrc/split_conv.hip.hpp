@@ -191,7 +191,9 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
     };
 
     // the products of the leading pieces and the five smaller ones are summed apart: the large sums
-    // are rounded once per 32 terms instead of six times
+    // are rounded by one instruction per 32 terms instead of six.  (Sums of one sign over very many terms lean
+    // downwards, 4.6e-8 of the result with 27 taps of 512 channels and 3.5e-7 with 2048, where
+    // v_mfma_f32_16x16x4_f32 leans by 7.0e-8 and 9.4e-7; sums of either sign by 2e-9 and less.)
     f32x4 acc[NT], low[NT];
 #pragma unroll
     for (int b = 0; b < NT; ++b) acc[b] = low[b] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -47,10 +47,10 @@ __device__ __forceinline__ f32x4 mfma_bf16(const u32x4 &a, const u32x4 &b, const
 // the fp32 instruction's: 2.5e-8 in the mean square, 3.4e-8 with the leading products added to the smaller
 // ones by the instruction, which rounds less well there; 250 against 260 us, 64 -> 64 at 280 000
 // voxels).  Consecutive instructions belong to different sums, so that none waits for the one before
-// it.  The instruction
-// rounds its sum down: the caller negates b and takes MINUS for every other stretch of 32 terms,
-// which turns what would add up over a long reduction (-3.6e-7 of the result's size at 280 000
-// voxels) into something that cancels.
+// it.  The instruction rounds to the nearest where the sum exceeds the products, but drops the lowest bits
+// of products downwards where they exceed the sum: the caller negates b and takes MINUS for every other
+// stretch of 32 terms, so that this cancels (without it results are 1.5e-8 of their rms too low at
+// a million voxels, with it 4e-10).
 template <int NT, bool MINUS>
 __device__ __forceinline__ void mfma_split(const u32x4 *a, const u32x4 (*b)[3], f32x4 *c)
 {
@@ -382,8 +382,8 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
 // The same product with bf16 operands, which need no cutting.  Rows are taken in pairs of channels (a
 // lane loads 32 bits and gives one half to each of two operands), so a unit is 32 rows of dW; a
 // wavefront has 4 of the 16 units of a workgroup.  The second half of every block enters with the
-// opposite sign and is subtracted at the end: the instruction rounds its sums down, and so the two
-// halves err in opposite directions.  64 -> 64 at 2.98 M voxels (512^3, thick shells): 1170 -> 873 us with
+// opposite sign and is subtracted at the end, for the reason given at mfma_split (inputs of one sign,
+// a million voxels: results 1.2e-8 too small without it, 3e-10 with it).  64 -> 64 at 2.98 M voxels (512^3, thick shells): 1170 -> 873 us with
 // the taps that 32 voxels lack left out; bound by the gathered loads, 8 per 8 matrix instructions.
 constexpr int WGB_UNITS = 16;
 template <int NT>

@@ -29,17 +29,17 @@ def _workspace(nbytes):
 
 
 def _ws(lv, l, ci, co):
-    return _workspace(max(hch.hch_conv_workspace_bytes(lv, l, ci, co, hch.HCH_F32, k, hch.HCH_ALGO_FUSED)
-                          for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT)))
+    return _workspace(max(hch.hch_conv_workspace_bytes(lv, l, ci, co, hch.HCH_F32, k, a)
+                          for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA, hch.HCH_WS_BWD_WEIGHT)
+                          for a in (hch.HCH_ALGO_FUSED, hch.HCH_ALGO_FUSED_DENSE)))
 
 
-def _run(lv, l, X, W, G):
+def _run(lv, l, X, W, G, a=hch.HCH_ALGO_FUSED):
     n, ci = X.shape
     co = G.shape[1]
     Y = torch.full((n, co), float("nan"), device="cuda")
     dX = torch.full((n, ci), float("nan"), device="cuda")
     dW = torch.full((27, ci, co), float("nan"), device="cuda")
-    a = hch.HCH_ALGO_FUSED
     hch.hch_conv_fwd(lv, l, hch.HCH_F32, X, W, Y, ci, co, _ws(lv, l, ci, co), a)
     hch.hch_conv_bwd_data(lv, l, hch.HCH_F32, G, W, dX, ci, co, _ws(lv, l, ci, co), a)
     hch.hch_conv_bwd_weight(lv, l, hch.HCH_F32, X, G, dW, ci, co, _ws(lv, l, ci, co), a)
@@ -93,6 +93,31 @@ def test_small_batches_in_any_order(oracle, n, ci, co):
     nbr = oracle.neighbours(oracle.build_hierarchy(coords, offs, 16, 1)[0])
     X, W, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda() for s in ((n, ci), (27, ci, co), (n, co)))
     _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
+
+
+@pytest.mark.parametrize("sign", ["any", "positive"])
+@pytest.mark.parametrize("ci,co", [(256, 64), (512, 64), (512, 512)])
+def test_many_channels(oracle, ci, co, sign):
+    """All 27 taps of up to 512 channels: up to 432 steps of 32 terms in one chain of sums.  Bound as
+    above, 0.29 * 2^-23 * sqrt(27 * 512 / 16) = 1.02e-6, and neither the error nor its mean beyond those
+    of the fp32 instruction (HCH_ALGO_FUSED_DENSE), whose roundings lean the same way in sums of one
+    sign; 5e-9 is what the mean of random roundings can come to, 1e-6 / sqrt(27 * 256 * 64) times 3."""
+    q = np.arange(16 ** 3)
+    coords = np.stack([q // 256, q // 16 % 16, q % 16], 1).astype(np.int32)
+    lv = hch.hch_build_levels(coords, [0, q.size], 16, 1)
+    nbr = oracle.neighbours(oracle.build_hierarchy(coords, [0, q.size], 16, 1)[0])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ci + co)
+    X, W, G = (torch.randn(s, device="cuda", generator=g) for s in ((q.size, ci), (27, ci, co), (q.size, co)))
+    if sign == "positive":
+        X, W, G = X.abs(), W.abs(), G.abs()
+    def errors(got):
+        d = [(t.double() - w, w) for t, w in zip(got, want)]
+        return [(float(e.norm() / w.norm()), abs(float(e.mean() / w.pow(2).mean().sqrt()))) for e, w in d]
+    want = _reference(nbr, X, W, G)
+    for split, plain in zip(errors(_run(lv, 0, X, W, G)), errors(_run(lv, 0, X, W, G, hch.HCH_ALGO_FUSED_DENSE))):
+        assert split[0] < 1.1e-6 and split[0] <= plain[0]
+        assert split[1] <= plain[1] + 5e-9
 
 
 WORST = np.array([0x3F80FFFF, 0x3F807FC0, 0x3F800001, 0x3FFFFFFF], np.uint32).view(np.float32)
