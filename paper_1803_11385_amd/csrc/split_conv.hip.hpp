@@ -262,6 +262,7 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
         acc[b] += low[b];
 #pragma unroll
         for (int e = 0; e < 4; ++e) bad |= non_finite(acc[b][e]);
+        acc[b] *= SPLIT_UNSCALE;
     }
     const int vox = idx[13 * ROWS + li];
     if (__builtin_expect(__ballot(bad) != 0, 0)) {

@@ -158,7 +158,7 @@ def test_single_products(values, ci, co):
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e12])
 def test_any_scale(oracle, batch, scale):
-    """The pieces have the exponent range of fp32: nothing is lost for small or large numbers."""
+    """The same relative error for small and for large numbers."""
     lv, olv = batch
     n = olv[2].Ntot
     X, W, G = (torch.randn(s, device="cuda") for s in ((n, 50), (27, 50, 50), (n, 50)))
@@ -168,6 +168,20 @@ def test_any_scale(oracle, batch, scale):
     _check(got[:2], want[:2])
     if scale >= 1e-12:
         _check([got[2]], [want[2]])
+
+
+@pytest.mark.parametrize("a,b", [(1e-34, 1.0), (1e-36, 1.0), (1.0, 1e-36), (1e-40, 1e20), (1e20, 1e-40), (1e30, 1e-30)])
+def test_ends_of_the_range(oracle, batch, a, b):
+    """Operands down to the smallest fp32 numbers (1e-40 is a few tens of thousands times the smallest),
+    with products in the ordinary range or exact to 2^-149: nothing is lost, the bound is the same."""
+    lv, olv = batch
+    n = olv[2].Ntot
+    nbr = oracle.neighbours(olv[2])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X, W, G = (torch.randn(s, device="cuda", generator=g) for s in ((n, 50), (27, 50, 50), (n, 50)))
+    _check(_run(lv, 2, X * a, W * b, G * a)[:2], _reference(nbr, X * a, W * b, G * a)[:2])
+    _check(_run(lv, 2, X * a, W, G * b)[2:], _reference(nbr, X * a, W, G * b)[2:])
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.2e38])
