@@ -6,6 +6,15 @@
 
 namespace hch {
 
+// the first `have` (none to all) of 8 consecutive numbers, zeros behind them
+__device__ __forceinline__ void load8(const float *p, int have, float *v)
+{
+    if (have >= 8) __builtin_memcpy(v, p, 32);
+    else
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = j < have ? p[j] : 0.f;
+}
+
 // A workgroup of 4 wavefronts computes 64 rows of the order `rowmap` by 16*NT columns; a wavefront has
 // 16 rows of its own.  The reduction runs over the taps that the workgroup's rows have
 // (`tilemask`), in units of 8 channels of one tap, 4 units (32 terms) to a step.
@@ -266,22 +275,37 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
     }
     const int vox = idx[13 * ROWS + li];
     if (__builtin_expect(__ballot(bad) != 0, 0)) {
-        // an infinity or NaN among the operands, or a sum out of range: plain fp32 sums
-#pragma unroll 1
-        for (int q = 0; q < NT * 4; ++q) {
-            const int col = n0 + (q >> 2) * 16 + lk * 4 + (q & 3);
-            if (vox < 0 || col >= N) continue;
-            float s = 0.f;
-            for (int u = s_beg * 4; u < min(s_end * 4, n_units); ++u) {
-                const int tap = taplist[u / c8], k0 = (u % c8) * 8;
-                const int32_t j = idx[tap * ROWS + li];
-                if (j < 0) continue;
-                for (int k = k0; k < min(k0 + 8, c); ++k)
-                    s += X[(int64_t)j * c + k] * W[BT ? ((int64_t)(26 - tap) * N + col) * c + k : ((int64_t)tap * c + k) * N + col];
+        // An infinity or NaN among the operands, or a sum out of range: the sums of this slice with the
+        // fp32 instruction, up to 32 channels of one tap at a time, added only where the row has the tap
+        // (an absent row is not zero times an infinity).  From memory, without LDS or barriers.  Every number
+        // a NaN, 32 -> 64 at 40 000 voxels: 110 us, 2.0 ms with the outputs summed one after the other; at
+        // 280 000 voxels forward 365 us and data gradient 392, 139 and 150 with finite numbers.
+#pragma unroll
+        for (int b = 0; b < NT; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int u_end = min(s_end * 4, n_units);
+        for (int u = s_beg * 4, cnt; u < u_end; u += cnt) {
+            const int tap = taplist[u / c8], u_tap = u % c8, k0 = (u_tap + lk) * 8;
+            cnt = min(min(4, c8 - u_tap), u_end - u);
+            const int row = idx[tap * ROWS + li];
+            if (__ballot(row >= 0) == 0) continue;
+            const int have = lk < cnt ? c - k0 : 0;
+            float x[8];
+            load8(X + (int64_t)max(row, 0) * c + k0, row >= 0 ? have : 0, x);
+#pragma unroll
+            for (int b = 0; b < NT; ++b) {
+                const int col = n0 + b * 16 + li;
+                float w[8];
+                if constexpr (BT) load8(W + ((int64_t)(26 - tap) * N + min(col, N - 1)) * c + k0, col < N ? have : 0, w);
+                else
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) w[j] = j < have && col < N ? W[((int64_t)tap * c + k0 + j) * N + col] : 0.f;
+                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < 8; ++j) t = mfma_f32(w[j], x[j], t);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[b][e] += row >= 0 ? t[e] : 0.f;
             }
-            C[(int64_t)vox * N + col] = s;
         }
-        return;
     }
     if (vox < 0) return;
 #pragma unroll

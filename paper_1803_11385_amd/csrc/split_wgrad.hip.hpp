@@ -77,6 +77,11 @@ __device__ __forceinline__ void mfma_split(const u32x4 *a, const u32x4 (*b)[3], 
     for (int nt = 0; nt < NT; ++nt) c[nt] = MINUS ? c[nt] - (t[nt] + low[nt]) : c[nt] + (t[nt] + low[nt]);
 }
 
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4 &c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ bool non_finite(float v) { return (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u; }
 
 // A workgroup of 8 wavefronts computes 28 units of 16 rows of dW by 16*NT columns over the blocks of
@@ -325,7 +330,7 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
     }
 
     // An infinity or NaN among the operands (or a sum out of range) has left a non-finite sum: such a
-    // wavefront takes the plain fp32 sums of its voxels instead, which is what such numbers mean.
+    // wavefront takes the fp32 sums of its voxels instead, which is what such numbers mean.
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < 7; ++i)
@@ -334,20 +339,62 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
 #pragma unroll
             for (int e = 0; e < 4; ++e) bad |= non_finite(acc[i][nt][e]);
     bad = __builtin_expect(__ballot(bad) != 0, 0);
-    auto plain = [&](int m, int col) -> float {
-        float s = 0.f;
-        if (m >= M || col >= N) return s;
-        const int tap = m / c;
-        for (int k = 0; k < my_blocks; ++k)
-            for (int q = 0; q < 64; ++q) {
-                const int64_t p = ((int64_t)slice + (int64_t)k * slices) * WG_VOX + half * 64 + q;
-                if (p >= n) break;
-                const int64_t v = order ? order[p] : p;
-                const int32_t j = nbr[v * taps + tap];
-                if (j >= 0) s += X[(int64_t)j * c + (m - tap * c)] * dY[v * N + col];
+    // (The fp32 instruction, 32 voxels at a time and tap by tap: dY counts only where the voxel has the tap --
+    // an absent row is not zero times an infinity -- and of the result only the rows of that tap.  From
+    // memory, without LDS or barriers.  Every number a NaN, 32 -> 64 at 40 000 voxels: 139 us, 9.1 ms with the
+    // outputs summed one after the other; at 280 000 voxels 554 us, 141 with finite numbers.)
+    if (bad) {
+#pragma unroll
+        for (int i = 0; i < 7; ++i)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < 2 * my_blocks; ++q) {
+            const int64_t p0 = ((int64_t)slice + (int64_t)(q >> 1) * slices) * WG_VOX + half * 64 + (q & 1) * 32 + lk * 8;
+            int vox[8];
+            float y[NT][8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool ok = p0 + j < n;
+                const int v = order ? order[ok ? p0 + j : 0] : (int)(p0 + j);
+                vox[j] = ok ? v : -1;
             }
-        return s;
-    };
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int col = n0 + nt * 16 + li;
+                    y[nt][j] = vox[j] >= 0 && col < N ? dY[(int64_t)vox[j] * N + col] : 0.f;
+                }
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                const int a = m0 + (g + 4 * i) * 16, m = min(a + li, M - 1), ch = m - m / c * c;
+                const int last = min(a + 15, M - 1) / c;
+#pragma unroll 1
+                for (int tap = a / c; tap <= last; ++tap) {
+                    int row[8];
+                    float x[8];
+                    bool any = false;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        row[j] = vox[j] >= 0 ? nbr[(int64_t)vox[j] * taps + tap] : -1;
+                        any |= row[j] >= 0;
+                    }
+                    if (__ballot(any) == 0) continue;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[j] = row[j] >= 0 ? X[(int64_t)row[j] * c + ch] : 0.f;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) t = mfma_f32(x[j], row[j] >= 0 ? y[nt][j] : 0.f, t);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][nt][e] += (a + lk * 4 + e) / c == tap ? t[e] : 0.f;
+                    }
+                }
+            }
+        }
+    }
+    const float unscale = bad ? 1.f : SPLIT_UNSCALE;
 
     // second half of every block -> LDS, added by the wavefront that has the first half
     f32x4 *sums = reinterpret_cast<f32x4 *>(lds) + g * 7 * NT * 64 + lane;
@@ -355,30 +402,16 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
 #pragma unroll
         for (int i = 0; i < 7; ++i)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) sums[(i * NT + nt) * 64] = acc[i][nt] * SPLIT_UNSCALE;
-        if (bad) {
-#pragma unroll 1
-            for (int q = 0; q < 7 * NT * 4; ++q)
-                sums[(q >> 2) * 64][q & 3] = plain(m0 + (g + 4 * (q / (4 * NT))) * 16 + lk * 4 + (q & 3), n0 + (q / 4 % NT) * 16 + li);
-        }
+            for (int nt = 0; nt < NT; ++nt) sums[(i * NT + nt) * 64] = acc[i][nt] * unscale;
     }
     __syncthreads();
     if (half == 1) return;
     C += (int64_t)slice * c_split_stride;
-    if (bad) {
-#pragma unroll 1
-        for (int q = 0; q < 7 * NT * 4; ++q) {
-            const int m = m0 + (g + 4 * (q / (4 * NT))) * 16 + lk * 4 + (q & 3), col = n0 + (q / 4 % NT) * 16 + li;
-            const float v = plain(m, col) + sums[(q >> 2) * 64][q & 3];
-            if (m < M && col < N) C[(int64_t)m * N + col] = v;
-        }
-        return;
-    }
 #pragma unroll
     for (int i = 0; i < 7; ++i)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const f32x4 v = acc[i][nt] * SPLIT_UNSCALE + sums[(i * NT + nt) * 64];
+            const f32x4 v = acc[i][nt] * unscale + sums[(i * NT + nt) * 64];
             const int col = n0 + nt * 16 + li;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
