@@ -294,3 +294,67 @@ def test_index_lists_alone(oracle):
         assert np.array_equal(lv.info(l).device_tile_taps(), before[l][1])
     with pytest.raises(hch.HchError):
         hch.hch_build_index_lists(lv, 2, 2)
+
+
+@pytest.mark.parametrize("F,stride,pad", [(2, 2, 0), (3, 2, 1), (5, 1, 2), (3, 4, 1), (7, 1, 3)])
+@pytest.mark.parametrize("ci,co", [(18, 22), (50, 50), (6, 22), (33, 130), (32, 64)])
+def test_strided_weight_gradient(batch, F, stride, pad, ci, co):
+    """wgrad_split_kernel on index rows of general fields: data order, X of another level than dY, 8 to 343
+    taps over several row tiles (windows of 28 taps); with more than 28 taps, rows of fewer than 16
+    channels stay with gemm_f32_kernel (6 -> 22), as does little work (32 -> 64, stride 4).  Against the definition over the index rows, which
+    the parity tests check bit by bit.  (7^3, stride 1: dW has millions of elements; the coarsest level.)"""
+    lv = batch[0]
+    l = 1 if F == 7 else 0
+    lo = l + {1: 0, 2: 1, 4: 2}[stride]
+    n_in, n_out, F3 = lv.n(l), lv.n(lo), F ** 3
+    field = torch.empty((n_out, F3), dtype=torch.int32, device="cuda")
+    hch.hch_field_build(lv, l, F, stride, pad, field, None)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(F * 100 + ci)
+    X, G = torch.randn((n_in, ci), device="cuda", generator=g), torch.randn((n_out, co), device="cuda", generator=g)
+    dW = torch.full((F3, ci, co), float("nan"), device="cuda")
+    ws = _workspace(hch.hch_sconv_workspace_bytes(lv, l, F, stride, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_WEIGHT))
+    hch.hch_sconv_bwd_weight(lv, l, F, stride, hch.HCH_F32, X, G, dW, field, ci, co, ws)
+    zero = torch.zeros((), dtype=torch.float64, device="cuda")
+    want = torch.stack([torch.where(field[:, k:k + 1] >= 0, X.double()[field[:, k].clamp(min=0).long()], zero).T @ G.double()
+                        for k in range(F3)])
+    err = float((dW.double() - want).norm() / want.norm())
+    assert err < BOUND, f"{err:.2e}"
+    assert float((dW.double() - want).abs().max() / want.pow(2).mean().sqrt()) < 30 * BOUND     # no element out of place
+
+
+@pytest.mark.parametrize("level,wide,narrow", [(1, 16384, 20), (1, 16384, 68), (0, 4352, 68)])
+def test_operands_of_two_gigabytes(oracle, batch, level, wide, narrow):
+    """Feature matrices of 2 GiB and more, which 32-bit byte offsets do not reach: the products on the fp32
+    instruction, rows in order and absent taps left out (128 x 32, 64 x 64 and 128 x 64 tiles), and the
+    dense weight gradient.  They round once per 4 terms: 0.29 * 2^-23 * sqrt(27 * 16384 / 8) = 8.1e-6."""
+    lv, olv = batch
+    n = olv[level].Ntot
+    assert n * wide * 4 >= 1 << 31
+    nb = torch.from_numpy(oracle.neighbours(olv[level]).astype(np.int64)).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(narrow)
+    big, small = torch.randn((n, wide), device="cuda", generator=g), torch.randn((n, narrow), device="cuda", generator=g)
+    a = hch.HCH_ALGO_FUSED
+
+    def rows(T, k):
+        return torch.where(nb[:, k:k + 1] >= 0, T[nb[:, k].clamp(min=0)], torch.zeros((), device="cuda")).double()
+
+    def check(got, want):
+        assert float((got.double() - want).norm() / want.norm()) < 1e-5
+    W = torch.randn((27, wide, narrow), device="cuda", generator=g)
+    Y = torch.full((n, narrow), float("nan"), device="cuda")
+    dW = torch.full((27, wide, narrow), float("nan"), device="cuda")
+    hch.hch_conv_fwd(lv, level, hch.HCH_F32, big, W, Y, wide, narrow, _ws(lv, level, wide, narrow), a)
+    hch.hch_conv_bwd_weight(lv, level, hch.HCH_F32, big, small, dW, wide, narrow, _ws(lv, level, wide, narrow), a)
+    want = 0.0
+    for k in range(27):
+        r = rows(big, k)
+        want = want + r @ W[k].double()
+        check(dW[k], r.T @ small.double())
+        del r
+    check(Y, want)
+    W = torch.randn((27, narrow, wide), device="cuda", generator=g)
+    dX = torch.full((n, narrow), float("nan"), device="cuda")
+    hch.hch_conv_bwd_data(lv, level, hch.HCH_F32, big, W, dX, narrow, wide, _ws(lv, level, narrow, wide), a)
+    check(dX, sum(rows(big, k) @ W[26 - k].double().T for k in range(27)))
