@@ -243,7 +243,7 @@ typedef enum { HCH_ALGO_COLUMNS = 0, HCH_ALGO_FUSED = 1, HCH_ALGO_COLUMNS_RESIDE
 typedef enum {
     HCH_WS_FWD = 0,         /* hch_conv_fwd: everything in one pass                            */
     HCH_WS_BWD_DATA = 1,    /* hch_conv_bwd_data: required size                                */
-    HCH_WS_BWD_WEIGHT = 2,  /* hch_conv_bwd_weight: required size                              */
+    HCH_WS_BWD_WEIGHT = 2,  /* hch_conv_bwd_weight: what it can use (less may do, see there)   */
     HCH_WS_MIN = 3          /* smallest workspace hch_conv_fwd accepts                         */
 } hch_ws_kind;
 
@@ -287,7 +287,10 @@ hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level, hch_dtype 
  * Weight gradient (Eq.7):  dW = hash2col(X)^T . dY
  *   X DEVICE [N_l][c_in], dY DEVICE [N_l][c_out] (dtype); dW DEVICE [27][c_in][c_out] float,
  *   overwritten.  Partial sums over blocks of voxels are combined in a fixed order
- *   (bit-reproducible).
+ *   (bit-reproducible).  Their number, and with it the rounding of dW, is the same for every
+ *   workspace of at least the queried size; HCH_ALGO_FUSED takes somewhat smaller ones as well (down to
+ *   what its kernels on the fp32 instruction would need) and then sums in fewer parts.  The same
+ *   holds for hch_sconv_bwd_weight and its query.
  */
 hch_status hch_conv_bwd_weight(const hch_levels *levels, int32_t level, hch_dtype dtype,
                                const void *X, const void *dY, float *dW, int32_t c_in,

@@ -2364,8 +2364,10 @@ extern "C" hch_status hch_field_build(const hch_levels *levels, int32_t level_in
 }
 
 // workspace of the three products of a general convolution: [ transposed weights (bwd_data on one
-// level) or the column-matrix gradient (bwd_data between two levels) | split partial sums ]
-static WsLayout sconv_layout(const Level &Li, const Level &Lo, int taps, int c_in, int c_out, hch_dtype dtype, hch_ws_kind kind)
+// level) or the column-matrix gradient (bwd_data between two levels) | split partial sums ];
+// least: as in ws_layout
+static WsLayout sconv_layout(const Level &Li, const Level &Lo, int taps, int c_in, int c_out, hch_dtype dtype, hch_ws_kind kind,
+                             bool least = false)
 {
     WsLayout w{0, 0};
     if (kind == HCH_WS_FWD) {
@@ -2379,8 +2381,12 @@ static WsLayout sconv_layout(const Level &Li, const Level &Lo, int taps, int c_i
         w.first_bytes = round_up((size_t)taps * c_in * c_out * elem_size(dtype), 256);
         if (p.splits > 1) w.part_bytes = round_up((size_t)p.splits * Li.n_total * c_in * 4, 256);
     } else {
-        const GemmPlan p = plan_wgrad(Lo.n_total, c_in, c_out, taps, k_gran(dtype));
-        if (p.splits > 1) w.part_bytes = round_up((size_t)p.splits * taps * c_in * c_out * 4, 256);
+        int splits = plan_wgrad(Lo.n_total, c_in, c_out, taps, k_gran(dtype)).splits;
+        if (dtype == HCH_F32 && !least) {
+            const WgradSplitPlan q = plan_wgrad_split(Lo.n_total, Li.n_total, c_in, c_out, taps, INT32_MAX);
+            if (q.ok) splits = std::max(splits, q.slices);
+        }
+        if (splits > 1) w.part_bytes = round_up((size_t)splits * taps * c_in * c_out * 4, 256);
     }
     return w;
 }
@@ -2411,7 +2417,8 @@ static hch_status sconv_args(const hch_levels *levels, int32_t level_in, int32_t
         return fail(HCH_EUNSUPPORTED, std::string(who) + ": too many voxels");
     if (std::max((*Li)->n_total, (*Lo)->n_total) * (int64_t)std::max(c_in, c_out) >= ((int64_t)1 << 31))
         return fail(HCH_EUNSUPPORTED, std::string(who) + ": a feature matrix of more than 2^31 elements");
-    if (ws_bytes < hch_sconv_workspace_bytes(levels, level_in, F, stride, c_in, c_out, dtype, kind))
+    const WsLayout w = sconv_layout(**Li, **Lo, F * F * F, c_in, c_out, dtype, kind, true);
+    if (ws_bytes < std::max<size_t>(256, w.first_bytes + w.part_bytes))
         return fail(HCH_EWORKSPACE, std::string(who) + ": workspace too small");
     return HCH_OK;
 }

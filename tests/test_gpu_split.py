@@ -323,6 +323,24 @@ def test_strided_weight_gradient(batch, F, stride, pad, ci, co):
     assert float((dW.double() - want).abs().max() / want.pow(2).mean().sqrt()) < 30 * BOUND     # no element out of place
 
 
+def test_weight_gradients_do_not_depend_on_what_the_workspace_has_to_spare(batch):
+    """The queried size and 64 MiB more give the same bits: plain and strided weight gradients."""
+    lv = batch[0]
+    n, no, ci, co = lv.n(0), lv.n(1), 32, 64
+    X, G = torch.randn((n, ci), device="cuda"), torch.randn((n, co), device="cuda")
+    field = torch.empty((no, 27), dtype=torch.int32, device="cuda")
+    hch.hch_field_build(lv, 0, 3, 2, 1, field, None)
+    need = hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_WEIGHT, hch.HCH_ALGO_FUSED)
+    strided = hch.hch_sconv_workspace_bytes(lv, 0, 3, 2, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_WEIGHT)
+    got = []
+    for spare in (0, 64 << 20):
+        a, b = (torch.full((27, ci, co), float("nan"), device="cuda") for _ in range(2))
+        hch.hch_conv_bwd_weight(lv, 0, hch.HCH_F32, X, G, a, ci, co, _workspace(need + spare), hch.HCH_ALGO_FUSED)
+        hch.hch_sconv_bwd_weight(lv, 0, 3, 2, hch.HCH_F32, X, G[:no], b, field, ci, co, _workspace(strided + spare))
+        got.append((a, b))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("level,wide,narrow", [(1, 16384, 20), (1, 16384, 68), (0, 4352, 68)])
 def test_operands_of_two_gigabytes(oracle, batch, level, wide, narrow):
     """Feature matrices of 2 GiB and more, which 32-bit byte offsets do not reach: the products on the fp32
