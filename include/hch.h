@@ -304,12 +304,13 @@ hch_status hch_conv_bwd_weight(const hch_levels *levels, int32_t level, hch_dtyp
  * routine): the partial sums of its split reduction go to an array of HCH_NOALLOC_SCRATCH_BYTES
  * bytes that is part of the library's device image, so every GPU the library runs on holds that
  * much memory until the process ends.  Same arguments (minus workspace and algorithm), same
- * kernels, same bits in dW as hch_conv_bwd_weight(..., HCH_ALGO_FUSED).
+ * kernels, same bits in dW as hch_conv_bwd_weight(..., HCH_ALGO_FUSED) with a workspace of the queried
+ * size or more.
  * Errors: as hch_conv_bwd_weight, and HCH_EWORKSPACE when the product's partial sums,
  * hch_conv_workspace_bytes(levels, level, c_in, c_out, dtype, HCH_WS_BWD_WEIGHT, HCH_ALGO_FUSED),
  * exceed HCH_NOALLOC_SCRATCH_BYTES (nothing is launched then; the library's split planning fills
- * one round of workgroups, which keeps those sums below 24 MiB for every level and channel count,
- * so this only guards against a change of that planning).
+ * one round of workgroups, which keeps those sums within 28 MiB with fp32 and 32 MiB with bf16 inputs
+ * for every level and channel count, so this only guards against a change of that planning).
  * All calls on one GPU share the one array: calls that may overlap on a GPU (different streams,
  * different host threads) race on it and must be serialised by the caller; calls on the same
  * stream are ordered.  The array keeps the last call's partial sums; every call overwrites all the

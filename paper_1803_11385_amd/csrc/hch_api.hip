@@ -1548,6 +1548,12 @@ static hch_status launch_reduce(const float *part, float *out, int64_t n, int sp
     return HCH_OK;
 }
 
+// One workgroup of the two weight-gradient kernels per CU; their partial sums, one tile per workgroup,
+// fit the built-in array of hch_conv_bwd_weight_noalloc.
+constexpr int64_t WG_RESIDENT = 256;
+static_assert(WG_RESIDENT * hch::WG_UNITS * 16 * 64 * 4 <= HCH_NOALLOC_SCRATCH_BYTES, "wgrad_split_kernel: 28 MiB");
+static_assert(WG_RESIDENT * hch::WGB_UNITS * 32 * 64 * 4 <= HCH_NOALLOC_SCRATCH_BYTES, "wgrad_bf16_kernel: 32 MiB");
+
 // The weight gradient on split operands (wgrad_split_kernel): rows of `nbr` hold `taps` indices into
 // the x_rows rows of X; `max_slices` partial sums fit the caller's workspace.
 struct WgradSplitPlan { bool ok; int slices, m_tiles, n_tiles; };
@@ -1566,7 +1572,7 @@ static WgradSplitPlan plan_wgrad_split(int64_t n, int64_t x_rows, int c, int N, 
     if (c % 4 == 0 && N % 4 == 0 && (double)n * c * N < 40e6) return p;
     const int64_t m_tiles = ((int64_t)taps * c + hch::WG_UNITS * 16 - 1) / (hch::WG_UNITS * 16), n_tiles = N <= 32 ? 1 : (N + 63) / 64;
     // one workgroup per CU; as a multiple of 8 (whole slices per XCD) where there are that many
-    int64_t s = std::max<int64_t>(1, 256 / (m_tiles * n_tiles));
+    int64_t s = std::max<int64_t>(1, WG_RESIDENT / (m_tiles * n_tiles));
     s = std::min({s, (n + hch::WG_VOX - 1) / hch::WG_VOX, max_slices});
     if (s >= 8) s = s / 8 * 8;
     p.ok = true; p.slices = (int)s; p.m_tiles = (int)m_tiles; p.n_tiles = (int)n_tiles;
@@ -1608,7 +1614,7 @@ static WgradSplitPlan plan_wgrad_bf16(int64_t n, int c, int N, int64_t max_slice
     // against 60, 64 -> 128 at 280k 213 against 162.  Other channel counts: 50 -> 50 at 280k 1090 against 103
     if (c % 8 == 0 && N % 8 == 0 && (double)n * c * N < 4e8) return p;
     const int64_t m_tiles = ((int64_t)27 * c + rows - 1) / rows, n_tiles = N <= 32 ? 1 : (N + 63) / 64;
-    int64_t s = std::max<int64_t>(1, 256 / (m_tiles * n_tiles));
+    int64_t s = std::max<int64_t>(1, WG_RESIDENT / (m_tiles * n_tiles));
     s = std::min({s, (n + hch::WG_VOX - 1) / hch::WG_VOX, max_slices});
     if (s >= 8) s = s / 8 * 8;
     p.ok = true; p.slices = (int)s; p.m_tiles = (int)m_tiles; p.n_tiles = (int)n_tiles;

@@ -63,19 +63,19 @@ def test_noalloc_weight_gradient_two_calls_in_a_row(oracle):
 
 def test_noalloc_limits_and_errors():
     """The partial sums of every product the split planning produces fit the built-in array (the
-    planning fills one round of workgroups, which bounds them by 24 MiB whatever the level and the
-    channel counts, so the HCH_EWORKSPACE guard only fires if the planning changes); bad arguments
+    planning fills one round of workgroups, which bounds them by 28 MiB (fp32) and 32 MiB (bf16) whatever the
+    level and the channel counts, so the HCH_EWORKSPACE guard only fires if the planning changes); bad arguments
     are refused before anything is launched."""
-    coords, offs, _ = S.config_batch(3, batch=4, u=64)
+    coords, offs, _ = S.config_batch(2)                  # 126k voxels: enough for 256 slices
     glv = hch.hch_build_levels(coords, offs, 64, 3)
     worst = 0
     for level in range(3):
         for dtype in (hch.HCH_F32, hch.HCH_BF16):
-            for c_in in (1, 3, 4, 16, 24, 64, 100, 128, 256, 512):
+            for c_in in (1, 3, 4, 16, 18, 24, 33, 64, 100, 128, 256, 512):
                 for c_out in (1, 4, 16, 32, 64, 96, 128, 256, 512):
                     worst = max(worst, hch.hch_conv_workspace_bytes(glv, level, c_in, c_out, dtype,
                                                                     hch.HCH_WS_BWD_WEIGHT, hch.HCH_ALGO_FUSED))
-    assert 0 < worst <= hch.HCH_NOALLOC_SCRATCH_BYTES, worst
+    assert 28 << 20 < worst <= hch.HCH_NOALLOC_SCRATCH_BYTES, worst
     n = glv.n(0)
     X = torch.zeros((n, 8), dtype=torch.float32, device="cuda")
     G = torch.zeros((n, 8), dtype=torch.float32, device="cuda")
