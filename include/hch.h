@@ -188,8 +188,9 @@ hch_status hch_build_neighbours(hch_levels *levels, int32_t level, void *stream)
 hch_status hch_build_neighbours_range(hch_levels *levels, int32_t first, int32_t count, void *stream);
 
 /* The index lists alone: what the columns algorithm, pooling and hch_hash2col / hch_col2hash read.  The
- * row orders that the fused products walk (row_order, tile_taps) keep their contents; a level set has
- * them from its construction on.  Same errors as hch_build_neighbours_range. */
+ * row orders that the fused products walk (row_order and tile_taps, on large levels a finer order of
+ * the library's own) keep their contents; a level set has them from its construction on.  Same errors
+ * as hch_build_neighbours_range. */
 hch_status hch_build_index_lists(hch_levels *levels, int32_t first, int32_t count, void *stream);
 
 /*
@@ -222,8 +223,10 @@ hch_status hch_hash2col(const hch_levels *levels, int32_t level, hch_dtype dtype
 hch_status hch_col2hash(const hch_levels *levels, int32_t level, const float *dcol,
                         int32_t c_in, float *dX, void *stream);
 
-/* How a convolution call computes its products.  Both give the same results up to the order
- * of fp32 additions.
+/* How a convolution call computes its products.  They give the same results up to rounding, in fp32
+ * throughout: HCH_ALGO_FUSED takes fp32 operands apart into three bf16 numbers each, whose leading
+ * products the bf16 instruction sums in fp32 (what is left out is at most 2^-24 of a product; results are
+ * closer to the exact ones than with the fp32 instruction, which the other algorithms use).
  *   HCH_ALGO_COLUMNS  the paper's three steps: hash2col writes the column matrix to the
  *                     workspace, a dense GEMM consumes it, col2hash folds gradients back.
  *   HCH_ALGO_FUSED    the same products with the column matrix gathered through the index rows
@@ -395,7 +398,8 @@ hch_status hch_unpool_bwd(const hch_levels *levels, int32_t level_out, const flo
  *   hch_sconv_bwd_data    dX[N_in][c_in]   = sum_rows dY[field_t[i][row]] . W[row]^T   (Eq.8 + Alg.2)
  * X / dX live on level_in, Y / dY on the output level; dtype, outputs (fp32, overwritten),
  * workspace rules (256-byte aligned, at least hch_sconv_workspace_bytes) and errors as for
- * hch_conv_*.  With F = 3, S = 1, P = 1 `field` equals nbr27 and the results equal hch_conv_*'s.
+ * hch_conv_*.  With F = 3, S = 1, P = 1 `field` equals nbr27 and the results equal hch_conv_*'s up to
+ * rounding.
  */
 hch_status hch_field_build(const hch_levels *levels, int32_t level_in, int32_t F, int32_t stride,
                            int32_t pad, int32_t *field, int32_t *field_t, void *stream);
@@ -499,13 +503,14 @@ hch_status hch_relu_bwd(const float *y, const float *dy, float *dx, int64_t n, v
 hch_status hch_probe_mfma(hch_dtype dtype, int32_t iters, int32_t workgroups, float *sink, void *stream);
 
 /*
- * Measurement and test aid: the products of a convolution have two forms of their main loop,
- * one that addresses memory with guarded 64-bit pointers and works for every shape, and a lean
- * one (loads through buffer descriptors, scalar offsets) that the library takes when the
+ * Measurement and test aid: the products on the fp32 and the bf16 matrix instruction have two forms of
+ * their main loop, one that addresses memory with guarded 64-bit pointers and works for every shape,
+ * and a lean one (loads through buffer descriptors, scalar offsets) that the library takes when the
  * operands allow it.  Both multiply the same tiles in the same order, so their results agree bit
- * for bit; `enabled` = 0 makes every later call take the first form, 1 (the default) restores the
- * choice.  Process-wide, not synchronised with calls running on other threads.  Returns the
- * previous setting.
+ * for bit; `enabled` = 0 makes every later call of such a product take the first form, 1 (the default)
+ * restores the choice.  The fp32 products of HCH_ALGO_FUSED that split their operands have one form
+ * and do not look at it.  Process-wide, not synchronised with calls running on other threads.
+ * Returns the previous setting.
  */
 int32_t hch_set_lean_loops(int32_t enabled);
 

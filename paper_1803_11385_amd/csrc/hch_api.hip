@@ -1091,7 +1091,7 @@ extern "C" hch_status hch_col2hash(const hch_levels *levels, int32_t level, cons
 static inline int k_gran(hch_dtype dtype) { return dtype == HCH_BF16 ? hch::BF16_BK : hch::GEMM_BK; }
 
 // tile shape and split of one product
-// hch_set_lean_loops: 0 = every product takes the pointer-based form of its main loop
+// hch_set_lean_loops: 0 = every product of launch_gemm_* takes the pointer-based form of its main loop
 static std::atomic<int> g_lean_loops{1};
 
 struct GemmPlan {
@@ -1917,8 +1917,8 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
                                   skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr);
         }
         const DirectPlan d = plan_direct(n, c_out, c_in);
-        // (gradients whose rows hold a multiple of 32 channels go to the LDS-tiled kernel's lean loop,
-        // which measured faster than this one: 56 against 67 us for 32 -> 16 channels on 176k voxels)
+        // (gradients whose rows hold a multiple of 32 channels are faster on split operands below: 32 -> 16
+        // channels on 280k voxels 67 us against 93, on 12k 18 against 20)
         if (d.ok && c_out % 32 != 0 && dtype == HCH_F32 && aligned16(dY) && aligned16(dX) && aligned16(W)) {
             const double bytes = (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in * d.splits) + 4.0 * wn;
             st = launch_direct(d, (const float *)dY, L->dnbr, (const float *)W, d.splits > 1 ? part : dX, n, c_out, c_in, bytes, s, 1,

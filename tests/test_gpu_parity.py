@@ -873,7 +873,9 @@ def test_lean_and_pointer_loops_agree_bit_for_bit(case_small, algo, c_in, c_out,
     counts that qualify for the lean loop (rows of a multiple of 32 channels, of 16 for the
     forward product's 16-wide tiles, of 64 with bf16) the outputs must not change by a bit.
     Both levels: the finest has enough voxels for the wide tiles, the next is split along the
-    reduction."""
+    reduction.  (The fp32 forward product and data gradient of the fused algorithm split their operands
+    and have one form only, so of that combination the weight gradient is compared, which at these
+    sizes is on the fp32 instruction.)"""
     case = case_small
     DT = hch.HCH_BF16 if bf16 else hch.HCH_F32
     put = (lambda a: dev(S.bf16_bits(S.to_bf16_grid(a)).view(np.int16))) if bf16 else dev
@@ -899,6 +901,8 @@ def test_lean_and_pointer_loops_agree_bit_for_bit(case_small, algo, c_in, c_out,
                 outs.append((Y, dX, dW))
         finally:
             assert hch.hch_set_lean_loops(1) == 0
+        one_form = algo == hch.HCH_ALGO_FUSED and not bf16
         for a, b, what in zip(outs[0], outs[1], ("Y", "dX", "dW")):
             assert not torch.isnan(a).any(), what
-            assert torch.equal(a, b), f"level {level} {what}: lean and pointer-based loops differ"
+            if what == "dW" or not one_form:
+                assert torch.equal(a, b), f"level {level} {what}: lean and pointer-based loops differ"
