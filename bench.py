@@ -25,7 +25,13 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
 MFMA_F32_PEAK_TFLOPS = 157.3  # dense fp32 matrix
 MFMA_BF16_PEAK_TFLOPS = 2500.0
+# fp32 products on split operands: six bf16 products for one
+MFMA_SPLIT_PEAK_TFLOPS = MFMA_BF16_PEAK_TFLOPS / 6
 CHANNELS = [4, 16, 32, 64, 128, 256]
+ARITHMETIC = {"fused": "fp32 operands as three bf16 numbers each, their six leading products on the bf16 matrix "
+                       "instruction, fp32 sums (small products: fp32 instruction)",
+              "fused_dense": "fp32 matrix instruction", "columns": "fp32 matrix instruction",
+              "bf16": "bf16 operands, fp32 sums"}
 ALGOS = {"fused": "HCH_ALGO_FUSED", "fused_dense": "HCH_ALGO_FUSED_DENSE", "columns": "HCH_ALGO_COLUMNS"}
 
 
@@ -87,6 +93,13 @@ def cpu_baseline(coords, offs, X0, W, u, max_shapes, budget_s=16.0):
             "single_thread": {"value": round(v_one, 6), "unit": "TFLOP/s", "cores": 1, "sample": note_one}}
 
 
+def mfma_peak(kernel):
+    """Dense peak of the matrix instruction that a kernel multiplies with, for the products it is asked for."""
+    if "_split_kernel" in kernel:
+        return MFMA_SPLIT_PEAK_TFLOPS
+    return MFMA_BF16_PEAK_TFLOPS if "bf16" in kernel else MFMA_F32_PEAK_TFLOPS
+
+
 def time_calls(torch, fn, steps, warmup):
     for _ in range(warmup):
         fn()
@@ -134,7 +147,8 @@ def conv_products(torch, hch, S, cfg, algo_name, steps, warmup, tap_major=True):
              ("weight_gradient", lambda: hch.hch_conv_bwd_weight(lv, 0, DT, X, G, dW, ci, co, ws, algo)))
     occupied = lv.info(0).nbr_valid
     flop, useful = 2.0 * n * 27 * ci * co, 2.0 * occupied * ci * co
-    peak = MFMA_BF16_PEAK_TFLOPS if bf else MFMA_F32_PEAK_TFLOPS
+    # at these sizes the fused fp32 products are on split operands, all three
+    peak = MFMA_BF16_PEAK_TFLOPS if bf else (MFMA_SPLIT_PEAK_TFLOPS if algo_name == "fused" else MFMA_F32_PEAK_TFLOPS)
     out = {}
     for name, fn in calls:
         ms = time_calls(torch, fn, steps, warmup)
@@ -145,7 +159,7 @@ def conv_products(torch, hch, S, cfg, algo_name, steps, warmup, tap_major=True):
             "products": out, "calls_timed": steps, "higher_is_better": False,
             "dtype": "bf16" if bf else "f32", "data": "synthetic", "algo": algo_name,
             "flop_count": "tflops: paper-method 2*27*c_in*c_out*N; useful_tflops: occupied taps only",
-            "mfma_peak_tflops": peak,
+            "mfma_peak_tflops": round(peak, 1), "arithmetic": ARITHMETIC["bf16" if bf else algo_name],
             "config": {"workload": f"{u}^3 grid, batch {len(offs) - 1}, random-primitive surfaces, {n} voxels, "
                                    f"{occupied / n:.2f} of 27 taps occupied per voxel"}}
 
@@ -303,16 +317,18 @@ def main():
     def roofline_of(name, st, steps, algo_name):
         """achieved = algorithmic bytes (or flops) of the timed launches / their event-measured
         time; a kernel counts as MFMA-bound when its arithmetic intensity is above the ridge.
+        Flops by the paper's count (taps that a kernel leaves out included), against the peak of the
+        instruction that the kernel multiplies with.
         traffic = counter-measured HBM bytes per launch from the committed summary; null when
         that summary was measured on other sources than the ones running now."""
         ai = st["flops"] / max(1.0, st["bytes"])
-        product = any(t in name for t in ("gemm", "conv_direct", "conv_narrow4"))
-        if product and ai >= MFMA_F32_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9):
-            bound, achieved, peak, unit = "mfma", st["flops"] / (st["ms"] * 1e-3) / 1e12, MFMA_F32_PEAK_TFLOPS, "TFLOP/s"
+        product = any(t in name for t in ("gemm", "conv_direct", "conv_narrow4", "conv_split", "wgrad_"))
+        if product and ai >= mfma_peak(name) * 1e12 / (HBM_PEAK_GBS * 1e9):
+            bound, achieved, peak, unit = "mfma", st["flops"] / (st["ms"] * 1e-3) / 1e12, mfma_peak(name), "TFLOP/s"
         else:
             bound, achieved, peak, unit = "hbm", st["bytes"] / (st["ms"] * 1e-3) / 1e9, HBM_PEAK_GBS, "GB/s"
         db, src = traffic[traffic_key(algo_name)]
-        return {"kernel": name, "bound": bound, "achieved": round(achieved, 3), "peak": peak, "unit": unit,
+        return {"kernel": name, "bound": bound, "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": unit,
                 "frac": round(achieved / peak, 4), "traffic": None if src["stale"] else db.get(name),
                 "launches_per_step": st["launches"] / steps,
                 "avg_launch_ms": round(st["ms"] / max(1, st["launches"]), 5),
@@ -368,7 +384,7 @@ def main():
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"5-level encoder fwd+bwd, {u}^3 grid, batch {b}, random-primitive surfaces, "
                                f"channels 4-16-32-64-128-256, N per level = {enc.n}",
-                   "algo": args.algo,
+                   "algo": args.algo, "arithmetic": ARITHMETIC[args.algo],
                    "flop_count": "value: paper-method 3 * 2*27*c_in*c_out*N_l per level; "
                                  "useful_value: 3 * 2*c_in*c_out*(occupied taps of level l)",
                    "gflop_per_step": round(flops / 1e9, 3), "useful_gflop_per_step": round(useful / 1e9, 3),
@@ -429,13 +445,15 @@ def main():
         out["other_algo"] = {
             "algo": other, "ms_per_step_all_kernels_timed": round(dt2 / args.steps * 1e3, 4),
             "value": round(flops / (dt2 / args.steps) / 1e12, 4), "unit": "TFLOP/s",
-            "kernels": [k for k in ks if any(t in k["kernel"] for t in ("hash2col", "col2hash", "gemm", "neighbour", "conv_"))],
+            "kernels": [k for k in ks if any(t in k["kernel"] for t in ("hash2col", "col2hash", "gemm", "neighbour", "conv_", "wgrad_"))],
             "traffic_source": traffic[traffic_key(other)][1],
         }
     del enc
     if not args.no_extra:
         roofs = measured_roofs(torch, hch)
-        measured = roofs["mfma_f32_TFLOPs"] if roofline["bound"] == "mfma" else roofs["copy_GBs"]
+        rate = {MFMA_F32_PEAK_TFLOPS: roofs["mfma_f32_TFLOPs"], MFMA_BF16_PEAK_TFLOPS: roofs["mfma_bf16_TFLOPs"],
+                MFMA_SPLIT_PEAK_TFLOPS: roofs["mfma_bf16_TFLOPs"] / 6}
+        measured = rate[mfma_peak(roofline["kernel"])] if roofline["bound"] == "mfma" else roofs["copy_GBs"]
         roofs["dominant_kernel_frac_of_measured"] = round(roofline["achieved"] / measured, 4)
         out["roofline_measured"] = roofs
         out["per_kernel_benches"] = {
