@@ -1566,9 +1566,9 @@ static WgradSplitPlan plan_wgrad_split(int64_t n, int64_t x_rows, int c, int N, 
     if (x_rows * c * 4 >= lim || n * N * 4 >= lim || n * taps * 4 >= lim || x_rows >= (1 << 23) || c * 4 >= (1 << 23) || (c < 16 && taps > hch::WG_UNITS)) return p;
     if (N <= 16 || (int64_t)taps * c < 16) return p;
     // a workgroup needs some blocks of voxels to get going, gemm_f32_kernel is ahead on little work: 16 -> 32
-    // at 32k voxels 21.7 us against 30.3, 32 -> 64 at 8k 21 against 34; 32 -> 64 at 32k 45 against 39, 64 -> 128
-    // at 8k 50 against 39, 16 -> 32 at 110k 42 against 38 (its path for channel counts that are not a
-    // multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 36 against 22)
+    // at 32k voxels 24 us against 35, 32 -> 64 at 8k 24 against 41; 32 -> 64 at 32k 50 against 48, 64 -> 128
+    // at 8k 54 against 47, 16 -> 32 at 110k 45 against 44 (its path for channel counts that are not a
+    // multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 39 against 27)
     if (c % 4 == 0 && N % 4 == 0 && (double)n * c * N < 40e6) return p;
     const int64_t m_tiles = ((int64_t)taps * c + hch::WG_UNITS * 16 - 1) / (hch::WG_UNITS * 16), n_tiles = N <= 32 ? 1 : (N + 63) / 64;
     // one workgroup per CU; as a multiple of 8 (whole slices per XCD) where there are that many
@@ -1655,7 +1655,7 @@ static ConvSplitPlan plan_conv_split(int64_t n, int c, int N, int max_splits)
     const int64_t n_tiles = (N + 16 * p.nt - 1) / (16 * p.nt);
     p.m_tiles = (unsigned)((n + 63) / 64);
     // 4 workgroups of 64 rows per CU (wider ones of 128 rows, two per CU, were slower from 2 500 to
-    // 280 000 voxels: 32 -> 64 at 280k 130 against 116 us); small levels split the reduction to fill them
+    // 280 000 voxels: 32 -> 64 at 280k an eighth); small levels split the reduction to fill them
     const int64_t blocks = p.m_tiles * n_tiles, steps = (int64_t)27 * ((c + 7) / 8) / 4;
     if (blocks < 512) p.splits = (int)std::max<int64_t>(1, std::min<int64_t>({1024 / blocks, steps / 6, max_splits}));
     p.ok = true;

@@ -178,8 +178,9 @@ BuildResult build_model_tables(const int32_t *xyz, int64_t n, int ubar, ModelTab
 void coarsen_model(const int32_t *xyz, int64_t n, int ubar_fine, int ratio, std::vector<int32_t> &out_xyz)
 {
     const int64_t uc = (ubar_fine + ratio - 1) / ratio;
-    // one bit per position of the coarse grid, read back in order, where the grid is no larger than
-    // the list (shapes of a mini-batch: about a tenth of the time of sorting); else a sorted list
+    // one bit per position of the coarse grid, read back in order, where the bit set is at most four
+    // times as large as the list of positions (shapes of a mini-batch: about a tenth of the time of
+    // sorting); else a sorted list
     const int64_t words = (uc * uc * uc + 63) / 64;
     if (words <= 4 * n + 1024) {
         std::vector<uint64_t> bits((size_t)words, 0);

@@ -26,9 +26,12 @@ __device__ __forceinline__ void load8(const float *p, int have, float *v)
 //   * Weights: one unit per thread and step, cut before it goes to LDS, two stages, one barrier a step.
 //   * Loads run two steps ahead in two sets of registers, as in gemm_f32_kernel.
 //   * The index rows of a wavefront are read once, whole rows at a time, into LDS.
-// Bound by vector and matrix instructions together (44 + 44 to cut a step's 16 rows and its share of the
-// weights, 24 matrix instructions) at four wavefronts per SIMD: 32 -> 64 at 280 000 voxels 116 us (159
-// with gemm_f32_kernel in the same row order), 64 -> 64 202 (293), 50 -> 50 206 (1109: element by element).
+// Bound by vector instructions and LDS together: of a busy CU's time the vector pipes issue 0.57, LDS works 0.60
+// (0.38 of that bank conflicts), the matrix pipes 0.31 (32 -> 64, 280 000 voxels; data gradient 0.66, 0.72,
+// 0.27), at four wavefronts per SIMD; a step costs 52 + 52 vector instructions to split its 16 rows and its
+// share of the weights, and 24 matrix instructions.  Forward and data gradient against gemm_f32_kernel over the
+// coarser row order: 32 -> 64 140 and 150 us (196, 196), 64 -> 64 216 and 214 (354, 365), 50 -> 50 233
+// and 265 (1112, 1117: element by element).
 // FAST: rows of a multiple of 32 channels; a step lies within one tap, offsets that change from step
 // to step are scalar, and a wavefront whose own rows lack the tap sits the step out.  Otherwise any
 // number of channels: a tap is padded to a multiple of 8, with weights of zero.

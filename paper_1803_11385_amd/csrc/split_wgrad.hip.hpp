@@ -97,11 +97,11 @@ __device__ __forceinline__ bool non_finite(float v) { return (__float_as_uint(v)
 // The rows of the next unit are requested before a unit is multiplied, across blocks as well; the
 // index rows run two blocks ahead, dY one.  The two halves of a block are added through LDS at the
 // end, which halves the partial sums that go to memory.
-// Bound by the issue of matrix and vector instructions (96 cycles and about 90 vector instructions
-// per unit and 16 columns x 32 voxels) and by the wait for the slowest wavefront of a block: 32 -> 64 at
-// 280 000 voxels 148 us (265 with every tap at the fp32 rate), 64 -> 64 225 (535), 50 -> 50 228 (885).
+// Bound by the wait for what a block needs next, at two wavefronts per SIMD (197 to 256 registers): of a busy
+// CU's time the vector pipes work 0.49, the matrix pipes 0.26, LDS 0.17.  Against gemm_f32_kernel, which
+// multiplies every tap: 32 -> 64 at 280 000 voxels 142 us (260), 64 -> 64 266 (540), 50 -> 50 288 (894).
 // A form with the units in a loop and a switch over their sums copied the sums through other registers
-// (254 us); requests further ahead than two units changed nothing.
+// (1.7 times as long); requests further ahead than two units changed nothing.
 constexpr int WG_VOX = 128, WG_UNITS = 28, WG_SLOTS = WG_UNITS + 1, WG_RS = WG_VOX + 4;
 template <int NT>
 struct WgradLds {
@@ -425,8 +425,10 @@ __global__ __launch_bounds__(512) void wgrad_split_kernel(
 // lane loads 32 bits and gives one half to each of two operands), so a unit is 32 rows of dW; a
 // wavefront has 4 of the 16 units of a workgroup.  The second half of every block enters with the
 // opposite sign and is subtracted at the end, for the reason given at mfma_split (inputs of one sign,
-// a million voxels: results 1.2e-8 too small without it, 3e-10 with it).  64 -> 64 at 2.98 M voxels (512^3, thick shells): 1170 -> 873 us with
-// the taps that 32 voxels lack left out; bound by the gathered loads, 8 per 8 matrix instructions.
+// a million voxels: results 1.2e-8 too small without it, 3e-10 with it).  64 -> 64 at 2.98 M voxels (512^3,
+// thick shells): 1170 -> 877 us with the taps that 32 voxels lack left out.  Bound by memory there: the
+// gathered rows, 0.31 of which are found in L2, are 5.3 GB from HBM, 6.0 TB/s; at 280 000 voxels 99 us
+// (120 with every tap).
 constexpr int WGB_UNITS = 16;
 template <int NT>
 struct WgradBfLds {
