@@ -660,25 +660,30 @@ __global__ __launch_bounds__(256) void child_kernel(
 //   TRANSPOSED = true :  out[i][row] = data index of the output voxel o whose field holds input
 //                        voxel i at this row, or -1 (rows owned by the input voxels; probes go to
 //                        the output level's tables): the index rows of Algorithm 2 turned into
-//                        a gather.
-// grid.y = model; a workgroup has `tv` voxels (64, or 32 with the longest rows), one per lane, and its wavefronts take the rows in
-// turn, so that a row's numbers are the same for all lanes.  `owner` = coordinates and N* prefix of the
-// level that owns the rows, `probe` = tables of the other level.  Per axis, output position minus input
-// position changes by one from row to row, so the residues of the hash are stepped, not divided; and of
-// the transposed rows of a stride S only every S-th per axis can have an owner: the ceil(F/S)^3 of them
-// are probed, the others are -1.  (With a thread per row and its divisions the kernel was bound by them:
-// 3^3, stride 2, 609k voxels 123 us.)  Rows leave through LDS, coalesced.
+//                        a gather.  With S = 1 these are the forward rows in reversed order, and
+//                        the first form writes them (`reversed`; 280k voxels, 3^3: 41 us, 56 with the second).
+// grid.y = model; a workgroup has `tv` voxels (64, or 32 with the longest rows), one per lane, and its
+// wavefronts take the rows in turn, so that a row's numbers are the same for all lanes.  `owner` =
+// coordinates and N* prefix of the level that owns the rows, `probe` = tables of the other level.  Per
+// axis, output position minus input position changes by one from row to row, so the residues of the
+// hash are stepped, not divided; and of the transposed rows of a stride S only every S-th per axis can have
+// an owner: the ceil(F/S)^3 of them are probed, the others are -1.  (With a thread per row and its
+// divisions the kernel was bound by them: 3^3, stride 2, 609k voxels 123 us.)  Along x the rows are shared
+// by grid.z workgroups, `slabs` of the ceil(F/S) planes that are probed to each: otherwise a wavefront's probes are
+// a serial chain of up to 86, and the longest rows fill LDS (7^3 rows: 3 000 voxels 65 -> 13.5 us, 280k
+// voxels 798 -> 345).
+// Rows leave through LDS, coalesced.
 template <bool TRANSPOSED>
-__global__ __launch_bounds__(256) void field_kernel(
+__global__ __launch_bounds__(512) void field_kernel(
     PshView probe, const int32_t *__restrict__ owner_coords, const int32_t *__restrict__ owner_N,
-    int32_t *__restrict__ out, int F, int S, int P, int tv)
+    int32_t *__restrict__ out, int F, int S, int P, int tv, int slabs, int reversed)
 {
-    extern __shared__ int32_t rows[];                 // tv * F^3
+    extern __shared__ int32_t rows[];                 // tv * n_rows
     const int v = blockIdx.y, F3 = F * F * F;
     const int32_t base = owner_N[v], n = owner_N[v + 1] - base;
     const int i0 = (int)blockIdx.x * tv;
     if (i0 >= n) return;                              // whole workgroups
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = min(tv, n - i0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6, nv = min(tv, n - i0);
     const int m = probe.mbar[v], r = probe.rbar[v];
     const unsigned Mv = (unsigned)probe.M[v], Rv = (unsigned)probe.R[v];
     const int32_t first = probe.N[v];
@@ -697,9 +702,13 @@ __global__ __launch_bounds__(256) void field_kernel(
         qm[a] = q0[a] % m; if (qm[a] < 0) qm[a] += m;
         qr[a] = q0[a] % r; if (qr[a] < 0) qr[a] += r;
     }
+    // this workgroup's planes js[0] along x, and the rows fx in [x_beg, x_end) that they are among
     const int step = TRANSPOSED ? S : 1, K = (F + step - 1) / step;
+    const int s_beg = (int)blockIdx.z * slabs, s_end = min(s_beg + slabs, K);
+    const int x_beg = s_beg * step, x_end = min(s_end * step, F), n_rows = (x_end - x_beg) * F * F;
+    const int row0 = (!TRANSPOSED && reversed ? F - x_end : x_beg) * F * F;
     if (step > 1) {
-        for (int t = threadIdx.x; t < nv * F3; t += 256) rows[t] = -1;
+        for (int t = threadIdx.x; t < nv * n_rows; t += blockDim.x) rows[t] = -1;
         __syncthreads();
     }
     auto moved = [](int x, int j, int d) {            // x +- j modulo d, given 0 <= x < d
@@ -708,7 +717,7 @@ __global__ __launch_bounds__(256) void field_kernel(
         return (unsigned)x;
     };
 #pragma unroll 2
-    for (int j = wave; j < K * K * K; j += 4) {
+    for (int j = s_beg * K * K + wave; j < s_end * K * K; j += waves) {
         const int js[3] = {j / (K * K), j / K % K, j % K};
         int q[3], row = 0;
         bool ok = lane < nv;
@@ -722,12 +731,17 @@ __global__ __launch_bounds__(256) void field_kernel(
         const uint32_t ph = psh_offset(probe, Rv, (unsigned)r, moved(qr[0], js[0], r), moved(qr[1], js[1], r), moved(qr[2], js[2], r));
         const u32x3 rec = psh_record(psh_slot(probe, Mv, (unsigned)m, ph, moved(qm[0], js[0], m), moved(qm[1], js[1], m), moved(qm[2], js[2], m)));
         const int32_t h = psh_match(rec[0], rec[1], rec[2], (unsigned)q[0], (unsigned)q[1], (unsigned)q[2]);
-        if (ok) rows[lane * F3 + row] = h >= 0 ? first + h : -1;
-        else if (step == 1 && lane < nv) rows[lane * F3 + row] = -1;
+        const int at = lane * n_rows + (!TRANSPOSED && reversed ? F3 - 1 - row : row) - row0;
+        if (ok) rows[at] = h >= 0 ? first + h : -1;
+        else if (step == 1 && lane < nv) rows[at] = -1;
     }
     __syncthreads();
-    int32_t *dst = out + (int64_t)(base + i0) * F3;
-    for (int t = threadIdx.x; t < nv * F3; t += 256) dst[t] = rows[t];
+    int32_t *dst = out + (int64_t)(base + i0) * F3 + row0;
+    if (n_rows == F3)
+        for (int t = threadIdx.x; t < nv * F3; t += blockDim.x) dst[t] = rows[t];
+    else
+        for (int i = wave; i < nv; i += waves)
+            for (int t = lane; t < n_rows; t += 64) dst[(int64_t)i * F3 + t] = rows[i * n_rows + t];
 }
 
 // ---------------------------------------------------------------------------------------
