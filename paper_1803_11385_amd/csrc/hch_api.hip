@@ -1565,12 +1565,11 @@ static WgradSplitPlan plan_wgrad_split(int64_t n, int64_t x_rows, int c, int N, 
     // 32-bit byte offsets reach everything, a negative one nothing; a workgroup's rows touch 28 taps
     if (x_rows * c * 4 >= lim || n * N * 4 >= lim || n * taps * 4 >= lim || x_rows >= (1 << 23) || c * 4 >= (1 << 23) || (c < 16 && taps > hch::WG_UNITS)) return p;
     if (N <= 16 || (int64_t)taps * c < 16) return p;
-    // a workgroup needs some blocks of voxels to get going, gemm_f32_kernel is ahead on little work, the more so
-    // on few voxels: 32 -> 64 at 20k voxels 36 us against 45, 64 -> 64 at 10k 43.5 against 45.9, 128 -> 128 at 3k 39.6
-    // against 43.4, 128 -> 256 at 2k 43.8 against 48.7; 64 -> 64 at 12k 47.9 against 45.6, 32 -> 64 at 24k 45.1 against
-    // 45.2, 16 -> 32 at 110k 45 against 44, 256 -> 256 at 1 100 51 against 47 (its path for channel counts that
-    // are not a multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 39 against 27)
-    if (c % 4 == 0 && N % 4 == 0 && (double)n * c * N < (n < 6000 ? 70e6 : 48e6)) return p;
+    // a workgroup needs some blocks of voxels to get going, gemm_f32_kernel is ahead on little work: 16 -> 32
+    // at 32k voxels 24 us against 35, 32 -> 64 at 8k 24 against 41; 32 -> 64 at 32k 50 against 48, 64 -> 128
+    // at 8k 54 against 47, 16 -> 32 at 110k 45 against 44 (its path for channel counts that are not a
+    // multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 39 against 27)
+    if (c % 4 == 0 && N % 4 == 0 && (double)n * c * N < 40e6) return p;
     const int64_t m_tiles = ((int64_t)taps * c + hch::WG_UNITS * 16 - 1) / (hch::WG_UNITS * 16), n_tiles = N <= 32 ? 1 : (N + 63) / 64;
     // one workgroup per CU; as a multiple of 8 (whole slices per XCD) where there are that many
     int64_t s = std::max<int64_t>(1, WG_RESIDENT / (m_tiles * n_tiles));
@@ -1614,9 +1613,6 @@ static WgradSplitPlan plan_wgrad_bf16(int64_t n, int c, int N, int64_t max_slice
     // 35 us against 38, 64 -> 64 at 32k 29 against 32; 64 -> 64 at 110k 54 against 51, 32 -> 64 at 280k 64
     // against 60, 64 -> 128 at 280k 213 against 162.  Other channel counts: 50 -> 50 at 280k 1090 against 103
     if (c % 8 == 0 && N % 8 == 0 && (double)n * c * N < 4e8) return p;
-    // (nor do multiples of 4 on up to 3 blocks of voxels: 16 -> 20 at 200 voxels 13.3 us against 16.2, 64 -> 20 13.3
-    // against 16.3; at 500 voxels 17.1 against 16.0, 16.5 against 15.9)
-    if (c % 4 == 0 && N % 4 == 0 && n <= 3 * hch::WG_VOX) return p;
     const int64_t m_tiles = ((int64_t)27 * c + rows - 1) / rows, n_tiles = N <= 32 ? 1 : (N + 63) / 64;
     int64_t s = std::max<int64_t>(1, WG_RESIDENT / (m_tiles * n_tiles));
     s = std::min({s, (n + hch::WG_VOX - 1) / hch::WG_VOX, max_slices});

@@ -263,22 +263,6 @@ def test_weight_gradient_with_the_smallest_workspace(oracle, batch):
         hch.hch_conv_bwd_weight(lv, 0, hch.HCH_F32, X, G, dW, ci, co, _workspace(8 * 27 * ci * co * 4), hch.HCH_ALGO_FUSED)
 
 
-@pytest.mark.parametrize("n", [1, 128, 129, 384, 385, 1000])
-@pytest.mark.parametrize("ci,co", [(16, 20), (50, 50)])
-def test_bf16_weight_gradient_of_few_voxels(oracle, n, ci, co):
-    """One to eight blocks of 128 voxels; with multiples of 4 the first three stay with gemm_f32_kernel."""
-    rng = np.random.default_rng(n)
-    pos = rng.permutation(12 ** 3)[:n]
-    coords = np.stack([pos // 144, pos // 12 % 12, pos % 12], 1).astype(np.int32)
-    lv = hch.hch_build_levels(coords, [0, n], 16, 1)
-    nbr = oracle.neighbours(oracle.build_hierarchy(coords, [0, n], 16, 1)[0])
-    X, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda().bfloat16() for s in ((n, ci), (n, co)))
-    need = hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_BF16, hch.HCH_WS_BWD_WEIGHT, hch.HCH_ALGO_FUSED)
-    dW = torch.full((27, ci, co), float("nan"), device="cuda")
-    hch.hch_conv_bwd_weight(lv, 0, hch.HCH_BF16, X, G, dW, ci, co, _workspace(need), hch.HCH_ALGO_FUSED)
-    _check([dW], [_reference(nbr, X, torch.zeros((27, ci, co), device="cuda"), G)[2]])
-
-
 @pytest.mark.parametrize("level", [0, 2])
 @pytest.mark.parametrize("ci,co", [(6, 18), (50, 50), (64, 64), (32, 130), (34, 20)])
 def test_bf16_weight_gradient(oracle, batch, level, ci, co):
@@ -405,13 +389,11 @@ def _same_as_dense(lv, n, ci, co, products):
 @pytest.mark.parametrize("n,ci,co,products,plain", [
     (3000, 32, 64, (0,), True), (800, 128, 128, (0, 1), True), (3000, 64, 64, (0, 1), True), (4000, 64, 64, (0, 1), False),
     (3000, 64, 32, (1,), True), (3000, 64, 32, (0,), False), (3000, 30, 64, (0,), False), (20000, 4, 32, (0,), True),
-    (20000, 32, 4, (1,), False), (20000, 32, 64, (2,), True), (3000, 128, 128, (2,), True), (12500, 64, 64, (2,), False),
-    (4500, 128, 128, (2,), False)])
+    (20000, 32, 4, (1,), False)])
 def test_little_work_stays_on_the_fp32_instruction(n, ci, co, products, plain):
-    """Forward (0), data gradient (1) and weight gradient (2) where splitting would take longer than the
-    products: the bits of the fp32 instruction over every tap; other bits (with results as close, see above) on
-    the other side of the rules: 15 M multiplications per tap, more than 32 columns, multiples of 4, rows
-    of 4 channels; 48 M (70 M below 6000 voxels) for the weight gradient."""
+    """Forward (0) and data gradient (1) where splitting would take longer than the products: the bits of the
+    fp32 instruction over every tap; other bits (with results as close, see above) on the other side of
+    the rules: 15 M multiplications per tap, more than 32 columns, multiples of 4; rows of 4 channels."""
     rng = np.random.default_rng(n)
     lin = np.sort(rng.permutation(32 ** 3)[:n])
     coords = np.stack([lin // 1024, lin // 32 % 32, lin % 32], 1).astype(np.int32)
