@@ -226,8 +226,7 @@ hch_status hch_col2hash(const hch_levels *levels, int32_t level, const float *dc
 /* How a convolution call computes its products.  They give the same results up to rounding, in fp32
  * throughout: HCH_ALGO_FUSED takes fp32 operands apart into three bf16 numbers each, whose leading
  * products the bf16 instruction sums in fp32 (what is left out is at most 2^-24 of a product; results are
- * closer to the exact ones than with the fp32 instruction, which the other algorithms use, and this one
- * for narrow and small products).
+ * closer to the exact ones than with the fp32 instruction, which the other algorithms use).
  *   HCH_ALGO_COLUMNS  the paper's three steps: hash2col writes the column matrix to the
  *                     workspace, a dense GEMM consumes it, col2hash folds gradients back.
  *   HCH_ALGO_FUSED    the same products with the column matrix gathered through the index rows

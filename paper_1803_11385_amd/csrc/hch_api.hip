@@ -1662,19 +1662,6 @@ static ConvSplitPlan plan_conv_split(int64_t n, int c, int N, int max_splits)
     return p;
 }
 
-// Products that stay on gemm_f32_kernel over every tap in data order: rows of 4 channels, half of whose
-// split terms would be padding (4 -> 32 at 280k voxels: 37 us against 46; the data gradient needs its weights
-// rearranged first, so few voxels are ahead there, 16 us against 13 at 3k, 40 against 45 at 280k), and little work
-// with more than 32 columns, where splitting takes longer than the products (32 -> 64 at 3k voxels 16.8 us
-// against 19.3, 12 -> 64 at 10k 13.9 against 19.2, 64 -> 128 at 1k 17.2 against 19.9; 64 -> 64 at 3k 21.3 against
-// 21.3, 24 -> 64 at 10k 24.3 against 23.8, 64 -> 128 at 3k 27.2 against 26.0).  Its vector path only.
-static bool plain_rows_ahead(int64_t n, int c, int N, bool data_gradient, const void *A, const void *B)
-{
-    if (c % 4 || N % 4 || !aligned16(A) || !aligned16(B)) return false;
-    if (c == 4 && (!data_gradient || n >= 128 * 1024)) return true;
-    return N > 32 && (double)n * c * N < 15e6;
-}
-
 // transposed: W(t, k, n) = W[26 - t][n][k]
 static hch_status launch_conv_split(const ConvSplitPlan &p, const Level &L, const float *X, const float *W, float *out, float *part,
                                     int64_t n, int c, int N, bool transposed, double bytes, hipStream_t s)
@@ -1849,8 +1836,7 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
             if (d.splits > 1) st = launch_reduce(part, Y, n * c_out, d.splits, s);
             return st;
         }
-        const bool plain = dtype == HCH_F32 && plain_rows_ahead(n, c_in, c_out, false, X, W);
-        if (skip && dtype == HCH_F32 && L->rows() && !plain) {
+        if (skip && dtype == HCH_F32 && L->rows()) {
             const ConvSplitPlan q = plan_conv_split(n, c_in, c_out, p.splits);
             if (q.ok)
                 return launch_conv_split(q, *L, (const float *)X, (const float *)W, Y, part, n, c_in, c_out, false,
@@ -1875,7 +1861,7 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
         st = launch_gemm<hch::A_GATHER, false>(dtype, p, X, W,
                                                p.splits > 1 ? part : Y, L->dnbr, (int)n, c_out, Kc, c_in,
                                                c_out, c_out, n * c_out, bytes, s, 0, 27, 0, 0, L->dnbr_t,
-                                               skip && !plain ? L->rows() : nullptr, skip && !plain ? L->row_taps() : nullptr, n);
+                                               skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr, n);
         if (st != HCH_OK) return st;
         if (p.splits > 1) st = launch_reduce(part, Y, n * c_out, p.splits, s);
         return st;
@@ -1942,8 +1928,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
             return st;
         }
         const GemmPlan p = plan_rows(n, c_in, Kd, true, k_gran(dtype));
-        const bool plain = dtype == HCH_F32 && plain_rows_ahead(n, c_out, c_in, true, dY, W);
-        if (skip && dtype == HCH_F32 && L->rows() && !plain) {
+        if (skip && dtype == HCH_F32 && L->rows()) {
             const ConvSplitPlan q = plan_conv_split(n, c_out, c_in, p.splits);
             if (q.ok)
                 return launch_conv_split(q, *L, (const float *)dY, (const float *)W, dX, part, n, c_out, c_in, true,
@@ -1957,7 +1942,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
             const double bytes = (double)n * (108.0 + es * c_out + 4.0 * c_in * p.splits) + es * wn;
             st = launch_gemm<hch::A_GATHER, true>(dtype, p, dY, Wlast, p.splits > 1 ? part : dX, L->dnbr, (int)n, c_in, Kd,
                                                   c_out, c_out, c_in, n * c_in, bytes, s, 0, 27, c_out, -per_tap, L->dnbr_t,
-                                                  skip && !plain ? L->rows() : nullptr, skip && !plain ? L->row_taps() : nullptr, n);
+                                                  skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr, n);
             if (st != HCH_OK) return st;
             if (p.splits > 1) st = launch_reduce(part, dX, n * c_in, p.splits, s);
             return st;
@@ -1976,7 +1961,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
         st = launch_gemm<hch::A_GATHER, false>(dtype, p, dY, Wt,
                                                p.splits > 1 ? part : dX, L->dnbr, (int)n, c_in, Kd, c_out,
                                                c_in, c_in, n * c_in, bytes, s, 0, 27, 0, 0, L->dnbr_t,
-                                               skip && !plain ? L->rows() : nullptr, skip && !plain ? L->row_taps() : nullptr, n);
+                                               skip ? L->rows() : nullptr, skip ? L->row_taps() : nullptr, n);
         if (st != HCH_OK) return st;
         if (p.splits > 1) st = launch_reduce(part, dX, n * c_in, p.splits, s);
         return st;

@@ -376,26 +376,3 @@ def test_operands_of_two_gigabytes(oracle, batch, level, wide, narrow):
     dX = torch.full((n, narrow), float("nan"), device="cuda")
     hch.hch_conv_bwd_data(lv, level, hch.HCH_F32, big, W, dX, narrow, wide, _ws(lv, level, narrow, wide), a)
     check(dX, sum(rows(big, k) @ W[26 - k].double().T for k in range(27)))
-
-
-def _same_as_dense(lv, n, ci, co, products):
-    g = torch.Generator(device="cuda")
-    g.manual_seed(ci + co)
-    X, W, G = (torch.randn(s, device="cuda", generator=g) for s in ((n, ci), (27, ci, co), (n, co)))
-    fused, dense = _run(lv, 0, X, W, G), _run(lv, 0, X, W, G, hch.HCH_ALGO_FUSED_DENSE)
-    return [torch.equal(fused[p], dense[p]) for p in products]
-
-
-@pytest.mark.parametrize("n,ci,co,products,plain", [
-    (3000, 32, 64, (0,), True), (800, 128, 128, (0, 1), True), (3000, 64, 64, (0, 1), True), (4000, 64, 64, (0, 1), False),
-    (3000, 64, 32, (1,), True), (3000, 64, 32, (0,), False), (3000, 30, 64, (0,), False), (20000, 4, 32, (0,), True),
-    (20000, 32, 4, (1,), False)])
-def test_little_work_stays_on_the_fp32_instruction(n, ci, co, products, plain):
-    """Forward (0) and data gradient (1) where splitting would take longer than the products: the bits of the
-    fp32 instruction over every tap; other bits (with results as close, see above) on the other side of
-    the rules: 15 M multiplications per tap, more than 32 columns, multiples of 4; rows of 4 channels."""
-    rng = np.random.default_rng(n)
-    lin = np.sort(rng.permutation(32 ** 3)[:n])
-    coords = np.stack([lin // 1024, lin // 32 % 32, lin % 32], 1).astype(np.int32)
-    lv = hch.hch_build_levels(coords, [0, n], 32, 1)
-    assert _same_as_dense(lv, n, ci, co, products) == [plain] * len(products)
