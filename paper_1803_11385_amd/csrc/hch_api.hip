@@ -1568,7 +1568,8 @@ static WgradSplitPlan plan_wgrad_split(int64_t n, int64_t x_rows, int c, int N, 
     // a workgroup needs some blocks of voxels to get going, gemm_f32_kernel is ahead on little work: 16 -> 32
     // at 32k voxels 24 us against 35, 32 -> 64 at 8k 24 against 41; 32 -> 64 at 32k 50 against 48, 64 -> 128
     // at 8k 54 against 47, 16 -> 32 at 110k 45 against 44 (its path for channel counts that are not a
-    // multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 39 against 27)
+    // multiple of 4 is behind everywhere: 50 -> 50 at 800 voxels 39 against 27).  Just above the line it is still
+    // ahead at some shapes, 32 -> 64 at 20k 36 us against 45, with twice the error, 2.1e-7 against 1.0e-7
     if (c % 4 == 0 && N % 4 == 0 && (double)n * c * N < 40e6) return p;
     const int64_t m_tiles = ((int64_t)taps * c + hch::WG_UNITS * 16 - 1) / (hch::WG_UNITS * 16), n_tiles = N <= 32 ? 1 : (N + 63) / 64;
     // one workgroup per CU; as a multiple of 8 (whole slices per XCD) where there are that many
@@ -1656,6 +1657,9 @@ static ConvSplitPlan plan_conv_split(int64_t n, int c, int N, int max_splits)
     p.m_tiles = (unsigned)((n + 63) / 64);
     // 4 workgroups of 64 rows per CU (wider ones of 128 rows, two per CU, were slower from 2 500 to
     // 280 000 voxels: 32 -> 64 at 280k an eighth); small levels split the reduction to fill them
+    // (Rows of 4 channels, half of whose split terms are padding, and little work with more than 32 columns are
+    // faster with gemm_f32_kernel, 4 -> 32 at 280k voxels 37 us against 46, 12 -> 64 at 10k 14 against 19, but
+    // its results are 2.5 and 3 times as far from the exact ones, 1.2e-7 against 4.6e-8 and 2.0e-7 against 6.4e-8.)
     const int64_t blocks = p.m_tiles * n_tiles, steps = (int64_t)27 * ((c + 7) / 8) / 4;
     if (blocks < 512) p.splits = (int)std::max<int64_t>(1, std::min<int64_t>({1024 / blocks, steps / 6, max_splits}));
     p.ok = true;

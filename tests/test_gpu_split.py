@@ -263,6 +263,22 @@ def test_weight_gradient_with_the_smallest_workspace(oracle, batch):
         hch.hch_conv_bwd_weight(lv, 0, hch.HCH_F32, X, G, dW, ci, co, _workspace(8 * 27 * ci * co * 4), hch.HCH_ALGO_FUSED)
 
 
+@pytest.mark.parametrize("n", [1, 128, 129, 384, 385, 1000])
+@pytest.mark.parametrize("ci,co", [(16, 20), (50, 50)])
+def test_bf16_weight_gradient_of_few_voxels(oracle, n, ci, co):
+    """One to eight blocks of 128 voxels, not in order of position."""
+    rng = np.random.default_rng(n)
+    pos = rng.permutation(12 ** 3)[:n]
+    coords = np.stack([pos // 144, pos // 12 % 12, pos % 12], 1).astype(np.int32)
+    lv = hch.hch_build_levels(coords, [0, n], 16, 1)
+    nbr = oracle.neighbours(oracle.build_hierarchy(coords, [0, n], 16, 1)[0])
+    X, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda().bfloat16() for s in ((n, ci), (n, co)))
+    need = hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_BF16, hch.HCH_WS_BWD_WEIGHT, hch.HCH_ALGO_FUSED)
+    dW = torch.full((27, ci, co), float("nan"), device="cuda")
+    hch.hch_conv_bwd_weight(lv, 0, hch.HCH_BF16, X, G, dW, ci, co, _workspace(need), hch.HCH_ALGO_FUSED)
+    _check([dW], [_reference(nbr, X, torch.zeros((27, ci, co), device="cuda"), G)[2]])
+
+
 @pytest.mark.parametrize("level", [0, 2])
 @pytest.mark.parametrize("ci,co", [(6, 18), (50, 50), (64, 64), (32, 130), (34, 20)])
 def test_bf16_weight_gradient(oracle, batch, level, ci, co):
