@@ -220,6 +220,29 @@ def test_numbers_that_are_not_finite(oracle, batch, value):
     assert bool((~torch.isfinite(dW[hit]) | (dW[hit].abs() > 1e35)).all())
 
 
+@pytest.mark.parametrize("ci,co", [(16, 32), (32, 64), (64, 64), (33, 17), (64, 18), (5, 130), (18, 22)])
+def test_sums_beyond_the_scaled_range(oracle, batch, ci, co):
+    """Operands of 1e15: sums of 1e30 are ordinary numbers, but scaled by 2^32 for the split products they leave
+    fp32's range, so that every wavefront repeats its sums with the fp32 instruction.  That rounds
+    once per 4 terms and once more per 32: 0.29 * 2^-23 * sqrt(27 * 64 * (1 / 8 + 1 / 64)) = 5.4e-7."""
+    lv, olv = batch
+    n, no = olv[0].Ntot, olv[1].Ntot
+    nbr = oracle.neighbours(olv[0])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(10 * ci + co)
+    X, W, G = (torch.randn(s, device="cuda", generator=g) * 1e15 for s in ((n, ci), (27, ci, co), (n, co)))
+    _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
+    field = torch.empty((no, 27), dtype=torch.int32, device="cuda")
+    hch.hch_field_build(lv, 0, 3, 2, 1, field, None)
+    dW = torch.full((27, ci, co), float("nan"), device="cuda")
+    ws = _workspace(hch.hch_sconv_workspace_bytes(lv, 0, 3, 2, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_WEIGHT))
+    hch.hch_sconv_bwd_weight(lv, 0, 3, 2, hch.HCH_F32, X, G[:no], dW, field, ci, co, ws)
+    rows = [torch.where(field[:, k:k + 1] >= 0, X.double()[field[:, k].clamp(min=0).long()], torch.zeros((), dtype=torch.float64, device="cuda"))
+            for k in range(27)]
+    want = torch.stack([r.T @ G[:no].double() for r in rows])
+    assert float((dW.double() - want).norm() / want.norm()) < BOUND
+
+
 @pytest.mark.parametrize("ci,co", [(32, 64), (50, 50)])
 def test_numbers_that_are_not_finite_cost_no_more_than_a_few_times_as_much(batch, ci, co):
     """A step that overflows (every step of loss scaling that is thrown away): all rows NaN.  The yardstick
