@@ -1644,19 +1644,22 @@ static hch_status launch_wgrad_bf16(const WgradSplitPlan &p, const uint16_t *X, 
 
 // Forward product and data gradient on split operands (conv_split_kernel); `max_splits` partial results fit
 // the caller's workspace.
-struct ConvSplitPlan { bool ok; int nt, splits; unsigned m_tiles; };
+struct ConvSplitPlan { bool ok; int nt, wv, splits; unsigned m_tiles; };
 
 static ConvSplitPlan plan_conv_split(int64_t n, int c, int N, int max_splits)
 {
-    ConvSplitPlan p{false, 4, 1, 0};
+    ConvSplitPlan p{false, 4, 4, 1, 0};
     const int64_t lim = (int64_t)1 << 31;
     // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors
     if (n >= (1 << 23) || c * 4 >= (1 << 23) || n * c * 4 >= lim || n * 108 >= lim || (int64_t)108 * c * N >= lim) return p;
     p.nt = N <= 16 ? 1 : (N <= 32 ? 2 : 4);
     const int64_t n_tiles = (N + 16 * p.nt - 1) / (16 * p.nt);
     p.m_tiles = (unsigned)((n + 63) / 64);
-    // 4 workgroups of 64 rows per CU (wider ones of 128 rows, two per CU, were slower from 2 500 to
-    // 280 000 voxels: 32 -> 64 at 280k an eighth); small levels split the reduction to fill them
+    // 16 wavefronts per CU, 64 or 128 rows to a workgroup.  128 rows share the weights' splitting: 64 -> 64 at 280 000
+    // voxels 198 -> 187 us, at 31 000 12 -> 64 24 -> 21; at 10 000 voxels 128 -> 256 123 -> 130 and 16 -> 32 14 -> 17.  A
+    // tile of 16 columns has too few weights for 512 threads (32 -> 16 at 280 000: 53 -> 62).  Small levels
+    // split the reduction to fill the chip
+    if (p.nt > 1 && p.m_tiles >= 384) p.wv = 8;
     // (Rows of 4 channels, half of whose split terms are padding, and little work with more than 32 columns are
     // faster with gemm_f32_kernel, 4 -> 32 at 280k voxels 37 us against 46, 12 -> 64 at 10k 14 against 19, but
     // its results are 2.5 and 3 times as far from the exact ones, 1.2e-7 against 4.6e-8 and 2.0e-7 against 6.4e-8.)
@@ -1673,28 +1676,31 @@ static hch_status launch_conv_split(const ConvSplitPlan &p, const Level &L, cons
     float *dst = p.splits > 1 ? part : out;
     const unsigned n_tiles = (unsigned)((N + 16 * p.nt - 1) / (16 * p.nt));
     const bool fast = c % 32 == 0;
-    static int ids[3][2][2];                           // [columns][fast][transposed]
+    static int ids[3][2][2][2];                        // [columns][wavefronts][fast][transposed]
     static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
     (void)ids_ready;
-    int &id = ids[p.nt / 2][fast][transposed];
+    int &id = ids[p.nt / 2][p.wv / 8][fast][transposed];
     if (id < 0) {
         char nm[96];
-        snprintf(nm, sizeof nm, "conv_split_kernel<%d, %s, %s>", p.nt, fast ? "true" : "false", transposed ? "true" : "false");
+        snprintf(nm, sizeof nm, "conv_split_kernel<%d, %d, %s, %s>", p.nt, p.wv, fast ? "true" : "false", transposed ? "true" : "false");
         id = hch::Profiler::get().id_for(nm);
     }
     {
         hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
-        const dim3 grid(hch::skip_grid(p.m_tiles, hch::skip_chunk(p.m_tiles, 1)), n_tiles, (unsigned)p.splits);
+        const unsigned group = (unsigned)p.wv / 4;     // 64-row tiles per workgroup
+        const dim3 grid(hch::skip_grid((p.m_tiles + group - 1) / group, hch::skip_chunk(p.m_tiles, group)), n_tiles, (unsigned)p.splits);
         const int vec_out = N % 4 == 0 && aligned16(dst);
-#define HCH_CONV_SPLIT(NT_, F_, T_)                                                                            \
-        HCH_LAUNCH((hch::conv_split_kernel<NT_, F_, T_>), grid, dim3(256), 0, s, X, W, dst, L.dnbr, L.rows(),  \
-                   (const uint32_t *)L.row_taps(), (const uint32_t *)L.dmask27, (int)n, N, c, p.m_tiles, n * N, vec_out)
-#define HCH_CONV_SPLIT_FT(NT_)                                                                                 \
+#define HCH_CONV_SPLIT(NT_, WV_, F_, T_)                                                                       \
+        HCH_LAUNCH((hch::conv_split_kernel<NT_, WV_, F_, T_>), grid, dim3(64 * WV_), 0, s, X, W, dst, L.dnbr, L.rows(),  \
+                   (const uint32_t *)L.row_taps(), (int)n, N, c, p.m_tiles, n * N, vec_out)
+#define HCH_CONV_SPLIT_FT(NT_, WV_)                                                                            \
         do {                                                                                                   \
-            if (fast) { if (transposed) HCH_CONV_SPLIT(NT_, true, true); else HCH_CONV_SPLIT(NT_, true, false); } \
-            else { if (transposed) HCH_CONV_SPLIT(NT_, false, true); else HCH_CONV_SPLIT(NT_, false, false); } \
+            if (fast) { if (transposed) HCH_CONV_SPLIT(NT_, WV_, true, true); else HCH_CONV_SPLIT(NT_, WV_, true, false); } \
+            else { if (transposed) HCH_CONV_SPLIT(NT_, WV_, false, true); else HCH_CONV_SPLIT(NT_, WV_, false, false); } \
         } while (0)
-        if (p.nt == 1) HCH_CONV_SPLIT_FT(1); else if (p.nt == 2) HCH_CONV_SPLIT_FT(2); else HCH_CONV_SPLIT_FT(4);
+        if (p.nt == 1) HCH_CONV_SPLIT_FT(1, 4);
+        else if (p.nt == 2) { if (p.wv == 8) HCH_CONV_SPLIT_FT(2, 8); else HCH_CONV_SPLIT_FT(2, 4); }
+        else { if (p.wv == 8) HCH_CONV_SPLIT_FT(4, 8); else HCH_CONV_SPLIT_FT(4, 4); }
 #undef HCH_CONV_SPLIT_FT
 #undef HCH_CONV_SPLIT
     }

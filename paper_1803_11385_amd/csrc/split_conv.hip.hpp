@@ -15,60 +15,76 @@ __device__ __forceinline__ void load8(const float *p, int have, float *v)
         for (int j = 0; j < 8; ++j) v[j] = j < have ? p[j] : 0.f;
 }
 
-// A workgroup of 4 wavefronts computes 64 rows of the order `rowmap` by 16*NT columns; a wavefront has
-// 16 rows of its own.  The reduction runs over the taps that the workgroup's rows have
+// A workgroup of WV wavefronts (4 or 8) computes 64 or 128 rows of the order `rowmap` by 16*NT columns; a
+// wavefront has 16 rows of its own.  The reduction runs over the taps that the workgroup's rows have
 // (`tilemask`), in units of 8 channels of one tap, 4 units (32 terms) to a step.
 //   * Gathered rows: a wavefront loads its own rows, 8 lanes per 128 bytes of a row, lays them into a
 //     stretch of LDS that nobody else reads (no barrier), reads them back as the operand wants them
-//     (8 consecutive terms of one row per lane; the 16-byte pieces of a row are permuted by its
-//     number, so neither side has bank conflicts) and cuts them in registers.  Each element is cut
+//     (8 consecutive terms of one row per lane) and cuts them in registers.  Each element is cut
 //     once per column tile of the output, which is why a wavefront takes all columns.
-//   * Weights: one unit per thread and step, cut before it goes to LDS, two stages, one barrier a step.
+//   * Weights: the same share of every step for each thread, cut before it goes to LDS, two stages, one
+//     barrier a step.
 //   * Loads run two steps ahead in two sets of registers, as in gemm_f32_kernel.
 //   * The index rows of a wavefront are read once, whole rows at a time, into LDS.
-// Bound by vector instructions and LDS together: of a busy CU's time the vector pipes issue 0.57, LDS works 0.60
-// (0.38 of that bank conflicts), the matrix pipes 0.31 (32 -> 64, 280 000 voxels; data gradient 0.66, 0.72,
-// 0.27), at four wavefronts per SIMD; a step costs 52 + 52 vector instructions to split its 16 rows and its
-// share of the weights, and 24 matrix instructions.  Forward and data gradient against gemm_f32_kernel over the
-// coarser row order: 32 -> 64 140 and 150 us (196, 196), 64 -> 64 216 and 214 (354, 365), 50 -> 50 233
-// and 265 (1112, 1117: element by element).
+//   * The last rows of the order have the most neighbours; their workgroups start first, or a launch ends with
+//     a few of them running alone (32 -> 64 at 280 000 voxels 141 -> 131 us).
+// Bound by no single unit: at four wavefronts per SIMD the vector pipes issue 0.53 of all cycles, the matrix
+// pipes are busy 0.32, LDS 0.5, fills of L1 run at 8.6 TB/s (64 -> 64, 280 000 voxels, 64 rows), and they
+// stand in each other's way.  Products of a step issued between the splitting of the next one took more registers
+// than that gave back (two wavefronts per SIMD: 196 -> 250 us), 32 rows per wavefront the same (203),
+// 16 wavefronts share one barrier (202).  Eight wavefronts load and split the weights for twice the rows:
+// 198 -> 187 us.  Forward and data gradient at 280 000 voxels, before (four wavefronts, rows in ascending
+// order, conflicts on half of the LDS reads, half of the threads without weights where there are 32
+// columns) -> now: 32 -> 64 145 and 155 us -> 126 and 130, 64 -> 64 217 and 215 -> 187 and 177, 50 -> 50 232 and 264 ->
+// 185 and 185; gemm_f32_kernel over the coarser row order took 196 and 196, 354 and 365, 1112 and 1117.
 // FAST: rows of a multiple of 32 channels; a step lies within one tap, offsets that change from step
 // to step are scalar, and a wavefront whose own rows lack the tap sits the step out.  Otherwise any
 // number of channels: a tap is padded to a multiple of 8, with weights of zero.
 // BT: W(t, k, n) = W[26 - t][n][k] (the data gradient's view of the weights), else W[t][k][n].
-template <int NT>
+
+// Where a 16-byte piece lies in LDS.  ds_read_b128 serves 16 lanes a clock, not 16 neighbours: lanes 0-3, 12-15 and
+// 20-27 of each half, then the others.  With these permutations any 16 of them read 16 different
+// sixteenths of the 256 bytes that the banks span (4 clocks a read; the plain layouts took 8), and the writes
+// of 8 neighbouring lanes stay apart too.  Gathered rows: piece ^ row_swap(row); weights: column ^ unit_swap(unit).
+__device__ __forceinline__ int row_swap(int r) { return (r >> 1 & 1) | (r >> 3 & 1) * 6; }
+__device__ __forceinline__ int unit_swap(int k) { return (k & 1) * 2 + (k >> 1) * 12; }
+
+template <int NT, int WV>
 struct ConvLds {
     static constexpr int BN = 16 * NT, ROWS = 16;
     static constexpr int A = ROWS * 128;                                   // one wavefront's rows of a step
-    static constexpr int LKS = BN * 16 + 16, PLANE = 4 * LKS, B = 3 * PLANE;   // one stage of weights
+    static constexpr int LKS = BN * 16, PLANE = 4 * LKS, B = 3 * PLANE;   // one stage of weights
     static constexpr int IDX = 27 * ROWS * 4;                              // one wavefront's index rows, tap-major
-    static constexpr int O_B = 4 * A, O_IDX = O_B + 2 * B, O_TAP = O_IDX + 4 * IDX, BYTES = O_TAP + 32;
+    static constexpr int O_B = WV * A, O_IDX = O_B + 2 * B, O_TAP = O_IDX + WV * IDX, BYTES = O_TAP + 32;
 };
 
-template <int NT, bool FAST, bool BT>
-__global__ __launch_bounds__(256) void conv_split_kernel(
+template <int NT, int WV, bool FAST, bool BT>
+__global__ __launch_bounds__(64 * WV) void conv_split_kernel(
     const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr,
-    const int32_t *__restrict__ rowmap, const uint32_t *__restrict__ tilemask, const uint32_t *__restrict__ mask27,
+    const int32_t *__restrict__ rowmap, const uint32_t *__restrict__ tilemask,
     int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
 {
-    typedef ConvLds<NT> L;
-    constexpr int BN = L::BN, ROWS = L::ROWS;
+    typedef ConvLds<NT, WV> L;
+    constexpr int BN = L::BN, ROWS = L::ROWS, GROUP = ROWS * WV / 64;     // 64-row tiles per workgroup
     constexpr uint32_t OUT = 0x80000000u;
     constexpr int SRD3 = 0x00020000;
     __shared__ __attribute__((aligned(16))) unsigned char lds[L::BYTES];
 
-    const unsigned mtile = xcd_chunk_tile(blockIdx.x, skip_chunk(m_tiles, 1));
-    if (mtile >= m_tiles) return;
+    unsigned mtile = xcd_chunk_tile(blockIdx.x, skip_chunk(m_tiles, GROUP));
+    const unsigned groups = (m_tiles + GROUP - 1) / GROUP;
+    if (mtile >= groups) return;
+    mtile = groups - 1 - mtile;                                           // most neighbours first
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = (int)blockIdx.y * BN;
-    const int row0 = (int)mtile * 64 + wave * ROWS;                   // this wavefront's first row of the order
+    const int row0 = ((int)mtile * WV + wave) * ROWS;                   // this wavefront's first row of the order
     unsigned char *a_lds = lds + wave * L::A;
     int32_t *idx = reinterpret_cast<int32_t *>(lds + L::O_IDX + wave * L::IDX);
     uint8_t *taplist = lds + L::O_TAP;
 
     // taps of the workgroup's rows, the list of them, and this slice's steps
-    uint32_t present = tilemask[mtile];
+    uint32_t present = tilemask[mtile * GROUP];
+    if (GROUP == 2 && mtile * 2 + 1 < m_tiles) present |= tilemask[mtile * 2 + 1];
     present = (uint32_t)__builtin_amdgcn_readfirstlane((int)present);
     if (tid < 32) {
         uint32_t m = present;
@@ -86,7 +102,6 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
         const int r = lane < ROWS ? lane : 0;
         const bool ok = lane < ROWS && row0 + r < M;
         const int vox = ok ? rowmap[row0 + r] : -1;
-        if (FAST) mine = ok ? mask27[vox] : 0u;
         if (lane < ROWS) idx[13 * ROWS + lane] = vox;
         __builtin_amdgcn_wave_barrier();
         const __amdgpu_buffer_rsrc_t rs_n = __builtin_amdgcn_make_buffer_rsrc((void *)nbr, 0, M * 27 * 4, SRD3);
@@ -96,7 +111,8 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
             const int e = q * 64 + lane, rr = min(e / 27, ROWS - 1), t = e - (e / 27) * 27;
             const int vx = idx[13 * ROWS + rr];
             v[q] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_n, vx >= 0 ? (vx * 27 + t) * 4 : (int)OUT, 0, 0);
-            if (vx < 0) v[q] = -1;
+            if (vx < 0 || e >= ROWS * 27) v[q] = -1;
+            if (FAST) mine |= v[q] >= 0 ? 1u << t : 0u;
         }
 #pragma unroll
         for (int q = 0; q < (ROWS * 27 + 63) / 64; ++q) {
@@ -117,10 +133,12 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
     // ---- one step's loads.  Gathered rows: piece ap (16 bytes) of rows ar, ar + 8, ...
     const int ap = lane & 7, ar = lane >> 3;
     constexpr int AU = ROWS / 8;
-    // weights: columns bn, terms 8*bk .. 8*bk + 7 of the step
-    const int bn = BT ? tid >> 2 : tid % BN, bk = BT ? tid & 3 : tid / BN;
-    const bool b_mine = BT ? bn < BN : bk < 4;
-    const bool b_col = b_mine && n0 + bn < N;
+    // weights: UN consecutive terms of one column per thread
+    constexpr int UN = BN * 32 / (64 * WV), KP = 32 / UN;
+    static_assert(UN >= 2 && UN <= 8, "whole pairs, within one unit");
+    const int bn = BT ? tid / KP : tid % BN, kp = BT ? tid % KP : tid / BN;
+    const int bk = kp * UN / 8, bs = kp * UN % 8;                           // unit, first term within it
+    const bool b_col = n0 + bn < N;
     // FAST: list position and channel block of the next step (scalar)
     uint32_t rem = present;
     int cb = 0;
@@ -147,17 +165,22 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
             }
             if constexpr (BT) {
                 const int base = __builtin_amdgcn_readfirstlane(((26 - tap) * N * c + cb) * 4);
-                const int off = b_col ? ((n0 + bn) * c + bk * 8) * 4 : (int)OUT;
+                const int off = b_col ? ((n0 + bn) * c + kp * UN) * 4 : (int)OUT;
+                if constexpr (UN >= 4) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x4 w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_w, off + 16 * h, base, 0));
+                    for (int h = 0; h < UN / 4; ++h) {
+                        const f32x4 w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_w, off + 16 * h, base, 0));
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) rb[4 * h + j] = w[j];
+                        for (int j = 0; j < 4; ++j) rb[4 * h + j] = w[j];
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < UN; ++j) rb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, off + 4 * j, base, 0));
                 }
             } else {
-                const int off = b_col ? (bk * 8 * N + n0 + bn) * 4 : (int)OUT;
+                const int off = b_col ? (kp * UN * N + n0 + bn) * 4 : (int)OUT;
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
+                for (int j = 0; j < UN; ++j)
                     rb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, off, __builtin_amdgcn_readfirstlane((tap * c + cb + j) * N * 4), 0));
             }
             cb += 32;
@@ -177,8 +200,8 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
             const int tb = taplist[min(b_tap, 31)];
             const bool ok = b_col && b_tap < n_present;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int k = b_u * 8 + j;
+            for (int j = 0; j < UN; ++j) {
+                const int k = b_u * 8 + bs + j;
                 const int at = BT ? ((26 - tb) * N + n0 + bn) * c + k : (tb * c + k) * N + n0 + bn;
                 rb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, ok && k < c ? at * 4 : (int)OUT, 0, 0));
             }
@@ -190,16 +213,15 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
 #pragma unroll
         for (int q = 0; q < AU; ++q) {
             const int r = ar + 8 * q;
-            *reinterpret_cast<u32x4 *>(a_lds + r * 128 + ((ap ^ (r & 7)) << 4)) = ra[q];
+            *reinterpret_cast<u32x4 *>(a_lds + r * 128 + ((ap ^ row_swap(r)) << 4)) = ra[q];
         }
     };
     auto stash_b = [&](int stage, const float *rb) {
-        if (!b_mine) return;
-        u32x4 p[3];
-        split3(rb, p[0], p[1], p[2]);
+        unsigned char *dst = lds + L::O_B + stage * L::B + bk * L::LKS + (bn ^ unit_swap(bk)) * 16 + bs * 2;
+        uint32_t p[3][UN / 2];
+        split3n<UN / 2>(rb, p[0], p[1], p[2]);
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl)
-            *reinterpret_cast<u32x4 *>(lds + L::O_B + stage * L::B + pl * L::PLANE + bk * L::LKS + bn * 16) = p[pl];
+        for (int pl = 0; pl < 3; ++pl) __builtin_memcpy(__builtin_assume_aligned(dst + pl * L::PLANE, UN * 2), p[pl], UN * 2);
     };
 
     // the products of the leading pieces and the five smaller ones are summed apart: the large sums
@@ -217,7 +239,7 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
         u32x4 raw[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            raw[h] = *reinterpret_cast<const u32x4 *>(a_lds + li * 128 + (((lk * 2 + h) ^ (li & 7)) << 4));
+            raw[h] = *reinterpret_cast<const u32x4 *>(a_lds + li * 128 + (((lk * 2 + h) ^ row_swap(li)) << 4));
         stash_a(ra);                                                       // step t + 1, after the reads of step t
         stash_b(stage ^ 1, rb);
         fetch(ra, rb);                                                     // step t + 3
@@ -239,7 +261,7 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
             for (int b = 0; b < NT; ++b)
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl)
-                    w[b][pl] = *reinterpret_cast<const u32x4 *>(lds + L::O_B + stage * L::B + pl * L::PLANE + lk * L::LKS + (b * 16 + li) * 16);
+                    w[b][pl] = *reinterpret_cast<const u32x4 *>(lds + L::O_B + stage * L::B + pl * L::PLANE + lk * L::LKS + (b * 16 + (li ^ unit_swap(lk))) * 16);
             constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
 #pragma unroll
             for (int b = 0; b < NT; ++b) acc[b] = mfma_bf16(w[b][0], x[0], acc[b]);
@@ -252,7 +274,7 @@ __global__ __launch_bounds__(256) void conv_split_kernel(
     };
     if (s_beg < s_end) {
         u32x4 ra0[AU], ra1[AU];
-        float rb0[8], rb1[8];
+        float rb0[UN], rb1[UN];
         fetch(ra0, rb0);
         fetch(ra1, rb1);
         stash_a(ra0);

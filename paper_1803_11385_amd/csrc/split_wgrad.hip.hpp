@@ -33,10 +33,11 @@ constexpr float SPLIT_SCALE = 0x1p16f, SPLIT_UNSCALE = 0x1p-32f;
 // infinity, a NaN or a number that goes beyond the largest bf16 makes m a NaN, so that whatever it is
 // multiplied into comes out non-finite (the caller then takes the plain fp32 sum).
 // (v_dot2_f32_bf16 with (-1, 0) would subtract straight from the packed pair, but its sum is not exact.)
-__device__ __forceinline__ void split3(const float *x, u32x4 &h, u32x4 &m, u32x4 &l)
+template <int PAIRS, typename V>
+__device__ __forceinline__ void split3n(const float *x, V &h, V &m, V &l)
 {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
+    for (int p = 0; p < PAIRS; ++p) {
         const float a = x[2 * p] * SPLIT_SCALE, b = x[2 * p + 1] * SPLIT_SCALE;
         h[p] = round_bf16(a, b);
         const float ra = a - __uint_as_float(h[p] << 16), rb = b - __uint_as_float(h[p] & 0xFFFF0000u);
@@ -44,6 +45,7 @@ __device__ __forceinline__ void split3(const float *x, u32x4 &h, u32x4 &m, u32x4
         l[p] = round_bf16(ra - __uint_as_float(m[p] << 16), rb - __uint_as_float(m[p] & 0xFFFF0000u));
     }
 }
+__device__ __forceinline__ void split3(const float *x, u32x4 &h, u32x4 &m, u32x4 &l) { split3n<4>(x, h, m, l); }
 
 __device__ __forceinline__ f32x4 mfma_bf16(const u32x4 &a, const u32x4 &b, const f32x4 &c)
 {

@@ -95,6 +95,20 @@ def test_small_batches_in_any_order(oracle, n, ci, co):
     _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
 
 
+@pytest.mark.parametrize("n", [24512, 24513, 24576, 24577, 24641])
+@pytest.mark.parametrize("ci,co", [(32, 64), (12, 20), (33, 50)])
+def test_around_the_wider_workgroups(oracle, n, ci, co):
+    """From 384 tiles of 64 rows on (24 513 voxels) a workgroup has 128 rows: the last one whole, a half
+    and a row of a half."""
+    rng = np.random.default_rng(n)
+    pos = np.sort(rng.permutation(48 ** 3)[:n])
+    coords = np.stack([pos // 2304, pos // 48 % 48, pos % 48], 1).astype(np.int32)
+    lv = hch.hch_build_levels(coords, [0, n], 64, 1)
+    nbr = oracle.neighbours(oracle.build_hierarchy(coords, [0, n], 64, 1)[0])
+    X, W, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda() for s in ((n, ci), (27, ci, co), (n, co)))
+    _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
+
+
 @pytest.mark.parametrize("sign", ["any", "positive"])
 @pytest.mark.parametrize("ci,co", [(256, 64), (512, 64), (512, 512)])
 def test_many_channels(oracle, ci, co, sign):
