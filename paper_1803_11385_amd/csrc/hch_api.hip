@@ -418,7 +418,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         if (round >= 24) return fail(HCH_EBUILD, "hch_build_levels_device: perfect hash construction failed");
         const int na = (int)active.size();
         std::vector<hch::PairDesc> desc((size_t)na);
-        int64_t cells = 0, vox = 0, slots = 0;
+        int64_t cells = 0, vox = 0, slots = 0, words = 0;       // words of taken bits: never more than slots
         int32_t max_n = 0, max_r3 = 0, max_m3 = 0;
         for (int a = 0; a < na; ++a) {
             PairWork &w = work[active[a]];
@@ -427,8 +427,8 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
                 return fail(HCH_EBUILD, "hch_build_levels_device: perfect hash construction failed");
             const int32_t r3 = w.r * w.r * w.r, m3 = w.m * w.m * w.m;
             desc[a] = hch::PairDesc{L.dcoords + 3 * L.N[w.v], L.dH + L.M[w.v], L.dT + 3 * L.M[w.v], w.n, w.m, w.r,
-                                    (int32_t)cells, (int32_t)vox, (int32_t)slots, active[a]};
-            cells += r3; vox += w.n; slots += m3;
+                                    (int32_t)cells, (int32_t)vox, (int32_t)slots, (int32_t)words, active[a]};
+            cells += r3; vox += w.n; slots += m3; words += (int64_t)w.m * w.m * hch::psh_row_words(w.m);
             max_n = std::max(max_n, w.n); max_r3 = std::max(max_r3, r3); max_m3 = std::max(max_m3, m3);
             ++w.attempts;
         }
@@ -438,6 +438,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         int32_t *d_cnt = nullptr, *d_first = nullptr, *d_sums = nullptr, *d_fill = nullptr, *d_bucket = nullptr, *d_members = nullptr;
         int32_t *d_counters = nullptr, *d_free = nullptr;
         uint32_t *d_phi = nullptr, *d_res = nullptr;
+        unsigned long long *d_bits = nullptr;
         int2 *d_cells = nullptr;
         // counters: [0, CLASSES) buckets per class, then per active pair: free slots, singles placed
         const size_t n_counters = (size_t)hch::PSH_CLASSES + 2 * (size_t)na;
@@ -446,6 +447,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
             P.take(d_fill, (size_t)cells * 4);
             P.take(d_phi, (size_t)cells * 4);
             P.take(d_counters, n_counters * 4);
+            P.take(d_bits, (size_t)words * 8);
             *zeroed = P.used;
             P.take(d_desc, desc.size() * sizeof(hch::PairDesc));
             P.take(d_first, (size_t)cells * 4);
@@ -481,13 +483,11 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         // largest buckets first: all of 9 voxels and more in one launch, then one size per launch
         for (int k = hch::PSH_CLASSES - 1; k >= 2; --k) {
             if (class_count[k] <= 0) continue;
-            HCH_HIP(hipMemsetAsync(d_nfree, 0, (size_t)na * 4, s));
-            HCH_LAUNCH(hch::psh_free_list_kernel, gs, dim3(256), 0, s, d_desc, d_nfree, d_free);
-            HCH_LAUNCH(hch::psh_place_kernel, dim3((unsigned)((class_count[k] + 3) / 4)), dim3(256), 0, s, d_desc,
-                               d_cells + (size_t)k * cells, class_count[k], d_cnt, d_first, d_members, d_res, d_nfree,
-                               d_free, d_phi, d_fail);
+            const int64_t waves = std::max<int64_t>(64, slots / (48 * k));     // see psh_place_kernel
+            HCH_LAUNCH(hch::psh_place_kernel, dim3((unsigned)((std::min<int64_t>(class_count[k], waves) + 3) / 4)), dim3(256), 0, s, d_desc,
+                               d_cells + (size_t)k * cells, class_count[k], d_cnt, d_first, d_members, d_res, d_bits,
+                               d_phi, d_fail);
         }
-        HCH_HIP(hipMemsetAsync(d_nfree, 0, (size_t)na * 4, s));
         HCH_LAUNCH(hch::psh_free_list_kernel, gs, dim3(256), 0, s, d_desc, d_nfree, d_free);
         HCH_LAUNCH(hch::psh_place_single_kernel, gc, dim3(256), 0, s, d_desc, d_cnt, d_first, d_members, d_res,
                            d_nfree, d_free, d_rank, d_phi, d_fail);

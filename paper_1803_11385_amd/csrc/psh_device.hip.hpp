@@ -9,13 +9,12 @@
 //   * every (level, model) pair of the batch is built in the same launches;
 //   * buckets (voxels sharing p mod r) are placed in classes of decreasing size (9 and more,
 //     8, 7, ..., 2, 1), one launch per class, all buckets of a class at once;
-//   * before each class the free slots of every table are listed; a bucket's candidates are the
-//     free slots (its first voxel goes there, which fixes the offset), starting at a hashed
-//     position of the list;
-//   * one wavefront per bucket: 64 candidates are examined at once (a lane looks whether the
-//     slots of all the bucket's voxels are free), then the first lane that found room claims the
-//     slots with compare-and-swap on H and, if another bucket was faster on one of them, gives
-//     the claimed ones back and the next lane tries;
+//   * a bit per slot says whether it is taken.  A lane looks at 64 offsets at once: those that differ
+//     in z only, for which a bucket's voxels read one stretch of 64 bits each; a wavefront looks at
+//     64 such rows side by side, starting at a hashed one;
+//   * one wavefront per bucket: the first offset with room for all of its voxels is claimed, every voxel's
+//     bit by a lane of its own and all at once; if another bucket was faster on one of them, the
+//     claimed ones are given back and the next offset is tried;
 //   * buckets of one voxel need no search: the i-th of them takes the i-th free slot;
 //   * a bucket that runs out of candidates fails its pair; failed pairs are cleared and repeated
 //     with the next r.
@@ -36,6 +35,7 @@ struct PairDesc {
     int32_t cell_base;       // first offset cell of the pair in this attempt's cell arrays
     int32_t vox_base;        // first entry of the pair in this attempt's member arrays
     int32_t slot_base;       // first entry of the pair in this attempt's free-slot list
+    int32_t row_base;        // first word of the pair in this attempt's bits (psh_row_words a row, m^2 rows)
     int32_t pair_id;         // index into the failure flags
 };
 
@@ -183,113 +183,143 @@ __device__ __forceinline__ int32_t psh_peek(const int32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// slot of a voxel with packed residues h under the offset (ox, oy, oz)
-__device__ __forceinline__ int psh_slot_of(uint32_t h, int ox, int oy, int oz, int m)
+// A row of the bits of taken slots, m of them in z, goes round: behind bit m - 1 come bits 0 .. 62 again, so
+// that 64 bits can be read from any of the m positions (two words, the second one always there).
+__host__ __device__ __forceinline__ int psh_row_words(int m) { return (m - 1) / 64 + 2; }
+__device__ __forceinline__ unsigned long long psh_peek_row(const unsigned long long *row, int at)
 {
-    int x = (int)(h & 255u) + ox; if (x >= m) x -= m;
-    int y = (int)((h >> 8) & 255u) + oy; if (y >= m) y -= m;
-    int z = (int)(h >> 16) + oz; if (z >= m) z -= m;
-    return (x * m + y) * m + z;
+    const unsigned long long lo = __hip_atomic_load(row + (at >> 6), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long hi = __hip_atomic_load(row + (at >> 6) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (at & 63) ? lo >> (at & 63) | hi << (64 - (at & 63)) : lo;
 }
 
-// Place the buckets of one class (2 voxels and more): one wavefront per bucket, 4 per workgroup.
-// phi4[cell] receives the offset, packed x | y << 8 | z << 16.
-constexpr int PSH_WIDE = 4;
-__global__ __launch_bounds__(256) void psh_place_kernel(
-    const PairDesc *__restrict__ pairs, const int2 *__restrict__ cells, int n_buckets,
-    const int32_t *__restrict__ cnt, const int32_t *__restrict__ first, const int32_t *__restrict__ members,
-    const uint32_t *__restrict__ residues, const int32_t *__restrict__ n_free,
-    const int32_t *__restrict__ free_list, uint32_t *__restrict__ phi4, int32_t *__restrict__ fail)
+// Place the bucket of c voxels in cell g of pair P: a wavefront.  phi4 receives the offset, packed
+// x | y << 8 | z << 16.
+__device__ __forceinline__ void psh_place_bucket(
+    const PairDesc &P, int g, int c, const int32_t *__restrict__ members, const uint32_t *__restrict__ residues,
+    unsigned long long *__restrict__ taken, uint32_t *__restrict__ phi4, int32_t *__restrict__ fail)
 {
-    const int lane = threadIdx.x & 63;
-    const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (b >= n_buckets) return;                       // whole wavefronts leave together
-    const int2 ag = cells[b];
-    const PairDesc P = pairs[ag.x];
-    const int g = ag.y, cell = P.cell_base + g;
-    const int c = cnt[cell], base = first[cell];
-    const int m = P.m;
-    const int nf = n_free[ag.x];
-    int32_t *H = P.H;
-    const int32_t *list = free_list + P.slot_base;
-    const uint32_t h_first = residues[base];
-    const int ax = h_first & 255u, ay = (h_first >> 8) & 255u, az = h_first >> 16;
-    const int start = nf > 0 ? (int)(((uint32_t)g * 2654435761u) % (uint32_t)nf) : 0;
+    const int lane = threadIdx.x & 63, m = P.m, rows = m * m, words = psh_row_words(m);
+    const uint32_t mine = residues[min(lane, c - 1)];             // lane k has voxel k; those beyond 64 come from memory
+    auto residue = [&](int k) -> uint32_t { return k < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)mine, k) : residues[k]; };
+    auto wrap = [&](int v) { return v >= m ? v - m : v; };
+    const uint32_t hash = (uint32_t)g * 2654435761u;
+    const int start = (int)(hash % (uint32_t)rows), bit0 = (int)(hash >> 26);
 
-    // 64 candidates at first, the usual case; then four times as many at a time, their loads side by
-    // side: a bucket that finds no room at all has to look at every free slot, and those buckets
-    // (their pair then tries the next r) are what a launch waits for at the end
-    for (int i0 = 0, wide = 1; i0 < nf; i0 += 64 * wide, wide = PSH_WIDE) {
-        if (psh_peek(&fail[P.pair_id])) return;       // the pair is lost anyway
-        int slot[PSH_WIDE];
-        bool rooms[PSH_WIDE];
+    bool raced = true, twins_checked = false;
+    // an offset lost to another bucket that then gave its slots back is worth another look, a few times
+    for (int pass = 0; pass < 4 && raced; ++pass) {
+        raced = false;
+        for (int i0 = 0; i0 < rows; i0 += 64) {
+            int q = start + i0 + lane;
+            if (q >= rows) q -= rows;
+            const bool real = i0 + lane < rows;
+            if (!real) q = 0;
+            const int ox = q / m, oy = q - ox * m;
+            for (int w = 0; w * 64 < m; ++w) {
+                const int n_oz = m - w * 64;
+                const unsigned long long offsets = !real ? 0ull : n_oz >= 64 ? ~0ull : (1ull << n_oz) - 1ull;
+                unsigned long long tried = 0;
+                for (;;) {                            // until these rows have no offset left: each turn tries one
+                    const int lost = __builtin_amdgcn_readfirstlane(psh_peek(fail));
+                    unsigned long long room = offsets & ~tried;
+                    for (int k0 = 0; k0 < c; k0 += 4) {
+                        unsigned long long seen[4];
 #pragma unroll
-        for (int q = 0; q < PSH_WIDE; ++q) {
-            const int i = i0 + q * 64 + lane;
-            rooms[q] = q < wide && i < nf;
-            int w = start + (rooms[q] ? i : 0); if (w >= nf) w -= nf;
-            slot[q] = list[w];
-        }
-#pragma unroll
-        for (int q = 0; q < PSH_WIDE; ++q) rooms[q] &= psh_peek(H + slot[q]) == -1;
-        int off[PSH_WIDE];
-#pragma unroll
-        for (int q = 0; q < PSH_WIDE; ++q) {
-            const int sx = slot[q] / (m * m), sy = (slot[q] / m) % m, sz = slot[q] % m;
-            int x = sx - ax; if (x < 0) x += m;
-            int y = sy - ay; if (y < 0) y += m;
-            int z = sz - az; if (z < 0) z += m;
-            off[q] = x | y << 8 | z << 16;
-        }
-        for (int k = 1; k < c; ++k) {
-            bool any = false;
-#pragma unroll
-            for (int q = 0; q < PSH_WIDE; ++q) any |= rooms[q];
-            if (!__ballot(any)) break;
-            const uint32_t h = residues[base + k];
-            int32_t seen[PSH_WIDE];
-#pragma unroll
-            for (int q = 0; q < PSH_WIDE; ++q)
-                seen[q] = rooms[q] ? psh_peek(H + psh_slot_of(h, off[q] & 255, off[q] >> 8 & 255, off[q] >> 16, m)) : 0;
-#pragma unroll
-            for (int q = 0; q < PSH_WIDE; ++q) rooms[q] &= seen[q] == -1;
-        }
-        for (int q = 0; q < wide; ++q) {
-            const bool room = q == 0 ? rooms[0] : q == 1 ? rooms[1] : q == 2 ? rooms[2] : rooms[3];
-            const int o = q == 0 ? off[0] : q == 1 ? off[1] : q == 2 ? off[2] : off[3];
-            const int ox = o & 255, oy = o >> 8 & 255, oz = o >> 16;
-            unsigned long long cand = __ballot(room);
-            while (cand) {                                // wave-uniform loop
-                const int j = __builtin_ctzll(cand);
-                cand &= cand - 1;
-                int won = 0;
-                if (lane == j) {
-                    int got = 0;
-                    bool twice = false;     // two voxels of the bucket on one slot: no offset can separate them
-                    for (int k = 0; k < c && got == k; ++k) {
-                        const int32_t old = atomicCAS(H + psh_slot_of(residues[base + k], ox, oy, oz, m), -1, members[base + k]);
-                        if (old == -1) got = k + 1;
-                        else for (int kk = 0; kk < k; ++kk) twice |= old == members[base + kk];
-                    }
-                    if (twice) { fail[P.pair_id] = 1; won = 1; }
-                    if (got == c) {
-                        for (int k = 0; k < c; ++k) {
-                            const int32_t *p = P.coords + 3 * (int64_t)members[base + k];
-                            uint16_t *tag = P.T + 3 * (int64_t)psh_slot_of(residues[base + k], ox, oy, oz, m);
-                            tag[0] = (uint16_t)p[0]; tag[1] = (uint16_t)p[1]; tag[2] = (uint16_t)p[2];
+                        for (int k = 0; k < 4; ++k) {
+                            const uint32_t h = residue(min(k0 + k, c - 1));
+                            const int x = wrap((int)(h & 255u) + ox), y = wrap((int)(h >> 8 & 255u) + oy);
+                            seen[k] = psh_peek_row(taken + (int64_t)(x * m + y) * words, wrap((int)(h >> 16) + w * 64));
                         }
-                        phi4[cell] = (uint32_t)ox | ((uint32_t)oy << 8) | ((uint32_t)oz << 16);
-                        won = 1;
-                    } else {
-                        for (int k = 0; k < got; ++k)     // give the claimed slots back
-                            atomicExch(H + psh_slot_of(residues[base + k], ox, oy, oz, m), -1);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) room &= ~seen[k];
+                        if (!__ballot(room != 0)) break;
                     }
+                    if (lost) return;                 // the pair is lost anyway
+                    const unsigned long long lanes = __ballot(room != 0);
+                    if (!lanes) break;
+                    // the first lane with room, and its first offset from a hashed one on: buckets keep apart
+                    const int j = __builtin_ctzll(lanes);
+                    const unsigned long long later = room >> bit0 << bit0;
+                    const int fz = room ? __builtin_ctzll(later ? later : room) : 0;
+                    const int cx = __builtin_amdgcn_readlane(ox, j), cy = __builtin_amdgcn_readlane(oy, j);
+                    const int cz = w * 64 + __builtin_amdgcn_readlane(fz, j);
+                    if (lane == j) tried |= 1ull << fz;
+                    // every voxel's bit, 64 of them at a time
+                    auto row_of = [&](uint32_t h) { return taken + (int64_t)(wrap((int)(h & 255u) + cx) * m + wrap((int)(h >> 8 & 255u) + cy)) * words; };
+                    auto give_back = [&](uint32_t h) {
+                        const int z = wrap((int)(h >> 16) + cz);
+                        __hip_atomic_fetch_and(row_of(h) + (z >> 6), ~(1ull << (z & 63)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    };
+                    int turn = 0;
+                    bool all = true;
+                    for (; turn * 64 < c && all; ++turn) {
+                        const int k = turn * 64 + lane;
+                        const uint32_t h = turn == 0 ? mine : residues[min(k, c - 1)];
+                        const int z = wrap((int)(h >> 16) + cz);
+                        bool got = false;
+                        if (k < c) got = !(__hip_atomic_fetch_or(row_of(h) + (z >> 6), 1ull << (z & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (z & 63) & 1ull);
+                        if (__ballot(k < c && !got)) {
+                            all = false;
+                            if (got) give_back(h);
+                        }
+                    }
+                    if (!all) {
+                        for (int t = 0; t < turn - 1; ++t) give_back(residues[t * 64 + lane]);    // whole turns before the one that failed
+                        raced = true;
+                        if (!twins_checked) {         // two voxels of the bucket on one slot: no offset can separate them
+                            twins_checked = true;
+                            bool twins = false;
+                            for (int k = lane; k - lane < c; k += 64) {
+                                const uint32_t h = residues[min(k, c - 1)];
+                                for (int e = 0; e < c; ++e) twins |= residue(e) == h && e < k && k < c;
+                            }
+                            if (__ballot(twins)) {
+                                if (lane == 0) *fail = 1;
+                                return;
+                            }
+                        }
+                        continue;                     // and a fresh look at the rows: others have moved on
+                    }
+                    for (int k = lane; k < c; k += 64) {
+                        const uint32_t h = residues[k];
+                        const int x = wrap((int)(h & 255u) + cx), y = wrap((int)(h >> 8 & 255u) + cy), z = wrap((int)(h >> 16) + cz);
+                        if (z < 63) __hip_atomic_fetch_or(row_of(h) + ((z + m) >> 6), 1ull << ((z + m) & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        const int32_t v = members[k];
+                        const int64_t e = (int64_t)(x * m + y) * m + z;
+                        P.H[e] = v;
+                        const int32_t *p = P.coords + 3 * (int64_t)v;
+                        uint16_t *tag = P.T + 3 * e;
+                        tag[0] = (uint16_t)p[0]; tag[1] = (uint16_t)p[1]; tag[2] = (uint16_t)p[2];
+                    }
+                    if (lane == 0) *phi4 = (uint32_t)cx | ((uint32_t)cy << 8) | ((uint32_t)cz << 16);
+                    return;
                 }
-                if (__ballot(won)) return;
             }
         }
     }
-    if (lane == 0) fail[P.pair_id] = 1;
+    if (lane == 0) *fail = 1;
+}
+
+// Place the buckets of one class (2 voxels and more), a wavefront at a time each, as many wavefronts as are
+// launched.  Bound by round trips: what other workgroups may change is read and claimed past the caches of the
+// XCDs, 1 to 2 us each time.  Two things keep buckets out of each other's way: after a lost claim the rows are looked
+// at anew (the offsets of the first look were gone one after the other, thousands of them: 3.2 ms for the
+// buckets of 9 and more voxels of a 256^3 batch of 8, now 0.4), and no more wavefronts are launched than claim
+// one slot in 48 at a time.  A whole build with 6 levels: 10.6 -> 7.2 ms; one slot in 190 and one in 6 measured the
+// same there, 4 shapes of 745 000 voxels take 45 ms with one in 190, 40 with one in 48.
+__global__ __launch_bounds__(256) void psh_place_kernel(
+    const PairDesc *__restrict__ pairs, const int2 *__restrict__ cells, int n_buckets,
+    const int32_t *__restrict__ cnt, const int32_t *__restrict__ first, const int32_t *__restrict__ members,
+    const uint32_t *__restrict__ residues, unsigned long long *__restrict__ bits, uint32_t *__restrict__ phi4,
+    int32_t *__restrict__ fail)
+{
+    for (int b = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6))); b < n_buckets; b += (int)gridDim.x * 4) {
+        const int2 ag = cells[b];
+        const PairDesc P = pairs[ag.x];
+        const int cell = P.cell_base + ag.y, base = first[cell];
+        psh_place_bucket(P, ag.y, cnt[cell], members + base, residues + base, bits + P.row_base, phi4 + cell, fail + P.pair_id);
+    }
 }
 
 // Buckets of one voxel: the i-th of a table takes the i-th entry of its (fresh) free-slot list.

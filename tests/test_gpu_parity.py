@@ -733,6 +733,40 @@ def test_device_built_tables(request, oracle, name):
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("case", ["side 63", "side 64", "side 65", "one bucket of 1000", "two buckets of 500", "bucket of 1000 and another model"])
+def test_device_build_edges(case):
+    """Tables whose rows of taken bits end at a word's edge; buckets of more voxels than a wavefront has
+    lanes (positions that agree modulo the offset side, 6 for 1000 voxels)."""
+    rng = np.random.default_rng(3)
+    if case.startswith("side"):
+        n = (int(case[5:]) - 1) ** 3 + 17                        # the smallest side whose cube exceeds n
+        u, q = 128, np.sort(rng.permutation(128 ** 3)[:n])
+        coords, offs = np.stack([q // 16384, q // 128 % 128, q % 128], 1), [0, n]
+    else:
+        q = np.arange(1000)
+        u, coords, offs = 64, np.stack([q // 100, q // 10 % 10, q % 10], 1) * 6, [0, 1000]
+        if case.startswith("two"):
+            coords[500:] += 1
+        if case.endswith("model"):
+            coords, offs = np.concatenate([coords, rng.permutation(64 ** 3)[:300, None] // [4096, 64, 1] % 64]), [0, 1000, 1300]
+    coords = np.ascontiguousarray(coords, np.int32)
+    lv = hch.hch_build_levels_device(coords, offs, u, 1)
+    torch.cuda.synchronize()
+    info = lv.info(0)
+    if case.startswith("side"):
+        assert info.mbar[0] == int(case[5:])
+    model = np.repeat(np.arange(len(offs) - 1), np.diff(offs))
+    key = lambda m, p: ((m * (u + 2) + p[:, 0] + 1) * (u + 2) + p[:, 1] + 1) * (u + 2) + p[:, 2] + 1
+    keys = key(model, coords.astype(np.int64))
+    order = np.argsort(keys)
+    want = np.empty((len(keys), 27), np.int32)
+    for k in range(27):
+        at = key(model, coords + np.array([k // 9 - 1, k // 3 % 3 - 1, k % 3 - 1], np.int64))
+        pos = np.searchsorted(keys, at, sorter=order).clip(max=len(keys) - 1)
+        want[:, k] = np.where(keys[order[pos]] == at, order[pos], -1)
+    assert np.array_equal(info.device_nbr27(), want)
+
+
 def test_device_build_tiny_and_errors():
     # one voxel per model, a full 2^3 block, and the argument checks of the host entry point
     coords = np.array([[0, 0, 0], [3, 3, 3]] + [[x, y, z] for x in (0, 1) for y in (0, 1) for z in (0, 1)], np.int32)
