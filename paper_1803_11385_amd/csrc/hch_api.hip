@@ -18,6 +18,7 @@
 #include "gemm_bf16.hip.hpp"
 #include "split_wgrad.hip.hpp"
 #include "split_conv.hip.hpp"
+#include "split_field.hip.hpp"
 #include "psh_device.hip.hpp"
 #include "profile.hpp"
 #include "psh_build.hpp"
@@ -2389,6 +2390,82 @@ extern "C" hch_status hch_field_build(const hch_levels *levels, int32_t level_in
     return HCH_OK;
 }
 
+// Products over general index rows on split operands (field_split_kernel): `M` index rows of `taps` entries into the
+// x_rows rows of X, c channels to N; the cut weights take field_weights_bytes of workspace.
+static size_t field_weights_bytes(int taps, int c, int N)
+{
+    return (size_t)taps * (size_t)((c + 7) / 8) * (size_t)((N + 15) / 16) * 768;
+}
+
+enum FieldUse { FIELD_FWD, FIELD_BWD, FIELD_BWD_STRIDED };
+
+// Whether that is the faster way, and within its limits.  Its results are closer to the exact ones than those of the
+// fp32 instruction, as everywhere on split operands.
+static bool field_split_ok(FieldUse use, int64_t M, int64_t x_rows, int taps, int c, int N, size_t ws_bytes)
+{
+    const int64_t lim = (int64_t)1 << 31;
+    // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors; a bit per tap
+    if (taps > 32 || x_rows >= (1 << 23) || c * 4 >= (1 << 23) || x_rows * c * 4 >= lim || M * taps >= lim || (int64_t)N * c * taps * 6 >= lim / 4 ||
+        field_weights_bytes(taps, c, N) > ws_bytes)
+        return false;
+    // 256 rows to a workgroup, and some 10 us until the first sums: with fewer rows the chip stands empty (16 000 rows, 32 ->
+    // 64, 3^3: forward 15 us on the fp32 instruction, 51 here; data gradient of stride 2 19 and 33)
+    if (M < 49152) return false;
+    const double work = (double)M * taps * c * N;
+    // Forward: 3^3, 64 000 rows 24 -> 40 (1.7e9) 60 -> 50 us, 16 -> 32 (0.9e9) 26.5 and 27.6; 197 000 rows 16 -> 32 (2.7e9) 77 ->
+    // 71, 32 -> 64 229 -> 175; 82 000 rows 32 -> 32 (2.3e9) 62 and 63; 2^3, 82 000 rows 32 -> 64 (1.3e9) 39 and 44.  Rows of 4
+    // channels are half padding.
+    if (use == FIELD_FWD) return c >= 16 && work >= 1.6e9 && (N > 32 || M >= 98304);
+    if (taps * c < 256) return false;                  // 2^3, 16 -> 4 at 609 000 rows: 30 us, 37 here
+    // Data gradient within a level: 64 000 rows 32 -> 16 (0.9e9) 33 and 35 us, 40 -> 24 (1.7e9) 57 -> 49; 280 000 rows 16 -> 4 67 -> 58,
+    // 32 -> 16 115 -> 91, 64 -> 32 305 -> 231
+    if (use == FIELD_BWD) return work >= 1.6e9 || M >= 262144;
+    // Between levels, against the gradient of the column matrix through memory: 609 000 rows, stride 2, 32 -> 16 208 -> 84 us, 64 -> 32
+    // 438 -> 176, 16 -> 4 84 -> 64; where that matrix is small (3^3, stride 4, 64 000 rows, 32 -> 16: 2.3 M elements) 14.6 and
+    // 15.6, with 3.5 M 25 -> 19.  Few columns leave most of the matrix tile empty: 280 000 rows, 64 -> 4 52 and 70, 50 -> 7 96 -> 66
+    return (N >= 16 || c < 8 * N) && (double)x_rows * taps * N >= 3e6;
+}
+
+static hch_status launch_field_split(const float *X, const float *W, float *out, const int32_t *field, void *ws, int64_t M, int64_t x_rows,
+                                     int taps, int c, int N, bool transposed, double bytes, hipStream_t s)
+{
+    hch::u32x4 *wp = (hch::u32x4 *)ws;
+    const size_t wbytes = field_weights_bytes(taps, c, N);
+    {
+        hch::LaunchTimer lt(transposed ? HCH_KERNEL_ID("split_weights_kernel<true>") : HCH_KERNEL_ID("split_weights_kernel<false>"), s,
+                            4.0 * taps * c * N + (double)wbytes, 0.0);
+        const dim3 grid(blocks_for((int64_t)(wbytes / 48)));
+        if (transposed) HCH_LAUNCH(hch::split_weights_kernel<true>, grid, dim3(256), 0, s, W, wp, taps, c, N);
+        else HCH_LAUNCH(hch::split_weights_kernel<false>, grid, dim3(256), 0, s, W, wp, taps, c, N);
+    }
+    HCH_LAUNCH_CHECK("split_weights_kernel");
+    const int nt = N <= 16 ? 1 : (N <= 32 ? 2 : 4);
+    const unsigned tiles = (unsigned)((M + hch::FIELD_ROWS - 1) / hch::FIELD_ROWS);
+    const dim3 grid((tiles + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD, (unsigned)((N + 16 * nt - 1) / (16 * nt)));
+    const int vec_out = N % 4 == 0 && aligned16(out);
+    const size_t lds = (size_t)hch::FieldLds::bytes(taps);
+    {
+        static int ids[3][2];
+        static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
+        (void)ids_ready;
+        int &id = ids[nt / 2][transposed];
+        if (id < 0) {
+            char nm[96];
+            snprintf(nm, sizeof nm, "field_split_kernel<%d, %s>", nt, transposed ? "true" : "false");
+            id = hch::Profiler::get().id_for(nm);
+        }
+        hch::LaunchTimer lt(id, s, bytes, 2.0 * taps * c * (double)N * M);
+#define HCH_FIELD_CASE(NT_, T_)                                                                                          \
+        HCH_LAUNCH((hch::field_split_kernel<NT_, T_>), grid, dim3(64 * hch::FIELD_WAVES), lds, s, X, W, (const hch::u32x4 *)wp, out, \
+                   field, (int)M, N, c, taps, x_rows, tiles, vec_out)
+        if (transposed) { if (nt == 1) HCH_FIELD_CASE(1, true); else if (nt == 2) HCH_FIELD_CASE(2, true); else HCH_FIELD_CASE(4, true); }
+        else { if (nt == 1) HCH_FIELD_CASE(1, false); else if (nt == 2) HCH_FIELD_CASE(2, false); else HCH_FIELD_CASE(4, false); }
+#undef HCH_FIELD_CASE
+    }
+    HCH_LAUNCH_CHECK("field_split_kernel");
+    return HCH_OK;
+}
+
 // workspace of the three products of a general convolution: [ transposed weights (bwd_data on one
 // level) or the column-matrix gradient (bwd_data between two levels) | split partial sums ];
 // least: as in ws_layout
@@ -2399,13 +2476,16 @@ static WsLayout sconv_layout(const Level &Li, const Level &Lo, int taps, int c_i
     if (kind == HCH_WS_FWD) {
         const GemmPlan p = plan_rows(Lo.n_total, c_out, taps * c_in, true, k_gran(dtype));
         if (p.splits > 1) w.part_bytes = round_up((size_t)p.splits * Lo.n_total * c_out * 4, 256);
+        if (dtype == HCH_F32 && !least) w.part_bytes = std::max(w.part_bytes, field_weights_bytes(taps, c_in, c_out));
     } else if (kind == HCH_WS_BWD_DATA && &Li != &Lo) {
         // between two levels: the gradient of the column matrix, [N_out][taps*c_in] floats
         w.first_bytes = round_up((size_t)Lo.n_total * taps * c_in * 4, 256);
+        if (dtype == HCH_F32 && !least) w.first_bytes = std::max(w.first_bytes, field_weights_bytes(taps, c_out, c_in));
     } else if (kind == HCH_WS_BWD_DATA) {
         const GemmPlan p = plan_rows(Li.n_total, c_in, taps * c_out, true, k_gran(dtype));
         w.first_bytes = round_up((size_t)taps * c_in * c_out * elem_size(dtype), 256);
         if (p.splits > 1) w.part_bytes = round_up((size_t)p.splits * Li.n_total * c_in * 4, 256);
+        if (dtype == HCH_F32 && !least) w.part_bytes = std::max(w.part_bytes, field_weights_bytes(taps, c_out, c_in));
     } else {
         int splits = plan_wgrad(Lo.n_total, c_in, c_out, taps, k_gran(dtype)).splits;
         if (dtype == HCH_F32 && !least) {
@@ -2464,6 +2544,9 @@ extern "C" hch_status hch_sconv_fwd(const hch_levels *levels, int32_t level_in, 
     const GemmPlan p = plan_rows(n, c_out, K, true, k_gran(dtype));
     float *part = (float *)workspace;
     const double bytes = (double)n * (4.0 * taps + 4.0 * c_out * p.splits) + es * (double)Li->n_total * c_in + es * K * c_out;
+    if (dtype == HCH_F32 && field_split_ok(FIELD_FWD, n, Li->n_total, taps, c_in, c_out, ws_bytes))
+        return launch_field_split((const float *)X, (const float *)W, Y, field, workspace, n, Li->n_total, taps, c_in, c_out, false,
+                                  (double)n * (4.0 * taps + 4.0 * c_out) + 4.0 * ((double)Li->n_total * c_in + (double)K * c_out), s);
     st = launch_gemm<hch::A_GATHER, false>(dtype, p, X, W, p.splits > 1 ? part : Y, field, (int)n, c_out, K, c_in,
                                            c_out, c_out, n * c_out, bytes, s, 0, taps);
     if (st != HCH_OK) return st;
@@ -2513,7 +2596,10 @@ extern "C" hch_status hch_sconv_bwd_data(const hch_levels *levels, int32_t level
     const int taps = F * F * F, Kd = taps * c_out;
     const int64_t n = Li->n_total, wn = (int64_t)taps * c_in * c_out;
     const double es = elem_size(dtype);
-    const WsLayout w = sconv_layout(*Li, *Lo, taps, c_in, c_out, dtype, HCH_WS_BWD_DATA);
+    const WsLayout w = sconv_layout(*Li, *Lo, taps, c_in, c_out, dtype, HCH_WS_BWD_DATA, true);
+    if (dtype == HCH_F32 && field_split_ok(Li == Lo ? FIELD_BWD : FIELD_BWD_STRIDED, n, Lo->n_total, taps, c_out, c_in, ws_bytes))
+        return launch_field_split((const float *)dY, (const float *)W, dX, field_t, workspace, n, Lo->n_total, taps, c_out, c_in, true,
+                                  (double)n * (4.0 * taps + 4.0 * c_in) + 4.0 * ((double)Lo->n_total * c_out + (double)wn), s);
     if (Li != Lo) {
         // Between two levels only about one field row in stride^3 of an input voxel has an owner,
         // so the gathered product below would multiply mostly zeros.  Here the paper's own order

@@ -429,3 +429,47 @@ def test_operands_of_two_gigabytes(oracle, batch, level, wide, narrow):
     dX = torch.full((n, narrow), float("nan"), device="cuda")
     hch.hch_conv_bwd_data(lv, level, hch.HCH_F32, big, W, dX, narrow, wide, _ws(lv, level, narrow, wide), a)
     check(dX, sum(rows(big, k) @ W[26 - k].double().T for k in range(27)))
+
+
+@pytest.mark.parametrize("F,stride,pad", [(2, 2, 0), (3, 2, 1), (3, 4, 1), (3, 1, 1)])
+@pytest.mark.parametrize("ci,co", [(18, 33), (20, 130), (33, 50), (64, 64)])
+def test_products_over_general_index_rows(batch, F, stride, pad, ci, co):
+    """field_split_kernel, forward and data gradient: 126 665 rows (the last workgroup has 201), index rows in any order,
+    rows without a single tap among them, channel counts with remainders; with the queried workspace and, on the ways
+    taken without room for the cut weights, with less.  An infinity reaches the rows that hold it and no others."""
+    lv = batch[0]
+    lo = {1: 0, 2: 1, 4: 2}[stride]
+    n_in, n_out, F3 = lv.n(0), lv.n(lo), F ** 3
+    field, field_t = torch.empty((n_out, F3), dtype=torch.int32, device="cuda"), torch.empty((n_in, F3), dtype=torch.int32, device="cuda")
+    hch.hch_field_build(lv, 0, F, stride, pad, field, field_t)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(F * 100 + ci)
+    X, G = torch.randn((n_in, ci), device="cuda", generator=g), torch.randn((n_out, co), device="cuda", generator=g)
+    W = torch.randn((F3, ci, co), device="cuda", generator=g)
+    zero = torch.zeros((), dtype=torch.float64, device="cuda")
+    for kind, call, A, idx, w, n in ((hch.HCH_WS_FWD, hch.hch_sconv_fwd, X, field, W, n_out),
+                                     (hch.HCH_WS_BWD_DATA, hch.hch_sconv_bwd_data, G, field_t, W.transpose(1, 2), n_in)):
+        idx = idx[torch.randperm(n, device="cuda", generator=g)].contiguous()
+        idx[n // 3: n // 3 + 40] = -1
+        want = sum(torch.where(idx[:, k:k + 1] >= 0, A.double()[idx[:, k].clamp(min=0).long()], zero) @ w[k].double() for k in range(F3))
+        out = torch.full((n, w.shape[2]), float("nan"), device="cuda")
+        ws = _workspace(hch.hch_sconv_workspace_bytes(lv, 0, F, stride, ci, co, hch.HCH_F32, kind))
+        call(lv, 0, F, stride, hch.HCH_F32, A, W, out, idx, ci, co, ws)
+        assert float((out.double() - want).norm() / want.norm()) < BOUND
+        assert float((out.double() - want).abs().max() / want.pow(2).mean().sqrt()) < 30 * BOUND
+        again = torch.full_like(out, float("nan"))
+        call(lv, 0, F, stride, hch.HCH_F32, A, W, again, idx, ci, co, ws)
+        assert torch.equal(out, again)
+        v = idx[idx >= 0][20000].item()
+        B = A.clone()
+        B[v, 3] = float("inf")
+        call(lv, 0, F, stride, hch.HCH_F32, B, W, again, idx, ci, co, ws)
+        holds = (idx == v).any(1)
+        # rows multiplied together with one of those are summed with the fp32 instruction: other roundings, the same bound
+        assert bool((~torch.isfinite(again[holds])).all()) and bool(torch.isfinite(again[~holds]).all())
+        assert float((again.double() - want)[~holds].norm() / want.norm()) < BOUND
+    if stride == 1:                                     # as little as the forward product has ever asked for
+        out = torch.full((n_out, co), float("nan"), device="cuda")
+        hch.hch_sconv_fwd(lv, 0, F, stride, hch.HCH_F32, X, W, out, field, ci, co, _workspace(256)[:256])
+        want = sum(torch.where(field[:, k:k + 1] >= 0, X.double()[field[:, k].clamp(min=0).long()], zero) @ W[k].double() for k in range(F3))
+        assert float((out.double() - want).norm() / want.norm()) < 4 * BOUND          # the fp32 instruction: a rounding per 4 terms
