@@ -125,8 +125,9 @@ hch_status hch_build_levels(const int32_t *coords_xyz, const int64_t *model_offs
 
 /*
  * The same object with the tables CONSTRUCTED ON THE DEVICE (Section 5.2 and the conclusion name
- * GPU construction as future work).  Host work: argument checks and the occupancy of the coarser
- * levels; then one set of launches builds every (level, model) pair: buckets of positions sharing
+ * GPU construction as future work).  The checks of the positions and the occupancy of the coarser
+ * levels run there too (a bit per position; where those are more than 512 MB, on the host); then
+ * one set of launches builds every (level, model) pair: buckets of positions sharing
  * p mod r are placed largest first, all buckets of one size in parallel, each claiming its slots
  * with compare-and-swap and backing off to the next candidate offset on a conflict; pairs that
  * fail are repeated with the next offset-table side.  Sizes (m, first r, growth of r), table

@@ -8,6 +8,7 @@
 #include <atomic>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <thread>
@@ -20,6 +21,7 @@
 #include "split_conv.hip.hpp"
 #include "split_field.hip.hpp"
 #include "psh_device.hip.hpp"
+#include "occupancy.hip.hpp"
 #include "profile.hpp"
 #include "psh_build.hpp"
 
@@ -69,6 +71,10 @@ struct Level {
     std::vector<int32_t> H, V;                 // host copies of the super tables
     std::vector<uint16_t> T;
     std::vector<uint8_t> Phi;
+    // ... and where the host copies are in hch_levels' own blocks instead (tables built on the device)
+    const int32_t *hH = nullptr, *hV = nullptr, *hcoords = nullptr;
+    const uint16_t *hT = nullptr;
+    const uint8_t *hPhi = nullptr;
     // device
     bool in_block = false;                     // tables and lists lie in blocks of the whole level set
     int32_t *dH = nullptr, *dV = nullptr, *dcoords = nullptr, *dnbr = nullptr, *dchild = nullptr;
@@ -134,7 +140,8 @@ struct hch_levels {
     uint8_t *d_sort_key = nullptr;
     int32_t *d_tile_hist = nullptr, *d_key_total = nullptr, *d_order = nullptr;
     uint32_t *d_fine = nullptr;                // everything of the fine order, in one allocation
-    std::vector<void *> blocks;                // device construction: one allocation for what is known before it, one after
+    std::vector<void *> blocks;                // allocations: the orders and prefixes; device construction: what is known before it, and after
+    std::unique_ptr<char[]> host_block, host_phi;   // its host copies: positions, H*, T*, V*; offset tables
 };
 
 extern "C" const char *hch_last_error(void) { return g_err.c_str(); }
@@ -143,10 +150,6 @@ extern "C" void hch_free_levels(hch_levels *levels)
 {
     if (!levels) return;
     for (Level &L : levels->lv) free_level(L);
-    if (levels->d_nbr_prefix) (void)hipFree(levels->d_nbr_prefix);
-    if (levels->d_child_prefix) (void)hipFree(levels->d_child_prefix);
-    void *sort_ptrs[] = {levels->d_sort_key, levels->d_tile_hist, levels->d_key_total, levels->d_order, levels->d_fine};
-    for (void *p : sort_ptrs) if (p) (void)hipFree(p);
     for (void *p : levels->blocks) (void)hipFree(p);
     delete levels;
 }
@@ -345,6 +348,16 @@ struct DeviceBlocks {            // device allocations that live until the end o
         return HCH_OK;
     }
 };
+// Occupancy of the levels on the device (occupancy.hip.hpp), between the checks and the tables
+struct Occupancy {
+    DeviceBlocks mem;
+    hch::OccupancySet set{};
+    const int32_t *host_coords = nullptr;      // the caller's
+    int32_t *d_coords = nullptr, *d_sums = nullptr, *d_first = nullptr;
+    unsigned long long *d_bits = nullptr;
+    std::vector<int32_t> first;
+    bool ready = false;
+};
 struct PairWork {
     int l, v;
     int32_t n, m, r, attempts;
@@ -353,10 +366,88 @@ struct PairWork {
 };
 }  // namespace
 
+// Checks the positions and fills ubar, ratio, b, N, n_total and max_n of every level on the device; the
+// coarse levels' voxels stay a bit set until device_construct lists them.  On the host the checks and the coarse
+// levels were 3.4 ms of a 256^3 batch of 8.  Not `ready` where a bit per position is too much memory: the host does it then.
+constexpr size_t OCCUPANCY_BYTES = (size_t)512 << 20;
+static hch_status device_occupancy(hch_levels *hl, const int32_t *coords, const int64_t *offsets, int32_t batch,
+                                   const std::vector<int32_t> &side, const std::vector<int32_t> &ratio_of, int n_levels,
+                                   hipStream_t s, Occupancy &o)
+{
+    if (n_levels > hch::MAX_LEVELS) return HCH_OK;
+    hch::OccupancySet &S = o.set;
+    S.n_levels = n_levels; S.batch = batch;
+    int64_t words = 0, blocks = 0, divide = 1;
+    for (int l = 0; l < n_levels; ++l) {
+        const int64_t u = side[l], per_model = ((u * u * u + 63) / 64 + hch::OCC_WORDS - 1) / hch::OCC_WORDS;
+        divide *= ratio_of[l];
+        if ((uint64_t)per_model * hch::OCC_WORDS * 8 > OCCUPANCY_BYTES / (size_t)batch) return HCH_OK;
+        S.side[l] = side[l]; S.ratio[l] = (int32_t)std::min<int64_t>(divide, 65536);       // past the side all divide to 0
+        divide = S.ratio[l];
+        S.word_off[l] = words; S.blocks[l] = (int32_t)per_model;
+        words += per_model * batch * hch::OCC_WORDS;
+        S.block_off[l] = (int32_t)blocks;
+        if (l > 0) blocks += per_model * batch;
+        S.block_off[l + 1] = (int32_t)blocks;
+    }
+    if ((size_t)words * 8 > OCCUPANCY_BYTES) return HCH_OK;
+    const int64_t n = offsets[batch], pairs = (int64_t)(n_levels - 1) * batch;
+    int32_t *d_flags = nullptr;                // [0] flags, then the number of voxels of every (level >= 1, model)
+    int64_t *d_offsets = nullptr;
+    auto lay = [&](Pieces &P, size_t *zeroed) {
+        P.take(o.d_bits, (size_t)words * 8);
+        P.take(d_flags, (size_t)(1 + pairs) * 4);
+        *zeroed = P.used;
+        P.take(d_offsets, ((size_t)batch + 1) * 8);
+        P.take(o.d_coords, (size_t)n * 12);
+        P.take(o.d_sums, (size_t)blocks * 4);
+        P.take(o.d_first, (size_t)pairs * 4);
+    };
+    Pieces size, place;
+    size_t zeroed = 0;
+    lay(size, &zeroed);
+    if (o.mem.get((void **)&place.base, size.used) != HCH_OK) return HCH_OK;
+    lay(place, &zeroed);
+    HCH_HIP(hipMemsetAsync(place.base, 0, zeroed, s));
+    HCH_HIP(hipMemcpyAsync(d_offsets, offsets, ((size_t)batch + 1) * 8, hipMemcpyHostToDevice, s));
+    HCH_HIP(hipMemcpyAsync(o.d_coords, coords, (size_t)n * 12, hipMemcpyHostToDevice, s));
+    int64_t most = 0;
+    for (int v = 0; v < batch; ++v) most = std::max(most, offsets[v + 1] - offsets[v]);
+    HCH_LAUNCH(hch::occupancy_mark_kernel, dim3(blocks_for(most), (unsigned)batch), dim3(256), 0, s, S, (const int32_t *)o.d_coords,
+               (const int64_t *)d_offsets, o.d_bits, d_flags);
+    HCH_LAUNCH_CHECK("occupancy_mark_kernel");
+    if (blocks > 0) {
+        HCH_LAUNCH(hch::occupancy_count_kernel, dim3((unsigned)blocks), dim3(hch::OCC_WORDS), 0, s, S, (const unsigned long long *)o.d_bits, o.d_sums);
+        HCH_LAUNCH(hch::occupancy_scan_kernel, dim3((unsigned)pairs), dim3(256), 0, s, S, o.d_sums, d_flags + 1);
+        HCH_LAUNCH_CHECK("occupancy_scan_kernel");
+    }
+    std::vector<int32_t> got((size_t)(1 + pairs));
+    HCH_HIP(hipMemcpyAsync(got.data(), d_flags, got.size() * 4, hipMemcpyDeviceToHost, s));
+    HCH_HIP(hipStreamSynchronize(s));
+    if (got[0] & 1) return fail(HCH_EINVAL, "hch_build_levels: coordinate outside [0, resolution)");
+    if (got[0] & 2) return fail(HCH_EINVAL, "hch_build_levels: duplicate voxel inside a model");
+    o.first.resize((size_t)pairs);
+    for (int l = 0; l < n_levels; ++l) {
+        Level &L = hl->lv[l];
+        L.ubar = side[l]; L.ratio = ratio_of[l]; L.b = batch;
+        L.N.assign((size_t)batch + 1, 0);
+        for (int v = 0; v < batch; ++v) {
+            const int64_t nv = l == 0 ? offsets[v + 1] - offsets[v] : got[(size_t)(1 + (int64_t)(l - 1) * batch + v)];
+            if (l > 0) o.first[(size_t)((int64_t)(l - 1) * batch + v)] = (int32_t)L.N[v];
+            L.N[v + 1] = L.N[v] + nv;
+            L.max_n = std::max<int32_t>(L.max_n, (int32_t)nv);
+        }
+        L.n_total = L.N[batch];
+    }
+    o.host_coords = coords;
+    o.ready = true;
+    return HCH_OK;
+}
+
 // Fills, for every level: mbar, rbar, attempts, M, R, m_total, r_total, the device tables dH, dT,
-// dV, dPhi, dslot3, dphi4, dcoords, dmeta and the host copies H, T, Phi, V.  Levels must have
-// ubar, b, coords, N, n_total.
-static hch_status device_construct(hch_levels *hl, hipStream_t s)
+// dV, dPhi, dslot3, dphi4, dcoords, dmeta and the host copies.  Levels must have ubar, b, N, n_total and, unless
+// `occ` has them, coords.
+static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s)
 {
     const int n_levels = (int)hl->lv.size();
     const int batch = hl->lv[0].b;
@@ -379,15 +470,19 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         if (L.m_total >= ((int64_t)1 << 31)) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: super table exceeds 32-bit indexing");
     }
     // what the level set keeps and whose size is known now, in one allocation (one by one the
-    // allocations and frees of a build took 6 ms); H* and T* first, so that one fill empties them
+    // allocations and frees of a build took 6 ms); H* and T* first, so that one fill empties them, then the
+    // positions, so that one copy brings all of them to the host
+    size_t copied = 0;
     auto lay = [&](Pieces &P, size_t *tables) {
         for (Level &L : hl->lv) { P.take(L.dH, (size_t)L.m_total * 4); P.take(L.dT, (size_t)L.m_total * 6); }
         *tables = P.used;
+        for (int l = 1; l < n_levels; ++l) P.take(hl->lv[l].dcoords, (size_t)hl->lv[l].n_total * 12);
+        copied = P.used;
+        P.take(hl->lv[0].dcoords, (size_t)hl->lv[0].n_total * 12);
         for (Level &L : hl->lv) {
             const size_t n = (size_t)L.n_total;
             P.take(L.dV, (size_t)L.m_total * 4);
             P.take(L.dslot3, (size_t)L.m_total * 4 * hch::SLOT_WORDS);
-            P.take(L.dcoords, n * 12);
             P.take(L.dnbr, n * 27 * 4);
             if (&L != &hl->lv[0] && L.ratio == 2) P.take(L.dchild, n * 8 * 4);
             P.take(L.dmask27, std::max<size_t>(n, 64) * 4);
@@ -406,8 +501,42 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
         for (Level &L : hl->lv) L.in_block = true;
         lay(place, &tables);
         HCH_HIP(hipMemsetAsync(block, 0xFF, tables, s));      // H* = -1: free slot; T* = 0xFFFF: no position
-        for (Level &L : hl->lv) HCH_HIP(hipMemcpyAsync(L.dcoords, L.coords.data(), L.coords.size() * 4, hipMemcpyHostToDevice, s));
+        if (!occ.ready) {
+            for (Level &L : hl->lv) HCH_HIP(hipMemcpyAsync(L.dcoords, L.coords.data(), L.coords.size() * 4, hipMemcpyHostToDevice, s));
+        } else {
+            HCH_HIP(hipMemcpyAsync(hl->lv[0].dcoords, occ.d_coords, (size_t)hl->lv[0].n_total * 12, hipMemcpyDeviceToDevice, s));
+            hch::OccupancyOut out{};
+            for (int l = 1; l < n_levels; ++l) out.coords[l] = hl->lv[l].dcoords;
+            if (n_levels > 1) {
+                HCH_HIP(hipMemcpyAsync(occ.d_first, occ.first.data(), occ.first.size() * 4, hipMemcpyHostToDevice, s));
+                HCH_LAUNCH(hch::occupancy_list_kernel, dim3((unsigned)occ.set.block_off[n_levels]), dim3(hch::OCC_WORDS), 0, s, occ.set,
+                           (const unsigned long long *)occ.d_bits, (const int32_t *)occ.d_sums, (const int32_t *)occ.d_first, out);
+                HCH_LAUNCH_CHECK("occupancy_list_kernel");
+            }
+        }
     }
+    // The host copies: a mirror of the first `copied` bytes, the finest positions, V*.  Fresh memory costs more to
+    // touch than to fill, so that is done while the device builds.
+    const char *const mirrored = (const char *)hl->lv[0].dH;
+    auto host_copies = [&]() {
+        const size_t finest = (size_t)hl->lv[0].n_total * 12;
+        size_t slots = 0;
+        for (const Level &L : hl->lv) slots += (size_t)L.m_total;
+        hl->host_block.reset(new char[copied + finest + slots * 4]);
+        char *h = hl->host_block.get();
+        for (size_t at = 0; at < copied; at += 4096) h[at] = 0;
+        memcpy(h + copied, occ.ready ? occ.host_coords : hl->lv[0].coords.data(), finest);
+        int32_t *V = (int32_t *)(h + copied + finest);
+        for (Level &L : hl->lv) {
+            L.hH = (const int32_t *)(h + ((const char *)L.dH - mirrored));
+            L.hT = (const uint16_t *)(h + ((const char *)L.dT - mirrored));
+            L.hcoords = (const int32_t *)(&L == &hl->lv[0] ? h + copied : h + ((const char *)L.dcoords - mirrored));
+            L.hV = V;
+            for (int v = 0; v < batch; ++v) std::fill(V + L.M[v], V + L.M[v + 1], v);
+            V += L.m_total;
+            std::vector<int32_t>().swap(L.coords);
+        }
+    };
     const int n_pairs = (int)work.size();
     int32_t *d_fail = nullptr;
     if ((st = tmp.get((void **)&d_fail, (size_t)n_pairs * 4)) != HCH_OK) return st;
@@ -494,6 +623,7 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
                            d_nfree, d_free, d_rank, d_phi, d_fail);
         HCH_LAUNCH(hch::psh_clear_kernel, gs, dim3(256), 0, s, d_desc, d_fail);
         HCH_LAUNCH_CHECK("psh construction");
+        if (round == 0) host_copies();
         HCH_HIP(hipMemcpyAsync(h_fail.data(), d_fail, (size_t)n_pairs * 4, hipMemcpyDeviceToHost, s));
         HCH_HIP(hipStreamSynchronize(s));
 
@@ -536,10 +666,13 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
     }
     int32_t *d_meta = nullptr;
     hch::PackDesc *d_pd = nullptr;
+    size_t phi_bytes = 0;
     if ((st = tmp.get((void **)&d_pd, pd.size() * sizeof(hch::PackDesc))) != HCH_OK) return st;
     {
         auto lay_offsets = [&](Pieces &P) {
-            for (Level &L : hl->lv) { P.take(L.dPhi, (size_t)L.r_total * 3); P.take(L.dphi4, (size_t)L.r_total * 4); }
+            for (Level &L : hl->lv) P.take(L.dPhi, (size_t)L.r_total * 3);
+            phi_bytes = P.used;
+            for (Level &L : hl->lv) P.take(L.dphi4, (size_t)L.r_total * 4);
             P.take(d_meta, meta.size() * 4);
         };
         Pieces size, place;
@@ -565,15 +698,11 @@ static hch_status device_construct(hch_levels *hl, hipStream_t s)
                            d_pd + (size_t)l * batch, L.dH, L.dT, L.dslot3, L.dV, L.dphi4, L.dPhi);
         HCH_LAUNCH_CHECK("psh_pack_kernel");
     }
-    for (Level &L : hl->lv) {
-        // host copies for hch_level_info; the model index of every slot follows from M*
-        L.H.resize((size_t)L.m_total); L.V.resize((size_t)L.m_total);
-        L.T.resize((size_t)L.m_total * 3); L.Phi.resize((size_t)L.r_total * 3);
-        for (int v = 0; v < batch; ++v) std::fill(L.V.begin() + L.M[v], L.V.begin() + L.M[v + 1], v);
-        HCH_HIP(hipMemcpyAsync(L.H.data(), L.dH, L.H.size() * 4, hipMemcpyDeviceToHost, s));
-        HCH_HIP(hipMemcpyAsync(L.T.data(), L.dT, L.T.size() * 2, hipMemcpyDeviceToHost, s));
-        if (L.r_total) HCH_HIP(hipMemcpyAsync(L.Phi.data(), L.dPhi, L.Phi.size(), hipMemcpyDeviceToHost, s));
-    }
+    // host copies for hch_level_info (a thread of its own for the large one was slower: 6.0 instead of 5.3 ms the whole call)
+    hl->host_phi.reset(new char[phi_bytes]);
+    HCH_HIP(hipMemcpyAsync(hl->host_block.get(), mirrored, copied, hipMemcpyDeviceToHost, s));
+    HCH_HIP(hipMemcpyAsync(hl->host_phi.get(), hl->lv[0].dPhi, phi_bytes, hipMemcpyDeviceToHost, s));
+    for (Level &L : hl->lv) L.hPhi = (const uint8_t *)(hl->host_phi.get() + (L.dPhi - hl->lv[0].dPhi));
     HCH_HIP(hipStreamSynchronize(s));         // `meta`, `pd` and the coordinates' copies are done
     return HCH_OK;
 }
@@ -639,11 +768,27 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
     const int64_t n_total = model_offsets[batch];
     if (n_total >= ((int64_t)1 << 31) / 27)
         return fail(HCH_EUNSUPPORTED, "hch_build_levels: more than 2^31/27 voxels in a batch");
-    for (int64_t i = 0; i < 3 * n_total; ++i)
+    hipStream_t s = (hipStream_t)stream;
+    hch_levels *hl = nullptr;
+    Occupancy occ;
+    hch_status st = HCH_OK;
+    if (device_tables) {
+        hl = new (std::nothrow) hch_levels;
+        if (!hl) return fail(HCH_ENOMEM, "hch_build_levels: out of host memory");
+        try {
+            hl->lv.resize((size_t)n_levels);
+            st = device_occupancy(hl, coords_xyz, model_offsets, batch, side, ratio_of, n_levels, s, occ);
+        } catch (const std::bad_alloc &) {
+            st = fail(HCH_ENOMEM, "hch_build_levels: out of host memory");
+        }
+        if (st != HCH_OK || !occ.ready) { hch_free_levels(hl); hl = nullptr; }
+        if (st != HCH_OK) return st;
+    }
+    for (int64_t i = 0; i < 3 * n_total && !occ.ready; ++i)
         if (coords_xyz[i] < 0 || coords_xyz[i] >= resolution)
             return fail(HCH_EINVAL, "hch_build_levels: coordinate outside [0, resolution)");
     // duplicates inside a model (models in parallel on host threads)
-    {
+    if (!occ.ready) {
         std::atomic<int> next_model(0), dup(0);
         auto check = [&]() {
             std::vector<int64_t> lin;
@@ -665,15 +810,13 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
         if (dup) return fail(HCH_EINVAL, "hch_build_levels: duplicate voxel inside a model");
     }
 
-    hch_levels *hl = new (std::nothrow) hch_levels;
+    if (!hl) hl = new (std::nothrow) hch_levels;
     if (!hl) return fail(HCH_ENOMEM, "hch_build_levels: out of host memory");
-    hipStream_t s = (hipStream_t)stream;
-    hch_status st = HCH_OK;
 
     try {
         hl->lv.resize((size_t)n_levels);
         // ---- occupancy of every level (host) ----
-        for (int l = 0; l < n_levels; ++l) {
+        for (int l = 0; l < n_levels && !occ.ready; ++l) {
             Level &L = hl->lv[l];
             L.ubar = side[l];
             L.ratio = ratio_of[l];
@@ -709,7 +852,7 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
 
         if (device_tables) {
             if (n_levels > hch::MAX_LEVELS) st = fail(HCH_EUNSUPPORTED, "hch_build_levels: too many levels");
-            if (st == HCH_OK) st = device_construct(hl, s);
+            if (st == HCH_OK) st = device_construct(hl, occ, s);
         }
         // ---- PSH construction of every (level, model), spread over host threads ----
         std::vector<std::vector<hch::ModelTables>> tabs((size_t)n_levels);
@@ -813,10 +956,35 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
             int64_t nbr_tiles = 0;
             for (int l = 0; l < n_levels; ++l)
                 for (int v = 0; v < batch; ++v) nbr_tiles += (hl->lv[l].N[v + 1] - hl->lv[l].N[v] + 255) / 256;
-            if (hipMalloc((void **)&hl->d_sort_key, std::max<size_t>(n_all, 64)) != hipSuccess) { hl->d_sort_key = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(pattern keys) failed"); }
-            if (st == HCH_OK && hipMalloc((void **)&hl->d_order, std::max<size_t>(n_all, 64) * 4) != hipSuccess) { hl->d_order = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(pattern order) failed"); }
-            if (st == HCH_OK && hipMalloc((void **)&hl->d_tile_hist, (size_t)std::max<int64_t>(nbr_tiles, 1) * hch::PATTERN_BINS * 4) != hipSuccess) { hl->d_tile_hist = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(tile histograms) failed"); }
-            if (st == HCH_OK && hipMalloc((void **)&hl->d_key_total, (size_t)hch::MAX_LEVELS * hch::PATTERN_BINS * 4) != hipSuccess) { hl->d_key_total = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(key totals) failed"); }
+            // the fine order: neighbour sets by position in both orders, the order, its tiles' taps,
+            // the histograms and their totals
+            const size_t na = round_up(std::max<size_t>(n_all, 64), 64);
+            size_t fine_tiles = 0, hist = 0;
+            for (int l = 0; l < n_levels; ++l) {
+                const int64_t n = hl->lv[l].n_total;
+                hl->set.n_total[l] = (int32_t)n;
+                hl->set.fine_off[l] = (int32_t)hist;
+                hl->set.fine_tiles[l] = n >= FINE_MIN_VOXELS ? (int32_t)((n + hch::FINE_TILE - 1) / hch::FINE_TILE) : 0;
+                hist += (size_t)hl->set.fine_tiles[l] * hch::FINE_BINS;
+                if (hl->set.fine_tiles[l]) fine_tiles += (size_t)((n + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
+            }
+            const size_t totals = hist ? (size_t)hch::MAX_LEVELS * hch::FINE_BINS : 0;
+            auto lay = [&](Pieces &P) {            // one allocation: seven took 0.5 ms of a build
+                P.take(hl->d_sort_key, std::max<size_t>(n_all, 64));
+                P.take(hl->d_order, std::max<size_t>(n_all, 64) * 4);
+                P.take(hl->d_tile_hist, (size_t)std::max<int64_t>(nbr_tiles, 1) * hch::PATTERN_BINS * 4);
+                P.take(hl->d_key_total, (size_t)hch::MAX_LEVELS * hch::PATTERN_BINS * 4);
+                P.take(hl->d_fine, (na + (hist ? 2 * na : 0) + fine_tiles + hist + totals) * 4);
+                P.take(hl->d_nbr_prefix, ((size_t)n_levels * batch + 1) * 4);
+                P.take(hl->d_child_prefix, ((size_t)n_levels * batch + 1) * 4);
+            };
+            Pieces size, place;
+            lay(size);
+            if (hipMalloc((void **)&place.base, size.used) != hipSuccess) { place.base = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(pattern and fine order) failed"); }
+            else {
+                hl->blocks.push_back(place.base);
+                lay(place);
+            }
             for (int l = 0; l < n_levels && st == HCH_OK; ++l) {
                 Level &L = hl->lv[l];
                 const size_t tiles = (size_t)((L.n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
@@ -825,36 +993,20 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
                 if (hipMalloc((void **)&L.dmask27, std::max<size_t>((size_t)L.n_total, 64) * 4) != hipSuccess) { L.dmask27 = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(mask27) failed"); break; }
                 if (hipMalloc((void **)&L.dtilemask, std::max<size_t>(tiles, 64) * 4) != hipSuccess) { L.dtilemask = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(tile masks) failed"); break; }
             }
-            // the fine order: neighbour sets by position in both orders, the order, its tiles' taps,
-            // the histograms and their totals
             if (st == HCH_OK) {
-                const size_t na = round_up(std::max<size_t>(n_all, 64), 64);
-                size_t tiles = 0, hist = 0;
-                for (int l = 0; l < n_levels; ++l) {
-                    const int64_t n = hl->lv[l].n_total;
-                    hl->set.n_total[l] = (int32_t)n;
-                    hl->set.fine_off[l] = (int32_t)hist;
-                    hl->set.fine_tiles[l] = n >= FINE_MIN_VOXELS ? (int32_t)((n + hch::FINE_TILE - 1) / hch::FINE_TILE) : 0;
-                    hist += (size_t)hl->set.fine_tiles[l] * hch::FINE_BINS;
-                    if (hl->set.fine_tiles[l]) tiles += (size_t)((n + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
-                }
-                const size_t totals = hist ? (size_t)hch::MAX_LEVELS * hch::FINE_BINS : 0;
-                if (hipMalloc((void **)&hl->d_fine, (na + (hist ? 2 * na : 0) + tiles + hist + totals) * 4) != hipSuccess) { hl->d_fine = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(fine order) failed"); }
-                else {
-                    uint32_t *p = hl->d_fine;
-                    hl->set.sorted_mask = p; p += na;
-                    if (hist) {
-                        hl->set.fine_mask = p; p += na;
-                        hl->set.fine_order = (int32_t *)p; p += na;
-                        hl->set.fine_hist = (int32_t *)p; p += hist;
-                        hl->set.fine_total = (int32_t *)p; p += totals;
-                        for (int l = 0; l < n_levels; ++l)
-                            if (hl->set.fine_tiles[l]) {
-                                hl->lv[l].dforder = hl->set.fine_order + hl->sort_off[l];
-                                hl->lv[l].dftilemask = p;
-                                p += (hl->lv[l].n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE;
-                            }
-                    }
+                uint32_t *p = hl->d_fine;
+                hl->set.sorted_mask = p; p += na;
+                if (hist) {
+                    hl->set.fine_mask = p; p += na;
+                    hl->set.fine_order = (int32_t *)p; p += na;
+                    hl->set.fine_hist = (int32_t *)p; p += hist;
+                    hl->set.fine_total = (int32_t *)p; p += totals;
+                    for (int l = 0; l < n_levels; ++l)
+                        if (hl->set.fine_tiles[l]) {
+                            hl->lv[l].dforder = hl->set.fine_order + hl->sort_off[l];
+                            hl->lv[l].dftilemask = p;
+                            p += (hl->lv[l].n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE;
+                        }
                 }
             }
         }
@@ -885,8 +1037,9 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
                 hl->set.level_tiles[l] = hl->nbr_prefix[(size_t)(l + 1) * batch] - hl->nbr_prefix[(size_t)l * batch];
                 hl->set.hist_off[l] = hl->set.level_tile0[l] * hch::PATTERN_BINS;
             }
-            if ((st = upload((void **)&hl->d_nbr_prefix, hl->nbr_prefix.data(), hl->nbr_prefix.size() * 4, s)) == HCH_OK)
-                st = upload((void **)&hl->d_child_prefix, hl->child_prefix.data(), hl->child_prefix.size() * 4, s);
+            hipError_t e = hipMemcpyAsync(hl->d_nbr_prefix, hl->nbr_prefix.data(), hl->nbr_prefix.size() * 4, hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipMemcpyAsync(hl->d_child_prefix, hl->child_prefix.data(), hl->child_prefix.size() * 4, hipMemcpyHostToDevice, s);
+            if (e != hipSuccess) st = fail(HCH_EHIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
             if (st == HCH_OK) st = hch_build_neighbours(hl, -1, s);
         }
         if (st == HCH_OK && with_device) {
@@ -967,9 +1120,9 @@ extern "C" hch_status hch_level_info(const hch_levels *levels, int32_t level, hc
     out->nbr_valid = L.nbr_valid;
     out->mbar = L.mbar.data(); out->rbar = L.rbar.data(); out->attempts = L.attempts.data();
     out->M = L.M.data(); out->R = L.R.data(); out->N = L.N.data();
-    out->coords_host = L.coords.data();
-    out->H_host = L.H.data(); out->T_host = L.T.data(); out->Phi_host = L.Phi.data();
-    out->V_host = L.V.data();
+    out->coords_host = L.hcoords ? L.hcoords : L.coords.data();
+    out->H_host = L.hH ? L.hH : L.H.data(); out->T_host = L.hT ? L.hT : L.T.data(); out->Phi_host = L.hPhi ? L.hPhi : L.Phi.data();
+    out->V_host = L.hV ? L.hV : L.V.data();
     out->H = L.dH; out->T = L.dT; out->Phi = L.dPhi; out->V = L.dV; out->coords = L.dcoords;
     out->nbr27 = L.dnbr; out->child8 = L.dchild;
     out->row_order = L.dorder; out->tile_taps = L.dtilemask;

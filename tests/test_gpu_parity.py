@@ -940,3 +940,43 @@ def test_lean_and_pointer_loops_agree_bit_for_bit(case_small, algo, c_in, c_out,
             assert not torch.isnan(a).any(), what
             if what == "dW" or not one_form:
                 assert torch.equal(a, b), f"level {level} {what}: lean and pointer-based loops differ"
+
+
+@pytest.mark.parametrize("u,ratios", [(2, [2]), (64, [2, 2, 2]), (50, [3, 2]), (129, [2, 5, 4]), (512, [2]), (4096, [2, 2])])
+def test_device_occupancy(oracle, u, ratios):
+    """The coarse levels' voxels and the checks of positions: models of one voxel, of one word of 64 positions and of
+    several workgroups, in any order; sides that are no multiple of 64 or of the ratio; a grid whose bits are too many (4096^3: host)."""
+    rng = np.random.default_rng(u)
+    side = min(u, 40)
+    sizes = [1, min(u ** 3, 64), 1, min(side ** 3, 7000), 2]
+    parts = []
+    for n in sizes:
+        q = rng.choice(side ** 3, n, replace=False)
+        p = np.stack([q // (side * side), q // side % side, q % side], 1)
+        parts.append(p + rng.integers(0, u - side + 1, 3))
+    parts[1] = np.stack(np.unravel_index(np.arange(sizes[1]), (u, u, u)), 1)[::-1]           # one word, backwards
+    parts[2] = np.full((1, 3), u - 1)
+    coords = np.concatenate(parts).astype(np.int32)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    want = oracle.build_hierarchy(coords, offs, u, len(ratios) + 1, ratios=ratios)
+    lv = hch.hch_build_levels_ratios(coords, offs, u, ratios, device_tables=True)
+    for l, L in enumerate(want):
+        info = lv.info(l)
+        assert np.array_equal(info.N, L.N) and np.array_equal(info.coords_host(), L.coords)
+        assert np.array_equal(info.device_coords(), L.coords) and np.array_equal(info.V_host(), info.device_V())
+        assert np.array_equal(info.H_host(), info.device_H()) and np.array_equal(info.Phi_host(), info.device_Phi())
+        assert np.array_equal(info.device_nbr27(), oracle.neighbours(L))
+    lv.free()
+    for a, b in ((offs[3], offs[4] - 1), (offs[3], offs[3] + 1)) if sizes[3] > 1 else ():   # the same position, far apart and side by side
+        bad = coords.copy()
+        bad[b] = bad[a]
+        with pytest.raises(hch.HchError) as e:
+            hch.hch_build_levels_ratios(bad, offs, u, ratios, device_tables=True)
+        assert e.value.status == 1 and "duplicate" in str(e.value)
+    for value in (-1, u):
+        bad = coords.copy()
+        bad[len(bad) // 2, 1] = value
+        with pytest.raises(hch.HchError) as e:
+            hch.hch_build_levels_ratios(bad, offs, u, ratios, device_tables=True)
+        assert e.value.status == 1 and "outside" in str(e.value)
+
