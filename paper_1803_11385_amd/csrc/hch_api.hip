@@ -20,6 +20,7 @@
 #include "split_wgrad.hip.hpp"
 #include "split_conv.hip.hpp"
 #include "split_field.hip.hpp"
+#include "conv_bf16.hip.hpp"
 #include "psh_device.hip.hpp"
 #include "occupancy.hip.hpp"
 #include "profile.hpp"
@@ -1862,6 +1863,56 @@ static hch_status launch_conv_split(const ConvSplitPlan &p, const Level &L, cons
     return p.splits > 1 ? launch_reduce(part, out, n * N, p.splits, s) : HCH_OK;
 }
 
+// Forward product and data gradient with bf16 operands over the row order (conv_bf16_kernel)
+static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n, int c, int N)
+{
+    const int64_t lim = (int64_t)1 << 31;
+    // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors; pairs of columns
+    if (!L.rows() || n >= (1 << 23) || c * 2 >= (1 << 23) || n * c * 2 >= lim || n * 108 >= lim || (int64_t)54 * c * N >= lim) return false;
+    if (c % 32 || N % 2 || N <= 16 || !aligned16(X) || !aligned16(W)) return false;
+    // 256 rows to a workgroup, two workgroups to a CU: with fewer rows than fill the chip gemm_bf16_kernel, which has smaller
+    // tiles and splits the reduction, is ahead: 32 -> 64 at 64 000 rows 22 us against 24, 64 -> 32 at 127 000 33 against 36.  A
+    // convolution with its gradients, 127 000 rows: 32 -> 64 101.5 and 101.4 (one product of the three), 64 -> 64 156 -> 140, 64 -> 128
+    // 249 -> 224; 280 000 rows: 32 -> 64 198 -> 173, 64 -> 64 291 -> 232, 64 -> 128 500 -> 391.
+    if (n < (c % 64 == 0 && N > 32 ? 98304 : 196608)) return false;
+    // The order scatters the rows that a tile reads over the whole of X; beyond the last-level cache (256 MB) that costs
+    // what the left-out taps give: 2.98 M rows of 64 channels (381 MB) 862 us against 882, 1.2 M (154 MB, thick shells as well) 1099 -> 1085 us
+    // with both gradients, 609 000 thin ones 556 -> 446.
+    return n * c * 2 <= (int64_t)256 << 20;
+}
+
+// transposed: W(t, k, n) = W[26 - t][n][k]
+static hch_status launch_conv_bf16(const Level &L, const uint16_t *X, const uint16_t *W, float *out, int64_t n, int c, int N, bool transposed,
+                                   double bytes, hipStream_t s)
+{
+    const int nt = N <= 32 ? 2 : 4, ks = c % 64 == 0 ? 64 : 32;
+    const unsigned m_tiles = (unsigned)((n + 63) / 64);
+    static int ids[2][2][2];                           // [columns][channels a step][transposed]
+    static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
+    (void)ids_ready;
+    int &id = ids[nt / 4][ks / 64][transposed];
+    if (id < 0) {
+        char nm[96];
+        snprintf(nm, sizeof nm, "conv_bf16_kernel<%d, %d, %s>", nt, ks, transposed ? "true" : "false");
+        id = hch::Profiler::get().id_for(nm);
+    }
+    {
+        hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
+        const dim3 grid(hch::skip_grid((m_tiles + 3) / 4, hch::skip_chunk(m_tiles, 4)), (unsigned)((N + 16 * nt - 1) / (16 * nt)));
+        const int vec_out = N % 4 == 0 && aligned16(out);
+#define HCH_CONV_BF16(NT_, KS_, T_)                                                                                             \
+        HCH_LAUNCH((hch::conv_bf16_kernel<NT_, KS_, T_>), grid, dim3(512), 0, s, X, W, out, (const int32_t *)L.dnbr, L.rows(), \
+                   (const uint32_t *)L.row_taps(), (int)n, N, c, m_tiles, vec_out)
+#define HCH_CONV_BF16_T(NT_, KS_) do { if (transposed) HCH_CONV_BF16(NT_, KS_, true); else HCH_CONV_BF16(NT_, KS_, false); } while (0)
+        if (nt == 2) { if (ks == 64) HCH_CONV_BF16_T(2, 64); else HCH_CONV_BF16_T(2, 32); }
+        else { if (ks == 64) HCH_CONV_BF16_T(4, 64); else HCH_CONV_BF16_T(4, 32); }
+#undef HCH_CONV_BF16_T
+#undef HCH_CONV_BF16
+    }
+    HCH_LAUNCH_CHECK("conv_bf16_kernel");
+    return HCH_OK;
+}
+
 // workspace layout, all offsets 256-byte aligned:
 //   columns algorithm : [ column matrix | split-K partial sums ]
 //   fused algorithm   : [ flipped+transposed weights (bwd_data only) | split-K partial sums ]
@@ -2007,6 +2058,9 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
                                          (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out * q.splits) + 4.0 * Kc * c_out, s);
         }
         const double bytes = (double)n * (108.0 + es * c_in + 4.0 * c_out * p.splits) + es * Kc * c_out;
+        if (skip && dtype == HCH_BF16 && conv_bf16_ok(*L, X, W, n, c_in, c_out))
+            return launch_conv_bf16(*L, (const uint16_t *)X, (const uint16_t *)W, Y, n, c_in, c_out, false,
+                                    (double)n * (108.0 + es * c_in + 4.0 * c_out) + es * Kc * c_out, s);
         if (fwd_transposed_weights(dtype, c_in, c_out) && aligned16(X) && aligned16(W) && aligned16(workspace)) {
             const int64_t wn = (int64_t)Kc * c_out, per_tap = (int64_t)c_in * c_out;
             {
@@ -2098,6 +2152,9 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
                 return launch_conv_split(q, *L, (const float *)dY, (const float *)W, dX, part, n, c_out, c_in, true,
                                          (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in * q.splits) + 4.0 * wn, s);
         }
+        if (skip && dtype == HCH_BF16 && conv_bf16_ok(*L, dY, W, n, c_out, c_in))
+            return launch_conv_bf16(*L, (const uint16_t *)dY, (const uint16_t *)W, dX, n, c_out, c_in, true,
+                                    (double)n * (108.0 + es * c_out + 4.0 * c_in) + es * wn, s);
         if (c_out % k_gran(dtype) == 0 && c_in % 4 == 0 && aligned16(dY) && aligned16(W)) {
             // the LDS-tiled kernel reads W[27][c_in][c_out] in place as the flipped, transposed
             // matrix: tap 26 - t of the weights for rows t*c_out .. (t+1)*c_out - 1

@@ -473,3 +473,38 @@ def test_products_over_general_index_rows(batch, F, stride, pad, ci, co):
         hch.hch_sconv_fwd(lv, 0, F, stride, hch.HCH_F32, X, W, out, field, ci, co, _workspace(256)[:256])
         want = sum(torch.where(field[:, k:k + 1] >= 0, X.double()[field[:, k].clamp(min=0).long()], zero) @ W[k].double() for k in range(F3))
         assert float((out.double() - want).norm() / want.norm()) < 4 * BOUND          # the fp32 instruction: a rounding per 4 terms
+
+
+@pytest.fixture(scope="module")
+def large():
+    coords, offs, _ = S.config_batch(3)
+    return hch.hch_build_levels_device(coords, offs, 128, 1)
+
+
+@pytest.mark.parametrize("ci,co", [(32, 64), (64, 64), (96, 34), (130, 32), (64, 20), (20, 64), (64, 130)])
+def test_bf16_products_over_the_row_order(batch, large, ci, co):
+    """conv_bf16_kernel: steps of 32 and of 64 channels, 32 and 64 columns and several tiles of them with remainders, a last
+    workgroup and a last wavefront that are not full; products are exact, so the bound is that of the fp32 sums.  Rows that
+    are not finite reach their neighbours' results and no others."""
+    lv = batch[0] if ci % 64 == 0 and co > 32 else large
+    n = lv.n(0)
+    assert n >= (98304 if lv is batch[0] else 196608) and n % 32
+    nbr = torch.from_numpy(lv.info(0).device_nbr27().astype(np.int64)).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ci * 1000 + co)
+    X, W, G = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((n, ci), (27, ci, co), (n, co)))
+    zero = torch.zeros((), dtype=torch.float64, device="cuda")
+    for name, kind, A, w, m in (("hch_conv_fwd", hch.HCH_WS_FWD, X, W, co), ("hch_conv_bwd_data", hch.HCH_WS_BWD_DATA, G, W.flip(0).transpose(1, 2), ci)):
+        want = sum(torch.where(nbr[:, k:k + 1] >= 0, A.double()[nbr[:, k].clamp(min=0)], zero) @ w[k].double() for k in range(27))
+        out, again = torch.full((n, m), float("nan"), device="cuda"), torch.full((n, m), float("nan"), device="cuda")
+        ws = _workspace(hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_BF16, kind, hch.HCH_ALGO_FUSED))
+        call = lambda B, Y: getattr(hch, name)(lv, 0, hch.HCH_BF16, B, W, Y, ci, co, ws, hch.HCH_ALGO_FUSED)
+        call(A, out)
+        assert float((out.double() - want).norm() / want.norm()) < BOUND
+        assert float((out.double() - want).abs().max() / want.pow(2).mean().sqrt()) < 30 * BOUND
+        B = A.clone()
+        v = n // 2
+        B[v, 1] = float("nan")
+        call(B, again)
+        near = (nbr == v).any(1)
+        assert bool(torch.isnan(again[near]).all()) and torch.equal(again[~near], out[~near])
