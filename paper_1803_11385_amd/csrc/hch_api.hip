@@ -2380,8 +2380,8 @@ extern "C" hch_status hch_pool_bwd(const hch_levels *levels, int32_t level_in, c
     if (Lc.ratio != 2) return fail(HCH_EUNSUPPORTED, "hch_pool_bwd: these two levels are not in ratio 2; use hch_field_build with hch_spool_* / hch_sconv_*");
     if (!Lc.dchild) return fail(HCH_EINVAL, "hch_pool_bwd: levels were built without device tables");
     const bool vec = c % 4 == 0 && aligned16(dY) && aligned16(dX) && aligned16(argmax);
-    const int64_t items = Lc.n_total * 8 * (vec ? c / 4 : c);
-    if (items > MAX_GRID_ITEMS) return fail(HCH_EUNSUPPORTED, "hch_pool_bwd: too large");
+    const int64_t items = Lc.n_total * (vec ? c / 4 : c);
+    if (Lc.n_total * 8 * (vec ? c / 4 : c) > MAX_GRID_ITEMS) return fail(HCH_EUNSUPPORTED, "hch_pool_bwd: too large");
     {
         const Level &Lf = levels->lv[level_in];
         const double bytes = (double)Lc.n_total * (32.0 + 8.0 * c) + (double)Lf.n_total * 4.0 * c;
@@ -2449,9 +2449,14 @@ extern "C" hch_status hch_unpool_bwd(const hch_levels *levels, int32_t level_out
     if (items > MAX_GRID_ITEMS) return fail(HCH_EUNSUPPORTED, "hch_unpool_bwd: too large");
     if (items == 0) return HCH_OK;
     {
-        hch::LaunchTimer lt(HCH_KERNEL_ID("unpool_bwd_kernel"), (hipStream_t)stream, 12.0 * items, 0.0);
-        HCH_LAUNCH(hch::unpool_bwd_kernel, dim3(blocks_for(items)), dim3(256), 0, (hipStream_t)stream,
-                           dY, argmax, dXc, Lc.n_total, c);
+        const bool vec = c % 4 == 0 && aligned16(argmax) && aligned16(dXc);
+        hch::LaunchTimer lt(vec ? HCH_KERNEL_ID("unpool_bwd_kernel<4>") : HCH_KERNEL_ID("unpool_bwd_kernel<1>"), (hipStream_t)stream, 12.0 * items, 0.0);
+        if (vec)
+            HCH_LAUNCH(hch::unpool_bwd_kernel<4>, dim3(blocks_for(items / 4)), dim3(256), 0, (hipStream_t)stream,
+                               dY, argmax, dXc, Lc.n_total, c);
+        else
+            HCH_LAUNCH(hch::unpool_bwd_kernel<1>, dim3(blocks_for(items)), dim3(256), 0, (hipStream_t)stream,
+                               dY, argmax, dXc, Lc.n_total, c);
     }
     HCH_LAUNCH_CHECK("unpool_bwd_kernel");
     return HCH_OK;
