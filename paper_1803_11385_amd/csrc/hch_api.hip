@@ -183,7 +183,7 @@ static hch_status transpose_neighbours(const Level &L, hipStream_t s)
     return HCH_OK;
 }
 
-// index lists of levels [l0, l1) in one launch each
+// index lists of levels [l0, l1) in one launch
 // (orders: and the row orders of the fused products)
 static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipStream_t s, bool orders = true)
 {
@@ -195,11 +195,16 @@ static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipSt
             double bytes = 0.0;   // per voxel: its position in, 27 indices out; the level's tables once
             for (int l = l0; l < l1; ++l)
                 bytes += (double)hl->lv[l].n_total * 120.0 + (double)hl->lv[l].m_total * 10.0 + (double)hl->lv[l].r_total * 3.0;
-            const unsigned n_tiles = (unsigned)(last - first);
-            const unsigned grid = (n_tiles + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD;
+            // per coarse voxel: position in, 8 indices out; the finer tables once
+            for (int l = std::max(l0, 1); l < l1; ++l)
+                if (hl->lv[l].ratio == 2) bytes += (double)hl->lv[l].n_total * 44.0 + (double)hl->lv[l - 1].m_total * 10.0 + (double)hl->lv[l - 1].r_total * 3.0;
+            const int child_first = hl->child_prefix[(size_t)l0 * b];
+            const unsigned n_tiles = (unsigned)(last - first), n_child = (unsigned)(hl->child_prefix[(size_t)l1 * b] - child_first);
+            const unsigned nbr_grid = (n_tiles + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD;
+            const unsigned grid = nbr_grid + (n_child + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD;
             hch::LaunchTimer lt(HCH_KERNEL_ID("neighbour_kernel"), s, bytes, 0.0);
             HCH_LAUNCH(hch::neighbour_kernel, dim3(grid), dim3(256), 0, s, hl->set, hl->d_nbr_prefix,
-                               n_entries, first, n_tiles);
+                               n_entries, first, n_tiles, nbr_grid, hl->d_child_prefix, child_first, n_child);
         }
         HCH_LAUNCH_CHECK("neighbour_kernel");
         for (int l = l0; l < l1; ++l) {            // keep the tap-major copies in step
@@ -260,20 +265,6 @@ static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipSt
             }
             HCH_LAUNCH_CHECK("tile_mask_kernel");
         }
-    }
-    {
-        const int first = hl->child_prefix[(size_t)l0 * b], last = hl->child_prefix[(size_t)l1 * b];
-        if (last > first) {
-            double bytes = 0.0;   // per coarse voxel: position in, 8 indices out; the finer tables once
-            for (int l = std::max(l0, 1); l < l1; ++l)
-                if (hl->lv[l].ratio == 2) bytes += (double)hl->lv[l].n_total * 44.0 + (double)hl->lv[l - 1].m_total * 10.0 + (double)hl->lv[l - 1].r_total * 3.0;
-            const unsigned n_tiles = (unsigned)(last - first);
-            const unsigned grid = (n_tiles + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD;
-            hch::LaunchTimer lt(HCH_KERNEL_ID("child_kernel"), s, bytes, 0.0);
-            HCH_LAUNCH(hch::child_kernel, dim3(grid), dim3(256), 0, s, hl->set, hl->d_child_prefix,
-                               n_entries, first, n_tiles);
-        }
-        HCH_LAUNCH_CHECK("child_kernel");
     }
     return HCH_OK;
 }

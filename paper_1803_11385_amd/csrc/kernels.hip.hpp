@@ -189,6 +189,51 @@ __device__ __forceinline__ int find_entry(const int32_t *__restrict__ prefix, in
     return lo;
 }
 
+// For every coarse voxel the global data indices, at the next finer level, of its 8 children
+// 2p + (dx,dy,dz), k = dx*4 + dy*2 + dz, or -1: the stride-2, F = 2, no-padding traversal of
+// Algorithm 1 (receptive field [2p, 2p+1]^3).  Tiles of 256 voxels; entries of level 0 have none.
+__device__ __forceinline__ void child_tile(const LevelSet &S, const int32_t *__restrict__ tile_prefix, int n_entries, int flat)
+{
+    const int e = find_entry(tile_prefix, n_entries, flat);
+    const int lev = e / S.batch, v = e - lev * S.batch;      // lev >= 1
+    const PshView &Lf = S.view[lev - 1];
+    const int32_t *Nc = S.view[lev].N;
+    const int32_t cbase = Nc[v];
+    const int32_t n = Nc[v + 1] - cbase;
+    const int32_t i = (flat - tile_prefix[e]) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const unsigned m = (unsigned)Lf.mbar[v], r = (unsigned)Lf.rbar[v];
+    const unsigned Mv = (unsigned)Lf.M[v], Rv = (unsigned)Lf.R[v];
+    const int32_t fbase = Lf.N[v];
+    const int32_t *p = S.coords[lev] + 3 * (int64_t)(cbase + i);
+    const unsigned x = 2u * (unsigned)p[0], y = 2u * (unsigned)p[1], z = 2u * (unsigned)p[2];
+    unsigned xm[2], ym[2], zm[2], xr[2], yr[2], zr[2];
+    xm[0] = x % m; xm[1] = xm[0] + 1 == m ? 0 : xm[0] + 1;
+    ym[0] = y % m; ym[1] = ym[0] + 1 == m ? 0 : ym[0] + 1;
+    zm[0] = z % m; zm[1] = zm[0] + 1 == m ? 0 : zm[0] + 1;
+    xr[0] = x % r; xr[1] = xr[0] + 1 == r ? 0 : xr[0] + 1;
+    yr[0] = y % r; yr[1] = yr[0] + 1 == r ? 0 : yr[0] + 1;
+    zr[0] = z % r; zr[1] = zr[0] + 1 == r ? 0 : zr[0] + 1;
+    int32_t out[8];
+    uint32_t ph[8], rh[8], rxy[8], rz[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) ph[q] = psh_offset(Lf, Rv, r, xr[q >> 2], yr[(q >> 1) & 1], zr[q & 1]);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const u32x3 rec = psh_record(psh_slot(Lf, Mv, m, ph[q], xm[q >> 2], ym[(q >> 1) & 1], zm[q & 1]));
+        rh[q] = rec[0]; rxy[q] = rec[1]; rz[q] = rec[2];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        // 2p + 1 < 2 * (coarse side) = fine side: always inside the grid
+        const int32_t h = psh_match(rh[q], rxy[q], rz[q], x + (q >> 2), y + ((q >> 1) & 1), z + (q & 1));
+        out[q] = h >= 0 ? fbase + h : -1;
+    }
+    int4 *dst = reinterpret_cast<int4 *>(S.child[lev] + (int64_t)(cbase + i) * 8);
+    dst[0] = make_int4(out[0], out[1], out[2], out[3]);
+    dst[1] = make_int4(out[4], out[5], out[6], out[7]);
+}
+
 // "Pre-stored neighbour information": for every voxel the global data indices of its 27
 // neighbours p + (dx,dy,dz), tap k = (dx+1)*9 + (dy+1)*3 + (dz+1), or -1 (empty, or outside
 // the grid).  This is the index side of the stride-1 traversal of Algorithm 1.
@@ -205,15 +250,22 @@ __device__ __forceinline__ int find_entry(const int32_t *__restrict__ prefix, in
 // slot records are.  The centre tap is the voxel itself; lanes whose voxels are z-neighbours hand
 // each other results (below), so a voxel makes 8 to 26 probes.  Results are kept in registers until
 // all probes of the workgroup are done, then go through the same LDS space so that the rows are
-// written coalesced.
+// written coalesced.  The workgroups from nbr_grid on make the child lists of the same levels, beside the others
+// instead of after them.
 constexpr int NBR_LDS_WORDS = 256 * 27;
 __global__ __launch_bounds__(256) void neighbour_kernel(
-    LevelSet S, const int32_t *__restrict__ tile_prefix, int n_entries, int tile_first, unsigned n_tiles)
+    LevelSet S, const int32_t *__restrict__ tile_prefix, int n_entries, int tile_first, unsigned n_tiles, unsigned nbr_grid,
+    const int32_t *__restrict__ child_prefix, int child_first, unsigned n_child)
 {
+    if (blockIdx.x >= nbr_grid) {
+        const unsigned t = xcd_tile(blockIdx.x - nbr_grid, (gridDim.x - nbr_grid) / NUM_XCD);
+        if (t < n_child) child_tile(S, child_prefix, n_entries, child_first + (int)t);
+        return;
+    }
     __shared__ uint32_t lds[NBR_LDS_WORDS];          // offset planes first, the 256 x 27 result tile afterwards
     __shared__ int32_t xrange[8];
     __shared__ int32_t hist[PATTERN_BINS];
-    const unsigned t = xcd_tile(blockIdx.x, gridDim.x / NUM_XCD);
+    const unsigned t = xcd_tile(blockIdx.x, nbr_grid / NUM_XCD);
     if (t >= n_tiles) return;
     const int flat = tile_first + (int)t;
     const int e = find_entry(tile_prefix, n_entries, flat);
@@ -599,56 +651,6 @@ __global__ __launch_bounds__(256) void tile_mask_kernel(TileMaskArgs A, const ui
         __syncthreads();
         if (count) hist[A.hist_off[l] + (int64_t)threadIdx.x * A.hist_tiles[l] + stretch] = cnt[threadIdx.x];
     }
-}
-
-// For every coarse voxel the global data indices, at the next finer level, of its 8 children
-// 2p + (dx,dy,dz), k = dx*4 + dy*2 + dz, or -1: the stride-2, F = 2, no-padding traversal of
-// Algorithm 1 (receptive field [2p, 2p+1]^3).  Same tiling as above; entries of level 0 have no
-// tiles in this kernel's prefix.
-__global__ __launch_bounds__(256) void child_kernel(
-    LevelSet S, const int32_t *__restrict__ tile_prefix, int n_entries, int tile_first, unsigned n_tiles)
-{
-    const unsigned t = xcd_tile(blockIdx.x, gridDim.x / NUM_XCD);
-    if (t >= n_tiles) return;
-    const int flat = tile_first + (int)t;
-    const int e = find_entry(tile_prefix, n_entries, flat);
-    const int lev = e / S.batch, v = e - lev * S.batch;      // lev >= 1
-    const PshView &Lf = S.view[lev - 1];
-    const int32_t *Nc = S.view[lev].N;
-    const int32_t cbase = Nc[v];
-    const int32_t n = Nc[v + 1] - cbase;
-    const int32_t i = (flat - tile_prefix[e]) * 256 + threadIdx.x;
-    if (i >= n) return;
-    const unsigned m = (unsigned)Lf.mbar[v], r = (unsigned)Lf.rbar[v];
-    const unsigned Mv = (unsigned)Lf.M[v], Rv = (unsigned)Lf.R[v];
-    const int32_t fbase = Lf.N[v];
-    const int32_t *p = S.coords[lev] + 3 * (int64_t)(cbase + i);
-    const unsigned x = 2u * (unsigned)p[0], y = 2u * (unsigned)p[1], z = 2u * (unsigned)p[2];
-    unsigned xm[2], ym[2], zm[2], xr[2], yr[2], zr[2];
-    xm[0] = x % m; xm[1] = xm[0] + 1 == m ? 0 : xm[0] + 1;
-    ym[0] = y % m; ym[1] = ym[0] + 1 == m ? 0 : ym[0] + 1;
-    zm[0] = z % m; zm[1] = zm[0] + 1 == m ? 0 : zm[0] + 1;
-    xr[0] = x % r; xr[1] = xr[0] + 1 == r ? 0 : xr[0] + 1;
-    yr[0] = y % r; yr[1] = yr[0] + 1 == r ? 0 : yr[0] + 1;
-    zr[0] = z % r; zr[1] = zr[0] + 1 == r ? 0 : zr[0] + 1;
-    int32_t out[8];
-    uint32_t ph[8], rh[8], rxy[8], rz[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) ph[q] = psh_offset(Lf, Rv, r, xr[q >> 2], yr[(q >> 1) & 1], zr[q & 1]);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const u32x3 rec = psh_record(psh_slot(Lf, Mv, m, ph[q], xm[q >> 2], ym[(q >> 1) & 1], zm[q & 1]));
-        rh[q] = rec[0]; rxy[q] = rec[1]; rz[q] = rec[2];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        // 2p + 1 < 2 * (coarse side) = fine side: always inside the grid
-        const int32_t h = psh_match(rh[q], rxy[q], rz[q], x + (q >> 2), y + ((q >> 1) & 1), z + (q & 1));
-        out[q] = h >= 0 ? fbase + h : -1;
-    }
-    int4 *dst = reinterpret_cast<int4 *>(S.child[lev] + (int64_t)(cbase + i) * 8);
-    dst[0] = make_int4(out[0], out[1], out[2], out[3]);
-    dst[1] = make_int4(out[4], out[5], out[6], out[7]);
 }
 
 // Receptive fields of the general traversal of Algorithm 1 (kernel side F, stride S, padding P)

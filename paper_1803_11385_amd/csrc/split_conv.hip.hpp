@@ -87,9 +87,8 @@ __global__ __launch_bounds__(64 * WV) void conv_split_kernel(
     if (GROUP == 2 && mtile * 2 + 1 < m_tiles) present |= tilemask[mtile * 2 + 1];
     present = (uint32_t)__builtin_amdgcn_readfirstlane((int)present);
     if (tid < 32) {
-        uint32_t m = present;
-        for (int q = 0; q < tid && m; ++q) m &= m - 1u;
-        taplist[tid] = m ? (uint8_t)(__ffs(m) - 1) : (uint8_t)0;           // past the last: tap 0, with no weights
+        if (tid >= __popc(present)) taplist[tid] = 0;                      // past the last: tap 0, with no weights
+        if (present >> tid & 1u) taplist[__popc(present & ((1u << tid) - 1u))] = (uint8_t)tid;
     }
     const int c8 = (c + 7) >> 3;
     const int n_units = __popc(present) * c8, n_steps = (n_units + 3) >> 2;
