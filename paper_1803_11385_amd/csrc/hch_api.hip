@@ -1867,9 +1867,10 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     // 249 -> 224; 280 000 rows: 32 -> 64 198 -> 173, 64 -> 64 291 -> 232, 64 -> 128 500 -> 391.
     if (n < (c % 64 == 0 && N > 32 ? 98304 : 196608)) return false;
     // The order scatters the rows that a tile reads over the whole of X; beyond the last-level cache (256 MB) that costs
-    // what the left-out taps give: 2.98 M rows of 64 channels (381 MB) 862 us against 882, 1.2 M (154 MB, thick shells as well) 1099 -> 1085 us
-    // with both gradients, 609 000 thin ones 556 -> 446.
-    return n * c * 2 <= (int64_t)256 << 20;
+    // what the left-out taps give: 2.98 M rows of 64 channels (381 MB) 862 us against 882.  Where voxels have many neighbours
+    // (thick shells, 17 each) there are fewer to leave out: a convolution with both gradients of 520 000 rows, 128 -> 64 (133 MB)
+    // 885 and 903 us, 64 -> 64 (67 MB) 481 -> 470; thin shells, 609 000 rows, 64 -> 128 (156 MB of dY) 1013 -> 798.
+    return n * c * 2 <= (int64_t)(L.nbr_valid > 15 * n ? 96 : 256) << 20;
 }
 
 // transposed: W(t, k, n) = W[26 - t][n][k]
