@@ -46,6 +46,15 @@ hch_status fail(hch_status st, const std::string &msg)
     return st;
 }
 
+// Every allocation of the library on the device.  The runtime keeps a failed one as its last error over later calls that
+// succeed; taken back here, or the next HCH_LAUNCH_CHECK, of this call or of another one, would report it as its own.
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    const hipError_t e = hipMalloc(p, bytes ? bytes : 16);
+    if (e != hipSuccess) { *p = nullptr; (void)hipGetLastError(); }
+    return e;
+}
+
 #define HCH_HIP(call)                                                                      \
     do {                                                                                   \
         hipError_t e_ = (call);                                                            \
@@ -166,9 +175,8 @@ extern "C" int32_t hch_num_levels(const hch_levels *levels)
 
 static hch_status upload(void **dst, const void *src, size_t bytes, hipStream_t s)
 {
-    *dst = nullptr;
-    hipError_t e = hipMalloc(dst, bytes ? bytes : 16);
-    if (e != hipSuccess) { *dst = nullptr; return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)); }
+    const hipError_t e = device_malloc(dst, bytes);
+    if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
     if (bytes) HCH_HIP(hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, s));
     return HCH_OK;
 }
@@ -286,10 +294,8 @@ extern "C" hch_status hch_build_tap_major(hch_levels *levels, int32_t level, voi
     const int l0 = level < 0 ? 0 : level, l1 = level < 0 ? (int)levels->lv.size() : level + 1;
     for (int l = l0; l < l1; ++l) {
         Level &L = levels->lv[l];
-        if (!L.dnbr_t && L.n_total > 0 && hipMalloc((void **)&L.dnbr_t, (size_t)L.n_total * 27 * 4) != hipSuccess) {
-            L.dnbr_t = nullptr;
+        if (!L.dnbr_t && L.n_total > 0 && device_malloc((void **)&L.dnbr_t, (size_t)L.n_total * 27 * 4) != hipSuccess)
             return fail(HCH_ENOMEM, "hch_build_tap_major: hipMalloc failed");
-        }
         hch_status st = transpose_neighbours(L, (hipStream_t)stream);
         if (st != HCH_OK) return st;
     }
@@ -331,13 +337,16 @@ struct Pieces {
 struct DeviceBlocks {            // device allocations that live until the end of the build call
     std::vector<void *> ptrs;
     ~DeviceBlocks() { for (void *p : ptrs) if (p) (void)hipFree(p); }
+    hipError_t try_get(void **out, size_t bytes)
+    {
+        const hipError_t e = device_malloc(out, bytes);
+        if (e == hipSuccess) ptrs.push_back(*out);
+        return e;
+    }
     hch_status get(void **out, size_t bytes)
     {
-        *out = nullptr;
-        hipError_t e = hipMalloc(out, bytes ? bytes : 16);
-        if (e != hipSuccess) { *out = nullptr; return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)); }
-        ptrs.push_back(*out);
-        return HCH_OK;
+        const hipError_t e = try_get(out, bytes);
+        return e == hipSuccess ? HCH_OK : fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
     }
 };
 // Occupancy of the levels on the device (occupancy.hip.hpp), between the checks and the tables
@@ -398,7 +407,7 @@ static hch_status device_occupancy(hch_levels *hl, const int32_t *coords, const 
     Pieces size, place;
     size_t zeroed = 0;
     lay(size, &zeroed);
-    if (o.mem.get((void **)&place.base, size.used) != HCH_OK) return HCH_OK;
+    if (o.mem.try_get((void **)&place.base, size.used) != hipSuccess) return HCH_OK;
     lay(place, &zeroed);
     HCH_HIP(hipMemsetAsync(place.base, 0, zeroed, s));
     HCH_HIP(hipMemcpyAsync(d_offsets, offsets, ((size_t)batch + 1) * 8, hipMemcpyHostToDevice, s));
@@ -486,7 +495,7 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         size_t tables = 0;
         lay(size, &tables);
         void *block = nullptr;
-        hipError_t e = hipMalloc(&block, size.used);
+        hipError_t e = device_malloc(&block, size.used);
         if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         hl->blocks.push_back(block);
         place.base = (char *)block;
@@ -670,7 +679,7 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         Pieces size, place;
         lay_offsets(size);
         void *block = nullptr;
-        hipError_t e = hipMalloc(&block, size.used);
+        hipError_t e = device_malloc(&block, size.used);
         if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         hl->blocks.push_back(block);
         place.base = (char *)block;
@@ -927,11 +936,11 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
                 phi4[q] = (uint32_t)L.Phi[3 * q] | ((uint32_t)L.Phi[3 * q + 1] << 8) | ((uint32_t)L.Phi[3 * q + 2] << 16);
             if ((st = upload((void **)&L.dslot3, slot3.data(), slot3.size() * 4, s)) != HCH_OK) break;
             if ((st = upload((void **)&L.dphi4, phi4.data(), phi4.size() * 4, s)) != HCH_OK) break;
-            if (hipMalloc((void **)&L.dnbr, (size_t)L.n_total * 27 * 4) != hipSuccess) {
-                L.dnbr = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(nbr27) failed"); break;
+            if (device_malloc((void **)&L.dnbr, (size_t)L.n_total * 27 * 4) != hipSuccess) {
+                st = fail(HCH_ENOMEM, "hipMalloc(nbr27) failed"); break;
             }
-            if (l > 0 && L.ratio == 2 && hipMalloc((void **)&L.dchild, (size_t)L.n_total * 8 * 4) != hipSuccess) {
-                L.dchild = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(child8) failed"); break;
+            if (l > 0 && L.ratio == 2 && device_malloc((void **)&L.dchild, (size_t)L.n_total * 8 * 4) != hipSuccess) {
+                st = fail(HCH_ENOMEM, "hipMalloc(child8) failed"); break;
             }
             // the staging vectors die at the end of this iteration: finish the copies first
             hipError_t e = hipStreamSynchronize(s);
@@ -972,7 +981,7 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
             };
             Pieces size, place;
             lay(size);
-            if (hipMalloc((void **)&place.base, size.used) != hipSuccess) { place.base = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(pattern and fine order) failed"); }
+            if (device_malloc((void **)&place.base, size.used) != hipSuccess) st = fail(HCH_ENOMEM, "hipMalloc(pattern and fine order) failed");
             else {
                 hl->blocks.push_back(place.base);
                 lay(place);
@@ -982,8 +991,8 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
                 const size_t tiles = (size_t)((L.n_total + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE);
                 L.dorder = hl->d_order + hl->sort_off[l];
                 if (L.in_block) continue;
-                if (hipMalloc((void **)&L.dmask27, std::max<size_t>((size_t)L.n_total, 64) * 4) != hipSuccess) { L.dmask27 = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(mask27) failed"); break; }
-                if (hipMalloc((void **)&L.dtilemask, std::max<size_t>(tiles, 64) * 4) != hipSuccess) { L.dtilemask = nullptr; st = fail(HCH_ENOMEM, "hipMalloc(tile masks) failed"); break; }
+                if (device_malloc((void **)&L.dmask27, std::max<size_t>((size_t)L.n_total, 64) * 4) != hipSuccess) { st = fail(HCH_ENOMEM, "hipMalloc(mask27) failed"); break; }
+                if (device_malloc((void **)&L.dtilemask, std::max<size_t>(tiles, 64) * 4) != hipSuccess) { st = fail(HCH_ENOMEM, "hipMalloc(tile masks) failed"); break; }
             }
             if (st == HCH_OK) {
                 uint32_t *p = hl->d_fine;
@@ -1042,7 +1051,7 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
         if (st == HCH_OK && with_device) {
             unsigned long long *d_cnt = nullptr;
             std::vector<unsigned long long> h_cnt((size_t)n_levels, 0);
-            if (hipMalloc((void **)&d_cnt, (size_t)n_levels * 8) != hipSuccess) st = fail(HCH_ENOMEM, "hipMalloc failed");
+            if (device_malloc((void **)&d_cnt, (size_t)n_levels * 8) != hipSuccess) st = fail(HCH_ENOMEM, "hipMalloc failed");
             if (st == HCH_OK) {
                 hipError_t e = hipMemsetAsync(d_cnt, 0, (size_t)n_levels * 8, s);
                 for (int l = 0; l < n_levels && e == hipSuccess; ++l) {
