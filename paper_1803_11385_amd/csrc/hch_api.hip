@@ -374,8 +374,12 @@ struct PairWork {
 
 // Checks the positions and fills ubar, ratio, b, N, n_total and max_n of every level on the device; the
 // coarse levels' voxels stay a bit set until device_construct lists them.  On the host the checks and the coarse
-// levels were 3.4 ms of a 256^3 batch of 8.  Not `ready` where a bit per position is too much memory: the host does it then.
-constexpr size_t OCCUPANCY_BYTES = (size_t)512 << 20;
+// levels were 3.4 ms of a 256^3 batch of 8.  Not `ready` where a bit per position is too much memory, altogether or for the
+// few voxels there are: the host does it then.  Clearing and reading the bits costs 2.5 us a MB, the host 50 to 90 ns a voxel
+// of one model and, from a few models on, its threads.  Whole builds, device and host: 1024^3, one model (153 MB), 300 voxels
+// 1.23 and 0.71 ms, 4000 1.85 and 1.65, 8000 2.26 and 2.32, 16 000 2.14 and 2.74; 512^3 (19 MB), 600 voxels 1.14 and 1.06, 2500
+// 1.05 and 1.10; 512^3, 4 models, 2400 voxels 1.61 and 1.49, 10 000 2.04 and 2.05; 256^3, 16 models (38 MB), 640 voxels 0.81 and 2.27.
+constexpr size_t OCCUPANCY_BYTES = (size_t)512 << 20, OCCUPANCY_PER_VOXEL = 16 << 10, OCCUPANCY_PER_MODEL = 4 << 20;
 static hch_status device_occupancy(hch_levels *hl, const int32_t *coords, const int64_t *offsets, int32_t batch,
                                    const std::vector<int32_t> &side, const std::vector<int32_t> &ratio_of, int n_levels,
                                    hipStream_t s, Occupancy &o)
@@ -396,8 +400,8 @@ static hch_status device_occupancy(hch_levels *hl, const int32_t *coords, const 
         if (l > 0) blocks += per_model * batch;
         S.block_off[l + 1] = (int32_t)blocks;
     }
-    if ((size_t)words * 8 > OCCUPANCY_BYTES) return HCH_OK;
     const int64_t n = offsets[batch], pairs = (int64_t)(n_levels - 1) * batch;
+    if ((size_t)words * 8 > std::min(OCCUPANCY_BYTES, (size_t)n * OCCUPANCY_PER_VOXEL + (size_t)batch * OCCUPANCY_PER_MODEL)) return HCH_OK;
     int32_t *d_flags = nullptr;                // [0] flags, then the number of voxels of every (level >= 1, model)
     int64_t *d_offsets = nullptr;
     auto lay = [&](Pieces &P, size_t *zeroed) {

@@ -115,3 +115,15 @@ for k in range(4):           # theirs, the tables, the failed pairs, the first a
     same(lv, want)
     assert build(args, (k, 256))[0] is None
 """)
+
+
+def test_few_voxels_in_a_large_grid(tmp_path):
+    """A bit for each of 2^30 positions is not made for a few hundred voxels.  On both sides of the line (16 KB a voxel and
+    4 MB a model: 9107 voxels) the levels are those of the host."""
+    _child(tmp_path, r"""
+for n in (300, 9106, 9107):
+    args = (*batch(1024, n, 1), 1024)
+    lv, asked, _ = build(args, levels=6)
+    assert (max(asked) > 1 << 27) == (n == 9107), (n, asked)
+    same(lv, build(args, levels=6, call=hch.hch_build_levels)[0])
+""")
