@@ -2633,9 +2633,35 @@ static size_t field_weights_bytes(int taps, int c, int N)
 
 enum FieldUse { FIELD_FWD, FIELD_BWD, FIELD_BWD_STRIDED };
 
+// Forward and the data gradient within a level against gemm_f32_kernel on its vector path.  Both take a time that goes with the
+// rows per CU in whole rounds of workgroups, of 64 or 128 rows there and of 256 here: 20 -> 64 at 66 000, 75 000 and 127 000
+// rows (258, 293 and 496 workgroups) 57, 58 and 86 us there, 69, 78 and 80 here.  A row and term of a tile of 16, 32 or 64 columns
+// takes 1.0, 1.5 or 2.66e-4 us there; here that times the factors below (the taps that 16 rows leave out), with channels
+// padded to 8.  Fitted to 4680 shapes (3^3 and 2^3, 8 to 128 channels, 50 000 to 420 000 rows): without this 533 of them were
+// slower here by more than 2 %, up to 38 %; with it 79, by 10 % at most, and 103 go there that would be faster here.
+static bool field_split_faster(int64_t M, int64_t x_rows, int taps, int c, int N)
+{
+    // one tap: nothing to leave out (279 722 rows, 256 -> 64 110 us there, 164 here; 64 -> 256 137 and 146)
+    if (taps == 1) return false;
+    // 2^3 fields of stride 2 read every row once, there in order: beyond the last-level cache that is what counts (609 000 rows
+    // of 128 channels, 312 MB, to 32: 149 us there, 180 here; 500 000, 256 MB: 112 and 125; 400 000, 205 MB: 89 and 77)
+    if (taps < 27 && x_rows * c * 4 > (int64_t)224 << 20) return false;
+    const GemmPlan p = plan_rows(M, N, taps * c, true);
+    const int64_t n_tiles = (N + p.bn - 1) / p.bn, tiles = (M + p.bm - 1) / p.bm * n_tiles;
+    const int64_t groups = (M + hch::FIELD_ROWS - 1) / hch::FIELD_ROWS * n_tiles, rest = groups % 256;
+    const double there = (double)((tiles + 255) / 256) * p.bm * taps * c;
+    // up to 5 workgroups more than a whole round are less than one
+    const double rounds = (double)(groups / 256) + (rest ? std::min(1.0, 0.5 + (double)rest / 10) : 0.0);
+    const double factor = taps < 27 ? 0.74 : (p.bn == 64 ? 0.66 : (p.bn == 32 ? 0.68 : 0.74));
+    const double here = rounds * hch::FIELD_ROWS * taps * ((c + 7) / 8 * 8) * factor;
+    const double unit = p.bn == 16 ? 1.0e-4 : (p.bn == 32 ? 1.5e-4 : 2.66e-4);
+    return 4.0 + unit * here < unit * there;          // 4 us: the weights are cut in a launch of their own
+}
+
 // Whether that is the faster way, and within its limits.  Its results are closer to the exact ones than those of the
-// fp32 instruction, as everywhere on split operands.
-static bool field_split_ok(FieldUse use, int64_t M, int64_t x_rows, int taps, int c, int N, size_t ws_bytes)
+// fp32 instruction, as everywhere on split operands.  gemm_vec: gemm_f32_kernel has its vector path for these operands, else it
+// takes 1.3 to 5 times as long.
+static bool field_split_ok(FieldUse use, bool gemm_vec, int64_t M, int64_t x_rows, int taps, int c, int N, size_t ws_bytes)
 {
     const int64_t lim = (int64_t)1 << 31;
     // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors; a bit per tap
@@ -2649,15 +2675,18 @@ static bool field_split_ok(FieldUse use, int64_t M, int64_t x_rows, int taps, in
     // Forward: 3^3, 64 000 rows 24 -> 40 (1.7e9) 60 -> 50 us, 16 -> 32 (0.9e9) 26.5 and 27.6; 197 000 rows 16 -> 32 (2.7e9) 77 ->
     // 71, 32 -> 64 229 -> 175; 82 000 rows 32 -> 32 (2.3e9) 62 and 63; 2^3, 82 000 rows 32 -> 64 (1.3e9) 39 and 44.  Rows of 4
     // channels are half padding.
-    if (use == FIELD_FWD) return c >= 16 && work >= 1.6e9 && (N > 32 || M >= 98304);
+    if (use == FIELD_FWD) return c >= 16 && work >= 1.6e9 && (N > 32 || M >= 98304) && (!gemm_vec || field_split_faster(M, x_rows, taps, c, N));
     if (taps * c < 256) return false;                  // 2^3, 16 -> 4 at 609 000 rows: 30 us, 37 here
     // Data gradient within a level: 64 000 rows 32 -> 16 (0.9e9) 33 and 35 us, 40 -> 24 (1.7e9) 57 -> 49; 280 000 rows 16 -> 4 67 -> 58,
     // 32 -> 16 115 -> 91, 64 -> 32 305 -> 231
-    if (use == FIELD_BWD) return work >= 1.6e9 || M >= 262144;
+    if (use == FIELD_BWD) return (work >= 1.6e9 || M >= 262144) && (!gemm_vec || field_split_faster(M, x_rows, taps, c, N));
     // Between levels, against the gradient of the column matrix through memory: 609 000 rows, stride 2, 32 -> 16 208 -> 84 us, 64 -> 32
     // 438 -> 176, 16 -> 4 84 -> 64; where that matrix is small (3^3, stride 4, 64 000 rows, 32 -> 16: 2.3 M elements) 14.6 and
-    // 15.6, with 3.5 M 25 -> 19.  Few columns leave most of the matrix tile empty: 280 000 rows, 64 -> 4 52 and 70, 50 -> 7 96 -> 66
-    return (N >= 16 || c < 8 * N) && (double)x_rows * taps * N >= 3e6;
+    // 15.6, with 3.5 M 25 -> 19.  Few columns leave most of the matrix tile empty: 280 000 rows, 64 -> 4 52 and 70, 50 -> 7 96 -> 66;
+    // of whole 16 bytes, 207 000 rows, 28 -> 4 35 and 38, 24 -> 4 35 and 36, 40 -> 8 55 -> 45, and 2^3, 32 -> 8 20 and 22 (400 000 27
+    // and 32), 32 -> 12 26 -> 22
+    if (N < 16 && (gemm_vec ? c > 6 * N || taps * N < 96 : c >= 8 * N)) return false;
+    return (double)x_rows * taps * N >= 3e6;
 }
 
 static hch_status launch_field_split(const float *X, const float *W, float *out, const int32_t *field, void *ws, int64_t M, int64_t x_rows,
@@ -2778,7 +2807,8 @@ extern "C" hch_status hch_sconv_fwd(const hch_levels *levels, int32_t level_in, 
     const GemmPlan p = plan_rows(n, c_out, K, true, k_gran(dtype));
     float *part = (float *)workspace;
     const double bytes = (double)n * (4.0 * taps + 4.0 * c_out * p.splits) + es * (double)Li->n_total * c_in + es * K * c_out;
-    if (dtype == HCH_F32 && field_split_ok(FIELD_FWD, n, Li->n_total, taps, c_in, c_out, ws_bytes))
+    const bool gemm_vec = c_in % 4 == 0 && c_out % 4 == 0 && aligned16(X) && aligned16(W);
+    if (dtype == HCH_F32 && field_split_ok(FIELD_FWD, gemm_vec, n, Li->n_total, taps, c_in, c_out, ws_bytes))
         return launch_field_split((const float *)X, (const float *)W, Y, field, workspace, n, Li->n_total, taps, c_in, c_out, false,
                                   (double)n * (4.0 * taps + 4.0 * c_out) + 4.0 * ((double)Li->n_total * c_in + (double)K * c_out), s);
     st = launch_gemm<hch::A_GATHER, false>(dtype, p, X, W, p.splits > 1 ? part : Y, field, (int)n, c_out, K, c_in,
@@ -2831,7 +2861,9 @@ extern "C" hch_status hch_sconv_bwd_data(const hch_levels *levels, int32_t level
     const int64_t n = Li->n_total, wn = (int64_t)taps * c_in * c_out;
     const double es = elem_size(dtype);
     const WsLayout w = sconv_layout(*Li, *Lo, taps, c_in, c_out, dtype, HCH_WS_BWD_DATA, true);
-    if (dtype == HCH_F32 && field_split_ok(Li == Lo ? FIELD_BWD : FIELD_BWD_STRIDED, n, Lo->n_total, taps, c_out, c_in, ws_bytes))
+    // (within a level the weights are transposed into the workspace first; between two, rows of c_in enter only the gather)
+    const bool gemm_vec = c_out % 4 == 0 && aligned16(dY) && (Li == Lo ? c_in % 4 == 0 : aligned16(W));
+    if (dtype == HCH_F32 && field_split_ok(Li == Lo ? FIELD_BWD : FIELD_BWD_STRIDED, gemm_vec, n, Lo->n_total, taps, c_out, c_in, ws_bytes))
         return launch_field_split((const float *)dY, (const float *)W, dX, field_t, workspace, n, Lo->n_total, taps, c_out, c_in, true,
                                   (double)n * (4.0 * taps + 4.0 * c_in) + 4.0 * ((double)Lo->n_total * c_out + (double)wn), s);
     if (Li != Lo) {

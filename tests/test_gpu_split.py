@@ -508,3 +508,68 @@ def test_bf16_products_over_the_row_order(batch, large, ci, co):
         call(B, again)
         near = (nbr == v).any(1)
         assert bool(torch.isnan(again[near]).all()) and torch.equal(again[~near], out[~near])
+
+
+def _launched(call):
+    """Names of the kernels that `call` launches."""
+    hch.hch_profile_reset()
+    hch.hch_profile_enable(-1, True)
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        hch.hch_profile_enable(-1, False)
+    return {hch.hch_kernel_name(i) for i in range(hch.hch_kernel_count()) if hch.hch_profile_read(i)["launches"]}
+
+
+def _gathered(A, idx, w):
+    zero = torch.zeros((), dtype=torch.float64, device="cuda")
+    return sum(torch.where(idx[:, k:k + 1] >= 0, A.double()[idx[:, k].clamp(min=0).long()], zero) @ w[k].double() for k in range(idx.shape[1]))
+
+
+def _sconv(lv, kind, F, stride, A, W, n, idx, ci, co):
+    out = torch.full((n, co if kind == hch.HCH_WS_FWD else ci), float("nan"), device="cuda")
+    call = hch.hch_sconv_fwd if kind == hch.HCH_WS_FWD else hch.hch_sconv_bwd_data
+    ws = _workspace(hch.hch_sconv_workspace_bytes(lv, 0, F, stride, ci, co, hch.HCH_F32, kind))
+    names = _launched(lambda: call(lv, 0, F, stride, hch.HCH_F32, A, W, out, idx, ci, co, ws))
+    return out, names
+
+
+@pytest.fixture(scope="module")
+def halves():
+    coords, offs, _ = S.config_batch(4)
+    return hch.hch_build_levels_device(coords, offs, 256, 2)
+
+
+@pytest.fixture(scope="module")
+def scattered():
+    pos = np.sort(np.random.default_rng(75).permutation(64 ** 3)[:75000])
+    return hch.hch_build_levels_device(np.stack([pos // 4096, pos // 64 % 64, pos % 64], 1).astype(np.int32), [0, 75000], 64, 1)
+
+
+@pytest.mark.parametrize("levels,F,stride,pad,ci,co,kind,split",
+                         [("scattered", 3, 1, 1, 20, 64, "fwd", False), ("scattered", 3, 1, 1, 24, 128, "fwd", True),
+                          ("scattered", 3, 1, 1, 18, 64, "fwd", True), ("scattered", 3, 1, 1, 20, 64, "fwd unaligned", True),
+                          ("scattered", 3, 1, 1, 64, 20, "bwd", False), ("scattered", 3, 1, 1, 62, 20, "bwd", True),
+                          ("halves", 1, 1, 0, 64, 64, "fwd", False), ("halves", 1, 1, 0, 32, 128, "bwd", False),
+                          ("halves", 2, 2, 0, 128, 64, "fwd", False), ("halves", 2, 2, 0, 64, 64, "fwd", True),
+                          ("halves", 2, 2, 0, 8, 32, "bwd", False), ("halves", 3, 2, 1, 8, 32, "bwd", True)])
+def test_where_general_index_rows_go(request, levels, F, stride, pad, ci, co, kind, split):
+    """Shapes on both sides of the lines of field_split_ok, with their results: one tap, rounds of workgroups that fill the chip or
+    hardly more than a half of it, operands beyond the last-level cache, few columns; without the vector path of
+    gemm_f32_kernel (channels, alignment) all of them on split operands."""
+    lv = request.getfixturevalue(levels)
+    n_in, n_out = lv.n(0), lv.n(stride // 2)
+    forward = kind.startswith("fwd")
+    idx = torch.empty((n_out if forward else n_in, F ** 3), dtype=torch.int32, device="cuda")
+    hch.hch_field_build(lv, 0, F, stride, pad, *((idx, None) if forward else (None, idx)))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ci * 1000 + co)
+    A, W = (torch.randn(s, device="cuda", generator=g) for s in ((n_in, ci) if forward else (n_out, co), (F ** 3, ci, co)))
+    if kind.endswith("unaligned"):
+        A = torch.empty(A.numel() + 1, device="cuda")[1:].view(A.shape).copy_(A)
+    out, names = _sconv(lv, hch.HCH_WS_FWD if forward else hch.HCH_WS_BWD_DATA, F, stride, A, W, idx.shape[0], idx, ci, co)
+    assert any(x.startswith("field_split_kernel") for x in names) == split, names
+    want = _gathered(A, idx, W if forward else W.transpose(1, 2))
+    # the fp32 instruction: a rounding per 4 terms
+    assert float((out.double() - want).norm() / want.norm()) < (BOUND if split else 4 * BOUND)
