@@ -1058,7 +1058,7 @@ static hch_status build_impl(const int32_t *coords_xyz, const int64_t *model_off
             hipError_t e = hipStreamSynchronize(s);
             if (e != hipSuccess) st = fail(HCH_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
         }
-        // occupied-neighbour count of every level (used only for reporting algorithmic traffic)
+        // occupied-neighbour count of every level (for the algorithmic traffic that is reported, and conv_bf16_ok)
         if (st == HCH_OK && with_device) {
             unsigned long long *d_cnt = nullptr;
             std::vector<unsigned long long> h_cnt((size_t)n_levels, 0);
@@ -1893,11 +1893,17 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     // convolution with its gradients, 127 000 rows: 32 -> 64 101.5 and 101.4 (one product of the three), 64 -> 64 156 -> 140, 64 -> 128
     // 249 -> 224; 280 000 rows: 32 -> 64 198 -> 173, 64 -> 64 291 -> 232, 64 -> 128 500 -> 391.
     if (n < (c % 64 == 0 && N > 32 ? 98304 : 196608)) return false;
-    // The order scatters the rows that a tile reads over the whole of X; beyond the last-level cache (256 MB) that costs
-    // what the left-out taps give: 2.98 M rows of 64 channels (381 MB) 862 us against 882.  Where voxels have many neighbours
-    // (thick shells, 17 each) there are fewer to leave out: a convolution with both gradients of 520 000 rows, 128 -> 64 (133 MB)
-    // 885 and 903 us, 64 -> 64 (67 MB) 481 -> 470; thin shells, 609 000 rows, 64 -> 128 (156 MB of dY) 1013 -> 798.
-    return n * c * 2 <= (int64_t)(L.nbr_valid > 15 * n ? 96 : 256) << 20;
+    // It lives on the taps that a tile's rows leave out: of 27, 256 rows of thin shells (9 neighbours a voxel) have 10 to 16, of
+    // thick ones (17) 18 to 20.  Times over those of gemm_bf16_kernel, index lists also tap-major (which that kernel is faster with) or
+    // not, at 0.25 to 1.3 million rows: 9 to 10.6 neighbours 0.58 to 0.97 and 0.56 to 0.91 (64 -> 32 at 10.6 1.02); spheres' shells, 14
+    // neighbours, 64 -> 64 0.98 to 1.06 and 0.93 to 0.98, 64 -> 32 1.07 to 1.19 and 0.92 to 1.04; 17 to 18, 64 -> 64 0.92 to 1.15 and 0.84
+    // to 1.07, 128 -> 128 1.02 to 1.23 and 0.84 to 1.10, 64 -> 32 0.95 to 1.37 and 0.85 to 1.16; 21, 64 -> 64 1.10 to 1.15.  Rows that are no
+    // multiple of 64 channels, for which gemm_bf16_kernel has the slower loop, to 64 columns and more: 17 to 18, 32 -> 64 0.88
+    // to 1.05, 96 -> 96 0.79 to 1.01; 19 to 21, 32 -> 64 1.02 to 1.13.
+    const double neighbours = (double)L.nbr_valid / (double)n;
+    if (neighbours > (N < 64 ? 11 : (c % 64 ? 18 : (L.dnbr_t ? 11 : 15)))) return false;
+    // The order scatters the rows that a tile reads over the whole of X, which is worst beyond the last-level cache (256 MB).
+    return n * c * 2 <= (int64_t)256 << 20;
 }
 
 // transposed: W(t, k, n) = W[26 - t][n][k]

@@ -573,3 +573,42 @@ def test_where_general_index_rows_go(request, levels, F, stride, pad, ci, co, ki
     want = _gathered(A, idx, W if forward else W.transpose(1, 2))
     # the fp32 instruction: a rounding per 4 terms
     assert float((out.double() - want).norm() / want.norm()) < (BOUND if split else 4 * BOUND)
+
+
+def _sphere_shells(radius, half):
+    """Two shells of a sphere of 2 * half voxels."""
+    g = np.arange(256) - 128
+    parts = [np.argwhere(np.abs(np.sqrt((g[:, None, None] + a) ** 2 + (g[None, :, None] + 0.2) ** 2 + (g[None, None, :] + 0.3) ** 2) - radius) < half)
+             for a in (0.0, 0.1)]
+    return hch.hch_build_levels_device(np.concatenate(parts).astype(np.int32), [0, len(parts[0]), len(parts[0]) + len(parts[1])], 256, 1)
+
+
+@pytest.fixture(scope="module")
+def shells():
+    sets = {(n, tap_major): _sphere_shells(*shape) for n, shape in ((14, (85, 0.7)), (18, (72, 0.99)), (21, (58, 1.5))) for tap_major in (False, True)}
+    for (_, tap_major), lv in sets.items():
+        if tap_major:
+            hch.hch_build_tap_major(lv, 0)
+    return sets
+
+
+@pytest.mark.parametrize("neighbours,tap_major,ci,co,fwd,bwd", [(14, False, 64, 64, True, True), (14, True, 64, 64, False, False),
+                                                               (14, False, 64, 32, False, True), (18, False, 64, 64, False, False),
+                                                               (18, False, 32, 64, True, False), (18, True, 96, 96, True, True),
+                                                               (18, False, 32, 32, False, False), (21, False, 32, 64, False, False)])
+def test_bf16_products_of_thick_shells(shells, neighbours, tap_major, ci, co, fwd, bwd):
+    """Levels whose voxels have 14, 18 and 21 neighbours, on both sides of the lines of conv_bf16_ok, with the results."""
+    lv = shells[neighbours, tap_major]
+    n = lv.n(0)
+    assert n >= 196608 and neighbours - 0.5 < lv.info(0).nbr_valid / n < neighbours + (0 if neighbours == 18 else 0.5)
+    nbr = torch.from_numpy(lv.info(0).device_nbr27()).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ci * 1000 + co)
+    X, G, W = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((n, ci), (n, co), (27, ci, co)))
+    for name, kind, A, w, over_order in (("hch_conv_fwd", hch.HCH_WS_FWD, X, W, fwd), ("hch_conv_bwd_data", hch.HCH_WS_BWD_DATA, G, W.flip(0).transpose(1, 2), bwd)):
+        out = torch.full((n, w.shape[2]), float("nan"), device="cuda")
+        ws = _workspace(hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_BF16, kind, hch.HCH_ALGO_FUSED))
+        names = _launched(lambda: getattr(hch, name)(lv, 0, hch.HCH_BF16, A, W, out, ci, co, ws, hch.HCH_ALGO_FUSED))
+        assert any(x.startswith("conv_bf16_kernel") for x in names) == over_order, names
+        want = _gathered(A, nbr, w)
+        assert float((out.double() - want).norm() / want.norm()) < BOUND
