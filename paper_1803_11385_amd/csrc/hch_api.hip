@@ -1902,7 +1902,8 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     // to 1.05, 96 -> 96 0.79 to 1.01; 19 to 21, 32 -> 64 1.02 to 1.13.
     const double neighbours = (double)L.nbr_valid / (double)n;
     if (neighbours > (N < 64 ? 11 : (c % 64 ? 18 : (L.dnbr_t ? 11 : 15)))) return false;
-    // The order scatters the rows that a tile reads over the whole of X, which is worst beyond the last-level cache (256 MB).
+    // Up to the last-level cache: the order scatters the rows that a tile reads over the whole of X.  (Thin shells would gain
+    // beyond it too, 1.5 million rows, 128 -> 128, 366 MB: 1469 us there, 925 here; thick ones of 64 channels 869 and 884.)
     return n * c * 2 <= (int64_t)256 << 20;
 }
 
@@ -2747,9 +2748,11 @@ static WsLayout sconv_layout(const Level &Li, const Level &Lo, int taps, int c_i
         if (p.splits > 1) w.part_bytes = round_up((size_t)p.splits * Lo.n_total * c_out * 4, 256);
         if (dtype == HCH_F32 && !least) w.part_bytes = std::max(w.part_bytes, field_weights_bytes(taps, c_in, c_out));
     } else if (kind == HCH_WS_BWD_DATA && &Li != &Lo) {
-        // between two levels: the gradient of the column matrix, [N_out][taps*c_in] floats
-        w.first_bytes = round_up((size_t)Lo.n_total * taps * c_in * 4, 256);
-        if (dtype == HCH_F32 && !least) w.first_bytes = std::max(w.first_bytes, field_weights_bytes(taps, c_out, c_in));
+        // between two levels: the gradient of the column matrix, [N_out][taps*c_in] floats, unless the product goes without it
+        // (what does so on the vector path of gemm_f32_kernel does so without it too)
+        const size_t cut = field_weights_bytes(taps, c_out, c_in);
+        if (dtype == HCH_F32 && field_split_ok(FIELD_BWD_STRIDED, true, Li.n_total, Lo.n_total, taps, c_out, c_in, cut)) w.first_bytes = round_up(cut, 256);
+        else w.first_bytes = round_up((size_t)Lo.n_total * taps * c_in * 4, 256);
     } else if (kind == HCH_WS_BWD_DATA) {
         const GemmPlan p = plan_rows(Li.n_total, c_in, taps * c_out, true, k_gran(dtype));
         w.first_bytes = round_up((size_t)taps * c_in * c_out * elem_size(dtype), 256);

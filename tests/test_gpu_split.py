@@ -612,3 +612,31 @@ def test_bf16_products_of_thick_shells(shells, neighbours, tap_major, ci, co, fw
         assert any(x.startswith("conv_bf16_kernel") for x in names) == over_order, names
         want = _gathered(A, nbr, w)
         assert float((out.double() - want).norm() / want.norm()) < BOUND
+
+
+@pytest.mark.parametrize("F,pad,ci,co", [(3, 1, 16, 32), (2, 0, 64, 64), (3, 1, 64, 4), (3, 1, 1, 256)])
+def test_workspace_of_strided_data_gradients(halves, F, pad, ci, co):
+    """What goes without the gradient of the column matrix asks for the cut weights only, 6 bytes a weight with channels
+    padded to 8 and columns to 16, works in that and is refused with less; what goes through it asks for it.  The old
+    answer is taken as before."""
+    lv = halves
+    n_in, n_out = lv.n(0), lv.n(1)
+    column = n_out * F ** 3 * ci * 4
+    need = hch.hch_sconv_workspace_bytes(lv, 0, F, 2, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_DATA)
+    split = (ci, co) not in ((64, 4), (1, 256))            # 27 * 4 terms are too few; a column is
+    assert need == -(-(F ** 3 * (-(-co // 8) * 8) * (-(-ci // 16) * 16) * 6 if split else column) // 256) * 256
+    field_t = torch.empty((n_in, F ** 3), dtype=torch.int32, device="cuda")
+    hch.hch_field_build(lv, 0, F, 2, pad, None, field_t)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ci)
+    G, W = (torch.randn(s, device="cuda", generator=g) for s in ((n_out, co), (F ** 3, ci, co)))
+    want = _gathered(G, field_t, W.transpose(1, 2))
+    outs = []
+    for size in {need, max(need, column)}:
+        outs.append(torch.full((n_in, ci), float("nan"), device="cuda"))
+        hch.hch_sconv_bwd_data(lv, 0, F, 2, hch.HCH_F32, G, W, outs[-1], field_t, ci, co, _workspace(size))
+        assert float((outs[-1].double() - want).norm() / want.norm()) < 4 * BOUND
+    assert all(torch.equal(o, outs[0]) for o in outs)
+    with pytest.raises(hch.HchError) as e:
+        hch.hch_sconv_bwd_data(lv, 0, F, 2, hch.HCH_F32, G, W, outs[0], field_t, ci, co, _workspace(need)[:need - 256])
+    assert e.value.status == 6
