@@ -672,6 +672,26 @@ def test_unpool(oracle, case_batch64):
     assert np.array_equal(dP.cpu().numpy(), oracle.unpool_max_bwd(oracle.to_paper_X(G), swo).T.astype(np.float32))
 
 
+@pytest.mark.parametrize("c", [1, 4, 64])
+@pytest.mark.parametrize("shifted", ["", "switches", "result", "gradient"])
+def test_unpool_backward_forms(oracle, case_batch64, c, shifted):
+    """unpool_bwd_kernel with four channels to a thread and with one: by the channels, and where the switches or the result do
+    not start at 16 bytes.  Some switches are -1 (no child)."""
+    lf, lc = case_batch64.olv[0], case_batch64.olv[1]
+
+    def place(a, shift):
+        t = torch.empty(a.size + 4, dtype=torch.from_numpy(a).dtype, device="cuda")[shift:shift + a.size].view(a.shape)
+        t.copy_(torch.from_numpy(a))
+        return t
+    sw = oracle.pool_max_fwd(lf, lc, oracle.to_paper_X(S.gaussian((lf.Ntot, c), 1.0, 90)))[1].T.astype(np.int32)
+    sw[5::97] = -1
+    G = S.gaussian((lf.Ntot, c), 1.0, 91)
+    want = np.where(sw >= 0, np.take_along_axis(G, np.maximum(sw, 0), 0), np.float32(0))
+    dP = place(np.full((lc.Ntot, c), np.nan, np.float32), int(shifted == "result"))
+    hch.hch_unpool_bwd(case_batch64.glv, 0, place(G, int(shifted == "gradient")), place(np.ascontiguousarray(sw), int(shifted == "switches")), dP, c)
+    assert np.array_equal(dP.cpu().numpy(), want)
+
+
 # --------------------------------------------------------------------------------------
 # tables constructed on the device: valid, and every lookup through them is the same
 # --------------------------------------------------------------------------------------

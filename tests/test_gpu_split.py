@@ -434,7 +434,8 @@ def test_operands_of_two_gigabytes(oracle, batch, level, wide, narrow):
 @pytest.mark.parametrize("F,stride,pad", [(2, 2, 0), (3, 2, 1), (3, 4, 1), (3, 1, 1)])
 @pytest.mark.parametrize("ci,co", [(18, 33), (20, 130), (33, 50), (64, 64)])
 def test_products_over_general_index_rows(batch, F, stride, pad, ci, co):
-    """field_split_kernel, forward and data gradient: 126 665 rows (the last workgroup has 201), index rows in any order,
+    """field_split_kernel, data gradient and, within a level, forward (between levels there are too few rows here for
+    it, see test_products_between_two_large_levels): 126 665 rows (the last workgroup has 201), index rows in any order,
     rows without a single tap among them, channel counts with remainders; with the queried workspace and, on the ways
     taken without room for the cut weights, with less.  An infinity reaches the rows that hold it and no others."""
     lv = batch[0]
@@ -539,6 +540,111 @@ def _sconv(lv, kind, F, stride, A, W, n, idx, ci, co):
 def halves():
     coords, offs, _ = S.config_batch(4)
     return hch.hch_build_levels_device(coords, offs, 256, 2)
+
+
+@pytest.mark.parametrize("F,pad,ci,co,fwd,bwd", [(3, 1, 16, 32, "2, false", "1, true"), (3, 1, 50, 13, "1, false", "4, true"),
+                                                (3, 1, 7, 50, None, "1, true"), (3, 1, 32, 16, "1, false", "2, true"),
+                                                (2, 0, 64, 20, "2, false", None), (2, 0, 18, 40, None, "2, true"),
+                                                (2, 0, 32, 64, "4, false", "2, true")])
+def test_products_between_two_large_levels(halves, F, pad, ci, co, fwd, bwd):
+    """field_split_kernel between two levels, the forward product with more rows in X than in the result and the data
+    gradient with fewer: 16, 32 and 64 columns to a workgroup, 27 and 8 taps, channels with remainders.  None: the product
+    goes another way."""
+    lv = halves
+    n_in, n_out = lv.n(0), lv.n(1)
+    assert n_in >= 262144 and n_out >= 98304
+    field, field_t = (torch.empty((n, F ** 3), dtype=torch.int32, device="cuda") for n in (n_out, n_in))
+    hch.hch_field_build(lv, 0, F, 2, pad, field, field_t)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(F * 100 + ci)
+    X, G, W = (torch.randn(s, device="cuda", generator=g) for s in ((n_in, ci), (n_out, co), (F ** 3, ci, co)))
+    for kind, A, idx, w, n, form in ((hch.HCH_WS_FWD, X, field, W, n_out, fwd), (hch.HCH_WS_BWD_DATA, G, field_t, W.transpose(1, 2), n_in, bwd)):
+        out, names = _sconv(lv, kind, F, 2, A, W, n, idx, ci, co)
+        assert [x for x in names if x.startswith("field_split")] == ([f"field_split_kernel<{form}>"] if form else []), names
+        want = _gathered(A, idx, w)
+        # the other ways are the fp32 instruction: a rounding per 4 terms
+        assert float((out.double() - want).norm() / want.norm()) < (BOUND if form else 4 * BOUND)
+        assert float((out.double() - want).abs().max() / want.pow(2).mean().sqrt()) < (30 if form else 120) * BOUND
+
+
+@pytest.fixture(scope="module")
+def fields(batch):
+    """Index rows of 3^3 fields of level 0: within it (forward) and from level 1 (data gradient of stride 2)."""
+    lv = batch[0]
+    within, between = (torch.empty((lv.n(0), 27), dtype=torch.int32, device="cuda") for _ in range(2))
+    hch.hch_field_build(lv, 0, 3, 1, 1, within, None)
+    hch.hch_field_build(lv, 0, 3, 2, 1, None, between)
+    return within, between
+
+
+def _both_products(lv, fields, X, G, W):
+    """Forward within level 0 and data gradient from level 1, each with its exact result and its index rows."""
+    ci, co = W.shape[1:]
+    for kind, stride, A, idx, w in ((hch.HCH_WS_FWD, 1, X, fields[0], W), (hch.HCH_WS_BWD_DATA, 2, G, fields[1], W.transpose(1, 2))):
+        out, names = _sconv(lv, kind, 3, stride, A, W, lv.n(0), idx, ci, co)
+        assert any(x.startswith("field_split_kernel") for x in names), names
+        yield out, A, idx, w
+
+
+@pytest.mark.parametrize("a,b", [(1e-30, 1.0), (1e30, 1e-30), (1e-36, 1.0), (1.0, 1e-36), (1e-40, 1e20), (1e20, 1e-40), (1e15, 1e15)])
+def test_ends_of_the_range_over_general_index_rows(batch, fields, a, b):
+    """As test_ends_of_the_range and, with 1e15, test_sums_beyond_the_scaled_range, for field_split_kernel."""
+    lv = batch[0]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    X, G, W = (torch.randn(s, device="cuda", generator=g) for s in ((lv.n(0), 50), (lv.n(1), 50), (27, 50, 50)))
+    for out, A, idx, w in _both_products(lv, fields, X * a, G * a, W * b):
+        want = _gathered(A, idx, w)
+        assert float((out.double() - want).norm() / want.norm()) < BOUND
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.2e38])
+def test_weights_that_are_not_finite_over_general_index_rows(batch, fields, value):
+    """One weight: exactly the results that it takes part in are not finite (or as large as they come)."""
+    lv = batch[0]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(12)
+    X, G, W = (t + torch.copysign(torch.full_like(t, 0.01), t) for t in
+               (torch.randn(s, device="cuda", generator=g) for s in ((lv.n(0), 50), (lv.n(1), 50), (27, 50, 50))))
+    B = W.clone()
+    B[4, 7, 9] = value
+    for (out, A, idx, w), column in zip(_both_products(lv, fields, X, G, B), (9, 7)):
+        want = _gathered(A, idx, w.where(torch.isfinite(w) & (w.abs() < 1e38), torch.zeros_like(w)))
+        hit = torch.zeros_like(out, dtype=torch.bool)
+        hit[idx[:, 4] >= 0, column] = True
+        assert bool(hit.any()) and bool(torch.isfinite(out[~hit]).all())
+        assert float((out.double() - want)[~hit].norm() / want.norm()) < BOUND
+        assert bool((~torch.isfinite(out[hit]) | (out[hit].abs() > 1e35)).all())
+
+
+@pytest.mark.parametrize("ci,co,fwd,bwd", [(32, 32, "2, 32, false", "2, 32, true"), (96, 20, "2, 32, false", None), (20, 96, None, "2, 32, true"),
+                                          (64, 64, "4, 64, false", "4, 64, true")])
+def test_bf16_weights_that_are_not_finite(large, ci, co, fwd, bwd):
+    """The forms of conv_bf16_kernel with steps of 32 channels and 32 columns (and one other): an infinite weight reaches the
+    rows that have its tap, in its column.  (Rows without the tap have 0 * inf there or leave the tap out, as their tile
+    has it: not looked at.)  Everything else is as with a finite weight, to the bit."""
+    lv, n = large, large.n(0)
+    assert n >= 196608
+    nbr = torch.from_numpy(lv.info(0).device_nbr27()).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ci * 1000 + co)
+    X, G, W = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((n, ci), (n, co), (27, ci, co)))
+    B = W.clone()
+    B[4, 7, 9] = float("inf")
+    for name, kind, A, w, tap, row, column, form in (("hch_conv_fwd", hch.HCH_WS_FWD, X, W, 4, 7, 9, fwd),
+                                                     ("hch_conv_bwd_data", hch.HCH_WS_BWD_DATA, G, W.flip(0).transpose(1, 2), 22, 9, 7, bwd)):
+        ws = _workspace(hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_BF16, kind, hch.HCH_ALGO_FUSED))
+        outs = [torch.full((n, w.shape[2]), float("nan"), device="cuda") for _ in range(2)]
+        for weights, out in zip((W, B), outs):
+            names = _launched(lambda: getattr(hch, name)(lv, 0, hch.HCH_BF16, A, weights, out, ci, co, ws, hch.HCH_ALGO_FUSED))
+            assert [x for x in names if x.startswith("conv_bf16")] == ([f"conv_bf16_kernel<{form}>"] if form else []), names
+        want = _gathered(A, nbr, w)
+        assert float((outs[0].double() - want).norm() / want.norm()) < BOUND
+        has = nbr[:, tap] >= 0
+        x = A[nbr[has, tap].long(), row].float()
+        assert torch.equal(outs[1][has, column][x != 0], (torch.sign(x) * float("inf"))[x != 0])
+        others = [c for c in range(w.shape[2]) if c != column]
+        assert torch.equal(outs[1][:, others], outs[0][:, others])
 
 
 @pytest.fixture(scope="module")
