@@ -322,7 +322,7 @@ def main():
         traffic = counter-measured HBM bytes per launch from the committed summary; null when
         that summary was measured on other sources than the ones running now."""
         ai = st["flops"] / max(1.0, st["bytes"])
-        product = any(t in name for t in ("gemm", "conv_direct", "conv_narrow4", "conv_split", "wgrad_"))
+        product = any(t in name for t in ("gemm", "conv_direct", "conv_narrow4", "conv_split", "conv_bf16", "field_split", "wgrad_"))
         if product and ai >= mfma_peak(name) * 1e12 / (HBM_PEAK_GBS * 1e9):
             bound, achieved, peak, unit = "mfma", st["flops"] / (st["ms"] * 1e-3) / 1e12, mfma_peak(name), "TFLOP/s"
         else:

@@ -126,10 +126,11 @@ hch_status hch_build_levels(const int32_t *coords_xyz, const int64_t *model_offs
 /*
  * The same object with the tables CONSTRUCTED ON THE DEVICE (Section 5.2 and the conclusion name
  * GPU construction as future work).  The checks of the positions and the occupancy of the coarser
- * levels run there too (a bit per position; where those are more than 512 MB, on the host); then
+ * levels run there too, with a bit per position; on the host where those bits are more than
+ * 512 MB, many for the few voxels there are (16 KB a voxel and 4 MB a model), or not to be had.  Then
  * one set of launches builds every (level, model) pair: buckets of positions sharing
- * p mod r are placed largest first, all buckets of one size in parallel, each claiming its slots
- * with compare-and-swap and backing off to the next candidate offset on a conflict; pairs that
+ * p mod r are placed largest first, all buckets of one size in parallel, each claiming its slots, a
+ * bit each, with atomics and backing off to the next candidate offset on a conflict; pairs that
  * fail are repeated with the next offset-table side.  Sizes (m, first r, growth of r), table
  * formats and everything computed through the tables (neighbour and child lists, every
  * convolution and pooling result) are the same as with hch_build_levels; the tables themselves
@@ -399,7 +400,9 @@ hch_status hch_unpool_bwd(const hch_levels *levels, int32_t level_out, const flo
  *   hch_sconv_bwd_data    dX[N_in][c_in]   = sum_rows dY[field_t[i][row]] . W[row]^T   (Eq.8 + Alg.2)
  * X / dX live on level_in, Y / dY on the output level; dtype, outputs (fp32, overwritten),
  * workspace rules (256-byte aligned, at least hch_sconv_workspace_bytes) and errors as for
- * hch_conv_*.  With F = 3, S = 1, P = 1 `field` equals nbr27 and the results equal hch_conv_*'s up to
+ * hch_conv_*.  In fp32 the forward product and, on one level, the data gradient also take workspaces
+ * without room for the cut weights that are part of that answer; they then multiply another
+ * way, with other roundings (either way a few 1e-7 of the result).  With F = 3, S = 1, P = 1 `field` equals nbr27 and the results equal hch_conv_*'s up to
  * rounding.
  */
 hch_status hch_field_build(const hch_levels *levels, int32_t level_in, int32_t F, int32_t stride,

@@ -10,7 +10,9 @@ namespace hch {
 // out.  Rows pass through LDS of the wavefront's own, weights through two shared stages, loads run two steps
 // ahead in two sets of registers, as in conv_split_kernel; nothing is cut here.
 // BT: W(t, k, n) = W[26 - t][n][k] (the data gradient's view of the weights), else W[t][k][n].
-// Bound by LDS (136 KB a step of 64 channels and 256 rows, 0.9 us of 1.5 at two workgroups per CU), then by the fills of L1.
+// Bound by waits of the two workgroups per CU, 0.45 of a wavefront's life, on LDS first: it is busy 0.57 of the time (data
+// gradient 0.55), 0.40 (0.33) of that with bank conflicts; matrix pipes 0.18 (0.19), vector pipes 0.21, 64 -> 64 at 280 000
+// rows.
 // Against gemm_bf16_kernel, which multiplies every tap of every row and transposes the weights in a launch of its own or on the
 // way: 64 -> 64 at 280 000 rows 102 -> 73 us and 97 -> 67 (data gradient), at 609 000 205 -> 145 and 193 -> 133.  The same
 // kernel over the rows as they come: 113 and 101, 215 and 192.

@@ -558,7 +558,7 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         if (round >= 24) return fail(HCH_EBUILD, "hch_build_levels_device: perfect hash construction failed");
         const int na = (int)active.size();
         std::vector<hch::PairDesc> desc((size_t)na);
-        int64_t cells = 0, vox = 0, slots = 0, words = 0;       // words of taken bits: never more than slots
+        int64_t cells = 0, vox = 0, slots = 0, words = 0;       // words of taken bits: no more than slots, but 2 where m is 1
         int32_t max_n = 0, max_r3 = 0, max_m3 = 0;
         for (int a = 0; a < na; ++a) {
             PairWork &w = work[active[a]];

@@ -35,8 +35,8 @@ __device__ __forceinline__ void load8(const float *p, int have, float *v)
 // 16 wavefronts share one barrier (202).  Eight wavefronts load and split the weights for twice the rows:
 // 198 -> 187 us.  Forward and data gradient at 280 000 voxels, before (four wavefronts, rows in ascending
 // order, conflicts on half of the LDS reads, half of the threads without weights where there are 32
-// columns) -> now: 32 -> 64 145 and 155 us -> 126 and 130, 64 -> 64 217 and 215 -> 187 and 177, 50 -> 50 232 and 264 ->
-// 185 and 185; gemm_f32_kernel over the coarser row order took 196 and 196, 354 and 365, 1112 and 1117.
+// columns) -> now: 32 -> 64 120 and 140 us -> 107 and 117 (bench.py's shapes 137 and 158 -> 116 and 138), 64 -> 64 210 and 207
+// -> 185 and 175, 50 -> 50 227 and 261 -> 184 and 183; gemm_f32_kernel over the coarser row order took 196 and 196, 354 and 365, 1112 and 1117.
 // FAST: rows of a multiple of 32 channels; a step lies within one tap, offsets that change from step
 // to step are scalar, and a wavefront whose own rows lack the tap sits the step out.  Otherwise any
 // number of channels: a tap is padded to a multiple of 8, with weights of zero.

@@ -37,8 +37,10 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restr
 // their first tap, in LDS, and a wavefront multiplies 16 rows of that order at a time over the taps that those
 // 16 have, in units of 8 channels of one tap, 4 units (32 terms) to an instruction, like conv_split_kernel but with
 // a tap list of its own and without barriers.
-// Bound by the waits of a step (weights from L2, rows, LDS) at 6 wavefronts per SIMD with 16 columns and 4 with more, and by
-// vector instructions (85 a step, 52 of them the cutting of the rows).  Data gradient of 32 -> 16, 3^3, stride 2, 609 000 rows:
+// Bound by vector instructions (85 a step, 52 of them the cutting of the rows) with 16 columns, at 6 wavefronts per SIMD: the
+// pipes issue 0.86 of the cycles, matrix pipes 0.11, LDS 0.29 (data gradient of 16 -> 32, 3^3, stride 2, 609 000 rows).  With
+// more columns, at 4, by the waits of a step as well (weights from L2, rows, LDS): 0.63, 0.21 and 0.21 (its forward
+// product).  Data gradient of 32 -> 16, 3^3, stride 2, 609 000 rows:
 // 84 us, where the gradient of the column matrix and its gather took 208; forward 197 000 rows 32 -> 64 229 -> 175.  More
 // requests ahead (rows two steps, weights one) at 4 wavefronts per SIMD were slower: 104 us and 188.
 constexpr int FIELD_ROWS = 256, FIELD_WAVES = 8;
