@@ -2411,13 +2411,16 @@ extern "C" hch_status hch_pool_bwd(const hch_levels *levels, int32_t level_in, c
     {
         const Level &Lf = levels->lv[level_in];
         const double bytes = (double)Lc.n_total * (32.0 + 8.0 * c) + (double)Lf.n_total * 4.0 * c;
-        hch::LaunchTimer lt(vec ? HCH_KERNEL_ID("pool_bwd_kernel<4>") : HCH_KERNEL_ID("pool_bwd_kernel<1>"), (hipStream_t)stream, bytes, 0.0);
-        if (vec)
-            HCH_LAUNCH(hch::pool_bwd_kernel<4>, dim3(blocks_for(items)), dim3(256), 0, (hipStream_t)stream,
-                               dY, argmax, Lc.dchild, dX, Lc.n_total, c);
-        else
-            HCH_LAUNCH(hch::pool_bwd_kernel<1>, dim3(blocks_for(items)), dim3(256), 0, (hipStream_t)stream,
-                               dY, argmax, Lc.dchild, dX, Lc.n_total, c);
+        const bool few = items < hch::POOL_BWD_FEW;
+#define HCH_POOL_BWD(VEC_, KIDS_)                                                                                     \
+        do {                                                                                                          \
+            hch::LaunchTimer lt(HCH_KERNEL_ID("pool_bwd_kernel<" #VEC_ ", " #KIDS_ ">"), (hipStream_t)stream, bytes, 0.0); \
+            HCH_LAUNCH((hch::pool_bwd_kernel<VEC_, KIDS_>), dim3(blocks_for(items * (8 / KIDS_))), dim3(256), 0,      \
+                               (hipStream_t)stream, dY, argmax, Lc.dchild, dX, Lc.n_total, c);                        \
+        } while (0)
+        if (vec) { if (few) HCH_POOL_BWD(4, 1); else HCH_POOL_BWD(4, 8); }
+        else { if (few) HCH_POOL_BWD(1, 1); else HCH_POOL_BWD(1, 8); }
+#undef HCH_POOL_BWD
     }
     HCH_LAUNCH_CHECK("pool_bwd_kernel");
     return HCH_OK;

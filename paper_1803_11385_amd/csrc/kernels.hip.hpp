@@ -1719,29 +1719,38 @@ __device__ __forceinline__ void row_unit(int64_t item, int64_t items, int cu, in
     else { row = item / cu; u = (int)(item - row * cu); }
 }
 
-// One thread per (coarse voxel, channel unit): gradient, switches and the eight children are read once; every
-// fine row is the child of exactly one coarse voxel, so this writes all of dX exactly once (the zero fill is part of it).
-// Bound by the rows out.  82 000 coarse voxels of 64 channels (117 MB in all): 41 us with a thread per child, so 21.
-template <int VEC>
+// One thread per (coarse voxel, channel unit) and KIDS of the eight children.  With all 8, gradient, switches and children are
+// read once; every fine row is the child of exactly one coarse voxel, so this writes all of dX exactly once (the zero fill
+// is part of it).  Bound by the rows out: 82 000 coarse voxels of 64 channels (117 MB in all) 28 us with a thread per child, 19 with
+// 8; where that leaves the chip empty (below POOL_BWD_FEW threads) by eight stores one after the other: 1300 coarse
+// voxels of 16 channels 3.0 and 3.8 us, 12 000 (49 000 threads with 8) 3.5 and 4.0, 12 000 of 6 (73 000) 3.7 and 3.6.
+constexpr int64_t POOL_BWD_FEW = 65536;
+template <int VEC, int KIDS>
 __global__ __launch_bounds__(256) void pool_bwd_kernel(
     const float *__restrict__ dY, const int32_t *__restrict__ argmax,
     const int32_t *__restrict__ child8, float *__restrict__ dX, int64_t n_coarse, int c)
 {
+    static_assert(KIDS == 8 || KIDS == 1, "all of them, or one");
     const int cu = c / VEC;
-    const int64_t item = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (item >= n_coarse * cu) return;
-    int64_t o;
+    const int64_t item = (int64_t)blockIdx.x * 256 + threadIdx.x, items = n_coarse * (8 / KIDS) * cu;
+    if (item >= items) return;
+    int64_t row;                                     // the coarse voxel's, or its child's
     int u;
-    row_unit(item, n_coarse * cu, cu, o, u);
-    const int4 k0 = reinterpret_cast<const int4 *>(child8)[2 * o], k1 = reinterpret_cast<const int4 *>(child8)[2 * o + 1];
-    const int32_t kids[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
+    row_unit(item, items, cu, row, u);
+    const int64_t o = KIDS == 8 ? row : row >> 3;
+    int32_t kids[KIDS];
+    if constexpr (KIDS == 8) {
+        const int4 k0 = reinterpret_cast<const int4 *>(child8)[2 * o], k1 = reinterpret_cast<const int4 *>(child8)[2 * o + 1];
+        kids[0] = k0.x; kids[1] = k0.y; kids[2] = k0.z; kids[3] = k0.w;
+        kids[4] = k1.x; kids[5] = k1.y; kids[6] = k1.z; kids[7] = k1.w;
+    } else kids[0] = child8[row];
     const float *g = dY + o * c + u * VEC;
     const int32_t *a = argmax + o * c + u * VEC;
     if constexpr (VEC == 4) {
         const f32x4 gv = *reinterpret_cast<const f32x4 *>(g);
         const int4 av = *reinterpret_cast<const int4 *>(a);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < KIDS; ++k) {
             const int32_t j = kids[k];
             if (j >= 0)
                 *reinterpret_cast<f32x4 *>(dX + (int64_t)j * c + u * 4) = f32x4{av.x == j ? gv[0] : 0.f, av.y == j ? gv[1] : 0.f,
@@ -1751,7 +1760,7 @@ __global__ __launch_bounds__(256) void pool_bwd_kernel(
         const float gv = *g;
         const int32_t av = *a;
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+        for (int k = 0; k < KIDS; ++k)
             if (kids[k] >= 0) dX[(int64_t)kids[k] * c + u] = av == kids[k] ? gv : 0.f;
     }
 }

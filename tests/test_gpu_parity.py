@@ -692,6 +692,31 @@ def test_unpool_backward_forms(oracle, case_batch64, c, shifted):
     assert np.array_equal(dP.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("c,name", [(1, "1, 1"), (4, "4, 1"), (7, "1, 8"), (64, "4, 8"), (27, "4, 8 shifted")])
+def test_pool_backward_forms(oracle, case_batch64, c, name):
+    """pool_bwd_kernel with a thread per child and with one for all eight, each with one and four channels; by the kernel's name."""
+    lf, lc = case_batch64.olv[0], case_batch64.olv[1]
+    c = c + 1 if name.endswith("shifted") else c
+    sw = oracle.pool_max_fwd(lf, lc, oracle.to_paper_X(S.gaussian((lf.Ntot, c), 1.0, 92)))[1].T.astype(np.int32)
+    sw[3::89] = -1
+    G = S.gaussian((lc.Ntot, c), 1.0, 93)
+    want = oracle.pool_max_bwd(lf.Ntot, oracle.to_paper_X(G), np.ascontiguousarray(sw.T)).T.astype(np.float32)
+    dX = torch.full((lf.Ntot, c), float("nan"), dtype=torch.float32, device="cuda")
+    if name.endswith("shifted"):                            # 28 channels, gradients that do not start at 16 bytes
+        dY = torch.empty(G.size + 1, dtype=torch.float32, device="cuda")[1:].view(G.shape)
+        dY.copy_(dev(G))
+        name = "1, 8"
+    else:
+        dY = dev(G)
+    hch.hch_profile_reset()
+    hch.hch_profile_enable(-1, True)
+    hch.hch_pool_bwd(case_batch64.glv, 0, dY, dev(np.ascontiguousarray(sw)), dX, c)
+    torch.cuda.synchronize()
+    hch.hch_profile_enable(-1, False)
+    assert [n for n in (hch.hch_kernel_name(i) for i in range(hch.hch_kernel_count()) if hch.hch_profile_read(i)["launches"])] == [f"pool_bwd_kernel<{name}>"]
+    assert np.array_equal(dX.cpu().numpy(), want)
+
+
 # --------------------------------------------------------------------------------------
 # tables constructed on the device: valid, and every lookup through them is the same
 # --------------------------------------------------------------------------------------
