@@ -1895,11 +1895,11 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     if (n < (c % 64 == 0 && N > 32 ? 98304 : 196608)) return false;
     // It lives on the taps that a tile's rows leave out: of 27, 256 rows of thin shells (9 neighbours a voxel) have 10 to 16, of
     // thick ones (17) 18 to 20.  Times over those of gemm_bf16_kernel, index lists also tap-major (which that kernel is faster with) or
-    // not, at 0.25 to 1.3 million rows: 9 to 10.6 neighbours 0.58 to 0.97 and 0.56 to 0.91 (64 -> 32 at 10.6 1.02); spheres' shells, 14
-    // neighbours, 64 -> 64 0.98 to 1.06 and 0.93 to 0.98, 64 -> 32 1.07 to 1.19 and 0.92 to 1.04; 17 to 18, 64 -> 64 0.92 to 1.15 and 0.84
+    // not, at 0.25 to 1.3 million rows: 9 to 10.6 neighbours 0.53 to 0.96 and 0.51 to 0.91 (64 -> 32 at 10.6 1.02); spheres' shells, 14
+    // neighbours, 64 -> 64 0.96 to 1.06 and 0.93 to 0.98, 64 -> 32 1.07 to 1.19 and 0.92 to 1.04; 17 to 18, 64 -> 64 0.92 to 1.15 and 0.90
     // to 1.07, 128 -> 128 1.02 to 1.23 and 0.84 to 1.10, 64 -> 32 0.95 to 1.37 and 0.85 to 1.16; 21, 64 -> 64 1.10 to 1.15.  Rows that are no
     // multiple of 64 channels, for which gemm_bf16_kernel has the slower loop, to 64 columns and more: 17 to 18, 32 -> 64 0.88
-    // to 1.05, 96 -> 96 0.79 to 1.01; 19 to 21, 32 -> 64 1.02 to 1.13.
+    // to 1.05, 96 -> 96 0.79 to 1.02; 19 to 21, 32 -> 64 1.00 to 1.08, 26 1.13.
     const double neighbours = (double)L.nbr_valid / (double)n;
     if (neighbours > (N < 64 ? 11 : (c % 64 ? 18 : (L.dnbr_t ? 11 : 15)))) return false;
     // Up to the last-level cache: the order scatters the rows that a tile reads over the whole of X.  (Thin shells would gain
