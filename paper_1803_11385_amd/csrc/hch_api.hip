@@ -127,8 +127,9 @@ void free_level(Level &L)
     L.dT = nullptr; L.dPhi = nullptr; L.dslot3 = L.dphi4 = nullptr;
 }
 
-inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline unsigned blocks_for(int64_t items) { return (unsigned)((items + 255) / 256); }
 
 // levels with a fine order (see corner_key): below, what it saves no longer pays for its launches
@@ -454,99 +455,11 @@ static hch_status device_occupancy(hch_levels *hl, const int32_t *coords, const 
     return HCH_OK;
 }
 
-// Fills, for every level: mbar, rbar, attempts, M, R, m_total, r_total, the device tables dH, dT,
-// dV, dPhi, dslot3, dphi4, dcoords, dmeta and the host copies.  Levels must have ubar, b, N, n_total and, unless
-// `occ` has them, coords.
-static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s)
+// Offsets of every table by launches over memory, H* and T* with them.
+template <typename Fn>
+static hch_status place_in_memory(hch_levels *hl, std::vector<PairWork> &work, DeviceBlocks &tmp, Fn &host_copies, hipStream_t s)
 {
-    const int n_levels = (int)hl->lv.size();
-    const int batch = hl->lv[0].b;
-    DeviceBlocks tmp;
-    std::vector<PairWork> work;
     hch_status st;
-    for (int l = 0; l < n_levels; ++l) {
-        Level &L = hl->lv[l];
-        L.mbar.assign((size_t)batch, 0); L.rbar.assign((size_t)batch, 0); L.attempts.assign((size_t)batch, 0);
-        L.M.assign((size_t)batch + 1, 0); L.R.assign((size_t)batch + 1, 0);
-        for (int v = 0; v < batch; ++v) {
-            const int64_t n = L.N[v + 1] - L.N[v];
-            const int m = hch::hash_side(n);
-            if (m > 256) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: a model needs a hash table side above 256");
-            L.mbar[v] = m;
-            L.M[v + 1] = L.M[v] + (int64_t)m * m * m;
-            work.push_back(PairWork{l, v, (int32_t)n, m, hch::offset_side_first(n, m), 0, nullptr, false});
-        }
-        L.m_total = L.M[batch];
-        if (L.m_total >= ((int64_t)1 << 31)) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: super table exceeds 32-bit indexing");
-    }
-    // what the level set keeps and whose size is known now, in one allocation (one by one the
-    // allocations and frees of a build took 6 ms); H* and T* first, so that one fill empties them, then the
-    // positions, so that one copy brings all of them to the host
-    size_t copied = 0;
-    auto lay = [&](Pieces &P, size_t *tables) {
-        for (Level &L : hl->lv) { P.take(L.dH, (size_t)L.m_total * 4); P.take(L.dT, (size_t)L.m_total * 6); }
-        *tables = P.used;
-        for (int l = 1; l < n_levels; ++l) P.take(hl->lv[l].dcoords, (size_t)hl->lv[l].n_total * 12);
-        copied = P.used;
-        P.take(hl->lv[0].dcoords, (size_t)hl->lv[0].n_total * 12);
-        for (Level &L : hl->lv) {
-            const size_t n = (size_t)L.n_total;
-            P.take(L.dV, (size_t)L.m_total * 4);
-            P.take(L.dslot3, (size_t)L.m_total * 4 * hch::SLOT_WORDS);
-            P.take(L.dnbr, n * 27 * 4);
-            if (&L != &hl->lv[0] && L.ratio == 2) P.take(L.dchild, n * 8 * 4);
-            P.take(L.dmask27, std::max<size_t>(n, 64) * 4);
-            P.take(L.dtilemask, std::max<size_t>((n + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE, 64) * 4);
-        }
-    };
-    {
-        Pieces size, place;
-        size_t tables = 0;
-        lay(size, &tables);
-        void *block = nullptr;
-        hipError_t e = device_malloc(&block, size.used);
-        if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-        hl->blocks.push_back(block);
-        place.base = (char *)block;
-        for (Level &L : hl->lv) L.in_block = true;
-        lay(place, &tables);
-        HCH_HIP(hipMemsetAsync(block, 0xFF, tables, s));      // H* = -1: free slot; T* = 0xFFFF: no position
-        if (!occ.ready) {
-            for (Level &L : hl->lv) HCH_HIP(hipMemcpyAsync(L.dcoords, L.coords.data(), L.coords.size() * 4, hipMemcpyHostToDevice, s));
-        } else {
-            HCH_HIP(hipMemcpyAsync(hl->lv[0].dcoords, occ.d_coords, (size_t)hl->lv[0].n_total * 12, hipMemcpyDeviceToDevice, s));
-            hch::OccupancyOut out{};
-            for (int l = 1; l < n_levels; ++l) out.coords[l] = hl->lv[l].dcoords;
-            if (n_levels > 1) {
-                HCH_HIP(hipMemcpyAsync(occ.d_first, occ.first.data(), occ.first.size() * 4, hipMemcpyHostToDevice, s));
-                HCH_LAUNCH(hch::occupancy_list_kernel, dim3((unsigned)occ.set.block_off[n_levels]), dim3(hch::OCC_WORDS), 0, s, occ.set,
-                           (const unsigned long long *)occ.d_bits, (const int32_t *)occ.d_sums, (const int32_t *)occ.d_first, out);
-                HCH_LAUNCH_CHECK("occupancy_list_kernel");
-            }
-        }
-    }
-    // The host copies: a mirror of the first `copied` bytes, the finest positions, V*.  Fresh memory costs more to
-    // touch than to fill, so that is done while the device builds.
-    const char *const mirrored = (const char *)hl->lv[0].dH;
-    auto host_copies = [&]() {
-        const size_t finest = (size_t)hl->lv[0].n_total * 12;
-        size_t slots = 0;
-        for (const Level &L : hl->lv) slots += (size_t)L.m_total;
-        hl->host_block.reset(new char[copied + finest + slots * 4]);
-        char *h = hl->host_block.get();
-        for (size_t at = 0; at < copied; at += 4096) h[at] = 0;
-        memcpy(h + copied, occ.ready ? occ.host_coords : hl->lv[0].coords.data(), finest);
-        int32_t *V = (int32_t *)(h + copied + finest);
-        for (Level &L : hl->lv) {
-            L.hH = (const int32_t *)(h + ((const char *)L.dH - mirrored));
-            L.hT = (const uint16_t *)(h + ((const char *)L.dT - mirrored));
-            L.hcoords = (const int32_t *)(&L == &hl->lv[0] ? h + copied : h + ((const char *)L.dcoords - mirrored));
-            L.hV = V;
-            for (int v = 0; v < batch; ++v) std::fill(V + L.M[v], V + L.M[v + 1], v);
-            V += L.m_total;
-            std::vector<int32_t>().swap(L.coords);
-        }
-    };
     const int n_pairs = (int)work.size();
     int32_t *d_fail = nullptr;
     if ((st = tmp.get((void **)&d_fail, (size_t)n_pairs * 4)) != HCH_OK) return st;
@@ -650,6 +563,199 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         }
         active.swap(again);
     }
+    return HCH_OK;
+}
+
+// Offsets of every table by a workgroup each (psh_build_kernel).  Up to three sides at once where that leaves a CU to each: the
+// second is needed by a third of the tables, the third by one or two of a batch, and they are known at the same time.
+constexpr int SIDES_AT_ONCE = 3;
+template <typename Fn>
+static hch_status place_in_lds(hch_levels *hl, std::vector<PairWork> &work, DeviceBlocks &tmp, Fn &host_copies, hipStream_t s)
+{
+    hch_status st;
+    const int n_pairs = (int)work.size();
+    std::vector<int> active((size_t)n_pairs);
+    for (int i = 0; i < n_pairs; ++i) active[i] = i;
+    for (int round = 0; !active.empty(); ++round) {
+        if (round >= 24) return fail(HCH_EBUILD, "hch_build_levels_device: perfect hash construction failed");
+        const int na = (int)active.size(), at_once = std::max(1, std::min(SIDES_AT_ONCE, 256 / na));
+        std::vector<hch::AttemptDesc> desc;
+        std::vector<int> pair_of;
+        int64_t cells = 0, vox = 0;
+        size_t lds = 0;
+        for (int a = 0; a < na; ++a) {
+            const PairWork &w = work[active[a]];
+            const Level &L = hl->lv[w.l];
+            int r = w.r;
+            for (int k = 0; k < at_once; ++k, r = hch::offset_side_next(r, w.m)) {
+                if (k > 0 && r > 100) break;                  // no memory for a second side that is large
+                if (r > 1024 || r > 2 * L.ubar + 1) {         // beyond one cell per grid position nothing can improve
+                    if (k == 0) return fail(HCH_EBUILD, "hch_build_levels_device: perfect hash construction failed");
+                    break;
+                }
+                desc.push_back(hch::AttemptDesc{L.dcoords + 3 * L.N[w.v], w.n, w.m, r, (int32_t)cells, (int32_t)vox});
+                pair_of.push_back(active[a]);
+                const int64_t r3 = (int64_t)r * r * r;
+                cells += r3; vox += w.n;
+                lds = std::max({lds, (size_t)w.m * w.m * 32, r3 * 4 <= hch::PSH_LDS_BYTES ? (size_t)r3 * 4 : (size_t)0});
+            }
+        }
+        if (cells >= ((int64_t)1 << 31) / hch::PSH_CLASSES || vox >= ((int64_t)1 << 31))
+            return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: offset tables exceed 32-bit indexing");
+        hch::AttemptDesc *d_desc = nullptr;
+        int32_t *d_ok = nullptr, *d_cnt = nullptr, *d_first = nullptr, *d_rank = nullptr;
+        uint32_t *d_phi = nullptr, *d_res = nullptr;
+        uint4 *d_list = nullptr;
+        auto lay_round = [&](Pieces &P, size_t *zeroed) {
+            P.take(d_phi, (size_t)cells * 4);
+            *zeroed = P.used;
+            P.take(d_ok, desc.size() * 4);
+            P.take(d_desc, desc.size() * sizeof(hch::AttemptDesc));
+            P.take(d_cnt, (size_t)cells * 4);
+            P.take(d_first, (size_t)cells * 4);
+            P.take(d_list, (size_t)cells * sizeof(uint4));
+            P.take(d_rank, (size_t)vox * 4);
+            P.take(d_res, (size_t)vox * 4);
+        };
+        Pieces size, place;
+        size_t zeroed = 0;
+        lay_round(size, &zeroed);
+        if ((st = tmp.get((void **)&place.base, size.used)) != HCH_OK) return st;
+        lay_round(place, &zeroed);
+        HCH_HIP(hipMemsetAsync(d_phi, 0, zeroed, s));          // unused cells keep (0, 0, 0)
+        HCH_HIP(hipMemcpyAsync(d_desc, desc.data(), desc.size() * sizeof(hch::AttemptDesc), hipMemcpyHostToDevice, s));
+        const int total = (int)desc.size();
+        HCH_LAUNCH(hch::psh_build_kernel, dim3((unsigned)total), dim3(hch::PSH_THREADS), lds, s, d_desc, d_cnt, d_first, d_phi, d_list, d_rank, d_res,
+                   d_ok, (int)lds);
+        HCH_LAUNCH_CHECK("psh_build_kernel");
+        if (round == 0) host_copies();
+        std::vector<int32_t> ok((size_t)total);
+        HCH_HIP(hipMemcpyAsync(ok.data(), d_ok, (size_t)total * 4, hipMemcpyDeviceToHost, s));
+        HCH_HIP(hipStreamSynchronize(s));
+        std::vector<int> again;
+        for (int q = 0; q < total; ++q) {
+            PairWork &w = work[pair_of[q]];
+            if (w.done) continue;                     // its smaller side was enough
+            ++w.attempts;
+            if (ok[q]) { w.r = desc[q].r; w.phi = d_phi + desc[q].cell_base; w.done = true; }
+            else {
+                w.r = hch::offset_side_next(desc[q].r, w.m);
+                if (q + 1 == total || pair_of[q + 1] != pair_of[q]) again.push_back(pair_of[q]);
+            }
+        }
+        active.swap(again);
+    }
+    return HCH_OK;
+}
+
+// Fills, for every level: mbar, rbar, attempts, M, R, m_total, r_total, the device tables dH, dT,
+// dV, dPhi, dslot3, dphi4, dcoords, dmeta and the host copies.  Levels must have ubar, b, N, n_total and, unless
+// `occ` has them, coords.
+static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s)
+{
+    const int n_levels = (int)hl->lv.size();
+    const int batch = hl->lv[0].b;
+    DeviceBlocks tmp;
+    std::vector<PairWork> work;
+    hch_status st;
+    for (int l = 0; l < n_levels; ++l) {
+        Level &L = hl->lv[l];
+        L.mbar.assign((size_t)batch, 0); L.rbar.assign((size_t)batch, 0); L.attempts.assign((size_t)batch, 0);
+        L.M.assign((size_t)batch + 1, 0); L.R.assign((size_t)batch + 1, 0);
+        for (int v = 0; v < batch; ++v) {
+            const int64_t n = L.N[v + 1] - L.N[v];
+            const int m = hch::hash_side(n);
+            if (m > 256) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: a model needs a hash table side above 256");
+            L.mbar[v] = m;
+            L.M[v + 1] = L.M[v] + (int64_t)m * m * m;
+            work.push_back(PairWork{l, v, (int32_t)n, m, hch::offset_side_first(n, m), 0, nullptr, false});
+        }
+        L.m_total = L.M[batch];
+        if (L.m_total >= ((int64_t)1 << 31)) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: super table exceeds 32-bit indexing");
+    }
+    // what the level set keeps and whose size is known now, in one allocation (one by one the
+    // allocations and frees of a build took 6 ms); H* and T* first, so that one fill empties them, then the
+    // positions, so that one copy brings all of them to the host
+    size_t copied = 0;
+    auto lay = [&](Pieces &P, size_t *tables) {
+        for (Level &L : hl->lv) { P.take(L.dH, (size_t)L.m_total * 4); P.take(L.dT, (size_t)L.m_total * 6); }
+        *tables = P.used;
+        for (int l = 1; l < n_levels; ++l) P.take(hl->lv[l].dcoords, (size_t)hl->lv[l].n_total * 12);
+        copied = P.used;
+        P.take(hl->lv[0].dcoords, (size_t)hl->lv[0].n_total * 12);
+        for (Level &L : hl->lv) {
+            const size_t n = (size_t)L.n_total;
+            P.take(L.dV, (size_t)L.m_total * 4);
+            P.take(L.dslot3, (size_t)L.m_total * 4 * hch::SLOT_WORDS);
+            P.take(L.dnbr, n * 27 * 4);
+            if (&L != &hl->lv[0] && L.ratio == 2) P.take(L.dchild, n * 8 * 4);
+            P.take(L.dmask27, std::max<size_t>(n, 64) * 4);
+            P.take(L.dtilemask, std::max<size_t>((n + hch::PATTERN_TILE - 1) / hch::PATTERN_TILE, 64) * 4);
+        }
+    };
+    {
+        Pieces size, place;
+        size_t tables = 0;
+        lay(size, &tables);
+        void *block = nullptr;
+        hipError_t e = device_malloc(&block, size.used);
+        if (e != hipSuccess) return fail(HCH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        hl->blocks.push_back(block);
+        place.base = (char *)block;
+        for (Level &L : hl->lv) L.in_block = true;
+        lay(place, &tables);
+        HCH_HIP(hipMemsetAsync(block, 0xFF, tables, s));      // H* = -1: free slot; T* = 0xFFFF: no position
+        if (!occ.ready) {
+            for (Level &L : hl->lv) HCH_HIP(hipMemcpyAsync(L.dcoords, L.coords.data(), L.coords.size() * 4, hipMemcpyHostToDevice, s));
+        } else {
+            HCH_HIP(hipMemcpyAsync(hl->lv[0].dcoords, occ.d_coords, (size_t)hl->lv[0].n_total * 12, hipMemcpyDeviceToDevice, s));
+            hch::OccupancyOut out{};
+            for (int l = 1; l < n_levels; ++l) out.coords[l] = hl->lv[l].dcoords;
+            if (n_levels > 1) {
+                HCH_HIP(hipMemcpyAsync(occ.d_first, occ.first.data(), occ.first.size() * 4, hipMemcpyHostToDevice, s));
+                HCH_LAUNCH(hch::occupancy_list_kernel, dim3((unsigned)occ.set.block_off[n_levels]), dim3(hch::OCC_WORDS), 0, s, occ.set,
+                           (const unsigned long long *)occ.d_bits, (const int32_t *)occ.d_sums, (const int32_t *)occ.d_first, out);
+                HCH_LAUNCH_CHECK("occupancy_list_kernel");
+            }
+        }
+    }
+    // The host copies: a mirror of the first `copied` bytes, the finest positions, V*.  Fresh memory costs more to
+    // touch than to fill, so that is done while the device builds.
+    const char *const mirrored = (const char *)hl->lv[0].dH;
+    auto host_copies = [&]() {
+        const size_t finest = (size_t)hl->lv[0].n_total * 12;
+        size_t slots = 0;
+        for (const Level &L : hl->lv) slots += (size_t)L.m_total;
+        hl->host_block.reset(new char[copied + finest + slots * 4]);
+        char *h = hl->host_block.get();
+        for (size_t at = 0; at < copied; at += 4096) h[at] = 0;
+        memcpy(h + copied, occ.ready ? occ.host_coords : hl->lv[0].coords.data(), finest);
+        int32_t *V = (int32_t *)(h + copied + finest);
+        for (Level &L : hl->lv) {
+            L.hH = (const int32_t *)(h + ((const char *)L.dH - mirrored));
+            L.hT = (const uint16_t *)(h + ((const char *)L.dT - mirrored));
+            L.hcoords = (const int32_t *)(&L == &hl->lv[0] ? h + copied : h + ((const char *)L.dcoords - mirrored));
+            L.hV = V;
+            for (int v = 0; v < batch; ++v) std::fill(V + L.M[v], V + L.M[v + 1], v);
+            V += L.m_total;
+            std::vector<int32_t>().swap(L.coords);
+        }
+    };
+    const int n_pairs = (int)work.size();
+    // A workgroup per table, where rows fit 64 bits and the largest table is not most of the work (then a chip full of wavefronts on
+    // that one is as fast).  Whole builds with 3 levels, there and by launches over memory: 40 models of 4000 voxels 0.78 and 1.89 ms, 1 of 3000
+    // 0.46 and 0.80, 1 of 25 000 0.69 and 0.70, 2 of 150 000 1.83 and 2.04; 1 of 90 000 1.45 and 1.38, 1 of 250 000 3.5 and 3.2; rows of
+    // 128 bits, 1 of 400 000 8.0 and 3.8, 4 of them 11 and 16.
+    int32_t widest_m = 0;
+    int64_t largest = 0, all_voxels = 0;
+    for (const PairWork &w : work) {
+        widest_m = std::max(widest_m, w.m);
+        largest = std::max<int64_t>(largest, w.n);
+        all_voxels += w.n;
+    }
+    const bool in_lds = widest_m <= hch::PSH_LDS_SIDE && (largest <= 32768 || all_voxels >= 2 * largest);
+    st = in_lds ? place_in_lds(hl, work, tmp, host_copies, s) : place_in_memory(hl, work, tmp, host_copies, s);
+    if (st != HCH_OK) return st;
 
     // super tables of every level from the pairs' results
     std::vector<hch::PackDesc> pd((size_t)n_pairs);
@@ -664,10 +770,6 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         }
         L.r_total = L.R[batch];
         if (L.r_total >= ((int64_t)1 << 31) / 3) return fail(HCH_EUNSUPPORTED, "hch_build_levels_device: super table exceeds 32-bit indexing");
-        for (int v = 0; v < batch; ++v) {
-            const PairWork &w = work[(size_t)l * batch + v];
-            pd[(size_t)l * batch + v] = hch::PackDesc{w.phi, w.m * w.m * w.m, w.r * w.r * w.r, (int32_t)L.M[v], (int32_t)L.R[v]};
-        }
         meta.insert(meta.end(), L.mbar.begin(), L.mbar.end());
         meta.insert(meta.end(), L.rbar.begin(), L.rbar.end());
         for (int64_t x : L.M) meta.push_back((int32_t)x);
@@ -677,13 +779,13 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
     int32_t *d_meta = nullptr;
     hch::PackDesc *d_pd = nullptr;
     size_t phi_bytes = 0;
-    if ((st = tmp.get((void **)&d_pd, pd.size() * sizeof(hch::PackDesc))) != HCH_OK) return st;
     {
         auto lay_offsets = [&](Pieces &P) {
             for (Level &L : hl->lv) P.take(L.dPhi, (size_t)L.r_total * 3);
             phi_bytes = P.used;
             for (Level &L : hl->lv) P.take(L.dphi4, (size_t)L.r_total * 4);
             P.take(d_meta, meta.size() * 4);
+            P.take(d_pd, pd.size() * sizeof(hch::PackDesc));
         };
         Pieces size, place;
         lay_offsets(size);
@@ -694,20 +796,25 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         place.base = (char *)block;
         lay_offsets(place);
     }
+    int32_t most = 0, widest = 0;
+    for (const PairWork &w : work) {
+        const Level &L = hl->lv[w.l];
+        pd[(size_t)w.l * batch + w.v] = hch::PackDesc{L.dcoords + 3 * L.N[w.v], w.phi, L.dH + L.M[w.v], L.dT + 3 * L.M[w.v],
+                                                      L.dslot3 + hch::SLOT_WORDS * L.M[w.v], L.dphi4 + L.R[w.v], L.dV + L.M[w.v], L.dPhi + 3 * L.R[w.v],
+                                                      w.n, w.m, w.r, w.v};
+        most = std::max(most, w.n);
+        widest = std::max({widest, w.m * w.m * w.m, w.r * w.r * w.r});
+    }
     HCH_HIP(hipMemcpyAsync(d_pd, pd.data(), pd.size() * sizeof(hch::PackDesc), hipMemcpyHostToDevice, s));
     HCH_HIP(hipMemcpyAsync(d_meta, meta.data(), meta.size() * 4, hipMemcpyHostToDevice, s));
-    for (int l = 0; l < n_levels; ++l) {
-        Level &L = hl->lv[l];
-        L.dmeta = d_meta + (size_t)l * meta_len;
-        int32_t widest = 0;
-        for (int v = 0; v < batch; ++v) {
-            const hch::PackDesc &q = pd[(size_t)l * batch + v];
-            widest = std::max(widest, std::max(q.m3, q.r3));
-        }
-        HCH_LAUNCH(hch::psh_pack_kernel, dim3((unsigned)((widest + 255) / 256), (unsigned)batch), dim3(256), 0, s,
-                           d_pd + (size_t)l * batch, L.dH, L.dT, L.dslot3, L.dV, L.dphi4, L.dPhi);
-        HCH_LAUNCH_CHECK("psh_pack_kernel");
+    for (int l = 0; l < n_levels; ++l) hl->lv[l].dmeta = d_meta + (size_t)l * meta_len;
+    // a grid's second side ends at 65535 tables
+    for (int p0 = 0; p0 < n_pairs; p0 += 65535) {
+        const unsigned tables = (unsigned)std::min(65535, n_pairs - p0);
+        if (in_lds) HCH_LAUNCH(hch::psh_emit_kernel, dim3(blocks_for(most), tables), dim3(256), 0, s, (const hch::PackDesc *)d_pd + p0);
+        HCH_LAUNCH(hch::psh_pack_kernel, dim3(blocks_for(widest), tables), dim3(256), 0, s, (const hch::PackDesc *)d_pd + p0);
     }
+    HCH_LAUNCH_CHECK("psh_pack_kernel");
     // host copies for hch_level_info (a thread of its own for the large one was slower: 6.0 instead of 5.3 ms the whole call)
     hl->host_phi.reset(new char[phi_bytes]);
     HCH_HIP(hipMemcpyAsync(hl->host_block.get(), mirrored, copied, hipMemcpyDeviceToHost, s));
