@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -129,6 +130,79 @@ void free_level(Level &L)
 
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Host memory that the device copies into (tables built there, for hch_level_info).  Copies into ordinary memory go by pieces
+// through a buffer of the runtime's and a copy by the host: 11.5 MB of a 256^3 batch of 8 took 1.8 of 4.0 ms, into pinned
+// memory 0.25.  Pinning costs more than that, so blocks of level sets that are gone are kept for the next ones: HOST_KEPT bytes at
+// most, the longest unused given back first; by any thread, since a block has one owner and its copies are over before it is freed.
+// Where there is no pinned memory it is ordinary memory.
+constexpr size_t HOST_KEPT = (size_t)128 << 20, HOST_STEP = (size_t)256 << 10;
+
+class HostBlocks {
+    struct Block { char *p; size_t bytes; };
+    std::mutex mu;
+    std::vector<Block> kept;                   // longest unused first
+    size_t held = 0;
+    void give_back(size_t i)
+    {
+        held -= kept[i].bytes;
+        (void)hipHostFree(kept[i].p);
+        kept.erase(kept.begin() + (std::ptrdiff_t)i);
+    }
+public:
+    static HostBlocks &get() { static HostBlocks *const all = new HostBlocks; return *all; }      // outlives every level set
+    char *take(size_t *bytes)                  // null: none to be had
+    {
+        *bytes = round_up(*bytes, HOST_STEP);
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            size_t best = kept.size();
+            for (size_t i = 0; i < kept.size(); ++i)
+                if (kept[i].bytes >= *bytes && kept[i].bytes <= 4 * *bytes && (best == kept.size() || kept[i].bytes < kept[best].bytes)) best = i;
+            if (best < kept.size()) {
+                char *p = kept[best].p;
+                *bytes = kept[best].bytes;
+                held -= *bytes;
+                kept.erase(kept.begin() + (std::ptrdiff_t)best);
+                return p;
+            }
+        }
+        void *p = nullptr;
+        if (hipHostMalloc(&p, *bytes, hipHostMallocPortable) == hipSuccess) return (char *)p;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void keep(char *p, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        try {
+            kept.push_back(Block{p, bytes});
+            held += bytes;
+        } catch (const std::bad_alloc &) {
+            (void)hipHostFree(p);
+        }
+        while (held > HOST_KEPT) give_back(0);
+    }
+};
+
+class HostBlock {
+    char *p = nullptr;
+    size_t bytes = 0;
+    std::unique_ptr<char[]> ordinary;
+public:
+    HostBlock() = default;
+    HostBlock(const HostBlock &) = delete;
+    HostBlock &operator=(const HostBlock &) = delete;
+    ~HostBlock() { if (p) HostBlocks::get().keep(p, bytes); }
+    char *get() const { return p ? p : ordinary.get(); }
+    bool pinned() const { return p != nullptr; }
+    void make(size_t n)                        // once
+    {
+        bytes = std::max<size_t>(n, 1);
+        p = HostBlocks::get().take(&bytes);
+        if (!p) ordinary.reset(new char[n]);
+    }
+};
+
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline unsigned blocks_for(int64_t items) { return (unsigned)((items + 255) / 256); }
 
@@ -152,7 +226,7 @@ struct hch_levels {
     int32_t *d_tile_hist = nullptr, *d_key_total = nullptr, *d_order = nullptr;
     uint32_t *d_fine = nullptr;                // everything of the fine order, in one allocation
     std::vector<void *> blocks;                // allocations: the orders and prefixes; device construction: what is known before it, and after
-    std::unique_ptr<char[]> host_block, host_phi;   // its host copies: positions, H*, T*, V*; offset tables
+    HostBlock host_block, host_phi;            // its host copies: positions, H*, T*, V*; offset tables
 };
 
 extern "C" const char *hch_last_error(void) { return g_err.c_str(); }
@@ -726,9 +800,9 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         const size_t finest = (size_t)hl->lv[0].n_total * 12;
         size_t slots = 0;
         for (const Level &L : hl->lv) slots += (size_t)L.m_total;
-        hl->host_block.reset(new char[copied + finest + slots * 4]);
+        hl->host_block.make(copied + finest + slots * 4);
         char *h = hl->host_block.get();
-        for (size_t at = 0; at < copied; at += 4096) h[at] = 0;
+        for (size_t at = 0; at < copied && !hl->host_block.pinned(); at += 4096) h[at] = 0;
         memcpy(h + copied, occ.ready ? occ.host_coords : hl->lv[0].coords.data(), finest);
         int32_t *V = (int32_t *)(h + copied + finest);
         for (Level &L : hl->lv) {
@@ -815,8 +889,8 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         HCH_LAUNCH(hch::psh_pack_kernel, dim3(blocks_for(widest), tables), dim3(256), 0, s, (const hch::PackDesc *)d_pd + p0);
     }
     HCH_LAUNCH_CHECK("psh_pack_kernel");
-    // host copies for hch_level_info (a thread of its own for the large one was slower: 6.0 instead of 5.3 ms the whole call)
-    hl->host_phi.reset(new char[phi_bytes]);
+    // host copies for hch_level_info
+    hl->host_phi.make(phi_bytes);
     HCH_HIP(hipMemcpyAsync(hl->host_block.get(), mirrored, copied, hipMemcpyDeviceToHost, s));
     HCH_HIP(hipMemcpyAsync(hl->host_phi.get(), hl->lv[0].dPhi, phi_bytes, hipMemcpyDeviceToHost, s));
     for (Level &L : hl->lv) L.hPhi = (const uint8_t *)(hl->host_phi.get() + (L.dPhi - hl->lv[0].dPhi));
