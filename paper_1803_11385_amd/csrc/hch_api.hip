@@ -208,6 +208,7 @@ inline unsigned blocks_for(int64_t items) { return (unsigned)((items + 255) / 25
 
 // levels with a fine order (see corner_key): below, what it saves no longer pays for its launches
 constexpr int64_t FINE_MIN_VOXELS = 32768;
+static_assert(hch::PATTERN_SMALL < FINE_MIN_VOXELS, "pattern_small_kernel makes no fine order");
 constexpr int64_t MAX_GRID_ITEMS = (int64_t)2147483647 * 256;   // grid.x limit * block size
 
 }  // namespace
@@ -297,7 +298,15 @@ static hch_status launch_index_lists(const hch_levels *hl, int l0, int l1, hipSt
         // pattern order of the levels' voxels (stable counting sort by pattern key), then the tap
         // masks of its 64-row tiles
         const int64_t cnt = (int64_t)hl->sort_off[l1] - hl->sort_off[l0];
-        if (orders && cnt > 0) {
+        int64_t most = 0;
+        for (int l = l0; l < l1; ++l) most = std::max(most, hl->lv[l].n_total);
+        if (orders && cnt > 0 && most <= hch::PATTERN_SMALL) {
+            hch::PatternSmallArgs A{};
+            for (int l = l0; l < l1; ++l) A.tile_mask[l] = hl->lv[l].dtilemask;
+            hch::LaunchTimer lt(HCH_KERNEL_ID("pattern_small_kernel"), s, 17.0 * (double)cnt, 0.0);
+            HCH_LAUNCH(hch::pattern_small_kernel, dim3((unsigned)(l1 - l0)), dim3(1024), 0, s, hl->set, A, l0, hl->d_order);
+            HCH_LAUNCH_CHECK("pattern_small_kernel");
+        } else if (orders && cnt > 0) {
             {
                 hch::LaunchTimer lt(HCH_KERNEL_ID("pattern_scan_kernel"), s, 8.0 * 64.0 * (double)(last - first), 0.0);
                 HCH_LAUNCH(hch::pattern_scan_kernel, dim3(hch::PATTERN_BINS, (unsigned)(l1 - l0)), dim3(256), 0, s, hl->set,

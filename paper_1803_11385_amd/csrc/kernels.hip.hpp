@@ -508,6 +508,99 @@ __global__ __launch_bounds__(256) void pattern_scatter_kernel(
     }
 }
 
+// The sum of what the threads before this one have, in a workgroup of 1024; `total` of all.  `part` holds 16 words.
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t *part, int32_t *total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t s = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t t = __shfl_up(s, d);
+        s += lane >= d ? t : 0;
+    }
+    __syncthreads();
+    if (lane == 63) part[wave] = s;
+    __syncthreads();
+    int32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const int32_t t = part[w];
+        before += w < wave ? t : 0;
+        all += t;
+    }
+    *total = all;
+    return before + s - v;
+}
+
+// Both steps and the tap masks (tile_mask_kernel) for levels of up to PATTERN_SMALL voxels, a workgroup of 1024 per level:
+// keys stay in registers, counts and the neighbour sets by position in LDS.  Bound by its launch and a dozen barriers: three
+// levels of 3177 voxels and less 8.7 us, the three launches 12.6 (and 4 us of the host's time each).
+constexpr int PATTERN_SMALL = 8192;
+struct PatternSmallArgs { uint32_t *tile_mask[MAX_LEVELS]; };
+__global__ __launch_bounds__(1024) void pattern_small_kernel(LevelSet S, PatternSmallArgs A, int level_first, int32_t *__restrict__ order)
+{
+    constexpr int ROUNDS = PATTERN_SMALL / 1024, CHUNKS = ROUNDS * 16;        // chunk: 64 consecutive voxels
+    __shared__ int32_t count[PATTERN_BINS * (CHUNKS + 1)];                    // [key][chunk], then first positions
+    __shared__ uint32_t sorted[PATTERN_SMALL];
+    __shared__ int32_t part[16];
+    const int lev = level_first + (int)blockIdx.x, n = S.n_total[lev], off = S.sort_off[lev];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rounds = (n + 1023) / 1024;
+    for (int q = tid; q < PATTERN_BINS * (CHUNKS + 1); q += 1024) count[q] = 0;
+    __syncthreads();
+    uint32_t key[ROUNDS], mask[ROUNDS];
+    int before[ROUNDS];
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        const int i = q * 1024 + tid;
+        const bool live = i < n;
+        key[q] = live ? S.sort_key[off + i] : 0u;
+        mask[q] = live ? S.mask27[lev][i] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        if (q >= rounds) break;
+        const bool live = q * 1024 + tid < n;
+        unsigned long long same = __ballot(live);         // lanes with the same key (dead lanes match nobody)
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            const unsigned long long bal = __ballot((key[q] >> b) & 1u);
+            same &= ((key[q] >> b) & 1u) ? bal : ~bal;
+        }
+        before[q] = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+        if (live && before[q] == 0) count[key[q] * (CHUNKS + 1) + q * 16 + wave] = __popcll(same);
+    }
+    __syncthreads();
+    // first position of every (key, chunk): a thread adds up ROUNDS chunks of one key
+    int32_t *mine = count + (tid >> 4) * (CHUNKS + 1) + (tid & 15) * ROUNDS, sum = 0, total;
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) sum += mine[q];
+    int32_t run = block_scan(sum, part, &total);
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        const int32_t c = mine[q];
+        mine[q] = run;
+        run += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        const int i = q * 1024 + tid;
+        if (i >= n) break;
+        const int pos = count[key[q] * (CHUNKS + 1) + q * 16 + wave] + before[q];
+        order[off + pos] = i;
+        S.sorted_mask[off + pos] = mask[q];
+        sorted[pos] = mask[q];
+    }
+    __syncthreads();
+    for (int b = wave; b * 64 < n; b += 16) {
+        uint32_t m = b * 64 + lane < n ? sorted[b * 64 + lane] : 0u;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) m |= (uint32_t)__shfl_xor((int)m, d);
+        if (lane == 0) A.tile_mask[lev][b] = m;
+    }
+}
+
 // The fine order: a stable counting sort of the pattern order by corner_key, in the manner of the
 // pattern sort above.  tile_mask_kernel counts the keys of
 // every FINE_TILE positions; one workgroup per (key, level) turns a key's counts into offsets; then

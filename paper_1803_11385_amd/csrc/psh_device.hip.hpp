@@ -598,30 +598,6 @@ __device__ __forceinline__ int psh_mod(int v, int d, float inv)
     return q < 0 ? q + d : q >= d ? q - d : q;
 }
 
-// the sum of what the threads before this one have; `total` of all.  `part` holds 16 words.
-__device__ __forceinline__ int32_t psh_block_scan(int32_t v, int32_t *part, int32_t *total)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t s = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t t = __shfl_up(s, d);
-        s += lane >= d ? t : 0;
-    }
-    __syncthreads();
-    if (lane == 63) part[wave] = s;
-    __syncthreads();
-    int32_t before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < PSH_THREADS / 64; ++w) {
-        const int32_t t = part[w];
-        before += w < wave ? t : 0;
-        all += t;
-    }
-    *total = all;
-    return before + s - v;
-}
-
 // One attempt at one table per workgroup; `ok` receives 1 where every bucket found its place.  cells: cnt, first
 // and phi [cells], list [cells]; voxels: rank and residues.  Dynamic LDS: the larger of the bits and, up to
 // PSH_LDS_BYTES, 4 bytes per offset cell.
@@ -669,7 +645,7 @@ __global__ __launch_bounds__(PSH_THREADS) void psh_build_kernel(
         s += c;
         if (c) atomicAdd(&hist[class_of(c)], 1);
     }
-    int32_t at = psh_block_scan(s, part, &all);
+    int32_t at = block_scan(s, part, &all);
     __syncthreads();
     if (tid == 0)
         for (int k = PSH_CLASSES - 1, q = 0; k >= 1; --k) { cursor[k] = q; q += hist[k]; }     // largest first
@@ -718,7 +694,7 @@ __global__ __launch_bounds__(PSH_THREADS) void psh_build_kernel(
     const int rper = (rows + PSH_THREADS - 1) / PSH_THREADS, q0 = min(tid * rper, rows), q1 = min(q0 + rper, rows);
     int32_t n_free = 0;
     for (int q = q0; q < q1; ++q) n_free += __popcll(~bits[q / m * pitch + q % m] & offsets);
-    int i = psh_block_scan(n_free, part, &all);       // m^3 > n: there are enough
+    int i = block_scan(n_free, part, &all);       // m^3 > n: there are enough
     for (int q = q0; q < q1 && i < n_single; ++q)
         for (unsigned long long vacant = ~bits[q / m * pitch + q % m] & offsets; vacant && i < n_single; vacant &= vacant - 1ull, ++i) {
             const uint4 e = list[n_multi + i];
