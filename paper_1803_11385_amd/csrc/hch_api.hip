@@ -20,6 +20,7 @@
 #include "gemm_bf16.hip.hpp"
 #include "split_wgrad.hip.hpp"
 #include "split_conv.hip.hpp"
+#include "conv_small.hip.hpp"
 #include "split_field.hip.hpp"
 #include "conv_bf16.hip.hpp"
 #include "psh_device.hip.hpp"
@@ -2071,6 +2072,35 @@ static hch_status launch_conv_split(const ConvSplitPlan &p, const Level &L, cons
     return p.splits > 1 ? launch_reduce(part, out, n * N, p.splits, s) : HCH_OK;
 }
 
+// The same products for few voxels (conv_small_kernel).  It reads all weights of its taps once per 16 rows, so the line lies at little
+// work, and for the data gradient, whose weights it reads in pieces of 16 bytes, lower.  Calls one after the other (10 us: what the
+// host takes for one) against conv_split_kernel with the launch that adds its parts: forward 16 -> 32 at 12 000 voxels 9.8 us and 11.1, 32 -> 64 at 3200
+// 10 and 16, at 6000 12.5 and 16.6, at 12 000 22 and 21.5, 64 -> 64 at 3200 16.5 and 21, 64 -> 128 at 800 10.5 and 16, at 3200 28 and 26,
+// 128 -> 256 at 250 18 and 18; data gradient 32 -> 16 at 12 000 10 and 12.5, 64 -> 32 at 3200 12 and 15, at 6000 18 and 16, 64 -> 64 at 800 11
+// and 15, at 3200 20 and 20, 128 -> 64 at 250 18 and 16.  (Tiles of 64 columns 10.2 and 16 with 32 -> 64 and 64 -> 64 at 3200, 16 wavefronts 11.5 and 18.)
+static bool conv_small_faster(int64_t n, int c, int N, bool transposed)
+{
+    if (n * c * 4 >= ((int64_t)1 << 31) || n * 108 >= ((int64_t)1 << 31)) return false;        // 32-bit byte offsets
+    return (int64_t)c * N <= (transposed ? 4096 : 8192) && (double)n * c * N <= (transposed ? 6.5e6 : 12.5e6);
+}
+
+static hch_status launch_conv_small(const Level &L, const float *X, const float *W, float *out, int64_t n, int c, int N, bool transposed,
+                                    double bytes, hipStream_t s)
+{
+    const int nt = N <= 16 ? 1 : 2;
+    const int id = nt == 1 ? (transposed ? HCH_KERNEL_ID("conv_small_kernel<1, true>") : HCH_KERNEL_ID("conv_small_kernel<1, false>"))
+                           : (transposed ? HCH_KERNEL_ID("conv_small_kernel<2, true>") : HCH_KERNEL_ID("conv_small_kernel<2, false>"));
+    hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
+    const dim3 grid((unsigned)((n + 15) / 16), (unsigned)((N + 16 * nt - 1) / (16 * nt)));
+    const int vec_out = N % 4 == 0 && aligned16(out);
+#define HCH_CONV_SMALL(NT_, T_) HCH_LAUNCH((hch::conv_small_kernel<NT_, T_>), grid, dim3(64 * hch::SMALL_WAVES), 0, s, X, W, out, (const int32_t *)L.dnbr, (int)n, N, c, vec_out)
+    if (nt == 1) { if (transposed) HCH_CONV_SMALL(1, true); else HCH_CONV_SMALL(1, false); }
+    else { if (transposed) HCH_CONV_SMALL(2, true); else HCH_CONV_SMALL(2, false); }
+#undef HCH_CONV_SMALL
+    HCH_LAUNCH_CHECK("conv_small_kernel");
+    return HCH_OK;
+}
+
 // Forward product and data gradient with bf16 operands over the row order (conv_bf16_kernel)
 static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n, int c, int N)
 {
@@ -2267,6 +2297,9 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
             if (d.splits > 1) st = launch_reduce(part, Y, n * c_out, d.splits, s);
             return st;
         }
+        if (skip && dtype == HCH_F32 && conv_small_faster(n, c_in, c_out, false))
+            return launch_conv_small(*L, (const float *)X, (const float *)W, Y, n, c_in, c_out, false,
+                                     (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out) + 4.0 * Kc * c_out, s);
         if (skip && dtype == HCH_F32 && L->rows()) {
             const ConvSplitPlan q = plan_conv_split(n, c_in, c_out, p.splits);
             if (q.ok)
@@ -2362,6 +2395,9 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
             return st;
         }
         const GemmPlan p = plan_rows(n, c_in, Kd, true, k_gran(dtype));
+        if (skip && dtype == HCH_F32 && conv_small_faster(n, c_out, c_in, true))
+            return launch_conv_small(*L, (const float *)dY, (const float *)W, dX, n, c_out, c_in, true,
+                                     (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in) + 4.0 * wn, s);
         if (skip && dtype == HCH_F32 && L->rows()) {
             const ConvSplitPlan q = plan_conv_split(n, c_out, c_in, p.splits);
             if (q.ok)

@@ -1,4 +1,9 @@
-"""The row order of few voxels, made by one workgroup per level (pattern_small_kernel): up to its 8192 voxels and beyond."""
+"""Few voxels: the gathered products whose wavefronts share out the reduction (conv_small_kernel), at the edges of their tiles of 16
+rows and 32 columns and on both sides of the line to conv_split_kernel, and the row order made by one workgroup per level
+(pattern_small_kernel), up to its 8192 voxels and beyond.
+
+Bound of a product: the pieces leave out at most 2^-24 of a term; a sum of K terms is rounded about K / 8 times and once per
+wavefront, 0.29 * 2^-23 * sqrt(27 * 130 / 16) = 5e-7 of the result's norm: below 1e-6."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +22,77 @@ def _levels(n, u, levels=1, models=1, seed=0):
         q = np.sort(rng.permutation(side ** 3)[:b - a])
         parts.append(np.stack([q // side ** 2, q // side % side, q % side], 1))
     return hch.hch_build_levels_device(np.ascontiguousarray(np.concatenate(parts), np.int32), cut, u, levels)
+
+
+def _products(lv, X, W, G):
+    n, ci, co = X.shape[0], X.shape[1], G.shape[1]
+    ws = torch.full((max(hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_F32, k, hch.HCH_ALGO_FUSED)
+                         for k in (hch.HCH_WS_FWD, hch.HCH_WS_BWD_DATA)) + 256,), 255, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:]
+    Y, dX = torch.full((n, co), float("nan"), device="cuda"), torch.full((n, ci), float("nan"), device="cuda")
+    hch.hch_profile_reset()
+    hch.hch_profile_enable(-1, True)
+    hch.hch_conv_fwd(lv, 0, hch.HCH_F32, X, W, Y, ci, co, ws, hch.HCH_ALGO_FUSED)
+    hch.hch_conv_bwd_data(lv, 0, hch.HCH_F32, G, W, dX, ci, co, ws, hch.HCH_ALGO_FUSED)
+    hch.hch_profile_enable(-1, False)
+    names = {hch.hch_kernel_name(i) for i in range(hch.hch_kernel_count()) if hch.hch_profile_read(i)["launches"]}
+    return Y, dX, names
+
+
+def _reference(lv, X, W, G):
+    nb = torch.from_numpy(lv.info(0).device_nbr27().astype(np.int64)).cuda()
+    X, W, G = X.double(), W.double(), G.double()
+
+    def rows(T, k):
+        return torch.where(nb[:, k:k + 1] >= 0, T[nb[:, k].clamp(min=0)], torch.zeros((), dtype=T.dtype, device="cuda"))
+    return sum(rows(X, k) @ W[k] for k in range(27)), sum(rows(G, k) @ W[26 - k].T for k in range(27))
+
+
+def _data(n, ci, co):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + 100 * ci + co)
+    return (torch.randn(s, device="cuda", generator=g) for s in ((n, ci), (27, ci, co), (n, co)))
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 700])
+@pytest.mark.parametrize("ci,co", [(3, 16), (5, 7), (8, 33), (16, 32), (31, 65), (24, 17), (64, 64), (50, 50), (130, 20)])
+def test_products(n, ci, co):
+    lv = _levels(n, 32)
+    X, W, G = _data(n, ci, co)
+    Y, dX, names = _products(lv, X, W, G)
+    assert any(k.startswith("conv_small_kernel") for k in names), names
+    for got, want in zip((Y, dX), _reference(lv, X, W, G)):
+        assert float((got.double() - want).norm() / want.norm()) < 1e-6
+
+
+@pytest.mark.parametrize("n,ci,co,small", [(24414, 16, 32, {"conv_small_kernel<2, false>"}), (24415, 16, 32, set()),
+                                           (12695, 16, 32, {"conv_small_kernel<2, false>", "conv_small_kernel<1, true>"}),
+                                           (12696, 16, 32, {"conv_small_kernel<2, false>"}),
+                                           (300, 64, 128, {"conv_small_kernel<2, false>"}), (300, 64, 129, set())])
+def test_line_to_conv_split_kernel(n, ci, co, small):
+    lv = _levels(n, 64, models=2)
+    X, W, G = _data(n, ci, co)
+    Y, dX, names = _products(lv, X, W, G)
+    assert {k for k in names if k.startswith("conv_small")} == small
+    for got, want in zip((Y, dX), _reference(lv, X, W, G)):
+        assert float((got.double() - want).norm() / want.norm()) < 1e-6
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_numbers_that_are_not_finite(value):
+    """They reach the voxels that have them as a neighbour and no others, which keep their values."""
+    n, ci, co, v = 300, 33, 40, 150
+    lv = _levels(n, 32)
+    X, W, G = _data(n, ci, co)
+    clean = _products(lv, X, W, G)
+    X[v, 7] = G[v, 39] = value
+    got = _products(lv, X, W, G)
+    row = lv.info(0).device_nbr27()[v]
+    near = torch.zeros(n, dtype=torch.bool, device="cuda")
+    near[torch.from_numpy(row[row >= 0].astype(np.int64)).cuda()] = True
+    for a, b in zip(got[:2], clean[:2]):
+        assert not torch.isfinite(a[near]).any()
+        assert float((a[~near] - b[~near]).norm() / b.norm()) < 1e-6
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 8191, 8192, 8193])
