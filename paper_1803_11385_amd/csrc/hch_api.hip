@@ -2107,12 +2107,20 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     const int64_t lim = (int64_t)1 << 31;
     // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors; pairs of columns
     if (!L.rows() || n >= (1 << 23) || c * 2 >= (1 << 23) || n * c * 2 >= lim || n * 108 >= lim || (int64_t)54 * c * N >= lim) return false;
-    if (c % 32 || N % 2 || N <= 16 || !aligned16(X) || !aligned16(W)) return false;
-    // 256 rows to a workgroup, two workgroups to a CU: with fewer rows than fill the chip gemm_bf16_kernel, which has smaller
-    // tiles and splits the reduction, is ahead: 32 -> 64 at 64 000 rows 22 us against 24, 64 -> 32 at 127 000 33 against 36.  A
-    // convolution with its gradients, 127 000 rows: 32 -> 64 101.5 and 101.4 (one product of the three), 64 -> 64 156 -> 140, 64 -> 128
-    // 249 -> 224; 280 000 rows: 32 -> 64 198 -> 173, 64 -> 64 291 -> 232, 64 -> 128 500 -> 391.
-    if (n < (c % 64 == 0 && N > 32 ? 98304 : 196608)) return false;
+    if (c % 2 || N % 2 || ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 3u)) return false;
+    const bool full = c % 32 == 0 && aligned16(X) && aligned16(W);
+    // Without gemm_bf16_kernel the products go to the fp32 instruction: 50 -> 50 at 800 rows 62 us and 31, at 16 000 101 and 32, at 127 000 606
+    // and 51.  Where that has its vector path it is ahead on few rows: 12 -> 20 at 16 000 13 us and 16, at 64 000 20.5 and 18, at
+    // 127 000 35 and 23, with 17 neighbours a voxel 65 and 45; and with rows of 4 channels, 4 -> 16 at 280 000 30 and 37
+    if (c % 8 || N % 8 || !aligned16(X) || !aligned16(W))
+        return c % 4 || N % 4 || !aligned16(X) || !aligned16(W) || full || (c >= 8 && n >= 40960);
+    // 16 columns: 32 -> 16 at 800 rows 17 us and 11.5, at 280 000 49 and 32, with 17 neighbours a voxel 44 and 39
+    if (N <= 16) return full && c == 32;
+    // Against gemm_bf16_kernel, which splits the reduction of few rows: 32 -> 64 at 16 000 rows 18 us and 15, data gradient 16 and 16, at
+    // 32 000 24 and 16, 19.5 and 16, at 64 000 21.5 and 20, 20 and 21, at 127 000 36 and 29, 32 and 30; 64 -> 64 at 16 000 23 and 23, 20.5 and 19, at 32 000 28.5 and 24; longer
+    // rows: 96 -> 32 at 32 000 26 and 30, at 64 000 35 and 33, 128 -> 128 49 and 53, 88 and 76; rows that fill a step in part: 24 -> 40 at 64 000
+    // 18 and 21, 21 and 27, at 127 000 29 and 27, 35 and 35, at 280 000 59 and 45, 65 and 55, 16 -> 32 at 280 000 35 and 38
+    if (n < (full ? (c <= 64 ? 16384 : 65536) : 98304) || (!full && c < 24)) return false;
     // It lives on the taps that a tile's rows leave out: of 27, 256 rows of thin shells (9 neighbours a voxel) have 10 to 16, of
     // thick ones (17) 18 to 20.  Times over those of gemm_bf16_kernel, index lists also tap-major (which that kernel is faster with) or
     // not, at 0.25 to 1.3 million rows: 9 to 10.6 neighbours 0.53 to 0.96 and 0.51 to 0.91 (64 -> 32 at 10.6 1.02); spheres' shells, 14
@@ -2133,25 +2141,34 @@ static hch_status launch_conv_bf16(const Level &L, const uint16_t *X, const uint
 {
     const int nt = N <= 32 ? 2 : 4, ks = c % 64 == 0 ? 64 : 32;
     const unsigned m_tiles = (unsigned)((n + 63) / 64);
-    static int ids[2][2][2];                           // [columns][channels a step][transposed]
+    const bool full = c % 32 == 0 && aligned16(X) && aligned16(W);
+    static int ids[2][3][2];                           // [columns][channels a step: part of 32, 32, 64][transposed]
     static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
     (void)ids_ready;
-    int &id = ids[nt / 4][ks / 64][transposed];
+    int &id = ids[nt / 4][full ? ks / 32 : 0][transposed];
     if (id < 0) {
         char nm[96];
-        snprintf(nm, sizeof nm, "conv_bf16_kernel<%d, %d, %s>", nt, ks, transposed ? "true" : "false");
+        if (full) snprintf(nm, sizeof nm, "conv_bf16_kernel<%d, %d, %s>", nt, ks, transposed ? "true" : "false");
+        else snprintf(nm, sizeof nm, "conv_ragged_bf16_kernel<%d, %s>", nt, transposed ? "true" : "false");
         id = hch::Profiler::get().id_for(nm);
     }
     {
         hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
-        const dim3 grid(hch::skip_grid((m_tiles + 3) / 4, hch::skip_chunk(m_tiles, 4)), (unsigned)((N + 16 * nt - 1) / (16 * nt)));
+        const int wv = full && nt == 4 && ks == 64 && n >= 98304 ? 8 : 4;       // see conv_bf16_rows
+        const unsigned group = wv / 2;
+        const dim3 grid(hch::skip_grid((m_tiles + group - 1) / group, hch::skip_chunk(m_tiles, group)), (unsigned)((N + 16 * nt - 1) / (16 * nt)));
         const int vec_out = N % 4 == 0 && aligned16(out);
-#define HCH_CONV_BF16(NT_, KS_, T_)                                                                                             \
-        HCH_LAUNCH((hch::conv_bf16_kernel<NT_, KS_, T_>), grid, dim3(512), 0, s, X, W, out, (const int32_t *)L.dnbr, L.rows(), \
-                   (const uint32_t *)L.row_taps(), (int)n, N, c, m_tiles, vec_out)
-#define HCH_CONV_BF16_T(NT_, KS_) do { if (transposed) HCH_CONV_BF16(NT_, KS_, true); else HCH_CONV_BF16(NT_, KS_, false); } while (0)
-        if (nt == 2) { if (ks == 64) HCH_CONV_BF16_T(2, 64); else HCH_CONV_BF16_T(2, 32); }
-        else { if (ks == 64) HCH_CONV_BF16_T(4, 64); else HCH_CONV_BF16_T(4, 32); }
+#define HCH_CONV_BF16(KERNEL_)                                                                                                    \
+        HCH_LAUNCH(KERNEL_, grid, dim3(64 * wv), 0, s, X, W, out, (const int32_t *)L.dnbr, L.rows(), (const uint32_t *)L.row_taps(), (int)n, N, c, \
+                   m_tiles, vec_out)
+#define HCH_CONV_BF16_T(NT_, KS_, WV_) do { if (transposed) HCH_CONV_BF16((hch::conv_bf16_kernel<NT_, KS_, WV_, true>)); else HCH_CONV_BF16((hch::conv_bf16_kernel<NT_, KS_, WV_, false>)); } while (0)
+#define HCH_CONV_RAGGED_T(NT_) do { if (transposed) HCH_CONV_BF16((hch::conv_ragged_bf16_kernel<NT_, true>)); else HCH_CONV_BF16((hch::conv_ragged_bf16_kernel<NT_, false>)); } while (0)
+        if (!full) { if (nt == 2) HCH_CONV_RAGGED_T(2); else HCH_CONV_RAGGED_T(4); }
+        else if (ks == 32) { if (nt == 2) HCH_CONV_BF16_T(2, 32, 4); else HCH_CONV_BF16_T(4, 32, 4); }
+        else if (nt == 2) HCH_CONV_BF16_T(2, 64, 4);
+        else if (wv == 8) HCH_CONV_BF16_T(4, 64, 8);
+        else HCH_CONV_BF16_T(4, 64, 4);
+#undef HCH_CONV_RAGGED_T
 #undef HCH_CONV_BF16_T
 #undef HCH_CONV_BF16
     }

@@ -1,0 +1,124 @@
+"""The bf16 products over the row order in workgroups of 128 rows (conv_bf16_kernel<..., 4>, conv_ragged_bf16_kernel): around the edges of
+their tiles of rows, columns and channels, and on both sides of the lines to the other kernels.
+
+Bound: products are exact; a sum of K terms is rounded about K / 8 times (8 lanes' terms an instruction, in the order of K): 0.29 * 2^-23 *
+sqrt(27 * 130 / 8) = 7.3e-7 of the result's norm, below 1e-6; a single result is looked at against 30 times that."""
+import pytest
+import torch
+
+import paper_1803_11385_amd as hch
+from tests.test_gpu_small import _levels
+
+pytestmark = pytest.mark.gpu
+
+
+def _odd_base(t):
+    """The same tensor 4 bytes past a 16-byte boundary."""
+    flat = torch.empty(t.numel() + 2, dtype=t.dtype, device="cuda")
+    flat[2:] = t.reshape(-1)
+    return flat[2:].view(t.shape)
+
+
+def _data(n, ci, co, shift=False):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + 100 * ci + co)
+    out = [torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((n, ci), (27, ci, co), (n, co))]
+    return [_odd_base(t) for t in out] if shift else out
+
+
+def _products(lv, X, W, G):
+    (n, ci), co = X.shape, G.shape[1]
+    out, names = [], []
+    for name, kind, A, m in (("hch_conv_fwd", hch.HCH_WS_FWD, X, co), ("hch_conv_bwd_data", hch.HCH_WS_BWD_DATA, G, ci)):
+        ws = torch.full((hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_BF16, kind, hch.HCH_ALGO_FUSED) + 256,), 255, dtype=torch.uint8, device="cuda")
+        Y = torch.full((n, m), float("nan"), device="cuda")
+        hch.hch_profile_reset()
+        hch.hch_profile_enable(-1, True)
+        getattr(hch, name)(lv, 0, hch.HCH_BF16, A, W, Y, ci, co, ws[(-ws.data_ptr()) % 256:], hch.HCH_ALGO_FUSED)
+        hch.hch_profile_enable(-1, False)
+        names.append([hch.hch_kernel_name(i) for i in range(hch.hch_kernel_count()) if hch.hch_profile_read(i)["launches"]])
+        out.append(Y)
+    return out, names
+
+
+def _wants(lv, X, W, G):
+    nb = lv.info(0).device_nbr27()
+    nb = torch.from_numpy(nb.astype("int64")).cuda()
+
+    def sums(A, w):
+        zero = torch.zeros((), dtype=torch.float64, device="cuda")
+        return sum(torch.where(nb[:, k:k + 1] >= 0, A.double()[nb[:, k].clamp(min=0)], zero) @ w[k].double() for k in range(27))
+    return sums(X, W), sums(G, W.flip(0).transpose(1, 2))
+
+
+def _check(got, want):
+    assert float((got.double() - want).norm() / want.norm()) < 1e-6
+    assert float((got.double() - want).abs().max() / want.pow(2).mean().sqrt()) < 3e-5
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 127, 128, 129, 300, 700])
+@pytest.mark.parametrize("ci,co", [(2, 2), (6, 18), (18, 6), (34, 66), (50, 50), (62, 30), (126, 130)])
+def test_ragged_rows(n, ci, co):
+    """Even numbers of channels, tails of 2 to 30; the last row's last piece ends at the end of the operand."""
+    lv = _levels(n, 32)
+    X, W, G = _data(n, ci, co)
+    out, names = _products(lv, X, W, G)
+    for k, (got, want) in enumerate(zip(out, _wants(lv, X, W, G))):
+        assert names[k] == [f"conv_ragged_bf16_kernel<{2 if (co, ci)[k] <= 32 else 4}, {'true' if k else 'false'}>"], names
+        _check(got, want)
+
+
+@pytest.mark.parametrize("ci,co", [(64, 32), (40, 24), (12, 20)])
+def test_operands_off_the_16_byte_boundary(ci, co):
+    lv = _levels(333, 32)
+    X, W, G = _data(333, ci, co, shift=True)
+    out, names = _products(lv, X, W, G)
+    assert all("ragged" in k[0] for k in names), names
+    for got, want in zip(out, _wants(lv, X, W, G)):
+        _check(got, want)
+
+
+ROWS, RAGGED = "conv_bf16", "conv_ragged_bf16"
+
+
+@pytest.mark.parametrize("n,ci,co,fwd,bwd", [
+    (16383, 32, 64, None, None), (16384, 32, 64, ROWS, ROWS), (16385, 64, 64, ROWS, ROWS), (700, 32, 16, ROWS, None), (700, 16, 32, None, ROWS),
+    (65535, 96, 32, None, ROWS), (65536, 96, 32, ROWS, ROWS), (98303, 24, 40, None, None), (98304, 24, 40, RAGGED, RAGGED), (98303, 64, 64, ROWS, ROWS),
+    (98304, 64, 64, ROWS, ROWS), (40959, 12, 20, None, None), (40960, 12, 20, RAGGED, RAGGED), (50000, 4, 16, None, RAGGED), (50000, 4, 20, None, RAGGED)])
+def test_lines_to_the_other_kernels(n, ci, co, fwd, bwd):
+    lv = _sheet(n)
+    X, W, G = _data(n, ci, co)
+    out, names = _products(lv, X, W, G)
+    for got, want, name, form in zip(out, _wants(lv, X, W, G), names, (fwd, bwd)):
+        assert [k.split("_kernel")[0] for k in name if "conv" in k] == ([form] if form else []), names
+        _check(got, want)
+
+
+def _sheet(n):
+    """A plane of voxels, so with up to 9 neighbours each."""
+    q = torch.arange(n)
+    c = torch.stack([q // 400, torch.full_like(q, 5), q % 400], 1).int().numpy()
+    return hch.hch_build_levels_device(c, [0, n], 512, 1)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("ci,co", [(50, 34), (6, 18)])
+def test_numbers_that_are_not_finite(value, ci, co):
+    """A row's reach the voxels that have it as a neighbour and no others, also from the channels next to a tail's end; a weight's its column."""
+    n = 500
+    lv = _levels(n, 32)
+    X, W, G = _data(n, ci, co)
+    clean, _ = _products(lv, X, W, G)
+    nb = torch.from_numpy(lv.info(0).device_nbr27().astype("int64")).cuda()
+    for v in (0, n // 2, n - 1):
+        B, H = X.clone(), G.clone()
+        B[v, 0] = B[v, ci - 1] = H[v, 0] = H[v, co - 1] = value
+        near = (nb == v).any(1)
+        for got, ref in zip(_products(lv, B, W, H)[0], clean):
+            assert not torch.isfinite(got[near]).any() and torch.equal(got[~near], ref[~near])
+    for tap in (0, 13, 26):
+        B = W.clone()
+        B[tap, 0, 0] = value                               # next to the end of the tap before
+        for k, (got, ref) in enumerate(zip(_products(lv, X, B, G)[0], clean)):
+            assert torch.equal(got[:, 1:], ref[:, 1:])
+            assert not torch.isfinite(got[nb[:, 26 - tap if k else tap] >= 0, 0]).any()
