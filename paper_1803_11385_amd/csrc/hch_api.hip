@@ -21,6 +21,7 @@
 #include "split_wgrad.hip.hpp"
 #include "split_conv.hip.hpp"
 #include "conv_small.hip.hpp"
+#include "split_dcol.hip.hpp"
 #include "split_field.hip.hpp"
 #include "conv_bf16.hip.hpp"
 #include "psh_device.hip.hpp"
@@ -2108,6 +2109,34 @@ static hch_status launch_columns_split(const ConvSplitPlan &p, const Level &L, c
     return p.splits > 1 ? launch_reduce(part, out, n * N, p.splits, s) : HCH_OK;
 }
 
+// The gradient of the column matrix on split operands (dcol_split_kernel): rows of 32, 64 or 128 gradients, which the wavefronts keep in
+// registers, 32-bit byte offsets.  Few rows of 128 are cut for too few columns each: with the gather that follows, 128 -> 128 at 800
+// voxels 17 us on the fp32 instruction, 20 here, 64 -> 128 at 2700 23 and 25, at 5400 37 and 32, 128 -> 128 65 and 47.5
+static bool dcol_split_ok(int64_t n, int c_in, int c_out)
+{
+    const int64_t lim = (int64_t)1 << 31;
+    if (c_out == 128 && n < 4096) return false;
+    return (c_out == 32 || c_out == 64 || c_out == 128) && c_in % 4 == 0 && (n + 128) * c_out * 4 < lim && (int64_t)(27 * c_in + 256) * c_out * 4 < lim;
+}
+
+static hch_status launch_dcol_split(const float *dY, const float *W, float *dcol, int64_t n, int c_in, int c_out, double bytes, hipStream_t s)
+{
+    const int N = 27 * c_in, bn = 4096 / c_out, chunks = (N + bn - 1) / bn;
+    const unsigned tiles = (unsigned)((n + 127) / 128);
+    // four workgroups per CU
+    const int per = (int)std::max<int64_t>(1, std::min<int64_t>(chunks, (int64_t)chunks * tiles / 1024));
+    const dim3 grid((tiles + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD, (unsigned)((chunks + per - 1) / per));
+    const int kid = c_out == 32 ? HCH_KERNEL_ID("dcol_split_kernel<1>") : (c_out == 64 ? HCH_KERNEL_ID("dcol_split_kernel<2>") : HCH_KERNEL_ID("dcol_split_kernel<4>"));
+    {
+        hch::LaunchTimer lt(kid, s, bytes, 2.0 * N * (double)c_out * n);
+        if (c_out == 32) HCH_LAUNCH(hch::dcol_split_kernel<1>, grid, dim3(512), 0, s, dY, W, dcol, (int)n, N, tiles, per);
+        else if (c_out == 64) HCH_LAUNCH(hch::dcol_split_kernel<2>, grid, dim3(512), 0, s, dY, W, dcol, (int)n, N, tiles, per);
+        else HCH_LAUNCH(hch::dcol_split_kernel<4>, grid, dim3(512), 0, s, dY, W, dcol, (int)n, N, tiles, per);
+    }
+    HCH_LAUNCH_CHECK("dcol_split_kernel");
+    return HCH_OK;
+}
+
 // The same products for few voxels (conv_small_kernel).  It reads all weights of its taps once per 16 rows, so the line lies at little
 // work, and for the data gradient, whose weights it reads in pieces of 16 bytes, lower.  Calls one after the other (10 us: what the
 // host takes for one) against conv_split_kernel with the launch that adds its parts: forward 16 -> 32 at 12 000 voxels 9.8 us and 11.1, 32 -> 64 at 3200
@@ -2519,9 +2548,11 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
     // bytes: dY and W in; of dcol the pieces that have a destination, and 4 per row for the bit set (all of dcol without it)
     const double bytes = es * ((double)n * c_out + (double)Kc * c_out) +
                          (masked ? 4.0 * ((double)L->nbr_valid * c_in + (double)n) : 4.0 * (double)n * Kc);
-    st = launch_gemm<hch::A_ROWS, true>(dtype, p, dY, W, dcol, nullptr,
-                                        (int)n, Kc, c_out, c_out, c_out, Kc, 0, bytes, s, planes ? c_in : 0,
-                                        27, 0, 0, nullptr, nullptr, nullptr, 0, rowmask, c_in);
+    if (!planes && dtype == HCH_F32 && dcol_split_ok(n, c_in, c_out)) st = launch_dcol_split((const float *)dY, (const float *)W, dcol, n, c_in, c_out, bytes, s);
+    else
+        st = launch_gemm<hch::A_ROWS, true>(dtype, p, dY, W, dcol, nullptr,
+                                            (int)n, Kc, c_out, c_out, c_out, Kc, 0, bytes, s, planes ? c_in : 0,
+                                            27, 0, 0, nullptr, nullptr, nullptr, 0, rowmask, c_in);
     if (st != HCH_OK) return st;
     return do_col2hash(*L, dcol, c_in, dX, planes, s);
 }

@@ -1,4 +1,5 @@
-"""The columns algorithm: the forward product that stores the column matrix on its way (columns_split_kernel).
+"""The columns algorithm: the forward product that stores the column matrix on its way (columns_split_kernel), the gradient of the
+column matrix on split operands (dcol_split_kernel).
 
 Bound of a product as in test_gpu_small.py, below 1e-6 of the result's norm; the column matrix is a copy, equal to the bit."""
 import pytest
@@ -92,3 +93,48 @@ def test_numbers_that_are_not_finite(value, ci, co):
     assert not torch.isfinite(Y[:, 3]).any()
     others = [k for k in range(co) if k != 3]
     assert float((Y[:, others] - clean[:, others]).norm() / clean.norm()) < 1e-6
+
+
+def _data_gradient(lv, G, W):
+    (n, co), ci = G.shape, W.shape[1]
+    ws = torch.full((hch.hch_conv_workspace_bytes(lv, 0, ci, co, hch.HCH_F32, hch.HCH_WS_BWD_DATA, hch.HCH_ALGO_COLUMNS) + 256,), 255, dtype=torch.uint8, device="cuda")
+    dX = torch.full((n, ci), float("nan"), device="cuda")
+    hch.hch_profile_reset()
+    hch.hch_profile_enable(-1, True)
+    hch.hch_conv_bwd_data(lv, 0, hch.HCH_F32, G, W, dX, ci, co, ws[(-ws.data_ptr()) % 256:], hch.HCH_ALGO_COLUMNS)
+    hch.hch_profile_enable(-1, False)
+    return dX, {hch.hch_kernel_name(i) for i in range(hch.hch_kernel_count()) if hch.hch_profile_read(i)["launches"]}
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 127, 128, 129, 1000, 4096, 20001])
+@pytest.mark.parametrize("ci,co", [(12, 32), (16, 32), (20, 64), (32, 64), (9, 64), (16, 48), (8, 64), (12, 128), (64, 128)])
+def test_data_gradient(n, ci, co):
+    """Rows of 32, 64 and 128 channels, shares of the columns that end within a workgroup's; c_in of 9 and 8, 48 channels and few rows of 128: as before."""
+    lv = _levels(n, 64, models=1 if n < 60 else 2)
+    X, W, G = _data(n, ci, co)
+    dX, names = _data_gradient(lv, G, W)
+    split = ci % 4 == 0 and ci > 8 and (co in (32, 64) or co == 128 and n >= 4096)
+    assert ({k for k in names if k.startswith("dcol")} == {f"dcol_split_kernel<{co // 32}>"}) if split else not [k for k in names if k.startswith("dcol")], names
+    want = _reference(lv, X, W, G)[1]
+    assert float((dX.double() - want).norm() / want.norm()) < (1e-6 if split else 2e-6)      # the fp32 instruction: a rounding per 4 terms
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("n,ci,co", [(300, 12, 32), (300, 32, 64), (4100, 16, 128)])
+def test_gradients_that_are_not_finite(value, n, ci, co):
+    """A row's reach its neighbours' and no others; a weight's the rows that have its tap, in its channel."""
+    v = n // 2
+    lv = _levels(n, 32)
+    _, W, G = _data(n, ci, co)
+    clean = _data_gradient(lv, G, W)[0]
+    nb = torch.from_numpy(lv.info(0).device_nbr27().astype("int64")).cuda()
+    H = G.clone()
+    H[v, co - 1] = value
+    got, near = _data_gradient(lv, H, W)[0], (nb == v).any(1)
+    assert not torch.isfinite(got[near]).any()
+    assert float((got[~near] - clean[~near]).norm() / clean.norm()) < 1e-6
+    U = W.clone()
+    U[5, ci - 1, 3] = value
+    got, has = _data_gradient(lv, G, U)[0], nb[:, 21] >= 0
+    assert not torch.isfinite(got[has, ci - 1]).any()
+    assert float((got[:, :-1] - clean[:, :-1]).norm() / clean.norm()) < 1e-6 and float((got[~has] - clean[~has]).norm() / clean.norm()) < 1e-6
