@@ -21,6 +21,7 @@
 #include "split_wgrad.hip.hpp"
 #include "split_conv.hip.hpp"
 #include "conv_small.hip.hpp"
+#include "split_columns.hip.hpp"
 #include "split_dcol.hip.hpp"
 #include "split_field.hip.hpp"
 #include "conv_bf16.hip.hpp"

@@ -58,25 +58,22 @@ struct ConvLds {
     static constexpr int O_B = WV * A, O_IDX = O_B + 2 * B, O_TAP = O_IDX + WV * IDX, BYTES = O_TAP + 32;
 };
 
-// COLS: rows in the order of the data, every tap, and the gathered rows also to `col`, row i of the column matrix of
-// hash2col: see columns_split_kernel.
-template <int NT, int WV, bool FAST, bool BT, bool COLS>
-__device__ __forceinline__ void conv_split_rows(
+template <int NT, int WV, bool FAST, bool BT>
+__global__ __launch_bounds__(64 * WV) void conv_split_kernel(
     const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr,
-    [[maybe_unused]] const int32_t *__restrict__ rowmap, [[maybe_unused]] const uint32_t *__restrict__ tilemask, [[maybe_unused]] float *__restrict__ col,
-    [[maybe_unused]] int col_stream, int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
+    const int32_t *__restrict__ rowmap, const uint32_t *__restrict__ tilemask,
+    int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
 {
-    static_assert(!(COLS && BT), "the column matrix of the forward product");
     typedef ConvLds<NT, WV> L;
     constexpr int BN = L::BN, ROWS = L::ROWS, GROUP = ROWS * WV / 64;     // 64-row tiles per workgroup
     constexpr uint32_t OUT = 0x80000000u;
     constexpr int SRD3 = 0x00020000;
     __shared__ __attribute__((aligned(16))) unsigned char lds[L::BYTES];
 
-    unsigned mtile = COLS ? xcd_tile(blockIdx.x, gridDim.x / NUM_XCD) : xcd_chunk_tile(blockIdx.x, skip_chunk(m_tiles, GROUP));
+    unsigned mtile = xcd_chunk_tile(blockIdx.x, skip_chunk(m_tiles, GROUP));
     const unsigned groups = (m_tiles + GROUP - 1) / GROUP;
     if (mtile >= groups) return;
-    if (!COLS) mtile = groups - 1 - mtile;                                // most neighbours first
+    mtile = groups - 1 - mtile;                                           // most neighbours first
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = (int)blockIdx.y * BN;
@@ -86,27 +83,24 @@ __device__ __forceinline__ void conv_split_rows(
     uint8_t *taplist = lds + L::O_TAP;
 
     // taps of the workgroup's rows, the list of them, and this slice's steps
-    uint32_t present = (1u << 27) - 1u;
-    if constexpr (!COLS) {
-        present = tilemask[mtile * GROUP];
-        if (GROUP == 2 && mtile * 2 + 1 < m_tiles) present |= tilemask[mtile * 2 + 1];
-        present = (uint32_t)__builtin_amdgcn_readfirstlane((int)present);
-    }
+    uint32_t present = tilemask[mtile * GROUP];
+    if (GROUP == 2 && mtile * 2 + 1 < m_tiles) present |= tilemask[mtile * 2 + 1];
+    present = (uint32_t)__builtin_amdgcn_readfirstlane((int)present);
     if (tid < 32) {
         if (tid >= __popc(present)) taplist[tid] = 0;                      // past the last: tap 0, with no weights
         if (present >> tid & 1u) taplist[__popc(present & ((1u << tid) - 1u))] = (uint8_t)tid;
     }
     const int c8 = (c + 7) >> 3;
-    const int n_units = __popc(present) * c8, n_steps = COLS ? (27 * c + 31) >> 5 : (n_units + 3) >> 2;
+    const int n_units = __popc(present) * c8, n_steps = (n_units + 3) >> 2;
     const int per = (n_steps + (int)gridDim.z - 1) / (int)gridDim.z;
     const int s_beg = min((int)blockIdx.z * per, n_steps), s_end = min(s_beg + per, n_steps);
 
     // index rows of the wavefront's rows, tap-major in LDS; the centre tap is the row's own voxel
-    [[maybe_unused]] uint32_t mine = 0;                                    // taps of this wavefront's rows
+    uint32_t mine = 0;                                                     // taps of this wavefront's rows
     {
         const int r = lane < ROWS ? lane : 0;
         const bool ok = lane < ROWS && row0 + r < M;
-        const int vox = ok ? (COLS ? row0 + r : rowmap[row0 + r]) : -1;
+        const int vox = ok ? rowmap[row0 + r] : -1;
         if (lane < ROWS) idx[13 * ROWS + lane] = vox;
         __builtin_amdgcn_wave_barrier();
         const __amdgpu_buffer_rsrc_t rs_n = __builtin_amdgcn_make_buffer_rsrc((void *)nbr, 0, M * 27 * 4, SRD3);
@@ -117,14 +111,14 @@ __device__ __forceinline__ void conv_split_rows(
             const int vx = idx[13 * ROWS + rr];
             v[q] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_n, vx >= 0 ? (vx * 27 + t) * 4 : (int)OUT, 0, 0);
             if (vx < 0 || e >= ROWS * 27) v[q] = -1;
-            if (FAST && !COLS) mine |= v[q] >= 0 ? 1u << t : 0u;
+            if (FAST) mine |= v[q] >= 0 ? 1u << t : 0u;
         }
 #pragma unroll
         for (int q = 0; q < (ROWS * 27 + 63) / 64; ++q) {
             const int e = q * 64 + lane, rr = e / 27, t = e - rr * 27;
             if (rr < ROWS && t != 13) idx[t * ROWS + rr] = v[q];
         }
-        if (FAST && !COLS) {
+        if (FAST) {
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) mine |= (uint32_t)__shfl_xor((int)mine, d);
             mine = (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
@@ -149,14 +143,11 @@ __device__ __forceinline__ void conv_split_rows(
     int cb = 0;
     // otherwise: list position and unit within the tap, of this lane's piece and of this thread's weights
     int a_tap = 0, a_u = 0, b_tap = 0, b_u = 0;
-    const int d_tap = COLS ? 32 / c : 4 / c8, d_u = COLS ? 32 - d_tap * c : 4 - d_tap * c8;
+    const int d_tap = 4 / c8, d_u = 4 - d_tap * c8;
     if constexpr (FAST) {
         const int per_tap = c >> 5, skip = s_beg / per_tap;
         for (int q = 0; q < skip; ++q) rem &= rem - 1u;
         cb = (s_beg - skip * per_tap) * 32;
-    } else if constexpr (COLS) {
-        a_tap = (s_beg * 32 + ap * 4) / c; a_u = s_beg * 32 + ap * 4 - a_tap * c;      // a_u: channel
-        b_u = s_beg * 32 + kp * UN;                                                    // b_u: row of the weights
     } else {
         const int ua = s_beg * 4 + (ap >> 1), ub = s_beg * 4 + bk;
         a_tap = ua / c8; a_u = ua - a_tap * c8;
@@ -193,20 +184,6 @@ __device__ __forceinline__ void conv_split_rows(
             }
             cb += 32;
             if (cb >= c) { cb = 0; rem &= rem - 1u; }
-        } else if constexpr (COLS) {
-            // tap after tap without padding: four channels of a row are within one
-            const int tap = min(a_tap, 26);
-#pragma unroll
-            for (int q = 0; q < AU; ++q) {
-                const int off = __mul24(idx[tap * ROWS + ar + 8 * q], c * 4);
-                ra[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_x, off < 0 ? off : off + a_u * 4, 0, 0));
-            }
-            a_tap += d_tap; a_u += d_u;
-            if (a_u >= c) { a_u -= c; ++a_tap; }
-#pragma unroll
-            for (int j = 0; j < UN; ++j)                                   // past the end: zero
-                rb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, b_col ? ((b_u + j) * N + n0 + bn) * 4 : (int)OUT, 0, 0));
-            b_u += 32;
         } else {
             // a tap past the list's end has no weights; channels past the row's end (the next row's
             // numbers) meet weights of zero -- and if they are not finite, the plain sums are taken
@@ -231,22 +208,11 @@ __device__ __forceinline__ void conv_split_rows(
             if (b_u >= c8) { b_u -= c8; ++b_tap; }
         }
     };
-    [[maybe_unused]] int k_col = s_beg * 32 + ap * 4;                       // COLS: place in the column matrix of the piece laid down next
     auto stash_a = [&](const u32x4 *ra) {
 #pragma unroll
         for (int q = 0; q < AU; ++q) {
             const int r = ar + 8 * q;
             *reinterpret_cast<u32x4 *>(a_lds + r * 128 + ((ap ^ row_swap(r)) << 4)) = ra[q];
-        }
-        if constexpr (COLS) {
-            if (n0 == 0 && k_col < min(s_end * 32, 27 * c))
-#pragma unroll
-                for (int q = 0; q < AU; ++q) {
-                    if (row0 + ar + 8 * q >= M) continue;
-                    u32x4 *dst = reinterpret_cast<u32x4 *>(col + (int64_t)(row0 + ar + 8 * q) * (27 * c) + k_col);
-                    if (col_stream) __builtin_nontemporal_store(ra[q], dst); else *dst = ra[q];
-                }
-            k_col += 32;
         }
     };
     auto stash_b = [&](int stage, const float *rb) {
@@ -277,7 +243,7 @@ __device__ __forceinline__ void conv_split_rows(
         stash_b(stage ^ 1, rb);
         fetch(ra, rb);                                                     // step t + 3
         bool run = true;
-        if constexpr (FAST && !COLS) {
+        if constexpr (FAST) {
             run = (mine >> (rem_m ? __builtin_ctz(rem_m) : 0)) & 1u;
             cb_m += 32;
             if (cb_m >= c) { cb_m = 0; rem_m &= rem_m - 1u; }
@@ -340,27 +306,7 @@ __device__ __forceinline__ void conv_split_rows(
         // 280 000 voxels forward 365 us and data gradient 392, 139 and 150 with finite numbers.
 #pragma unroll
         for (int b = 0; b < NT; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (COLS) {
-            for (int k0 = s_beg * 32 + lk * 8; k0 - lk * 8 < min(s_end * 32, 27 * c); k0 += 32) {
-                float x[8];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int k = k0 + 4 * h, tap = min(k / c, 26), row = idx[tap * ROWS + li];
-                    const float *src = X + (int64_t)max(row, 0) * c + k - tap * c;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[4 * h + j] = row >= 0 && k < 27 * c ? src[j] : 0.f;
-                }
-#pragma unroll
-                for (int b = 0; b < NT; ++b) {
-                    const int col = n0 + b * 16 + li;
-                    f32x4 t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) t = mfma_f32(k0 + j < 27 * c && col < N ? W[(int64_t)(k0 + j) * N + col] : 0.f, x[j], t);
-                    acc[b] += t;
-                }
-            }
-        }
-        const int u_end = COLS ? 0 : min(s_end * 4, n_units);
+        const int u_end = min(s_end * 4, n_units);
         for (int u = s_beg * 4, cnt; u < u_end; u += cnt) {
             const int tap = taplist[u / c8], u_tap = u % c8, k0 = (u_tap + lk) * 8;
             cnt = min(min(4, c8 - u_tap), u_end - u);
@@ -396,33 +342,6 @@ __device__ __forceinline__ void conv_split_rows(
             for (int e = 0; e < 4; ++e)
                 if (col + e < N) dst[e] = acc[b][e];
     }
-}
-
-template <int NT, int WV, bool FAST, bool BT>
-__global__ __launch_bounds__(64 * WV) void conv_split_kernel(
-    const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr,
-    const int32_t *__restrict__ rowmap, const uint32_t *__restrict__ tilemask,
-    int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
-{
-    conv_split_rows<NT, WV, FAST, BT, false>(X, W, C, nbr, rowmap, tilemask, nullptr, 0, M, N, c, m_tiles, c_split_stride, vec_out);
-}
-
-// The forward product of the columns algorithm together with the column matrix that it leaves in the workspace: the rows that are
-// gathered for a product are stored as they come, instead of written by hash2col_kernel and read back by gemm_f32_kernel.  All 27 taps
-// of every row, one after the other without padding; an absent row is a row of zeros, in the products as well.  Rows of a multiple of 4
-// channels.  Bound by the stores of the column matrix with few output columns (4 -> 16 at 280 000 rows: 121 MB in 34 us), by the matrix
-// instructions and the cutting, as conv_split_kernel, with more.  The two launches -> this one: 4 -> 16 at 280 000 rows 66 -> 34 us,
-// 12 -> 20 199 -> 138, 16 -> 32 237 -> 122, 32 -> 64 503 -> 232; at 82 000 16 -> 32 67 -> 38, 32 -> 64 144 -> 85; at 23 000 32 -> 64
-// 49 -> 33, 64 -> 128 115 -> 79; at 800 18 -> 14.5, 128 -> 256 34 -> 26.
-// col_stream: stores past the caches.  64-byte pieces only (pieces that share a sector with the next step's become two writes: 12 -> 20 at
-// 280 000 258 us), and with matrices beyond the last-level cache: 16 -> 32 at 159 000 (275 MB) 91 -> 73, 32 -> 64 at 282 000 292 -> 232, at 49 000
-// (171 MB) 48 -> 46, but 32 -> 16 there 33 -> 42.
-template <int NT, int WV, bool FAST>
-__global__ __launch_bounds__(64 * WV) void columns_split_kernel(
-    const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr, float *__restrict__ col, int col_stream,
-    int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
-{
-    conv_split_rows<NT, WV, FAST, false, true>(X, W, C, nbr, nullptr, nullptr, col, col_stream, M, N, c, m_tiles, c_split_stride, vec_out);
 }
 
 }  // namespace hch
