@@ -2147,7 +2147,10 @@ static hch_status launch_dcol_split(const float *dY, const float *W, float *dcol
 static bool conv_small_faster(int64_t n, int c, int N, bool transposed)
 {
     if (n * c * 4 >= ((int64_t)1 << 31) || n * 108 >= ((int64_t)1 << 31)) return false;        // 32-bit byte offsets
-    return (int64_t)c * N <= (transposed ? 4096 : 8192) && (double)n * c * N <= (transposed ? 6.5e6 : 12.5e6);
+    // work with what tiles and loads are padded to: 6 -> 7 at 236 000 voxels (10 million terms without) is slower here with its gradients, 169 and 192 us.  Rows of no
+    // multiple of 16 channels are behind earlier: 12 -> 20 at 12 000 11.4 and 9.6, at 22 000 14.6 and 15.6, at 29 000 14.3 and 19; 8 -> 40 at 16 000 10.3 and 11.2
+    const double work = (double)n * ((c + 15) / 16 * 16) * ((N + 15) / 16 * 16);
+    return (int64_t)c * N <= (transposed ? 4096 : 8192) && work <= (transposed ? 6.5e6 : (c % 16 ? 8e6 : 12.5e6));
 }
 
 static hch_status launch_conv_small(const Level &L, const float *X, const float *W, float *out, int64_t n, int c, int N, bool transposed,

@@ -68,7 +68,8 @@ def test_products(n, ci, co):
 @pytest.mark.parametrize("n,ci,co,small", [(24414, 16, 32, {"conv_small_kernel<2, false>"}), (24415, 16, 32, set()),
                                            (12695, 16, 32, {"conv_small_kernel<2, false>", "conv_small_kernel<1, true>"}),
                                            (12696, 16, 32, {"conv_small_kernel<2, false>"}),
-                                           (300, 64, 128, {"conv_small_kernel<2, false>"}), (300, 64, 129, set())])
+                                           (300, 64, 128, {"conv_small_kernel<2, false>"}), (300, 64, 129, set()),
+                                           (15625, 12, 20, {"conv_small_kernel<2, false>"}), (15626, 12, 20, set()), (40000, 6, 7, set())])
 def test_line_to_conv_split_kernel(n, ci, co, small):
     lv = _levels(n, 64, models=2)
     X, W, G = _data(n, ci, co)
