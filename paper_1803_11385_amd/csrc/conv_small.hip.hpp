@@ -9,7 +9,8 @@ namespace hch {
 // A workgroup computes 16 rows by 16*NT columns, rows in data order; its WV = 8 wavefronts share out the reduction, not the
 // rows: in units of 8 channels of one tap that any of the 16 rows has, 4 units (32 terms) to a step, a wavefront takes every WV-th
 // step.  Each reads its rows and weights from memory straight into the operands' layout, cuts both and keeps sums of its own,
-// which meet in LDS, in the order of the wavefronts.  Nothing is shared on the way, so there is no barrier between the index rows and
+// which meet in LDS as they are, leading pieces' and the others' apart, and are added in 64 bits and rounded once (with a rounding per
+// wavefront short reductions came out further from the exact sums than conv_split_kernel's one chain: 1 -> 4 channels 5.5e-8 for 3.2e-8).  Nothing is shared on the way, so there is no barrier between the index rows and
 // the end, and no launch that adds up partial sums.
 // Bound by the latency of that chain: index rows, rows and weights, the last sum; conv_split_kernel, whose workgroups walk through
 // all steps one after the other, or through a part of them with a launch to add the parts, takes longer wherever all workgroups of
@@ -25,7 +26,7 @@ __global__ __launch_bounds__(64 * SMALL_WAVES, 2) void conv_small_kernel(
     constexpr uint32_t OUT = 0x80000000u;
     __shared__ __attribute__((aligned(16))) int32_t idx[ROWS * 27];
     __shared__ uint8_t taplist[32];
-    __shared__ __attribute__((aligned(16))) f32x4 sums[WV][NT][64];
+    __shared__ __attribute__((aligned(16))) f32x4 sums[WV][2][NT][64];
 
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,16 +119,16 @@ __global__ __launch_bounds__(64 * SMALL_WAVES, 2) void conv_small_kernel(
     bool bad = false;
 #pragma unroll
     for (int b = 0; b < NT; ++b) {
-        acc[b] += low[b];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bad |= non_finite(acc[b][e]);
+        for (int e = 0; e < 4; ++e) bad |= non_finite(acc[b][e] + low[b][e]);
         acc[b] *= SPLIT_UNSCALE;
+        low[b] *= SPLIT_UNSCALE;
     }
     if (__builtin_expect(__ballot(bad) != 0, 0)) {
         // an infinity or NaN among the operands, or a sum out of range: this wavefront's sums with the fp32 instruction, one
         // unit at a time, added only where the row has the tap, as in conv_split_kernel
 #pragma unroll
-        for (int b = 0; b < NT; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < NT; ++b) acc[b] = low[b] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int s = wave; s < n_steps; s += WV)
             for (int u = s * 4; u < min(s * 4 + 4, n_units); ++u) {
                 const int tap = taplist[u / c8], k0 = u % c8 * 8 + lk * 2, row = idx[li * 27 + tap];
@@ -149,13 +150,23 @@ __global__ __launch_bounds__(64 * SMALL_WAVES, 2) void conv_small_kernel(
             }
     }
 #pragma unroll
-    for (int b = 0; b < NT; ++b) sums[wave][b][lane] = acc[b];
+    for (int b = 0; b < NT; ++b) {
+        sums[wave][0][b][lane] = acc[b];
+        sums[wave][1][b][lane] = low[b];
+    }
     __syncthreads();
     for (int q = tid; q < NT * 64; q += 64 * WV) {
         const int b = q >> 6, l = q & 63;
-        f32x4 v = sums[0][b][l];
+        double t[4] = {0., 0., 0., 0.};
 #pragma unroll
-        for (int w = 1; w < WV; ++w) v += sums[w][b][l];
+        for (int w = 0; w < WV; ++w)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 part = sums[w][h][b][l];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[e] += (double)part[e];
+            }
+        const f32x4 v = {(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
         const int row = row0 + (l & 15), col = n0 + b * 16 + (l >> 4) * 4;
         if (row >= M) continue;
         float *dst = C + (int64_t)row * N + col;

@@ -65,6 +65,19 @@ def test_products(n, ci, co):
         assert float((got.double() - want).norm() / want.norm()) < 1e-6
 
 
+@pytest.mark.parametrize("n,ci,co", [(700, 1, 4), (700, 2, 8), (3177, 1, 16), (3177, 3, 16), (12000, 2, 7)])
+def test_sums_of_few_terms_are_rounded_once(n, ci, co):
+    """A rounding errs by 2^-23 / sqrt(12) at the lower end of a binade, 2.25e-8 of values spread evenly over it.  Two of them, one within a
+    wavefront's instruction and the result's own, are 3.2e-8 of the norm, below 4e-8; with the wavefronts' sums rounded one by one, and after
+    each addition, it was 5.0e-8 to 5.9e-8."""
+    lv = _levels(n, 32)
+    X, W, G = _data(n, ci, co)
+    Y, dX, names = _products(lv, X, W, G)
+    assert "conv_small_kernel<1, false>" in names, names
+    want = _reference(lv, X, W, G)[0]
+    assert float((Y.double() - want).norm() / want.norm()) < 4e-8
+
+
 @pytest.mark.parametrize("n,ci,co,small", [(24414, 16, 32, {"conv_small_kernel<2, false>"}), (24415, 16, 32, set()),
                                            (12695, 16, 32, {"conv_small_kernel<2, false>", "conv_small_kernel<1, true>"}),
                                            (12696, 16, 32, {"conv_small_kernel<2, false>"}),
