@@ -48,6 +48,22 @@ def test_forward_and_its_column_matrix(n, ci, co):
     assert float((Y.double() - want).norm() / want.norm()) < 1e-6
 
 
+@pytest.mark.parametrize("n", [65, 300, 25000])
+@pytest.mark.parametrize("ci,co", [(12, 40), (44, 70), (76, 33), (4, 64), (20, 16)])
+def test_weights_end_where_they_end(n, ci, co):
+    """Terms past the last one, up to three steps of 32, have weights of zero, whatever lies behind the weights in memory; the rows' side
+    of these terms is other rows' numbers.  27 * 12, 44, 76 = 4 modulo 32: half of the eight terms of a thread are past the end."""
+    lv = _levels(n, 64)
+    X, W, G = _data(n, ci, co)
+    inside = torch.full((W.numel() + 256 * co,), 1e6, device="cuda")
+    inside[:W.numel()] = W.reshape(-1)
+    Y, _, names = _forward(lv, X, inside[:W.numel()].view(W.shape))
+    assert [k for k in names if k.startswith("columns_split_kernel")], names
+    want = _reference(lv, X, W, G)[0]
+    assert float((Y.double() - want).norm() / want.norm()) < 1e-6
+    assert torch.equal(Y, _forward(lv, X, W)[0])
+
+
 def test_column_matrix_beyond_the_caches():
     """More than 256 MB with rows of whole 64-byte pieces: stored past the caches."""
     lv = _levels(170000, 128, models=2)
