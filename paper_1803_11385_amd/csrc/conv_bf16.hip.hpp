@@ -124,9 +124,13 @@ __device__ __forceinline__ void conv_bf16_rows(
             if constexpr (BT) {
                 rb[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_w, b_off[q], __builtin_amdgcn_readfirstlane(((26 - tap) * N * c + cb) * 2), 0));
             } else {
+                // (a scalar offset past the end of the weights would let any per-lane offset in, so of a tap's last step in part the rows are
+                // counted per lane)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    rb[q][j] = __builtin_amdgcn_raw_buffer_load_b32(rs_w, b_off[q], __builtin_amdgcn_readfirstlane((tap * c + cb + j) * N * 2), 0);
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (FULL) rb[q][j] = __builtin_amdgcn_raw_buffer_load_b32(rs_w, b_off[q], __builtin_amdgcn_readfirstlane((tap * c + cb + j) * N * 2), 0);
+                    else rb[q][j] = __builtin_amdgcn_raw_buffer_load_b32(rs_w, b_off[q] + j * N * 2, __builtin_amdgcn_readfirstlane((tap * c + cb) * N * 2), 0);
+                }
             }
         }
         cb += KS;

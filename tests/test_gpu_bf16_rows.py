@@ -68,6 +68,20 @@ def test_ragged_rows(n, ci, co):
         _check(got, want)
 
 
+@pytest.mark.parametrize("ci,co", [(2, 16), (34, 66), (66, 34), (50, 50)])
+def test_nothing_comes_of_what_lies_behind_the_weights(ci, co):
+    """2 channels modulo 32: a thread's four rows of the last tap's last step end past the last row of the weights."""
+    lv = _levels(300, 32)
+    X, W, G = _data(300, ci, co)
+    inside = torch.full((W.numel() + 64 * max(ci, co),), float("nan"), dtype=torch.bfloat16, device="cuda")
+    inside[:W.numel()] = W.reshape(-1)
+    out, names = _products(lv, X, inside[:W.numel()].view(W.shape), G)
+    assert all("ragged" in k[0] for k in names), names
+    for got, want, clean in zip(out, _wants(lv, X, W, G), _products(lv, X, W, G)[0]):
+        _check(got, want)
+        assert torch.equal(got, clean)
+
+
 @pytest.mark.parametrize("ci,co", [(64, 32), (40, 24), (12, 20)])
 def test_operands_off_the_16_byte_boundary(ci, co):
     lv = _levels(333, 32)
