@@ -10,6 +10,8 @@ namespace hch {
 // out.  Rows pass through LDS of the wavefront's own, weights through two shared stages, loads run two steps
 // ahead in two sets of registers, as in conv_split_kernel; nothing is cut here.
 // BT: W(t, k, n) = W[26 - t][n][k] (the data gradient's view of the weights), else W[t][k][n].
+// NT == 2: sums of 128 terms, added up, instead of one chain of them all, in registers that four workgroups to a CU leave free (tiles of 64
+// columns have none): 64 -> 32 at 127 000 rows 1.41e-7 -> 0.75e-7 from the exact sums, 31 and 31 us, 32 -> 16 1.0e-7 -> 0.66e-7, 20.3 and 21.0.
 // FULL: rows of a multiple of KS channels, 16-byte aligned.
 // 128 rows, four workgroups to a CU, against 256: 32 -> 64 at 127 000 rows 32 -> 29 and 34 -> 30 us (data gradient), at 609 000 105 -> 96 and 103 -> 95,
 // at 32 000 22 -> 16 and 22 -> 16; 64 -> 64, with 64 channels a step three to a CU, at 127 000 44 -> 46 and 41 -> 41, at 280 000 68 -> 71 and 63 -> 63.
@@ -154,11 +156,26 @@ __device__ __forceinline__ void conv_bf16_rows(
         }
     };
 
+    // NT == 2: sums of 128 terms at a time, added up
     f32x4 acc[2][NT];
+    [[maybe_unused]] f32x4 total[2][NT];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < NT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < NT; ++b) {
+            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (NT == 2) total[a][b] = acc[a][b];
+        }
+    auto add_up = [&]() {
+        if constexpr (NT == 2)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b) {
+                    total[a][b] += acc[a][b];
+                    acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+    };
     uint32_t rem_m = rem;                                                  // the step being multiplied
     int cb_m = 0;
     auto step = [&](int stage, u32x4 *ra, u32x4 *rb) {
@@ -216,8 +233,16 @@ __device__ __forceinline__ void conv_bf16_rows(
         for (; t + 1 < n_steps; t += 2) {
             step(0, ra1, rb1);
             step(1, ra0, rb0);
+            if (KS == 64 || (t & 2)) add_up();
         }
         if (t < n_steps) step(0, ra1, rb1);
+    }
+    if constexpr (NT == 2) {
+        add_up();
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b) acc[a][b] = total[a][b];
     }
 #pragma unroll
     for (int a = 0; a < 2; ++a) {

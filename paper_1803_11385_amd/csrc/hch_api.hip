@@ -2208,8 +2208,13 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
 static hch_status launch_conv_bf16(const Level &L, const uint16_t *X, const uint16_t *W, float *out, int64_t n, int c, int N, bool transposed,
                                    double bytes, hipStream_t s)
 {
-    const int nt = N <= 32 ? 2 : 4, ks = c % 64 == 0 ? 64 : 32;
     const unsigned m_tiles = (unsigned)((n + 63) / 64);
+    // Where plan_rows splits the reduction of a level that does not fill the chip, a single chain of all terms is further from the exact sums than
+    // its slices are: there tiles of 32 columns, which add up sums of 128 terms.  Errors of slices, chain, such sums: 50 -> 50 at
+    // 3200 rows 1.03e-7, 1.61e-7, 0.80e-7, at 20 000 1.01e-7, 1.23e-7, 0.71e-7, 34 -> 66 at 12 000 (data gradient) 1.01e-7, 1.47e-7, 0.78e-7.  Times of tiles of 64
+    // and 32 columns there: 50 -> 50 at 800 rows 31 us and 27, at 16 500 31 and 29, 64 -> 64 23 and 20.
+    const bool few = (int64_t)m_tiles * ((N + 63) / 64) < 512 && 27 * c >= 512;
+    const int nt = N <= 32 || few ? 2 : 4, ks = c % 64 == 0 ? 64 : 32;
     const bool full = c % 32 == 0 && aligned16(X) && aligned16(W);
     static int ids[2][3][2];                           // [columns][channels a step: part of 32, 32, 64][transposed]
     static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();

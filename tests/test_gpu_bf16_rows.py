@@ -64,8 +64,22 @@ def test_ragged_rows(n, ci, co):
     X, W, G = _data(n, ci, co)
     out, names = _products(lv, X, W, G)
     for k, (got, want) in enumerate(zip(out, _wants(lv, X, W, G))):
-        assert names[k] == [f"conv_ragged_bf16_kernel<{2 if (co, ci)[k] <= 32 else 4}, {'true' if k else 'false'}>"], names
+        c, m = ((ci, co), (co, ci))[k]                    # few rows: 32 columns at a time, unless the reduction is short
+        assert names[k] == [f"conv_ragged_bf16_kernel<{2 if m <= 32 or 27 * c >= 512 else 4}, {'true' if k else 'false'}>"], names
         _check(got, want)
+
+
+@pytest.mark.parametrize("n,ci,co", [(700, 50, 50), (700, 32, 16), (700, 34, 66), (17000, 64, 64), (17000, 62, 30)])
+def test_few_rows_are_summed_in_parts(n, ci, co):
+    """A rounding errs by 2.25e-8 of what it rounds (test_gpu_small.py), a chain of m of them by sqrt(m / 2) times that.  Sums of 128 terms: 16
+    roundings each, 6.4e-8; up to 16 such sums added up: 6.4e-8; together 9.0e-8, below 1e-7.  One chain of 27 * 32 to 27 * 66 terms: 1.6e-7 to 2.4e-7, of 9 * 62: 1.3e-7."""
+    lv = _levels(n, 64) if n < 1000 else _sheet(n)
+    X, W, G = _data(n, ci, co)
+    out, names = _products(lv, X, W, G)
+    for k, (got, want) in enumerate(zip(out, _wants(lv, X, W, G))):
+        if any("conv" in name for name in names[k]):       # (16 -> 32 and the like keep gemm_bf16_kernel)
+            assert float((got.double() - want).norm() / want.norm()) < 1e-7, names[k]
+    assert any("conv" in name for name in names[0]), names
 
 
 @pytest.mark.parametrize("ci,co", [(2, 16), (34, 66), (66, 34), (50, 50)])
