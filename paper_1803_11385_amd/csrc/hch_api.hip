@@ -2170,26 +2170,48 @@ static hch_status launch_conv_small(const Level &L, const float *X, const float 
     return HCH_OK;
 }
 
-// Forward product and data gradient with bf16 operands over the row order (conv_bf16_kernel)
-static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n, int c, int N)
+// Forward product and data gradient (transposed) with bf16 operands over the row order (conv_bf16_kernel).  Its lines: calls of both directions, 170
+// pairs of channels at 9 to 24 sizes each from 800 to 609 000 rows, that took longer than the kernel below stay there.
+static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n, int c, int N, bool transposed)
 {
     const int64_t lim = (int64_t)1 << 31;
     // 32-bit byte offsets reach everything, a negative one nothing; 24-bit row and row-length factors; pairs of columns
     if (!L.rows() || n >= (1 << 23) || c * 2 >= (1 << 23) || n * c * 2 >= lim || n * 108 >= lim || (int64_t)54 * c * N >= lim) return false;
     if (c % 2 || N % 2 || ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 3u)) return false;
     const bool full = c % 32 == 0 && aligned16(X) && aligned16(W);
-    // Without gemm_bf16_kernel the products go to the fp32 instruction: 50 -> 50 at 800 rows 62 us and 31, at 16 000 101 and 32, at 127 000 606
-    // and 51.  Where that has its vector path it is ahead on few rows: 12 -> 20 at 16 000 13 us and 16, at 64 000 20.5 and 18, at
-    // 127 000 35 and 23, with 17 neighbours a voxel 65 and 45; and with rows of 4 channels, 4 -> 16 at 280 000 30 and 37
-    if (c % 8 || N % 8 || !aligned16(X) || !aligned16(W))
-        return c % 4 || N % 4 || !aligned16(X) || !aligned16(W) || full || (c >= 8 && n >= 40960);
-    // 16 columns: 32 -> 16 at 800 rows 17 us and 11.5, at 280 000 49 and 32, with 17 neighbours a voxel 44 and 39
-    if (N <= 16) return full && c == 32;
-    // Against gemm_bf16_kernel, which splits the reduction of few rows: 32 -> 64 at 16 000 rows 18 us and 15, data gradient 16 and 16, at
-    // 32 000 24 and 16, 19.5 and 16, at 64 000 21.5 and 20, 20 and 21, at 127 000 36 and 29, 32 and 30; 64 -> 64 at 16 000 23 and 23, 20.5 and 19, at 32 000 28.5 and 24; longer
-    // rows: 96 -> 32 at 32 000 26 and 30, at 64 000 35 and 33, 128 -> 128 49 and 53, 88 and 76; rows that fill a step in part: 24 -> 40 at 64 000
-    // 18 and 21, 21 and 27, at 127 000 29 and 27, 35 and 35, at 280 000 59 and 45, 65 and 55, 16 -> 32 at 280 000 35 and 38
-    if (n < (full ? (c <= 64 ? 16384 : 65536) : 98304) || (!full && c < 24)) return false;
+    const double neighbours = (double)L.nbr_valid / (double)n;
+    if (c % 8 || N % 8 || !aligned16(X) || !aligned16(W)) {
+        // Without gemm_bf16_kernel the products go to the fp32 instruction: 50 -> 50 at 800 rows 62 us and 27, at 16 500 101 and 29, at 127 000 606
+        // and 51; rows of 2 channels are mostly padding here: 2 -> 16 at 800 rows 13 and 16, at 80 000 17.5 and 19, at 98 400 27 and 20.5, 2 -> 64 at 64 000 25 and 25
+        if (c % 4 || N % 4 || !aligned16(X) || !aligned16(W)) return c > 2 || n >= (N > 32 ? 65536 : 98304);
+        // Where that has its vector path it is ahead on few rows, the longer with little to multiply: 12 -> 20 at 44 000 0.89 of its time, 20 -> 4 0.94,
+        // 12 -> 16 1.22, at 80 000 0.98, 8 -> 20 1.23 and 1.00, 8 -> 12 1.62, 1.38, at 160 000 1.22; rows of 4 channels, 4 -> 16 at 280 000 30 us and 37
+        if (!full) return c >= 20 || (c >= 12 && N > 16) ? n >= 40960 : c >= 8 && (c > 8 || N > 16) && n >= 81920;
+        // It splits the reduction of few rows, here 27 * c terms follow one another: 64 -> 12 at 7000 rows 1.06 of its time, at 12 000 0.92, 96 -> 12 1.72 and 1.23, at
+        // 16 500 1.01, 64 -> 20 at 3200 1.12, at 7000 0.78, 96 -> 36 1.36 and 0.86, 128 -> 20 1.43 and 0.99.  With transposed weights it has its better loop
+        // for rows of a multiple of 64: to 12 channels 1.16 to 1.29 up to 64 000, 0.90 to 1.06 beyond, with 17 neighbours a voxel 1.18; to 20 1.11, 0.84 to 0.98, 1.10; to
+        // 36 and 60 1.28, 0.99, 0.95
+        if (c == 32) return true;
+        if (transposed && c % 64 == 0) return n >= 98304 && (N > 32 || (N > 16 && neighbours <= 11));
+        return n >= (N < 20 ? 192 : 96) * (int64_t)c;
+    }
+    // 16 columns: 32 -> 16 at 800 to 44 000 rows 0.89 to 0.99 of gemm_bf16_kernel's time, at 64 000 1.11 (32 -> 8 1.03 and 1.14), at 80 000 0.94, at 280 000 0.75; data gradient
+    // 0.71 to 0.90 at all sizes
+    if (N <= 16) return full && c == 32 && (transposed || n >= 81920);
+    // Against gemm_bf16_kernel, which splits the reduction of few rows: 32 -> 64 at 16 500 to 32 000 rows 0.76 to 0.87, data gradient 0.64 to 0.74, 64 -> 64 0.88 to 0.97 and 0.89
+    // to 1.02, 32 -> 24 and 64 -> 24 at 16 500 1.02 to 1.10, at 24 000 0.85 and 0.94; longer rows: 96 -> 32 at 32 000 26 us and 30, from 66 000 on 0.61 to 0.84, 128 -> 128 0.86 to 1.00.  Rows that fill a step in part: from 98 000 on 0.71
+    // to 0.95 with 24, 56, 80 channels, 0.90 to 1.03 with 72; with 40, 3 of 8 padding, 0.96 to 1.15 at 98 000 and 127 000, 0.89 to 0.99 at 160 000; with 17 neighbours a
+    // voxel 48 -> 64 1.09 to 1.15, 24 -> 128 1.04 to 1.08
+    if (!full) {
+        if (c < 24 || neighbours > 11 || n < (c * 4 >= (c + 31) / 32 * 96 ? 98304 : 160000)) return false;
+    } else if (n < (c > 64 ? 65536 : N <= 32 && !transposed ? 20480 : 16384)) return false;
+    // Where that kernel's tiles just fill a round of workgroups without splitting: to 32 columns, 52 000 to 64 000 rows, 32 -> 32 1.04 to 1.08, 64 -> 32 0.99 to 1.08 and the
+    // same back (48 000 0.72 to 0.78, 72 000 0.90); to 64, 33 000 to 48 000, 32 -> 64 1.03 to 1.09, 64 -> 64 1.06 to 1.13, back 1.02 to 1.11 (32 000 0.88, 52 000 0.95); to 128, 16 500 to
+    // 32 000, 32 -> 128 1.03 to 1.19, 64 -> 128 1.08 to 1.26, back 1.13 to 1.31 (36 000 0.95 to 1.01).  Data gradients of 32 channels have no such stretch
+    if (full && c <= 64 && (!transposed || c == 64)) {
+        const int64_t tiles = N <= 32 ? (n + 127) / 128 : (n + 63) / 64 * ((N + 63) / 64);
+        if (N <= 32 ? tiles > 384 && tiles <= 540 : tiles > 512 && tiles <= (N <= 64 ? 768 : 1024)) return false;
+    }
     // It lives on the taps that a tile's rows leave out: of 27, 256 rows of thin shells (9 neighbours a voxel) have 10 to 16, of
     // thick ones (17) 18 to 20.  Times over those of gemm_bf16_kernel, index lists also tap-major (which that kernel is faster with) or
     // not, at 0.25 to 1.3 million rows: 9 to 10.6 neighbours 0.53 to 0.96 and 0.51 to 0.91 (64 -> 32 at 10.6 1.02); spheres' shells, 14
@@ -2197,7 +2219,6 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     // to 1.07, 128 -> 128 1.02 to 1.23 and 0.84 to 1.10, 64 -> 32 0.95 to 1.37 and 0.85 to 1.16; 21, 64 -> 64 1.10 to 1.15.  Rows that are no
     // multiple of 64 channels, for which gemm_bf16_kernel has the slower loop, to 64 columns and more: 17 to 18, 32 -> 64 0.88
     // to 1.05, 96 -> 96 0.79 to 1.02; 19 to 21, 32 -> 64 1.00 to 1.08, 26 1.13.
-    const double neighbours = (double)L.nbr_valid / (double)n;
     if (neighbours > (N < 64 ? 11 : (c % 64 ? 18 : (L.dnbr_t ? 11 : 15)))) return false;
     // Up to the last-level cache: the order scatters the rows that a tile reads over the whole of X.  (Thin shells would gain
     // beyond it too, 1.5 million rows, 128 -> 128, 366 MB: 1469 us there, 925 here; thick ones of 64 channels 869 and 884.)
@@ -2398,7 +2419,7 @@ extern "C" hch_status hch_conv_fwd(const hch_levels *levels, int32_t level, hch_
                                          (double)n * (108.0 + 4.0 * c_in + 4.0 * c_out * q.splits) + 4.0 * Kc * c_out, s);
         }
         const double bytes = (double)n * (108.0 + es * c_in + 4.0 * c_out * p.splits) + es * Kc * c_out;
-        if (skip && dtype == HCH_BF16 && conv_bf16_ok(*L, X, W, n, c_in, c_out))
+        if (skip && dtype == HCH_BF16 && conv_bf16_ok(*L, X, W, n, c_in, c_out, false))
             return launch_conv_bf16(*L, (const uint16_t *)X, (const uint16_t *)W, Y, n, c_in, c_out, false,
                                     (double)n * (108.0 + es * c_in + 4.0 * c_out) + es * Kc * c_out, s);
         if (fwd_transposed_weights(dtype, c_in, c_out) && aligned16(X) && aligned16(W) && aligned16(workspace)) {
@@ -2502,7 +2523,7 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
                 return launch_conv_split(q, *L, (const float *)dY, (const float *)W, dX, part, n, c_out, c_in, true,
                                          (double)n * (108.0 + 4.0 * c_out + 4.0 * c_in * q.splits) + 4.0 * wn, s);
         }
-        if (skip && dtype == HCH_BF16 && conv_bf16_ok(*L, dY, W, n, c_out, c_in))
+        if (skip && dtype == HCH_BF16 && conv_bf16_ok(*L, dY, W, n, c_out, c_in, true))
             return launch_conv_bf16(*L, (const uint16_t *)dY, (const uint16_t *)W, dX, n, c_out, c_in, true,
                                     (double)n * (108.0 + es * c_out + 4.0 * c_in) + es * wn, s);
         if (c_out % k_gran(dtype) == 0 && c_in % 4 == 0 && aligned16(dY) && aligned16(W)) {

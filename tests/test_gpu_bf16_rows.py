@@ -57,7 +57,7 @@ def _check(got, want):
 
 
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 127, 128, 129, 300, 700])
-@pytest.mark.parametrize("ci,co", [(2, 2), (6, 18), (18, 6), (34, 66), (50, 50), (62, 30), (126, 130)])
+@pytest.mark.parametrize("ci,co", [(4, 6), (6, 18), (18, 6), (34, 66), (50, 50), (62, 30), (126, 130)])
 def test_ragged_rows(n, ci, co):
     """Even numbers of channels, tails of 2 to 30; the last row's last piece ends at the end of the operand."""
     lv = _levels(n, 32)
@@ -69,7 +69,7 @@ def test_ragged_rows(n, ci, co):
         _check(got, want)
 
 
-@pytest.mark.parametrize("n,ci,co", [(700, 50, 50), (700, 32, 16), (700, 34, 66), (17000, 64, 64), (17000, 62, 30)])
+@pytest.mark.parametrize("n,ci,co", [(700, 50, 50), (700, 16, 32), (700, 34, 66), (17000, 64, 64), (17000, 62, 30)])
 def test_few_rows_are_summed_in_parts(n, ci, co):
     """A rounding errs by 2.25e-8 of what it rounds (test_gpu_small.py), a chain of m of them by sqrt(m / 2) times that.  Sums of 128 terms: 16
     roundings each, 6.4e-8; up to 16 such sums added up: 6.4e-8; together 9.0e-8, below 1e-7.  One chain of 27 * 32 to 27 * 66 terms: 1.6e-7 to 2.4e-7, of 9 * 62: 1.3e-7."""
@@ -77,12 +77,12 @@ def test_few_rows_are_summed_in_parts(n, ci, co):
     X, W, G = _data(n, ci, co)
     out, names = _products(lv, X, W, G)
     for k, (got, want) in enumerate(zip(out, _wants(lv, X, W, G))):
-        if any("conv" in name for name in names[k]):       # (16 -> 32 and the like keep gemm_bf16_kernel)
+        if any("conv" in name for name in names[k]):       # (16 -> 32 stays on gemm_bf16_kernel)
             assert float((got.double() - want).norm() / want.norm()) < 1e-7, names[k]
-    assert any("conv" in name for name in names[0]), names
+    assert any("conv" in name for name in names[0] + names[1]), names
 
 
-@pytest.mark.parametrize("ci,co", [(2, 16), (34, 66), (66, 34), (50, 50)])
+@pytest.mark.parametrize("ci,co", [(98, 6), (34, 66), (66, 34), (50, 50)])
 def test_nothing_comes_of_what_lies_behind_the_weights(ci, co):
     """2 channels modulo 32: a thread's four rows of the last tap's last step end past the last row of the weights."""
     lv = _levels(300, 32)
@@ -110,9 +110,17 @@ ROWS, RAGGED = "conv_bf16", "conv_ragged_bf16"
 
 
 @pytest.mark.parametrize("n,ci,co,fwd,bwd", [
-    (16383, 32, 64, None, None), (16384, 32, 64, ROWS, ROWS), (16385, 64, 64, ROWS, ROWS), (700, 32, 16, ROWS, None), (700, 16, 32, None, ROWS),
-    (65535, 96, 32, None, ROWS), (65536, 96, 32, ROWS, ROWS), (98303, 24, 40, None, None), (98304, 24, 40, RAGGED, RAGGED), (98303, 64, 64, ROWS, ROWS),
-    (98304, 64, 64, ROWS, ROWS), (40959, 12, 20, None, None), (40960, 12, 20, RAGGED, RAGGED), (50000, 4, 16, None, RAGGED), (50000, 4, 20, None, RAGGED)])
+    (16383, 32, 64, None, None), (16384, 32, 64, ROWS, ROWS), (16385, 64, 64, ROWS, ROWS), (700, 32, 16, None, None), (700, 16, 32, None, ROWS),
+    (81919, 32, 16, None, None), (81920, 32, 16, ROWS, None), (65535, 96, 32, None, ROWS), (65536, 96, 32, ROWS, ROWS), (98303, 24, 40, None, None),
+    (98304, 24, 40, RAGGED, None), (160000, 40, 24, RAGGED, RAGGED), (159999, 40, 24, None, RAGGED), (98303, 64, 64, ROWS, ROWS), (98304, 64, 64, ROWS, ROWS),
+    # stretches where gemm_bf16_kernel's tiles fill a round
+    (20479, 32, 32, None, ROWS), (20480, 32, 32, ROWS, ROWS), (49152, 32, 32, ROWS, ROWS), (49153, 32, 32, None, ROWS), (49153, 64, 64, ROWS, ROWS), (69121, 32, 32, ROWS, ROWS), (32768, 32, 64, ROWS, ROWS),
+    (32769, 32, 64, None, ROWS), (32769, 64, 64, None, None), (16384, 64, 128, ROWS, None), (16448, 64, 128, None, None), (32769, 64, 128, ROWS, None),
+    # without gemm_bf16_kernel
+    (40959, 12, 20, None, None), (40960, 12, 20, RAGGED, RAGGED), (50000, 4, 16, None, None), (50000, 4, 20, None, RAGGED), (81920, 12, 12, RAGGED, RAGGED),
+    (81919, 12, 12, None, None), (90000, 8, 12, None, RAGGED), (700, 2, 6, None, RAGGED), (98303, 2, 2, None, None), (98304, 2, 2, RAGGED, RAGGED),
+    (65536, 2, 64, RAGGED, ROWS), (700, 32, 12, ROWS, None), (12287, 64, 12, None, None), (12288, 64, 12, ROWS, None), (6144, 64, 20, ROWS, None),
+    (98304, 20, 64, RAGGED, ROWS), (98303, 20, 64, RAGGED, None)])
 def test_lines_to_the_other_kernels(n, ci, co, fwd, bwd):
     lv = _sheet(n)
     X, W, G = _data(n, ci, co)
