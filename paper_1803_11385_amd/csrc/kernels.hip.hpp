@@ -534,8 +534,9 @@ __device__ __forceinline__ int32_t block_scan(int32_t v, int32_t *part, int32_t 
 
 // Both steps and the tap masks (tile_mask_kernel) for levels of up to PATTERN_SMALL voxels, a workgroup of 1024 per level:
 // keys stay in registers, counts and the neighbour sets by position in LDS.  Bound by its launch and a dozen barriers: three
-// levels of 3177 voxels and less 8.7 us, the three launches 12.6 (and 4 us of the host's time each).
-constexpr int PATTERN_SMALL = 8192;
+// levels of 3177 voxels and less 8.7 us, the three launches 12.6 (and 4 us of the host's time each).  It takes a round of 1024 voxels longer, they do
+// not: calls one after the other 64 voxels 11.8 us and 17.6, 3177 17.4 and 20.6, 6000 20.0 and 20.8, 8100 (with 8192) 23.3 and 20.8.
+constexpr int PATTERN_SMALL = 6144;
 struct PatternSmallArgs { uint32_t *tile_mask[MAX_LEVELS]; };
 __global__ __launch_bounds__(1024) void pattern_small_kernel(LevelSet S, PatternSmallArgs A, int level_first, int32_t *__restrict__ order)
 {

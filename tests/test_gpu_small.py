@@ -1,6 +1,6 @@
 """Few voxels: the gathered products whose wavefronts share out the reduction (conv_small_kernel), at the edges of their tiles of 16
 rows and 32 columns and on both sides of the line to conv_split_kernel, and the row order made by one workgroup per level
-(pattern_small_kernel), up to its 8192 voxels and beyond.
+(pattern_small_kernel), up to its 6144 voxels and beyond.
 
 Bound of a product: the pieces leave out at most 2^-24 of a term; a sum of K terms is rounded about K / 8 times and once per
 wavefront, 0.29 * 2^-23 * sqrt(27 * 130 / 16) = 5e-7 of the result's norm: below 1e-6."""
@@ -109,7 +109,7 @@ def test_numbers_that_are_not_finite(value):
         assert float((a[~near] - b[~near]).norm() / b.norm()) < 1e-6
 
 
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 6143, 6144, 6145, 8191, 8192, 8193])
 def test_row_order(n):
     lv = _levels(n, 64, levels=3, models=1 if n < 60 else 3, seed=1)
     for l in range(3):
