@@ -135,25 +135,29 @@ inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Host memory that the device copies into (tables built there, for hch_level_info).  Copies into ordinary memory go by pieces
 // through a buffer of the runtime's and a copy by the host: 11.5 MB of a 256^3 batch of 8 took 1.8 of 4.0 ms, into pinned
-// memory 0.25.  Pinning costs more than that, so blocks of level sets that are gone are kept for the next ones: HOST_KEPT bytes at
-// most, the longest unused given back first; by any thread, since a block has one owner and its copies are over before it is freed.
-// Where there is no pinned memory it is ordinary memory.
-constexpr size_t HOST_KEPT = (size_t)128 << 20, HOST_STEP = (size_t)256 << 10;
+// memory 0.25.  Making pinned memory costs as much as that saves or more (first build of such a batch in a process 6.4 ms, with ordinary memory 3.0; 192 MB
+// at once 33.4 and 32.4; twenty level sets that stay 5.9 and 6.2 each), so it is made only where one level set follows another: for
+// as many bytes as blocks of ordinary memory have been given back.  Pinned blocks of level sets that are gone are kept for the next ones, HOST_KEPT bytes
+// at most, the longest unused given back first; there are never more than HOST_PINNED bytes, in use and kept.  By any thread: a block has one owner,
+// whose copies are over before it is freed.  Everything else is ordinary memory: level sets that are all kept, larger ones than
+// HOST_KEPT, and where the runtime has no pinned memory.
+constexpr size_t HOST_KEPT = (size_t)128 << 20, HOST_PINNED = 2 * HOST_KEPT, HOST_STEP = (size_t)256 << 10;
 
 class HostBlocks {
     struct Block { char *p; size_t bytes; };
     std::mutex mu;
     std::vector<Block> kept;                   // longest unused first
-    size_t held = 0;
-    void give_back(size_t i)
+    size_t held = 0, pinned = 0;               // bytes kept; of all pinned blocks
+    size_t wanted = 0;                         // of ordinary memory given back, less what was pinned instead; HOST_KEPT at most
+    void unpin(const Block &b)
     {
-        held -= kept[i].bytes;
-        (void)hipHostFree(kept[i].p);
-        kept.erase(kept.begin() + (std::ptrdiff_t)i);
+        (void)hipHostFree(b.p);
+        std::lock_guard<std::mutex> lock(mu);
+        pinned -= b.bytes;
     }
 public:
     static HostBlocks &get() { static HostBlocks *const all = new HostBlocks; return *all; }      // outlives every level set
-    char *take(size_t *bytes)                  // null: none to be had
+    char *take(size_t *bytes)                  // null: ordinary memory will do
     {
         *bytes = round_up(*bytes, HOST_STEP);
         {
@@ -168,22 +172,45 @@ public:
                 kept.erase(kept.begin() + (std::ptrdiff_t)best);
                 return p;
             }
+            if (*bytes > wanted || pinned + *bytes > HOST_PINNED) return nullptr;
+            wanted -= *bytes;
+            pinned += *bytes;
         }
         void *p = nullptr;
         if (hipHostMalloc(&p, *bytes, hipHostMallocPortable) == hipSuccess) return (char *)p;
         (void)hipGetLastError();
+        std::lock_guard<std::mutex> lock(mu);
+        pinned -= *bytes;
         return nullptr;
     }
     void keep(char *p, size_t bytes)
     {
-        std::lock_guard<std::mutex> lock(mu);
-        try {
-            kept.push_back(Block{p, bytes});
-            held += bytes;
-        } catch (const std::bad_alloc &) {
-            (void)hipHostFree(p);
+        Block out{nullptr, 0};
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            try {
+                kept.push_back(Block{p, bytes});
+                held += bytes;
+            } catch (const std::bad_alloc &) {
+                out = Block{p, bytes};
+            }
         }
-        while (held > HOST_KEPT) give_back(0);
+        if (out.p) unpin(out);
+        for (;;) {                             // (the runtime takes its time over a block: not while others wait)
+            {
+                std::lock_guard<std::mutex> lock(mu);
+                if (held <= HOST_KEPT) return;
+                out = kept.front();
+                held -= out.bytes;
+                kept.erase(kept.begin());
+            }
+            unpin(out);
+        }
+    }
+    void gone(size_t bytes)                    // ordinary memory
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        wanted = std::min(wanted + round_up(bytes, HOST_STEP), HOST_KEPT);
     }
 };
 
@@ -195,7 +222,11 @@ public:
     HostBlock() = default;
     HostBlock(const HostBlock &) = delete;
     HostBlock &operator=(const HostBlock &) = delete;
-    ~HostBlock() { if (p) HostBlocks::get().keep(p, bytes); }
+    ~HostBlock()
+    {
+        if (p) HostBlocks::get().keep(p, bytes);
+        else if (ordinary) HostBlocks::get().gone(bytes);
+    }
     char *get() const { return p ? p : ordinary.get(); }
     bool pinned() const { return p != nullptr; }
     void make(size_t n)                        // once

@@ -39,6 +39,31 @@ int hipFree(void *p)
         if (block[k] == p) { block[k] = 0; live -= size_of[k]; break; }
     return f(p);
 }
+long host_made, host_freed, host_fail;
+size_t host_live, host_most;
+static void *host_block[256];
+static size_t host_size[256];
+int hipHostMalloc(void **p, size_t n, unsigned flags)
+{
+    static int (*f)(void **, size_t, unsigned);
+    if (!f) f = (int (*)(void **, size_t, unsigned))real("hipHostMalloc");
+    int e = f(p, host_fail ? (size_t)1 << 60 : n, flags);
+    for (int k = 0; k < 256 && !e; ++k)
+        if (!host_block[k]) {
+            host_block[k] = *p; host_size[k] = n; host_live += n; ++host_made;
+            if (host_live > host_most) host_most = host_live;
+            break;
+        }
+    return e;
+}
+int hipHostFree(void *p)
+{
+    static int (*f)(void *);
+    if (!f) f = (int (*)(void *))real("hipHostFree");
+    for (int k = 0; k < 256 && p; ++k)
+        if (host_block[k] == p) { host_block[k] = 0; host_live -= host_size[k]; ++host_freed; break; }
+    return f(p);
+}
 """
 
 CHILD = r"""
@@ -126,4 +151,86 @@ for n in (300, 9106, 9107):
     lv, asked, _ = build(args, levels=6)
     assert (max(asked) > 1 << 27) == (n == 9107), (n, asked)
     same(lv, build(args, levels=6, call=hch.hch_build_levels)[0])
+""")
+
+
+HOST = r"""
+made, freed, refused = (C.c_long.in_dll(hook, k) for k in ("host_made", "host_freed", "host_fail"))
+pinned, most = (C.c_size_t.in_dll(hook, k) for k in ("host_live", "host_most"))
+
+def check(lv, coords):
+    # the host copies are perfect hashes of the positions (Eq.1)
+    assert np.array_equal(lv.info(0).coords_host(), coords)
+    for l in range(lv.n_levels):
+        i = lv.info(l)
+        H, T, Phi, V, pos = i.H_host(), i.T_host(), i.Phi_host().astype(np.int64), i.V_host(), i.coords_host().astype(np.int64)
+        for v in range(len(i.mbar)):
+            m, r, p = int(i.mbar[v]), int(i.rbar[v]), pos[i.N[v]:i.N[v + 1]]
+            s = (p % m + Phi[i.R[v] + ((p[:, 0] % r) * r + p[:, 1] % r) * r + p[:, 2] % r]) % m
+            slot = i.M[v] + (s[:, 0] * m + s[:, 1]) * m + s[:, 2]
+            assert np.array_equal(H[slot], np.arange(len(p))) and np.array_equal(T[slot], p)
+            assert np.all(V[i.M[v]:i.M[v + 1]] == v) and int((H[i.M[v]:i.M[v + 1]] >= 0).sum()) == len(p)
+"""
+
+
+def test_pinned_host_copies(tmp_path):
+    """Level sets that stay have their host copies in ordinary memory; one that follows another takes pinned memory, once, and it
+    passes on to the next.  Without pinned memory it is ordinary memory again, and no error is left behind."""
+    _child(tmp_path, HOST + r"""
+args = (*batch(256, 30000), 256)
+new = lambda: hch.hch_build_levels_device(*args, 5, stream=0)
+some = [new() for _ in range(3)]
+assert made.value == 0
+for lv in some: check(lv, args[0]); lv.free()
+for k in range(4):
+    lv = new(); check(lv, args[0])
+    other = batch(256, 20000)
+    lw = hch.hch_build_levels_device(*other, 256, 5, stream=0); check(lw, other[0]); check(lv, args[0])
+    assert made.value == 4 and freed.value == 0, (k, made.value)        # two blocks each, the tables' and the offsets'
+    lv.free(); lw.free()
+refused.value = 1
+some = [new() for _ in range(5)]                 # 3 more than there are blocks for
+for lv in some: check(lv, args[0]); lv.free()
+assert made.value == 4
+refused.value = 0
+lv = new(); check(lv, args[0]); lv.free()
+""")
+
+
+def test_pinned_host_memory_is_bounded(tmp_path):
+    """256 MB of it at most, 128 MB while no level set lives; a level set with more than that takes none for its tables and does not empty the pool."""
+    _child(tmp_path, HOST + r"""
+args = (*batch(256, 30000, 40), 256)             # some 40 MB
+new = lambda: hch.hch_build_levels_device(*args, 4, stream=0)
+for k in range(4):
+    some = [new() for _ in range(8)]
+    assert pinned.value <= 256 << 20
+    for lv in some: check(lv, args[0]); lv.free()
+    assert pinned.value <= 128 << 20, k
+assert most.value > 128 << 20 and freed.value > 0
+counts = made.value, freed.value
+large = (*batch(256, 30000, 160), 256)
+lv = hch.hch_build_levels_device(*large, 4, stream=0); check(lv, large[0]); lv.free()
+assert made.value <= counts[0] + 1 and freed.value <= counts[1] + 1, (made.value, freed.value, counts)      # its offsets' own block
+""")
+
+
+def test_host_copies_of_several_threads(tmp_path):
+    """Blocks pass between level sets of three threads; nobody reads another's."""
+    _child(tmp_path, HOST + r"""
+import threading
+wrong = []
+def work(seed):
+    try:
+        for k in range(12):
+            a = batch(256, 9000 + 4000 * ((seed + k) % 3) + seed)
+            lv = hch.hch_build_levels_device(*a, 256, 4, stream=0)
+            check(lv, a[0])
+            lv.free()
+    except BaseException as e:
+        wrong.append(repr(e))
+threads = [threading.Thread(target=work, args=(s,)) for s in range(3)]
+for t in threads: t.start()
+for t in threads: t.join()
+assert not wrong and made.value > 0, wrong
 """)
