@@ -2268,19 +2268,19 @@ static hch_status launch_conv_bf16(const Level &L, const uint16_t *X, const uint
     const bool few = (int64_t)m_tiles * ((N + 63) / 64) < 512 && 27 * c >= 512;
     const int nt = N <= 32 || few ? 2 : 4, ks = c % 64 == 0 ? 64 : 32;
     const bool full = c % 32 == 0 && aligned16(X) && aligned16(W);
-    static int ids[2][3][2];                           // [columns][channels a step: part of 32, 32, 64][transposed]
+    const int wv = full && nt == 4 && ks == 64 && n >= 98304 ? 8 : 4;           // see conv_bf16_rows
+    static int ids[2][3][2][2];                        // [columns][channels a step: part of 32, 32, 64][wavefronts][transposed]
     static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
     (void)ids_ready;
-    int &id = ids[nt / 4][full ? ks / 32 : 0][transposed];
+    int &id = ids[nt / 4][full ? ks / 32 : 0][wv / 8][transposed];
     if (id < 0) {
         char nm[96];
-        if (full) snprintf(nm, sizeof nm, "conv_bf16_kernel<%d, %d, %s>", nt, ks, transposed ? "true" : "false");
+        if (full) snprintf(nm, sizeof nm, "conv_bf16_kernel<%d, %d, %d, %s>", nt, ks, wv, transposed ? "true" : "false");
         else snprintf(nm, sizeof nm, "conv_ragged_bf16_kernel<%d, %s>", nt, transposed ? "true" : "false");
         id = hch::Profiler::get().id_for(nm);
     }
     {
         hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
-        const int wv = full && nt == 4 && ks == 64 && n >= 98304 ? 8 : 4;       // see conv_bf16_rows
         const unsigned group = wv / 2;
         const dim3 grid(hch::skip_grid((m_tiles + group - 1) / group, hch::skip_chunk(m_tiles, group)), (unsigned)((N + 16 * nt - 1) / (16 * nt)));
         const int vec_out = N % 4 == 0 && aligned16(out);

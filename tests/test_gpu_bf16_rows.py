@@ -130,6 +130,13 @@ def test_lines_to_the_other_kernels(n, ci, co, fwd, bwd):
         _check(got, want)
 
 
+@pytest.mark.parametrize("n,waves", [(98303, 4), (98304, 8)])
+def test_workgroups_of_256_rows(n, waves):
+    """64 channels to 64 columns, by the names that a profiler prints."""
+    _, names = _products(_sheet(n), *_data(n, 64, 64))
+    assert names == [[f"conv_bf16_kernel<4, 64, {waves}, false>"], [f"conv_bf16_kernel<4, 64, {waves}, true>"]]
+
+
 def _sheet(n):
     """A plane of voxels, so with up to 9 neighbours each."""
     q = torch.arange(n)

@@ -617,8 +617,8 @@ def test_weights_that_are_not_finite_over_general_index_rows(batch, fields, valu
         assert bool((~torch.isfinite(out[hit]) | (out[hit].abs() > 1e35)).all())
 
 
-@pytest.mark.parametrize("ci,co,fwd,bwd", [(32, 32, "2, 32, false", "2, 32, true"), (96, 20, "2, 32, false", None), (20, 96, None, "2, 32, true"),
-                                          (64, 64, "4, 64, false", "4, 64, true")])
+@pytest.mark.parametrize("ci,co,fwd,bwd", [(32, 32, "2, 32, 4, false", "2, 32, 4, true"), (96, 20, "2, 32, 4, false", None), (20, 96, None, "2, 32, 4, true"),
+                                          (64, 64, "4, 64, 8, false", "4, 64, 8, true")])
 def test_bf16_weights_that_are_not_finite(large, ci, co, fwd, bwd):
     """The forms of conv_bf16_kernel with steps of 32 channels and 32 columns (and one other): an infinite weight reaches the
     rows that have its tap, in its column.  (Rows without the tap have 0 * inf there or leave the tap out, as their tile
