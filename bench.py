@@ -95,7 +95,7 @@ def cpu_baseline(coords, offs, X0, W, u, max_shapes, budget_s=16.0):
 
 def mfma_peak(kernel):
     """Dense peak of the matrix instruction that a kernel multiplies with, for the products it is asked for."""
-    if "_split_kernel" in kernel:
+    if "_split_kernel" in kernel or "conv_small_kernel" in kernel:
         return MFMA_SPLIT_PEAK_TFLOPS
     return MFMA_BF16_PEAK_TFLOPS if "bf16" in kernel else MFMA_F32_PEAK_TFLOPS
 
@@ -322,7 +322,8 @@ def main():
         traffic = counter-measured HBM bytes per launch from the committed summary; null when
         that summary was measured on other sources than the ones running now."""
         ai = st["flops"] / max(1.0, st["bytes"])
-        product = any(t in name for t in ("gemm", "conv_direct", "conv_narrow4", "conv_split", "conv_bf16", "field_split", "wgrad_"))
+        product = any(t in name for t in ("gemm", "conv_direct", "conv_narrow4", "conv_split", "conv_small", "columns_split", "dcol_split", "conv_bf16",
+                                          "conv_ragged_bf16", "field_split", "wgrad_"))
         if product and ai >= mfma_peak(name) * 1e12 / (HBM_PEAK_GBS * 1e9):
             bound, achieved, peak, unit = "mfma", st["flops"] / (st["ms"] * 1e-3) / 1e12, mfma_peak(name), "TFLOP/s"
         else:
