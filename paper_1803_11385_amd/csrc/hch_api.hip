@@ -2112,30 +2112,32 @@ static hch_status launch_columns_split(const ConvSplitPlan &p, const Level &L, c
     float *dst = p.splits > 1 ? part : out;
     const unsigned n_tiles = (unsigned)((N + 16 * p.nt - 1) / (16 * p.nt));
     const bool fast = c % 32 == 0;
-    static int ids[3][2][2];                           // [columns][wavefronts][fast]
+    const bool stream = c % 16 == 0 && n * 108 * c > (int64_t)(c == 16 ? 256 : 288) << 20;
+    static int ids[3][2][2][2];                        // [columns][wavefronts][fast][stream]
     static const bool ids_ready = [] { memset(ids, 0xFF, sizeof ids); return true; }();
     (void)ids_ready;
-    int &id = ids[p.nt / 2][p.wv / 8][fast];
+    int &id = ids[p.nt / 2][p.wv / 8][fast][stream];
     if (id < 0) {
         char nm[96];
-        snprintf(nm, sizeof nm, "columns_split_kernel<%d, %d, %s>", p.nt, p.wv, fast ? "true" : "false");
+        snprintf(nm, sizeof nm, "columns_split_kernel<%d, %d, %s, %s>", p.nt, p.wv, fast ? "true" : "false", stream ? "true" : "false");
         id = hch::Profiler::get().id_for(nm);
     }
     {
         hch::LaunchTimer lt(id, s, bytes, 2.0 * 27 * c * (double)N * n);
-        const int col_stream = c % 16 == 0 && n * 108 * c > (int64_t)256 << 20;
         const unsigned group = (unsigned)p.wv / 4, groups = (p.m_tiles + group - 1) / group;
         const dim3 grid((groups + hch::NUM_XCD - 1) / hch::NUM_XCD * hch::NUM_XCD, n_tiles, (unsigned)p.splits);
         const int vec_out = N % 4 == 0 && aligned16(dst);
-#define HCH_COLUMNS_SPLIT(NT_, WV_)                                                                            \
-        do {                                                                                                   \
-            if (fast) HCH_LAUNCH((hch::columns_split_kernel<NT_, WV_, true>), grid, dim3(64 * WV_), 0, s, X, W, dst, L.dnbr, col, col_stream, (int)n, N, c, p.m_tiles, n * N, vec_out); \
-            else HCH_LAUNCH((hch::columns_split_kernel<NT_, WV_, false>), grid, dim3(64 * WV_), 0, s, X, W, dst, L.dnbr, col, col_stream, (int)n, N, c, p.m_tiles, n * N, vec_out); \
+#define HCH_COLUMNS_SPLIT_F(NT_, WV_, FAST_)                                                                                                     \
+        do {                                                                                                                                     \
+            if (stream) HCH_LAUNCH((hch::columns_split_kernel<NT_, WV_, FAST_, true>), grid, dim3(64 * WV_), 0, s, X, W, dst, L.dnbr, col, (int)n, N, c, p.m_tiles, n * N, vec_out); \
+            else HCH_LAUNCH((hch::columns_split_kernel<NT_, WV_, FAST_, false>), grid, dim3(64 * WV_), 0, s, X, W, dst, L.dnbr, col, (int)n, N, c, p.m_tiles, n * N, vec_out); \
         } while (0)
+#define HCH_COLUMNS_SPLIT(NT_, WV_) do { if (fast) HCH_COLUMNS_SPLIT_F(NT_, WV_, true); else HCH_COLUMNS_SPLIT_F(NT_, WV_, false); } while (0)
         if (p.nt == 1) HCH_COLUMNS_SPLIT(1, 4);
         else if (p.nt == 2) { if (p.wv == 8) HCH_COLUMNS_SPLIT(2, 8); else HCH_COLUMNS_SPLIT(2, 4); }
         else { if (p.wv == 8) HCH_COLUMNS_SPLIT(4, 8); else HCH_COLUMNS_SPLIT(4, 4); }
 #undef HCH_COLUMNS_SPLIT
+#undef HCH_COLUMNS_SPLIT_F
     }
     HCH_LAUNCH_CHECK("columns_split_kernel");
     return p.splits > 1 ? launch_reduce(part, out, n * N, p.splits, s) : HCH_OK;

@@ -12,14 +12,14 @@ namespace hch {
 // instructions and the cutting, as conv_split_kernel, with more.  The two launches -> this one: 4 -> 16 at 280 000 rows 66 -> 34 us,
 // 12 -> 20 199 -> 138, 16 -> 32 237 -> 122, 32 -> 64 503 -> 232; at 82 000 16 -> 32 67 -> 38, 32 -> 64 144 -> 85; at 23 000 32 -> 64
 // 49 -> 33, 64 -> 128 115 -> 79; at 800 18 -> 14.5, 128 -> 256 34 -> 26.
-// col_stream: stores past the caches.  64-byte pieces only (pieces that share a sector with the next step's become two writes: 12 -> 20 at
-// 280 000 258 us), and with matrices beyond the last-level cache: 16 -> 32 at 159 000 (275 MB) 91 -> 73, 32 -> 64 at 282 000 292 -> 232, at 49 000
-// (171 MB) 48 -> 46, but 32 -> 16 there 33 -> 42.
+// STREAM: stores past the caches, a form of the kernel (as a condition in the loop the compiler makes one store of both).  64-byte pieces only (pieces
+// that share a sector with the next step's become two writes: 12 -> 20 at 280 000 258 us), and with matrices beyond the last-level cache: 16 -> 32 at
+// 159 000 (263 MB) 93 -> 75, 32 -> 64 at 282 000 298 -> 230, 16 -> 16 197 -> 124, at 593 000 32 -> 64 615 -> 583, with the weight gradient that reads the matrix
+// 305 -> 278 (16 -> 32), 593 -> 571, 301 -> 277, 1190 -> 1150; below, 32 -> 16 at 82 000 (270 MB) 56 -> 62.
 // FAST: rows of a multiple of 32 channels; a step lies within one tap.
-template <int NT, int WV, bool FAST>
+template <int NT, int WV, bool FAST, bool STREAM>
 __global__ __launch_bounds__(64 * WV) void columns_split_kernel(
-    const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr, float *__restrict__ col, int col_stream,
-    int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
+    const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr, float *__restrict__ col, int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
 {
     typedef ConvLds<NT, WV> L;
     constexpr int BN = L::BN, ROWS = L::ROWS, GROUP = ROWS * WV / 64;     // 64-row tiles per workgroup
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(64 * WV) void columns_split_kernel(
             for (int q = 0; q < AU; ++q) {
                 if (row0 + ar + 8 * q >= M) continue;
                 u32x4 *dst = reinterpret_cast<u32x4 *>(col + (int64_t)(row0 + ar + 8 * q) * K + k_col);
-                if (col_stream) __builtin_nontemporal_store(ra[q], dst); else *dst = ra[q];
+                if constexpr (STREAM) __builtin_nontemporal_store(ra[q], dst); else *dst = ra[q];
             }
         k_col += 32;
     };

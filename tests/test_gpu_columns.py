@@ -64,11 +64,14 @@ def test_weights_end_where_they_end(n, ci, co):
     assert torch.equal(Y, _forward(lv, X, W)[0])
 
 
-def test_column_matrix_beyond_the_caches():
-    """More than 256 MB with rows of whole 64-byte pieces: stored past the caches."""
-    lv = _levels(170000, 128, models=2)
-    X, W, G = _data(170000, 16, 32)
-    Y, col, _ = _forward(lv, X, W)
+@pytest.mark.parametrize("n,ci,co,stream", [(170000, 16, 32, True), (155345, 16, 16, True), (155344, 16, 16, False), (90000, 32, 64, True), (87381, 32, 16, False),
+                                            (60000, 48, 20, True), (110000, 24, 16, False), (40000, 96, 130, True)])
+def test_column_matrix_beyond_the_caches(n, ci, co, stream):
+    """More than 256 MB (288 with more than 16 channels) with rows of whole 64-byte pieces: stored past the caches."""
+    lv = _levels(n, 128, models=2)
+    X, W, G = _data(n, ci, co)
+    Y, col, names = _forward(lv, X, W)
+    assert [k.endswith("true>") for k in names if k.startswith("columns_split_kernel")] == [stream], names
     assert torch.equal(col, _columns(lv, X))
     want = _reference(lv, X, W, G)[0]
     assert float((Y.double() - want).norm() / want.norm()) < 1e-6
