@@ -114,8 +114,8 @@ def test_allocation_failures(tmp_path):
     for the checks of the positions: the host does them then.  What was out of memory leaves nothing behind for
     the next call, which succeeds."""
     _child(tmp_path, r"""
-for call, n in ((hch.hch_build_levels_device, 30000), (hch.hch_build_levels, 3000)):
-    args = (*batch(256, n), 256)
+for call, u, n, models in ((hch.hch_build_levels_device, 256, 30000, 2), (hch.hch_build_levels_device, 64, 40000, 1), (hch.hch_build_levels, 256, 3000, 2)):
+    args = (*batch(u, n, models), u)             # two models: a workgroup per table; one of 40 000 voxels: launches over memory
     want, asked, _ = build(args, call=call)
     if call is hch.hch_build_levels_device:
         same(build(args, (0, 1))[0], want)
@@ -130,15 +130,17 @@ def test_memory_of_the_checks(tmp_path):
     """The checks of the positions on the device are no reason to run out of memory: where an allocation fails while
     theirs is held, the build does without it.  It is held until the tables are made, not for what comes after."""
     _child(tmp_path, r"""
-args = (*batch(256, 30000), 256)
-want, asked, used = build(args)
-held = [i for i in range(1, len(asked)) if used[i] >= sum(asked[:i])]        # with everything before them still there
-assert held == list(range(1, len(asked) - 2)) and max(used[-2:]) < sum(asked[:-2]) - asked[0], (asked, used)
-for k in range(4):           # theirs, the tables, the failed pairs, the first attempt; later ones depend on the attempts
-    lv, _, _ = build(args, (k, k + 1))
-    assert lv is not None, k
-    same(lv, want)
-    assert build(args, (k, 256))[0] is None
+for args, first_ones in (((*batch(256, 30000), 256), 3), ((*batch(64, 40000, 1), 64), 4)):
+    want, asked, used = build(args)
+    used = [u - used[0] for u in used]
+    held = [i for i in range(1, len(asked)) if used[i] >= sum(asked[:i])]        # with everything before them still there
+    assert held == list(range(1, len(asked) - 2)) and max(used[-2:]) < sum(asked[:-2]) - asked[0], (asked, used)
+    # theirs, the tables, (launches over memory: the failed pairs,) the first attempt; later ones depend on the attempts
+    for k in range(first_ones):
+        lv, _, _ = build(args, (k, k + 1))
+        assert lv is not None, k
+        same(lv, want)
+        assert build(args, (k, 256))[0] is None
 """)
 
 

@@ -109,6 +109,36 @@ def test_numbers_that_are_not_finite(value):
         assert float((a[~near] - b[~near]).norm() / b.norm()) < 1e-6
 
 
+@pytest.mark.parametrize("a,b", [(1e-34, 1.0), (1.0, 1e-36), (1e-40, 1e20), (1e20, 1e-40), (1e30, 1e-30), (1e15, 1e15)])
+@pytest.mark.parametrize("ci,co", [(3, 16), (33, 40)])
+def test_ends_of_the_range(ci, co, a, b):
+    """As test_gpu_split.py, with sums that leave the scaled range (1e15) and are repeated with the fp32 instruction, a rounding per 4 terms."""
+    lv = _levels(700, 32)
+    X, W, G = _data(700, ci, co)
+    X, W, G = X * a, W * b, G * a
+    Y, dX, names = _products(lv, X, W, G)
+    assert {k.split("<")[0] for k in names} == {"conv_small_kernel"}, names
+    for got, want in zip((Y, dX), _reference(lv, X, W, G)):
+        assert float((got.double() - want).norm() / want.norm()) < 1e-6
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_weights_that_are_not_finite(value):
+    """They reach the rows that have their tap, in their column, and no others."""
+    n, ci, co = 300, 33, 40
+    lv = _levels(n, 32)
+    X, W, G = _data(n, ci, co)
+    clean = _products(lv, X, W, G)
+    W[5, 3, 7] = value
+    got = _products(lv, X, W, G)
+    nb = torch.from_numpy(lv.info(0).device_nbr27().astype(np.int64)).cuda()
+    for a, b, tap, column in ((got[0], clean[0], 5, 7), (got[1], clean[1], 21, 3)):
+        hit = torch.zeros_like(a, dtype=torch.bool)
+        hit[nb[:, tap] >= 0, column] = True
+        assert bool(hit.any()) and not torch.isfinite(a[hit]).any()
+        assert float((a[~hit] - b[~hit]).norm() / b.norm()) < 1e-6
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 6143, 6144, 6145, 8191, 8192, 8193])
 def test_row_order(n):
     lv = _levels(n, 64, levels=3, models=1 if n < 60 else 3, seed=1)

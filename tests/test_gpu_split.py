@@ -58,6 +58,14 @@ def _reference(nbr, X, W, G):
     return Y, dX, dW
 
 
+def _forms(lv, X, W, G):
+    """The kernels of the forward product and the data gradient, without their arguments."""
+    (n, ci), co, Y, dX = X.shape, G.shape[1], torch.empty_like(G), torch.empty_like(X)
+    names = [_launched(lambda: hch.hch_conv_fwd(lv, 0, hch.HCH_F32, X, W, Y, ci, co, _ws(lv, 0, ci, co), hch.HCH_ALGO_FUSED)),
+             _launched(lambda: hch.hch_conv_bwd_data(lv, 0, hch.HCH_F32, G, W, dX, ci, co, _ws(lv, 0, ci, co), hch.HCH_ALGO_FUSED))]
+    return {k.split("<")[0] for some in names for k in some if not k.startswith("splitk_reduce")}
+
+
 def _check(got, want):
     for g, w, what in zip(got, want, ("Y", "dX", "dW")):
         err = float((g.double() - w).norm() / w.norm())
@@ -82,9 +90,10 @@ def test_products_on_split_operands(oracle, batch, level, ci, co):
 
 
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 1000])
-@pytest.mark.parametrize("ci,co", [(33, 50), (64, 18)])
+@pytest.mark.parametrize("ci,co", [(33, 50), (64, 18), (64, 130), (96, 96)])
 def test_small_batches_in_any_order(oracle, n, ci, co):
-    """Voxels in an order of their own (not by position), in two models."""
+    """Voxels in an order of their own (not by position), in two models.  The first two pairs of channels are conv_small_kernel's, the
+    others conv_split_kernel's."""
     rng = np.random.default_rng(n)
     pos = rng.permutation(12 ** 3)[:n]
     coords = np.stack([pos // 144, pos // 12 % 12, pos % 12], 1).astype(np.int32)
@@ -93,6 +102,7 @@ def test_small_batches_in_any_order(oracle, n, ci, co):
     nbr = oracle.neighbours(oracle.build_hierarchy(coords, offs, 16, 1)[0])
     X, W, G = (torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).cuda() for s in ((n, ci), (27, ci, co), (n, co)))
     _check(_run(lv, 0, X, W, G), _reference(nbr, X, W, G))
+    assert _forms(lv, X, W, G) == ({"conv_split_kernel"} if ci * co > 8192 else {"conv_small_kernel"})
 
 
 @pytest.mark.parametrize("n", [24512, 24513, 24576, 24577, 24641])
@@ -138,7 +148,7 @@ WORST = np.array([0x3F80FFFF, 0x3F807FC0, 0x3F800001, 0x3FFFFFFF], np.uint32).vi
 
 
 @pytest.mark.parametrize("values", ["worst", "random"])
-@pytest.mark.parametrize("ci,co", [(33, 50), (64, 64)])
+@pytest.mark.parametrize("ci,co", [(33, 50), (64, 64), (91, 92), (64, 130)])
 def test_single_products(values, ci, co):
     """Voxels without neighbours and rows with one number that is not zero: every result is one
     product.  The pieces leave out at most
@@ -163,6 +173,7 @@ def test_single_products(values, ci, co):
     dW = _run(lv, 0, X, W, full)[2]
     C = W[13].double()
     x, g = X[q, q].double(), G[q, q].double()
+    assert _forms(lv, X, W, G) == ({"conv_split_kernel"} if ci * co > 8192 else {"conv_small_kernel"})
     for got, want in ((Y, x[:, None] * C[:n]), (dX, g[:, None] * C.T[:n]), (dW[13, :n], x[:, None] * full.double())):
         err = (got.double() - want) / want.abs()
         assert float(err.abs().max()) <= 2.0 ** -23
