@@ -134,9 +134,9 @@ void free_level(Level &L)
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Host memory that the device copies into (tables built there, for hch_level_info).  Copies into ordinary memory go by pieces
-// through a buffer of the runtime's and a copy by the host: 11.5 MB of a 256^3 batch of 8 took 1.8 of 4.0 ms, into pinned
-// memory 0.25.  Making pinned memory costs as much as that saves or more (first build of such a batch in a process 6.4 ms, with ordinary memory 3.0; 192 MB
-// at once 33.4 and 32.4; twenty level sets that stay 5.9 and 6.2 each), so it is made only where one level set follows another: for
+// through a buffer of the runtime's and a copy by the host: builds of a 256^3 batch of 8 (17 MB), one after the other in a process of their own, 7.9 ms,
+// with pinned memory 7.0.  Making pinned memory costs more than that (the build that makes it 6.4 where the next ones take 2.8) or as much as it
+// saves (192 MB in each build 33.4, ordinary 32.4; twenty level sets that stay 5.9 and 6.2 each), so it is made only where one level set follows another: for
 // as many bytes as blocks of ordinary memory have been given back.  Pinned blocks of level sets that are gone are kept for the next ones, HOST_KEPT bytes
 // at most, the longest unused given back first; there are never more than HOST_PINNED bytes, in use and kept.  By any thread: a block has one owner,
 // whose copies are over before it is freed.  Everything else is ordinary memory: level sets that are all kept, larger ones than
@@ -695,7 +695,7 @@ static hch_status place_in_lds(hch_levels *hl, std::vector<PairWork> &work, Devi
     for (int i = 0; i < n_pairs; ++i) active[i] = i;
     for (int round = 0; !active.empty(); ++round) {
         if (round >= 24) return fail(HCH_EBUILD, "hch_build_levels_device: perfect hash construction failed");
-        const int na = (int)active.size(), at_once = std::max(1, std::min(SIDES_AT_ONCE, 256 / na));
+        const int na = (int)active.size(), at_once = std::max(1, std::min(SIDES_AT_ONCE, (int)hch::NUM_CU / na));
         std::vector<hch::AttemptDesc> desc;
         std::vector<int> pair_of;
         int64_t cells = 0, vox = 0;
@@ -2144,7 +2144,9 @@ static hch_status launch_columns_split(const ConvSplitPlan &p, const Level &L, c
 }
 
 // The gradient of the column matrix on split operands (dcol_split_kernel): rows of 32, 64 or 128 gradients, which the wavefronts keep in
-// registers, 32-bit byte offsets.  Few rows of 128 are cut for too few columns each: with the gather that follows, 128 -> 128 at 800
+// registers and whose weights share out evenly over 512 threads (not 96 or 160), 32-bit byte offsets.  256 take twice the registers, two workgroups to
+// a CU: 64 -> 256 at 800 voxels 19 us on the fp32 instruction and 29, at 5400 57 and 64.5, at 23 000 195 and 164, and levels with so many channels
+// have few voxels.  Few rows of 128 are cut for too few columns each: with the gather that follows, 128 -> 128 at 800
 // voxels 17 us on the fp32 instruction, 20 here, 64 -> 128 at 2700 23 and 25, at 5400 37 and 32, 128 -> 128 65 and 47.5
 static bool dcol_split_ok(int64_t n, int c_in, int c_out)
 {
@@ -2172,18 +2174,23 @@ static hch_status launch_dcol_split(const float *dY, const float *W, float *dcol
 }
 
 // The same products for few voxels (conv_small_kernel).  It reads all weights of its taps once per 16 rows, so the line lies at little
-// work, and for the data gradient, whose weights it reads in pieces of 16 bytes, lower.  Calls one after the other (10 us: what the
-// host takes for one) against conv_split_kernel with the launch that adds its parts: forward 16 -> 32 at 12 000 voxels 9.8 us and 11.1, 32 -> 64 at 3200
-// 10 and 16, at 6000 12.5 and 16.6, at 12 000 22 and 21.5, 64 -> 64 at 3200 16.5 and 21, 64 -> 128 at 800 10.5 and 16, at 3200 28 and 26,
-// 128 -> 256 at 250 18 and 18; data gradient 32 -> 16 at 12 000 10 and 12.5, 64 -> 32 at 3200 12 and 15, at 6000 18 and 16, 64 -> 64 at 800 11
-// and 15, at 3200 20 and 20, 128 -> 64 at 250 18 and 16.  (Tiles of 64 columns 10.2 and 16 with 32 -> 64 and 64 -> 64 at 3200, 16 wavefronts 11.5 and 18.)
+// work, and for the data gradient, whose weights it reads in pieces of 16 bytes, or one by one where rows are no multiple of 8 channels, lower.  Calls one
+// after the other (10 us: what the host takes for one) against conv_split_kernel with the launch that adds its parts: forward 16 -> 32 at 12 000 voxels 9.8 us
+// and 11.1, 32 -> 64 at 3200 10 and 16, at 6000 12.5 and 16.6, 64 -> 64 at 1500 10.5 and 16, 64 -> 128 at 800 10.5 and 16; data gradient 32 -> 16 at
+// 12 000 10 and 12.5, 64 -> 32 at 2200 11 and 15.  (Tiles of 64 columns 10.2 and 16 with 32 -> 64 and 64 -> 64 at 3200, 16 wavefronts 11.5 and 18.)
+// The lines keep every call that was behind (of 25 by 16 pairs of channels at 23 level sets from 60 to 40 000 voxels, both directions) with conv_split_kernel, which
+// splits long reductions over workgroups: 256 -> 32 at 800 voxels 14 us, 31 here, 128 -> 32 14.5 and 17.5, 96 -> 20 13.4 and 14.9; 16 -> 32 at 24 000 14 and 16, 12 -> 5 at
+// 30 000 11.3 and 14.1, 32 -> 5 at 18 000 14.3 and 15.9, 80 -> 40 at 2200 17 and 20, 60 -> 40 15 and 16.5; data gradient of 100 channels to 32 at 800 13.5 and 26, of 60 to 32
+// 13 and 17.5, of 128 to 32 14 and 20, of 12 to 32 at 10 000 12 and 13.7.
 static bool conv_small_faster(int64_t n, int c, int N, bool transposed)
 {
     if (n * c * 4 >= ((int64_t)1 << 31) || n * 108 >= ((int64_t)1 << 31)) return false;        // 32-bit byte offsets
-    // work with what tiles and loads are padded to: 6 -> 7 at 236 000 voxels (10 million terms without) is slower here with its gradients, 169 and 192 us.  Rows of no
-    // multiple of 16 channels are behind earlier: 12 -> 20 at 12 000 11.4 and 9.6, at 22 000 14.6 and 15.6, at 29 000 14.3 and 19; 8 -> 40 at 16 000 10.3 and 11.2
-    const double work = (double)n * ((c + 15) / 16 * 16) * ((N + 15) / 16 * 16);
-    return (int64_t)c * N <= (transposed ? 4096 : 8192) && work <= (transposed ? 6.5e6 : (c % 16 ? 8e6 : 12.5e6));
+    const double work = (double)n * ((c + 15) / 16 * 16) * ((N + 15) / 16 * 16);               // as tiles and loads are padded
+    if ((int64_t)c * N > (transposed ? 4096 : 8192)) return false;
+    if (transposed) return c <= (N <= 16 ? 112 : c % 8 ? 40 : 88) && work <= (c % 8 && (c <= 32 || c > 40) ? 4.2e6 : 6.5e6);
+    if (c > (N > 16 && N <= 32 ? 88 : 112)) return false;
+    if (c <= 16 || c > 64) return work <= 6.2e6;
+    return work <= (c % 16 ? (c <= 56 ? 8e6 : 6.2e6) : (N <= 16 ? 8e6 : 12.5e6));
 }
 
 static hch_status launch_conv_small(const Level &L, const float *X, const float *W, float *out, int64_t n, int c, int N, bool transposed,
@@ -2229,7 +2236,8 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
         return n >= (N < 20 ? 192 : 96) * (int64_t)c;
     }
     // 16 columns: 32 -> 16 at 800 to 44 000 rows 0.89 to 0.99 of gemm_bf16_kernel's time, at 64 000 1.11 (32 -> 8 1.03 and 1.14), at 80 000 0.94, at 280 000 0.75; data gradient
-    // 0.71 to 0.90 at all sizes
+    // 0.71 to 0.90 at all sizes.  Longer rows to 16 columns, half of a tile, 64 -> 16, 96 -> 16, 128 -> 16: at 64 000 1.21, 1.08, 1.23, at 127 000 1.03, 0.80, 1.05, with 17 neighbours a
+    // voxel 1.15, 1.13, 1.39; at 280 000 0.86, 0.69, 0.84
     if (N <= 16) return full && c == 32 && (transposed || n >= 81920);
     // Against gemm_bf16_kernel, which splits the reduction of few rows: 32 -> 64 at 16 500 to 32 000 rows 0.76 to 0.87, data gradient 0.64 to 0.74, 64 -> 64 0.88 to 0.97 and 0.89
     // to 1.02, 32 -> 24 and 64 -> 24 at 16 500 1.02 to 1.10, at 24 000 0.85 and 0.94; longer rows: 96 -> 32 at 32 000 26 us and 30, from 66 000 on 0.61 to 0.84, 128 -> 128 0.86 to 1.00.  Rows that fill a step in part: from 98 000 on 0.71
@@ -2608,10 +2616,11 @@ extern "C" hch_status hch_conv_bwd_data(const hch_levels *levels, int32_t level,
     // gather gained: 96 -> 111 us and 45 -> 31 us at level 1, 72 -> 81 and 13 -> 13 at level 2.)
     const bool masked = planes && L->dmask27 != nullptr;
     const uint32_t *rowmask = masked ? L->dmask27 : nullptr;
-    // bytes: dY and W in; of dcol the pieces that have a destination, and 4 per row for the bit set (all of dcol without it)
+    // bytes: dY and W in; all of dcol, or of it the pieces that have a destination, and 4 per row for the bit set
+    const bool split = !planes && dtype == HCH_F32 && dcol_split_ok(n, c_in, c_out);
     const double bytes = es * ((double)n * c_out + (double)Kc * c_out) +
-                         (masked ? 4.0 * ((double)L->nbr_valid * c_in + (double)n) : 4.0 * (double)n * Kc);
-    if (!planes && dtype == HCH_F32 && dcol_split_ok(n, c_in, c_out)) st = launch_dcol_split((const float *)dY, (const float *)W, dcol, n, c_in, c_out, bytes, s);
+                         (masked && !split ? 4.0 * ((double)L->nbr_valid * c_in + (double)n) : 4.0 * (double)n * Kc);
+    if (split) st = launch_dcol_split((const float *)dY, (const float *)W, dcol, n, c_in, c_out, bytes, s);
     else
         st = launch_gemm<hch::A_ROWS, true>(dtype, p, dY, W, dcol, nullptr,
                                             (int)n, Kc, c_out, c_out, c_out, Kc, 0, bytes, s, planes ? c_in : 0,

@@ -14,7 +14,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a 16-byte unit 
 // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin.  Kernels whose
 // neighbouring tiles touch the same memory launch 8*per_xcd workgroups and use this mapping
 // so that every XCD works on one contiguous range of tiles.
-constexpr unsigned NUM_XCD = 8;
+constexpr unsigned NUM_XCD = 8, NUM_CU = 256;
 __device__ __forceinline__ unsigned xcd_tile(unsigned bid, unsigned per_xcd)
 {
     return (bid % NUM_XCD) * per_xcd + bid / NUM_XCD;

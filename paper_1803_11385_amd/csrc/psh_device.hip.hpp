@@ -367,8 +367,8 @@ __global__ __launch_bounds__(256) void psh_clear_kernel(const PairDesc *__restri
 // the placing and the buckets of one voxel.  The bits of a table of side m <= PSH_LDS_SIDE are m^2 words of 8 bytes in LDS,
 // four times, side by side in x and y so that a look need not wrap round, so that a look at a row and a claim take some 100 cycles instead of the 1 to 2 us of
 // memory past the caches, and nothing of an attempt returns to the host.  What is left of the parallelism is enough:
-// a batch has some 50 tables, and where the chip has room for it (psh_attempts_at_once) each table's next
-// offset side is tried beside the first one, which a third of the tables need.
+// a batch has some 50 tables, and where the chip has room for it (SIDES_AT_ONCE in place_in_lds) each table's next
+// two offset sides are tried beside the first one, which a third of the tables find too small.
 //   * Bucket sizes are counted in LDS where the offset cells fit it (else in memory), and the count before a
 //     voxel was added is its place in the bucket.
 //   * 4 lanes per bucket, 16 buckets to a wavefront: a lane looks at one row, all offsets of it at once, and the residues
@@ -604,7 +604,7 @@ __device__ __forceinline__ int psh_mod(int v, int d, float inv)
 // Every wait ends: a turn of the placing loop finishes the bucket, moves on to other rows or has one offset less to try.
 // 256^3, batch of 8, 6 levels, 609 000 voxels: 1.1 ms for all tables, three sides tried at once (an attempt that succeeds at its
 // second side 0.3, the ones that just succeed or fail at the first up to 1.1), where the launches over memory (psh_place_kernel
-// and those around it) took 2.2 ms in two rounds with the host between them.
+// and those around it) took 1.9 ms in two rounds with the host between them.
 __global__ __launch_bounds__(PSH_THREADS) void psh_build_kernel(
     const AttemptDesc *__restrict__ attempts, int32_t *__restrict__ cnt_mem, int32_t *__restrict__ first_mem, uint32_t *__restrict__ phi_mem,
     uint4 *__restrict__ list_mem, int32_t *__restrict__ rank_mem, uint32_t *__restrict__ residue_mem, int32_t *__restrict__ ok, int lds_bytes)

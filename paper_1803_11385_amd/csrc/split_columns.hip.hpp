@@ -10,7 +10,7 @@ namespace hch {
 // tap after the other without padding; an absent row is a row of zeros, in the products as well.  Rows of a multiple of 4
 // channels.  Bound by the stores of the column matrix with few output columns (4 -> 16 at 280 000 rows: 121 MB in 34 us), by the matrix
 // instructions and the cutting, as conv_split_kernel, with more.  The two launches -> this one: 4 -> 16 at 280 000 rows 66 -> 34 us,
-// 12 -> 20 199 -> 138, 16 -> 32 237 -> 122, 32 -> 64 503 -> 232; at 82 000 16 -> 32 67 -> 38, 32 -> 64 144 -> 85; at 23 000 32 -> 64
+// 12 -> 20 199 -> 138, 16 -> 32 237 -> 127, 32 -> 64 503 -> 230; at 82 000 16 -> 32 67 -> 38, 32 -> 64 144 -> 85; at 23 000 32 -> 64
 // 49 -> 33, 64 -> 128 115 -> 79; at 800 18 -> 14.5, 128 -> 256 34 -> 26.
 // STREAM: stores past the caches, a form of the kernel (as a condition in the loop the compiler makes one store of both).  64-byte pieces only (pieces
 // that share a sector with the next step's become two writes: 12 -> 20 at 280 000 258 us), and with matrices beyond the last-level cache: 16 -> 32 at
@@ -19,7 +19,8 @@ namespace hch {
 // FAST: rows of a multiple of 32 channels; a step lies within one tap.
 template <int NT, int WV, bool FAST, bool STREAM>
 __global__ __launch_bounds__(64 * WV) void columns_split_kernel(
-    const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr, float *__restrict__ col, int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
+    const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr, float *__restrict__ col,
+    int M, int N, int c, unsigned m_tiles, int64_t c_split_stride, int vec_out)
 {
     typedef ConvLds<NT, WV> L;
     constexpr int BN = L::BN, ROWS = L::ROWS, GROUP = ROWS * WV / 64;     // 64-row tiles per workgroup

@@ -78,11 +78,15 @@ def test_sums_of_few_terms_are_rounded_once(n, ci, co):
     assert float((Y.double() - want).norm() / want.norm()) < 4e-8
 
 
-@pytest.mark.parametrize("n,ci,co,small", [(24414, 16, 32, {"conv_small_kernel<2, false>"}), (24415, 16, 32, set()),
-                                           (12695, 16, 32, {"conv_small_kernel<2, false>", "conv_small_kernel<1, true>"}),
-                                           (12696, 16, 32, {"conv_small_kernel<2, false>"}),
-                                           (300, 64, 128, {"conv_small_kernel<2, false>"}), (300, 64, 129, set()),
-                                           (15625, 12, 20, {"conv_small_kernel<2, false>"}), (15626, 12, 20, set()), (40000, 6, 7, set())])
+FWD, BWD = "conv_small_kernel<2, false>", "conv_small_kernel<2, true>"
+
+
+@pytest.mark.parametrize("n,ci,co,small", [
+    (12109, 16, 32, {FWD, "conv_small_kernel<1, true>"}), (12110, 16, 32, {"conv_small_kernel<1, true>"}), (12695, 16, 32, {"conv_small_kernel<1, true>"}),
+    (12696, 16, 32, set()), (6103, 32, 64, {FWD}), (6104, 32, 64, set()), (300, 64, 128, {FWD}), (300, 64, 129, set()), (300, 112, 72, {FWD}), (300, 128, 64, set()),
+    (300, 88, 32, {FWD, BWD}), (300, 96, 32, {BWD}), (300, 32, 88, {FWD, BWD}), (300, 32, 96, {FWD}), (300, 20, 40, {FWD, BWD}), (300, 40, 50, {FWD}),
+    (12109, 12, 20, {FWD}), (12110, 12, 20, set()), (7812, 24, 20, {FWD}), (7813, 24, 20, set()), (24218, 6, 7, {"conv_small_kernel<1, false>"}),
+    (24219, 6, 7, set()), (16406, 6, 7, {"conv_small_kernel<1, false>", "conv_small_kernel<1, true>"}), (16407, 6, 7, {"conv_small_kernel<1, false>"}), (40000, 6, 7, set())])
 def test_line_to_conv_split_kernel(n, ci, co, small):
     lv = _levels(n, 64, models=2)
     X, W, G = _data(n, ci, co)
