@@ -861,8 +861,8 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
     const int n_pairs = (int)work.size();
     // A workgroup per table, where rows fit 64 bits and the largest table is not most of the work (then a chip full of wavefronts on
     // that one is as fast).  Whole builds with 3 levels, there and by launches over memory: 40 models of 4000 voxels 0.78 and 1.89 ms, 1 of 3000
-    // 0.46 and 0.80, 1 of 25 000 0.69 and 0.70, 2 of 150 000 1.83 and 2.04; 1 of 90 000 1.45 and 1.38, 1 of 250 000 3.5 and 3.2; rows of
-    // 128 bits, 1 of 400 000 8.0 and 3.8, 4 of them 11 and 16.
+    // 0.46 and 0.80, 1 of 25 000 0.69 and 0.70, 2 of 150 000 1.83 and 2.04, 3 of 230 000 3.7 and 4.3; 1 of 90 000 1.45 and 1.38, 1 of 250 000 3.5 and 3.2, 2 of 250 000
+    // 7.5 and 6.9; one level of 2 of 100 000 1.4 and 1.2, of 200 000 2.7 and 2.2; rows of 128 bits, 1 of 400 000 8.0 and 3.8, 4 of them 11 and 16.
     int32_t widest_m = 0;
     int64_t largest = 0, all_voxels = 0;
     for (const PairWork &w : work) {
@@ -870,7 +870,7 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         largest = std::max<int64_t>(largest, w.n);
         all_voxels += w.n;
     }
-    const bool in_lds = widest_m <= hch::PSH_LDS_SIDE && (largest <= 32768 || all_voxels >= 2 * largest);
+    const bool in_lds = widest_m <= hch::PSH_LDS_SIDE && (largest <= 32768 || (double)all_voxels >= (largest > 229376 ? 3.0 : 2.2) * (double)largest);
     st = in_lds ? place_in_lds(hl, work, tmp, host_copies, s) : place_in_memory(hl, work, tmp, host_copies, s);
     if (st != HCH_OK) return st;
 
