@@ -134,13 +134,12 @@ void free_level(Level &L)
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Host memory that the device copies into (tables built there, for hch_level_info).  Copies into ordinary memory go by pieces
-// through a buffer of the runtime's and a copy by the host: builds of a 256^3 batch of 8 (17 MB), one after the other in a process of their own, 7.9 ms,
-// with pinned memory 7.0.  Making pinned memory costs more than that (the build that makes it 6.4 where the next ones take 2.8) or as much as it
-// saves (192 MB in each build 33.4, ordinary 32.4; twenty level sets that stay 5.9 and 6.2 each), so it is made only where one level set follows another: for
-// as many bytes as blocks of ordinary memory have been given back.  Pinned blocks of level sets that are gone are kept for the next ones, HOST_KEPT bytes
-// at most, the longest unused given back first; there are never more than HOST_PINNED bytes, in use and kept.  By any thread: a block has one owner,
-// whose copies are over before it is freed.  Everything else is ordinary memory: level sets that are all kept, larger ones than
-// HOST_KEPT, and where the runtime has no pinned memory.
+// through a buffer of the runtime's and a copy by the host: builds of a 256^3 batch of 8 (17 MB) one after the other 3.3 ms, with pinned memory 2.7, of a
+// 64^3 batch of 32 1.04 and 0.94.  Making such a block costs what it saves the first time (twenty level sets that stay 6.2 ms each either way; the
+// first build of a single model of 90 000 voxels 2.5 and 2.0), so blocks of level sets that are gone are kept for the next ones: HOST_KEPT bytes at most, the longest
+// unused given back first.  In use and kept there are HOST_PINNED bytes at most; beyond that, for more than HOST_KEPT at once (192 MB in each build 33.4 ms,
+// ordinary 32.4) and where the runtime has no pinned memory it is ordinary memory.  By any thread: a block has one owner, whose copies are over before it is
+// freed.
 constexpr size_t HOST_KEPT = (size_t)128 << 20, HOST_PINNED = 2 * HOST_KEPT, HOST_STEP = (size_t)256 << 10;
 
 class HostBlocks {
@@ -148,7 +147,6 @@ class HostBlocks {
     std::mutex mu;
     std::vector<Block> kept;                   // longest unused first
     size_t held = 0, pinned = 0;               // bytes kept; of all pinned blocks
-    size_t wanted = 0;                         // of ordinary memory given back, less what was pinned instead; HOST_KEPT at most
     void unpin(const Block &b)
     {
         (void)hipHostFree(b.p);
@@ -172,8 +170,7 @@ public:
                 kept.erase(kept.begin() + (std::ptrdiff_t)best);
                 return p;
             }
-            if (*bytes > wanted || pinned + *bytes > HOST_PINNED) return nullptr;
-            wanted -= *bytes;
+            if (*bytes > HOST_KEPT || pinned + *bytes > HOST_PINNED) return nullptr;
             pinned += *bytes;
         }
         void *p = nullptr;
@@ -207,11 +204,6 @@ public:
             unpin(out);
         }
     }
-    void gone(size_t bytes)                    // ordinary memory
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        wanted = std::min(wanted + round_up(bytes, HOST_STEP), HOST_KEPT);
-    }
 };
 
 class HostBlock {
@@ -222,11 +214,7 @@ public:
     HostBlock() = default;
     HostBlock(const HostBlock &) = delete;
     HostBlock &operator=(const HostBlock &) = delete;
-    ~HostBlock()
-    {
-        if (p) HostBlocks::get().keep(p, bytes);
-        else if (ordinary) HostBlocks::get().gone(bytes);
-    }
+    ~HostBlock() { if (p) HostBlocks::get().keep(p, bytes); }
     char *get() const { return p ? p : ordinary.get(); }
     bool pinned() const { return p != nullptr; }
     void make(size_t n)                        // once
