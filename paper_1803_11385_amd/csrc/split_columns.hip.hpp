@@ -69,7 +69,7 @@ __global__ __launch_bounds__(64 * WV) void columns_split_kernel(
     const bool b_col = n0 + bn < N;
     // this thread's first weight of the next step: the reduction advances the per-lane offset, which decides inside or outside (zero weights
     // past term K), and the scalar offset stays within the first rows
-    int w_off = b_col ? ((s_beg * 32 + kp * UN) * N + n0 + bn) * 4 : (int)OUT;
+    uint32_t w_off = b_col ? ((uint32_t)(s_beg * 32 + kp * UN) * N + n0 + bn) * 4u : OUT;
     // tap and channel of the next step (FAST) or of this lane's piece of it
     int tap = (s_beg * 32 + (FAST ? 0 : ap * 4)) / c, ch = s_beg * 32 + (FAST ? 0 : ap * 4) - tap * c;
     if constexpr (FAST) { tap = __builtin_amdgcn_readfirstlane(tap); ch = __builtin_amdgcn_readfirstlane(ch); }
@@ -85,8 +85,8 @@ __global__ __launch_bounds__(64 * WV) void columns_split_kernel(
         tap += d_tap; ch += d_ch;
         if (ch >= c) { ch -= c; ++tap; }
 #pragma unroll
-        for (int j = 0; j < UN; ++j) rb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, w_off, j * N * 4, 0));
-        w_off += 32 * N * 4;
+        for (int j = 0; j < UN; ++j) rb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, (int)w_off, j * N * 4, 0));
+        w_off += 128u * N;
     };
     int k_col = s_beg * 32 + ap * 4;                                       // place in the column matrix of the piece laid down next
     auto stash_a = [&](const u32x4 *ra) {
