@@ -30,7 +30,9 @@ MFMA_SPLIT_PEAK_TFLOPS = MFMA_BF16_PEAK_TFLOPS / 6
 CHANNELS = [4, 16, 32, 64, 128, 256]
 ARITHMETIC = {"fused": "fp32 operands as three bf16 numbers each, their six leading products on the bf16 matrix "
                        "instruction, fp32 sums (small products: fp32 instruction)",
-              "fused_dense": "fp32 matrix instruction", "columns": "fp32 matrix instruction",
+              "fused_dense": "fp32 matrix instruction",
+              "columns": "fp32 operands as three bf16 numbers each, their six leading products on the bf16 matrix instruction, fp32 sums "
+                         "(forward; data gradients of 32, 64 and 128 channels); fp32 instruction (weight gradients, the rest)",
               "bf16": "bf16 operands, fp32 sums"}
 ALGOS = {"fused": "HCH_ALGO_FUSED", "fused_dense": "HCH_ALGO_FUSED_DENSE", "columns": "HCH_ALGO_COLUMNS"}
 
@@ -147,19 +149,20 @@ def conv_products(torch, hch, S, cfg, algo_name, steps, warmup, tap_major=True):
              ("weight_gradient", lambda: hch.hch_conv_bwd_weight(lv, 0, DT, X, G, dW, ci, co, ws, algo)))
     occupied = lv.info(0).nbr_valid
     flop, useful = 2.0 * n * 27 * ci * co, 2.0 * occupied * ci * co
-    # at these sizes the fused fp32 products are on split operands, all three
-    peak = MFMA_BF16_PEAK_TFLOPS if bf else (MFMA_SPLIT_PEAK_TFLOPS if algo_name == "fused" else MFMA_F32_PEAK_TFLOPS)
     out = {}
     for name, fn in calls:
+        # at these sizes the fp32 products are on split operands, all three fused ones, two of the columns algorithm
+        split = algo_name == "fused" or (algo_name == "columns" and name != "weight_gradient")
+        peak = MFMA_BF16_PEAK_TFLOPS if bf else (MFMA_SPLIT_PEAK_TFLOPS if split else MFMA_F32_PEAK_TFLOPS)
         ms = time_calls(torch, fn, steps, warmup)
         out[name] = {"ms": round(ms, 4), "tflops": round(flop / ms / 1e9, 1),
                      "useful_tflops": round(useful / ms / 1e9, 1),
-                     "frac_of_mfma_peak": round(flop / ms / 1e9 / peak, 4)}
+                     "mfma_peak_tflops": round(peak, 1), "frac_of_mfma_peak": round(flop / ms / 1e9 / peak, 4)}
     return {"metric": f"one 3x3x3 convolution {ci} -> {co}: time per product", "unit": "ms",
             "products": out, "calls_timed": steps, "higher_is_better": False,
             "dtype": "bf16" if bf else "f32", "data": "synthetic", "algo": algo_name,
             "flop_count": "tflops: paper-method 2*27*c_in*c_out*N; useful_tflops: occupied taps only",
-            "mfma_peak_tflops": round(peak, 1), "arithmetic": ARITHMETIC["bf16" if bf else algo_name],
+            "mfma_peak_tflops": out["forward"]["mfma_peak_tflops"], "arithmetic": ARITHMETIC["bf16" if bf else algo_name],
             "config": {"workload": f"{u}^3 grid, batch {len(offs) - 1}, random-primitive surfaces, {n} voxels, "
                                    f"{occupied / n:.2f} of 27 taps occupied per voxel"}}
 
