@@ -133,12 +133,12 @@ hch_status hch_build_levels(const int32_t *coords_xyz, const int64_t *model_offs
  * conflict; pairs (level, model) that fail are repeated with the next offset-table side.  Most batches
  * have a workgroup for each pair, with the bits in LDS and the next two sides tried at the same time;
  * tables of a side above 64, and models of more than 32 768 voxels of which one or two are most of
- * the work, are built by one set of launches for all pairs, with the bits in memory.  Sizes (m, first r, growth of r), table
- * formats and everything computed through the tables (neighbour and child lists, every
- * convolution and pooling result) are the same as with hch_build_levels; the tables themselves
- * are valid but differ from the host-built ones and from run to run (which of two racing buckets
- * gets a slot depends on timing), and `attempts` / r may differ.  Same arguments, ownership and
- * errors as hch_build_levels; BLOCKS.
+ * the work, are built by one set of launches for all pairs, with the bits in memory.  Sizes (m,
+ * first r, growth of r), table formats and everything computed through the tables (neighbour and
+ * child lists, every convolution and pooling result) are the same as with hch_build_levels; the
+ * tables themselves are valid but differ from the host-built ones and from run to run (which of two
+ * racing buckets gets a slot depends on timing), and `attempts` / r may differ.  Same arguments,
+ * ownership and errors as hch_build_levels; BLOCKS.
  */
 hch_status hch_build_levels_device(const int32_t *coords_xyz, const int64_t *model_offsets,
                                    int32_t batch, int32_t resolution, int32_t n_levels,

@@ -6,16 +6,15 @@
 
 namespace hch {
 
-// A workgroup computes 16 rows by 16*NT columns, rows in data order; its WV = 8 wavefronts share out the reduction, not the
-// rows: in units of 8 channels of one tap that any of the 16 rows has, 4 units (32 terms) to a step, a wavefront takes every WV-th
-// step.  Each reads its rows and weights from memory straight into the operands' layout, cuts both and keeps sums of its own,
-// which meet in LDS as they are, leading pieces' and the others' apart, and are added in 64 bits and rounded once (with a rounding per
-// wavefront short reductions came out further from the exact sums than conv_split_kernel's one chain: 1 -> 4 channels 5.5e-8 for 3.2e-8).  Nothing is shared on the way, so there is no barrier between the index rows and
+// A workgroup computes 16 rows by 16*NT columns, rows in data order; its WV = 8 wavefronts share out the reduction, not the rows: in units of 8
+// channels of one tap that any of the 16 rows has, 4 units (32 terms) to a step, a wavefront takes every WV-th step.  Each reads its rows and weights
+// from memory straight into the operands' layout, cuts both and keeps sums of its own, which meet in LDS as they are, leading pieces' and the others'
+// apart, and are added in 64 bits and rounded once (with a rounding per wavefront short reductions came out further from the exact sums than
+// conv_split_kernel's one chain: 1 -> 4 channels 5.5e-8 for 3.2e-8).  Nothing is shared on the way, so there is no barrier between the index rows and
 // the end, and no launch that adds up partial sums.
-// Bound by the latency of that chain: index rows, rows and weights, the last sum; conv_split_kernel, whose workgroups walk through
-// all steps one after the other, or through a part of them with a launch to add the parts, takes longer wherever all workgroups of
-// this one are resident at once.  It reads and cuts every weight for 16 rows only, which is what it loses with more rows (figures
-// at conv_small_faster).
+// Bound by the latency of that chain: index rows, rows and weights, the last sum; conv_split_kernel, whose workgroups walk through all steps one
+// after the other, or through a part of them with a launch to add the parts, takes longer wherever all workgroups of this one are resident at once.
+// It reads and cuts every weight for 16 rows only, which is what it loses with more rows (figures at conv_small_faster).
 // BT: W(t, k, n) = W[26 - t][n][k] (the data gradient's view of the weights), else W[t][k][n].
 constexpr int SMALL_WAVES = 8;
 template <int NT, bool BT>

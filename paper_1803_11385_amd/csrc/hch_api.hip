@@ -133,13 +133,13 @@ void free_level(Level &L)
 
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Host memory that the device copies into (tables built there, for hch_level_info).  Copies into ordinary memory go by pieces
-// through a buffer of the runtime's and a copy by the host: builds of a 256^3 batch of 8 (17 MB) one after the other 3.3 ms, with pinned memory 2.7, of a
-// 64^3 batch of 32 1.04 and 0.94.  Making such a block costs what it saves the first time (twenty level sets that stay 6.2 ms each either way; the
-// first build of a single model of 90 000 voxels 2.5 and 2.0), so blocks of level sets that are gone are kept for the next ones: HOST_KEPT bytes at most, the longest
-// unused given back first.  In use and kept there are HOST_PINNED bytes at most; beyond that, for more than HOST_KEPT at once (192 MB in each build 33.4 ms,
-// ordinary 32.4) and where the runtime has no pinned memory it is ordinary memory.  By any thread: a block has one owner, whose copies are over before it is
-// freed.
+// Host memory that the device copies into (tables built there, for hch_level_info).  Copies into ordinary memory go by pieces through a buffer of the
+// runtime's and a copy by the host: builds of a 256^3 batch of 8 (17 MB) one after the other 3.3 ms, with pinned memory 2.7, of a 64^3 batch of 32
+// 1.04 and 0.94.  Making such a block costs what it saves the first time (twenty level sets that stay 6.2 ms each either way; the first build of a
+// single model of 90 000 voxels 2.5 and 2.0), so blocks of level sets that are gone are kept for the next ones: HOST_KEPT bytes at most, the longest
+// unused given back first.  In use and kept there are HOST_PINNED bytes at most; beyond that, for more than HOST_KEPT at once (192 MB in each build
+// 33.4 ms, ordinary 32.4) and where the runtime has no pinned memory it is ordinary memory.  By any thread: a block has one owner, whose copies are
+// over before it is freed.
 constexpr size_t HOST_KEPT = (size_t)128 << 20, HOST_PINNED = 2 * HOST_KEPT, HOST_STEP = (size_t)256 << 10;
 
 class HostBlocks {
@@ -847,9 +847,9 @@ static hch_status device_construct(hch_levels *hl, Occupancy &occ, hipStream_t s
         }
     };
     const int n_pairs = (int)work.size();
-    // A workgroup per table, where rows fit 64 bits and the largest table is not most of the work (then a chip full of wavefronts on
-    // that one is as fast).  Whole builds with 3 levels, there and by launches over memory: 40 models of 4000 voxels 0.78 and 1.89 ms, 1 of 3000
-    // 0.46 and 0.80, 1 of 25 000 0.69 and 0.70, 2 of 150 000 1.83 and 2.04, 3 of 230 000 3.7 and 4.3; 1 of 90 000 1.45 and 1.38, 1 of 250 000 3.5 and 3.2, 2 of 250 000
+    // A workgroup per table, where rows fit 64 bits and the largest table is not most of the work (then a chip full of wavefronts on that one is as
+    // fast).  Whole builds with 3 levels, there and by launches over memory: 40 models of 4000 voxels 0.78 and 1.89 ms, 1 of 3000 0.46 and 0.80, 1 of
+    // 25 000 0.69 and 0.70, 2 of 150 000 1.83 and 2.04, 3 of 230 000 3.7 and 4.3; 1 of 90 000 1.45 and 1.38, 1 of 250 000 3.5 and 3.2, 2 of 250 000
     // 7.5 and 6.9; one level of 2 of 100 000 1.4 and 1.2, of 200 000 2.7 and 2.2; rows of 128 bits, 1 of 400 000 8.0 and 3.8, 4 of them 11 and 16.
     int32_t widest_m = 0;
     int64_t largest = 0, all_voxels = 0;
@@ -2161,15 +2161,15 @@ static hch_status launch_dcol_split(const float *dY, const float *W, float *dcol
     return HCH_OK;
 }
 
-// The same products for few voxels (conv_small_kernel).  It reads all weights of its taps once per 16 rows, so the line lies at little
-// work, and for the data gradient, whose weights it reads in pieces of 16 bytes, or one by one where rows are no multiple of 8 channels, lower.  Calls one
-// after the other (10 us: what the host takes for one) against conv_split_kernel with the launch that adds its parts: forward 16 -> 32 at 12 000 voxels 9.8 us
-// and 11.1, 32 -> 64 at 3200 10 and 16, at 6000 12.5 and 16.6, 64 -> 64 at 1500 10.5 and 16, 64 -> 128 at 800 10.5 and 16; data gradient 32 -> 16 at
-// 12 000 10 and 12.5, 64 -> 32 at 2200 11 and 15.  (Tiles of 64 columns 10.2 and 16 with 32 -> 64 and 64 -> 64 at 3200, 16 wavefronts 11.5 and 18.)
-// The lines keep every call that was behind (of 25 by 16 pairs of channels at 23 level sets from 60 to 40 000 voxels, both directions) with conv_split_kernel, which
-// splits long reductions over workgroups: 256 -> 32 at 800 voxels 14 us, 31 here, 128 -> 32 14.5 and 17.5, 96 -> 20 13.4 and 14.9; 16 -> 32 at 24 000 14 and 16, 12 -> 5 at
-// 30 000 11.3 and 14.1, 32 -> 5 at 18 000 14.3 and 15.9, 80 -> 40 at 2200 17 and 20, 60 -> 40 15 and 16.5; data gradient of 100 channels to 32 at 800 13.5 and 26, of 60 to 32
-// 13 and 17.5, of 128 to 32 14 and 20, of 12 to 32 at 10 000 12 and 13.7.
+// The same products for few voxels (conv_small_kernel).  It reads all weights of its taps once per 16 rows, so the line lies at little work, and for
+// the data gradient, whose weights it reads in pieces of 16 bytes, or one by one where rows are no multiple of 8 channels, lower.  Calls one after
+// the other (10 us: what the host takes for one) against conv_split_kernel with the launch that adds its parts: forward 16 -> 32 at 12 000 voxels 9.8
+// us and 11.1, 32 -> 64 at 3200 10 and 16, at 6000 12.5 and 16.6, 64 -> 64 at 1500 10.5 and 16, 64 -> 128 at 800 10.5 and 16; data gradient 32 -> 16
+// at 12 000 10 and 12.5, 64 -> 32 at 2200 11 and 15.  (Tiles of 64 columns 10.2 and 16 with 32 -> 64 and 64 -> 64 at 3200, 16 wavefronts 11.5 and
+// 18.) The lines keep every call that was behind (of 25 by 16 pairs of channels at 23 level sets from 60 to 40 000 voxels, both directions) with
+// conv_split_kernel, which splits long reductions over workgroups: 256 -> 32 at 800 voxels 14 us, 31 here, 128 -> 32 14.5 and 17.5, 96 -> 20 13.4 and
+// 14.9; 16 -> 32 at 24 000 14 and 16, 12 -> 5 at 30 000 11.3 and 14.1, 32 -> 5 at 18 000 14.3 and 15.9, 80 -> 40 at 2200 17 and 20, 60 -> 40 15 and
+// 16.5; data gradient of 100 channels to 32 at 800 13.5 and 26, of 60 to 32 13 and 17.5, of 128 to 32 14 and 20, of 12 to 32 at 10 000 12 and 13.7.
 static bool conv_small_faster(int64_t n, int c, int N, bool transposed)
 {
     if (n * c * 4 >= ((int64_t)1 << 31) || n * 108 >= ((int64_t)1 << 31)) return false;        // 32-bit byte offsets
@@ -2198,8 +2198,8 @@ static hch_status launch_conv_small(const Level &L, const float *X, const float 
     return HCH_OK;
 }
 
-// Forward product and data gradient (transposed) with bf16 operands over the row order (conv_bf16_kernel).  Its lines: calls of both directions, 170
-// pairs of channels at 9 to 24 sizes each from 800 to 609 000 rows, that took longer than the kernel below stay there.
+// Forward product and data gradient (transposed) with bf16 operands over the row order (conv_bf16_kernel).  Its lines are by direction: of 170 pairs of
+// channels at 9 to 24 sizes each, 800 to 609 000 rows, what takes longer with it than without stays with the kernel named.
 static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n, int c, int N, bool transposed)
 {
     const int64_t lim = (int64_t)1 << 31;
@@ -2210,33 +2210,36 @@ static bool conv_bf16_ok(const Level &L, const void *X, const void *W, int64_t n
     const double neighbours = (double)L.nbr_valid / (double)n;
     if (c % 8 || N % 8 || !aligned16(X) || !aligned16(W)) {
         // Without gemm_bf16_kernel the products go to the fp32 instruction: 50 -> 50 at 800 rows 62 us and 27, at 16 500 101 and 29, at 127 000 606
-        // and 51; rows of 2 channels are mostly padding here: 2 -> 16 at 800 rows 13 and 16, at 80 000 17.5 and 19, at 98 400 27 and 20.5, 2 -> 64 at 64 000 25 and 25
+        // and 51; rows of 2 channels are mostly padding here: 2 -> 16 at 800 rows 13 and 16, at 80 000 17.5 and 19, at 98 400 27 and 20.5, 2 -> 64 at
+        // 64 000 25 and 25
         if (c % 4 || N % 4 || !aligned16(X) || !aligned16(W)) return c > 2 || n >= (N > 32 ? 65536 : 98304);
         // Where that has its vector path it is ahead on few rows, the longer with little to multiply: 12 -> 20 at 44 000 0.89 of its time, 20 -> 4 0.94,
         // 12 -> 16 1.22, at 80 000 0.98, 8 -> 20 1.23 and 1.00, 8 -> 12 1.62, 1.38, at 160 000 1.22; rows of 4 channels, 4 -> 16 at 280 000 30 us and 37
         if (!full) return c >= 20 || (c >= 12 && N > 16) ? n >= 40960 : c >= 8 && (c > 8 || N > 16) && n >= 81920;
-        // It splits the reduction of few rows, here 27 * c terms follow one another: 64 -> 12 at 7000 rows 1.06 of its time, at 12 000 0.92, 96 -> 12 1.72 and 1.23, at
-        // 16 500 1.01, 64 -> 20 at 3200 1.12, at 7000 0.78, 96 -> 36 1.36 and 0.86, 128 -> 20 1.43 and 0.99.  With transposed weights it has its better loop
-        // for rows of a multiple of 64: to 12 channels 1.16 to 1.29 up to 64 000, 0.90 to 1.06 beyond, with 17 neighbours a voxel 1.18; to 20 1.11, 0.84 to 0.98, 1.10; to
-        // 36 and 60 1.28, 0.99, 0.95
+        // It splits the reduction of few rows, here 27 * c terms follow one another: 64 -> 12 at 7000 rows 1.06 of its time, at 12 000 0.92, 96 -> 12
+        // 1.72 and 1.23, at 16 500 1.01, 64 -> 20 at 3200 1.12, at 7000 0.78, 96 -> 36 1.36 and 0.86, 128 -> 20 1.43 and 0.99.  With transposed
+        // weights it has its better loop for rows of a multiple of 64: to 12 channels 1.16 to 1.29 up to 64 000, 0.90 to 1.06 beyond, with 17
+        // neighbours a voxel 1.18; to 20 1.11, 0.84 to 0.98, 1.10; to 36 and 60 1.28, 0.99, 0.95
         if (c == 32) return true;
         if (transposed && c % 64 == 0) return n >= 98304 && (N > 32 || (N > 16 && neighbours <= 11));
         return n >= (N < 20 ? 192 : 96) * (int64_t)c;
     }
-    // 16 columns: 32 -> 16 at 800 to 44 000 rows 0.89 to 0.99 of gemm_bf16_kernel's time, at 64 000 1.11 (32 -> 8 1.03 and 1.14), at 80 000 0.94, at 280 000 0.75; data gradient
-    // 0.71 to 0.90 at all sizes.  Longer rows to 16 columns, half of a tile, 64 -> 16, 96 -> 16, 128 -> 16: at 64 000 1.21, 1.08, 1.23, at 127 000 1.03, 0.80, 1.05, with 17 neighbours a
-    // voxel 1.15, 1.13, 1.39; at 280 000 0.86, 0.69, 0.84
+    // 16 columns: 32 -> 16 at 800 to 44 000 rows 0.89 to 0.99 of gemm_bf16_kernel's time, at 64 000 1.11 (32 -> 8 1.03 and 1.14), at 80 000 0.94, at
+    // 280 000 0.75; data gradient 0.71 to 0.90 at all sizes.  Longer rows to 16 columns, half of a tile, 64 -> 16, 96 -> 16, 128 -> 16: at 64 000
+    // 1.21, 1.08, 1.23, at 127 000 1.03, 0.80, 1.05, with 17 neighbours a voxel 1.15, 1.13, 1.39; at 280 000 0.86, 0.69, 0.84
     if (N <= 16) return full && c == 32 && (transposed || n >= 81920);
-    // Against gemm_bf16_kernel, which splits the reduction of few rows: 32 -> 64 at 16 500 to 32 000 rows 0.76 to 0.87, data gradient 0.64 to 0.74, 64 -> 64 0.88 to 0.97 and 0.89
-    // to 1.02, 32 -> 24 and 64 -> 24 at 16 500 1.02 to 1.10, at 24 000 0.85 and 0.94; longer rows: 96 -> 32 at 32 000 26 us and 30, from 66 000 on 0.61 to 0.84, 128 -> 128 0.86 to 1.00.  Rows that fill a step in part: from 98 000 on 0.71
-    // to 0.95 with 24, 56, 80 channels, 0.90 to 1.03 with 72; with 40, 3 of 8 padding, 0.96 to 1.15 at 98 000 and 127 000, 0.89 to 0.99 at 160 000; with 17 neighbours a
+    // Against gemm_bf16_kernel, which splits the reduction of few rows: 32 -> 64 at 16 500 to 32 000 rows 0.76 to 0.87, data gradient 0.64 to 0.74,
+    // 64 -> 64 0.88 to 0.97 and 0.89 to 1.02, 32 -> 24 and 64 -> 24 at 16 500 1.02 to 1.10, at 24 000 0.85 and 0.94; longer rows: 96 -> 32 at 32 000
+    // 26 us and 30, from 66 000 on 0.61 to 0.84, 128 -> 128 0.86 to 1.00.  Rows that fill a step in part: from 98 000 on 0.71 to 0.95 with 24, 56, 80
+    // channels, 0.90 to 1.03 with 72; with 40, 3 of 8 padding, 0.96 to 1.15 at 98 000 and 127 000, 0.89 to 0.99 at 160 000; with 17 neighbours a
     // voxel 48 -> 64 1.09 to 1.15, 24 -> 128 1.04 to 1.08
     if (!full) {
         if (c < 24 || neighbours > 11 || n < (c * 4 >= (c + 31) / 32 * 96 ? 98304 : 160000)) return false;
     } else if (n < (c > 64 ? 65536 : N <= 32 && !transposed ? 20480 : 16384)) return false;
-    // Where that kernel's tiles just fill a round of workgroups without splitting: to 32 columns, 52 000 to 64 000 rows, 32 -> 32 1.04 to 1.08, 64 -> 32 0.99 to 1.08 and the
-    // same back (48 000 0.72 to 0.78, 72 000 0.90); to 64, 33 000 to 48 000, 32 -> 64 1.03 to 1.09, 64 -> 64 1.06 to 1.13, back 1.02 to 1.11 (32 000 0.88, 52 000 0.95); to 128, 16 500 to
-    // 32 000, 32 -> 128 1.03 to 1.19, 64 -> 128 1.08 to 1.26, back 1.13 to 1.31 (36 000 0.95 to 1.01).  Data gradients of 32 channels have no such stretch
+    // Where that kernel's tiles just fill a round of workgroups without splitting: to 32 columns, 52 000 to 64 000 rows, 32 -> 32 1.04 to 1.08, 64 ->
+    // 32 0.99 to 1.08 and the same back (48 000 0.72 to 0.78, 72 000 0.90); to 64, 33 000 to 48 000, 32 -> 64 1.03 to 1.09, 64 -> 64 1.06 to 1.13,
+    // back 1.02 to 1.11 (32 000 0.88, 52 000 0.95); to 128, 16 500 to 32 000, 32 -> 128 1.03 to 1.19, 64 -> 128 1.08 to 1.26, back 1.13 to 1.31 (36
+    // 000 0.95 to 1.01).  Data gradients of 32 channels have no such stretch
     if (full && c <= 64 && (!transposed || c == 64)) {
         const int64_t tiles = N <= 32 ? (n + 127) / 128 : (n + 63) / 64 * ((N + 63) / 64);
         if (N <= 32 ? tiles > 384 && tiles <= 540 : tiles > 512 && tiles <= (N <= 64 ? 768 : 1024)) return false;
@@ -2260,9 +2263,9 @@ static hch_status launch_conv_bf16(const Level &L, const uint16_t *X, const uint
 {
     const unsigned m_tiles = (unsigned)((n + 63) / 64);
     // Where plan_rows splits the reduction of a level that does not fill the chip, a single chain of all terms is further from the exact sums than
-    // its slices are: there tiles of 32 columns, which add up sums of 128 terms.  Errors of slices, chain, such sums: 50 -> 50 at
-    // 3200 rows 1.03e-7, 1.61e-7, 0.80e-7, at 20 000 1.01e-7, 1.23e-7, 0.71e-7, 34 -> 66 at 12 000 (data gradient) 1.01e-7, 1.47e-7, 0.78e-7.  Times of tiles of 64
-    // and 32 columns there: 50 -> 50 at 800 rows 31 us and 27, at 16 500 31 and 29, 64 -> 64 23 and 20.
+    // its slices are: there tiles of 32 columns, which add up sums of 128 terms.  Errors of slices, chain, such sums: 50 -> 50 at 3200 rows 1.03e-7,
+    // 1.61e-7, 0.80e-7, at 20 000 1.01e-7, 1.23e-7, 0.71e-7, 34 -> 66 at 12 000 (data gradient) 1.01e-7, 1.47e-7, 0.78e-7.  Times of tiles of 64 and
+    // 32 columns there: 50 -> 50 at 800 rows 31 us and 27, at 16 500 31 and 29, 64 -> 64 23 and 20.
     const bool few = (int64_t)m_tiles * ((N + 63) / 64) < 512 && 27 * c >= 512;
     const int nt = N <= 32 || few ? 2 : 4, ks = c % 64 == 0 ? 64 : 32;
     const bool full = c % 32 == 0 && aligned16(X) && aligned16(W);

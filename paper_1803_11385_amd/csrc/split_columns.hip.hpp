@@ -5,18 +5,17 @@
 
 namespace hch {
 
-// conv_split_kernel's way through LDS and registers over all 27 taps and the rows in the order of the data; the rows that are
-// gathered for a product are also stored as they come, instead of written by hash2col_kernel and read back by gemm_f32_kernel.  One
-// tap after the other without padding; an absent row is a row of zeros, in the products as well.  Rows of a multiple of 4
-// channels.  Bound by the stores of the column matrix with few output columns (4 -> 16 at 280 000 rows: 121 MB in 34 us), by the matrix
-// instructions and the cutting, as conv_split_kernel, with more.  The two launches -> this one: 4 -> 16 at 280 000 rows 66 -> 34 us,
-// 12 -> 20 199 -> 138, 16 -> 32 237 -> 127, 32 -> 64 503 -> 230; at 82 000 16 -> 32 67 -> 38, 32 -> 64 144 -> 85; at 23 000 32 -> 64
-// 49 -> 33, 64 -> 128 115 -> 79; at 800 18 -> 14.5, 128 -> 256 34 -> 26.
-// STREAM: stores past the caches, a form of the kernel (as a condition in the loop the compiler makes one store of both).  64-byte pieces only (pieces
-// that share a sector with the next step's become two writes: 12 -> 20 at 280 000 258 us), and with matrices beyond the last-level cache: 16 -> 32 at
-// 159 000 (263 MB) 93 -> 75, 32 -> 64 at 282 000 298 -> 230, 16 -> 16 197 -> 124, at 593 000 32 -> 64 615 -> 583, with the weight gradient that reads the matrix
-// 305 -> 278 (16 -> 32), 593 -> 571, 301 -> 277, 1190 -> 1150; below, 32 -> 16 at 82 000 (270 MB) 56 -> 62.
-// FAST: rows of a multiple of 32 channels; a step lies within one tap.
+// conv_split_kernel's way through LDS and registers over all 27 taps and the rows in the order of the data; the rows that are gathered for a product
+// are also stored as they come, instead of written by hash2col_kernel and read back by gemm_f32_kernel.  One tap after the other without padding; an
+// absent row is a row of zeros, in the products as well.  Rows of a multiple of 4 channels.  Bound by the stores of the column matrix with few output
+// columns (4 -> 16 at 280 000 rows: 121 MB in 34 us), by the matrix instructions and the cutting, as conv_split_kernel, with more.  The two launches
+// -> this one: 4 -> 16 at 280 000 rows 66 -> 34 us, 12 -> 20 199 -> 138, 16 -> 32 237 -> 127, 32 -> 64 503 -> 230; at 82 000 16 -> 32 67 -> 38, 32 ->
+// 64 144 -> 85; at 23 000 32 -> 64 49 -> 33, 64 -> 128 115 -> 79; at 800 18 -> 14.5, 128 -> 256 34 -> 26.
+// STREAM: stores past the caches, a form of the kernel (as a condition in the loop the compiler makes one store of both).  64-byte pieces only
+// (pieces that share a sector with the next step's become two writes: 12 -> 20 at 280 000 258 us), and with matrices beyond the last-level cache: 16
+// -> 32 at 159 000 (263 MB) 93 -> 75, 32 -> 64 at 282 000 298 -> 230, 16 -> 16 197 -> 124, at 593 000 32 -> 64 615 -> 583, with the weight gradient
+// that reads the matrix 305 -> 278 (16 -> 32), 593 -> 571, 301 -> 277, 1190 -> 1150; below, 32 -> 16 at 82 000 (270 MB) 56 -> 62. FAST: rows of a
+// multiple of 32 channels; a step lies within one tap.
 template <int NT, int WV, bool FAST, bool STREAM>
 __global__ __launch_bounds__(64 * WV) void columns_split_kernel(
     const float *__restrict__ X, const float *__restrict__ W, float *__restrict__ C, const int32_t *__restrict__ nbr, float *__restrict__ col,
